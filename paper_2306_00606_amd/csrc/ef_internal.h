@@ -362,11 +362,6 @@ hipError_t launch_pass2(const Graph &g, const int32_t *seeds, const int32_t *fla
 size_t topk_scratch_bytes(int32_t n, int32_t k);
 hipError_t launch_topk(const double *ef, int32_t n, int32_t k, void *scratch,
                        size_t scratch_bytes, int32_t *nodes, double *ef_out, hipStream_t st);
-// the same over non-negative float scores (surrogate predictions)
-hipError_t launch_topk_f32(const float *score, int32_t n, int32_t k, void *scratch,
-                           size_t scratch_bytes, int32_t *nodes, double *score_out,
-                           hipStream_t st);
-
 // Schedule of the persistent batch kernel (one launch for the whole exact
 // path of a disjoint union of graphs), all device arrays. Work lists per bin,
 // each ordered by graph: pair centres (tiny, 16-, 32-, 64-lane segments, mid
