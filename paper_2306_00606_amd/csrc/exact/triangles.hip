@@ -784,7 +784,8 @@ __global__ __launch_bounds__(64) void k_tri_long(TriArgs A, const int32_t *__res
 
 // One node w per lane (|up(w)| <= M, a walk of at most kTriLaneWork entries),
 // for the many nodes whose whole triangle work is a few membership tests: a
-// wavefront per node would spend its time on setup. up(w) sits in registers
+// wavefront per node would spend its time on setup. Used by the persistent
+// batch kernel, whose LDS has no room for the rows of k_tri_pack below. up(w) sits in registers
 // (a test compares against all M entries), the credits to x by position and
 // to u by segment in per-lane integer slots (the LDS slots' representation,
 // so the records are the same bits as the other bins would write). Nodes are
@@ -857,12 +858,160 @@ __device__ __forceinline__ void tri_lane_node(const TriArgs &A, const int4 rc) {
   A.ZT[w] = cntw;
 }
 
-template <typename T, int M>
-__global__ __launch_bounds__(256) void k_tri_lane(TriArgs A, const int4 *__restrict__ recs,
+// The lane bin's nodes in the stand-alone pass: a wavefront takes kPackNodes
+// of them at a time, one segment per lane (64 segments of those nodes per
+// chunk), and each lane walks its segment's tail, four entries' loads in
+// flight and the next chunk's segments loaded meanwhile. One lane per node
+// instead waits on a chain of up to kTriLaneWork dependent loads, every lane
+// for the longest walk of its wavefront; tails differ far less than walks.
+// up(w) of every node sits in an LDS row of kTriLaneM ids (a test compares
+// against the whole row), the credits to x by row position in integer LDS
+// slots and those to u, whose segment is one lane's, in its registers (both
+// in the representation of the other bins, so the records are the same bits).
+// Bound by the dependent loads of a chunk on small graphs and by the row
+// comparisons on large ones.
+// BA n = 200k, m = 5 (FP32C): 39.5 us, one lane per node 93; a graph of
+// 1000 nodes and 4000 edges: 6.2 us against 17.9; 600k nodes of 64
+// Watts-Strogatz and configuration-model graphs: 52 us against 117 (12 nodes
+// per wavefront; 8 nodes: 35.4, 5.3 and 57 us, 16 nodes: 45.4, 7.6 and 51).
+constexpr int kPackNodes = 12;
+constexpr int kPackSpan = 16;  // the next power of two: lanes of the per-node prefix and search
+static_assert(kPackNodes <= kPackSpan && kPackNodes * kTriLaneM % 64 == 0, "rows of whole wavefronts");
+static_assert(kTriLaneM == 16, "a node's row is 16 lanes' worth of slots");
+
+template <typename T> struct TriPackLds {
+  static constexpr int kRows = kPackNodes * kTriLaneM;
+  __align__(16) int32_t up[kRows];  // ids of up(w) by node and position, -1 past its end
+  unsigned long long acc[kRows];    // credits to x
+  int32_t cnt[Credit<T>::kPacked ? 1 : kRows];
+  long long z[Credit<T>::kPacked ? 1 : kPackNodes];  // FP64: credits to w, 2^-44 units
+};
+constexpr double kPackZFix = 17592186044416.0;  // 2^44: |sum| < 2^13, beyond the records' 2^-36
+
+template <typename T>
+__global__ __launch_bounds__(256) void k_tri_pack(TriArgs A, const int4 *__restrict__ recs,
                                                   int64_t count) {
-  for (int64_t it = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; it < count;
-       it += (int64_t)gridDim.x * blockDim.x)
-    tri_lane_node<T, M>(A, recs[it]);
+  using S = SumT<T>;
+  constexpr int M = kTriLaneM, kRows = kPackNodes * M;
+  __shared__ TriPackLds<T> lds[4];
+  const int lane = threadIdx.x & 63;
+  TriPackLds<T> &L = lds[threadIdx.x >> 6];
+  const int64_t groups = (count + kPackNodes - 1) / kPackNodes;
+  const int64_t nwaves = (int64_t)gridDim.x * 4;
+  for (int64_t gi = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); gi < groups; gi += nwaves) {
+    // lane i < kPackNodes: node i's record; lanes without one: no entries
+    const int64_t it = gi * kPackNodes + lane;
+    const bool have = lane < kPackNodes && it < count;
+    const int4 rc = have ? recs[it] : make_int4(0, 0, 0, 0);
+    const int32_t m = rc.w & 0xFF, nd = (rc.w >> 8) & 0xFF;
+    int32_t incl = nd, mx = m;  // prefix of the segments, longest up(w)
+#pragma unroll
+    for (int o = 1; o < kPackSpan; o <<= 1) {
+      const int32_t y = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += y;
+      mx = max(mx, __shfl_xor(mx, o, 64));
+    }
+    const int32_t nseg = __builtin_amdgcn_readlane(incl, kPackNodes - 1);
+    const int32_t quads = (__builtin_amdgcn_readfirstlane(mx) + 3) >> 2;
+    const int32_t excl = incl - nd;
+    // segment si of the group: its node is the last one (of those with a
+    // record: lanes past them hold no segments) whose first is not past it
+    auto node_of = [&](int32_t si) {
+      int32_t node = 0;
+#pragma unroll
+      for (int st = kPackSpan / 2; st > 0; st >>= 1) {
+        const int32_t ex = __shfl(excl, node + st, 64), dn = __shfl(nd, node + st, 64);
+        if (dn > 0 && ex <= si) node += st;
+      }
+      return node;
+    };
+    auto segment = [&](int32_t si, int32_t &node) {
+      node = node_of(si);
+      const int32_t d0 = __shfl(rc.z, node, 64), e0 = __shfl(excl, node, 64);
+      return A.dn[d0 + (si - e0)];
+    };
+    // (nseg >= 1: every record has a segment)
+    int32_t node;
+    int4 sg = segment(min(lane, nseg - 1), node);
+    wave_sync();  // the previous group's rows have been read
+    // rows: slot r = 64 q + lane belongs to position r mod M of node r / M
+#pragma unroll
+    for (int q = 0; q < kRows / 64; ++q) {
+      const int r = 64 * q + lane, nq = r / M, pos = r % M;
+      const int32_t mn = __shfl(m, nq, 64), wn = __shfl(rc.y, nq, 64);
+      L.up[r] = pos < mn ? A.up_col[wn + pos] : -1;
+      L.acc[r] = 0ull;
+      if constexpr (!Credit<T>::kPacked) L.cnt[r] = 0;
+    }
+    if constexpr (!Credit<T>::kPacked)
+      if (lane < kPackNodes) L.z[lane] = 0;
+    wave_sync();
+    for (int32_t c0 = 0; c0 < nseg; c0 += 64) {
+      const bool live = c0 + lane < nseg;
+      const int32_t len = live ? sg.y : 0, row = node * M, slot = sg.x, ks = sg.z;
+      const int32_t e0 = slot + 1;
+      const int32_t znode = node;
+      if (c0 + 64 < nseg) sg = segment(min(c0 + 64 + lane, nseg - 1), node);
+      LaneSlot<T> su;
+      for (int32_t j = 0; __ballot(j < len) != 0ull; j += 4) {
+        int32_t x[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) x[q] = A.up_col[j + q < len ? e0 + j + q : slot];
+        int32_t p[4] = {-1, -1, -1, -1};
+        for (int32_t b = 0; b < quads; ++b) {
+          const int4 r = *reinterpret_cast<const int4 *>(&L.up[row + 4 * b]);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            p[q] = r.x == x[q] ? 4 * b : p[q];
+            p[q] = r.y == x[q] ? 4 * b + 1 : p[q];
+            p[q] = r.z == x[q] ? 4 * b + 2 : p[q];
+            p[q] = r.w == x[q] ? 4 * b + 3 : p[q];
+          }
+        }
+        // hits: a byte per entry, 0x80 | position (few: scored one at a time)
+        uint32_t hits = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          hits |= (j + q < len && p[q] >= 0) ? (uint32_t)(0x80 | p[q]) << (8 * q) : 0u;
+        while (hits != 0) {
+          const int q8 = (__ffs((int)hits) - 1) & 0x18;
+          const int32_t at = row + ((hits >> q8) & 0xF);
+          const T dl = tri_delta<T>(ks + A.up_deg[e0 + j + (q8 >> 3)]);
+          hits &= ~(0xFFu << q8);
+          Credit<T>::add(L.acc, L.cnt, at, dl);
+          su.add(dl);
+          if constexpr (!Credit<T>::kPacked)
+            atomicAdd((unsigned long long *)&L.z[znode],
+                      (unsigned long long)__double2ll_rn((double)dl * kPackZFix));
+        }
+      }
+      if (live) A.Y[A.nup + slot] = su.slot();
+    }
+    wave_sync();
+    // the rows' upper-end records; a node's sum over its row of M lanes
+#pragma unroll
+    for (int q = 0; q < kRows / 64; ++q) {
+      const int r = 64 * q + lane, nq = r / M, pos = r % M;
+      const int32_t mn = __shfl(m, nq, 64), wn = __shfl(rc.y, nq, 64),
+                    w = __shfl(rc.x, nq, 64);
+      TriSlot t{0, 0, 0};
+      Credit<T>::load(L.acc, L.cnt, r, t.y, t.t);
+      if (pos < mn) A.Y[wn + pos] = t;
+      long long zs = t.y;
+      int32_t zt = t.t;
+      for (int o = M / 2; o > 0; o >>= 1) {
+        zs += __shfl_xor(zs, o, 64);
+        zt += __shfl_xor(zt, o, 64);
+      }
+      if (pos == 0 && mn > 0) {  // every listed node has up(w) non-empty
+        typename S::type acc = typename S::type();
+        if constexpr (kZFromSlots<T>) acc = dfv_from_fix(zs);
+        else acc = (double)L.z[nq] * (1.0 / kPackZFix);
+        S::store(acc, A.Z, w);
+        A.ZT[w] = zt;
+      }
+    }
+  }
 }
 
 // Clear the listed records (upper-end records of long-list nodes, which
@@ -889,9 +1038,10 @@ static hipError_t tri_impl(const Graph &g, TriSlot *Y, void *Z, int64_t *ZT, hip
                        dim3(256), 0, st, Y, g.tri_zero, g.n_tri_zero);
   const int64_t *counts = g.n_tri;
   if (g.n_tri_lane > 0)
-    hipLaunchKernelGGL((k_tri_lane<T, kTriLaneM>),
-                       dim3(cap_blocks_tri((g.n_tri_lane + 255) / 256, 1 << 16)), dim3(256), 0, st,
-                       A, g.tri_recL, g.n_tri_lane);
+    hipLaunchKernelGGL(k_tri_pack<T>,
+                       dim3(cap_blocks_tri((g.n_tri_lane + 4 * kPackNodes - 1) / (4 * kPackNodes),
+                                           1 << 16)),
+                       dim3(256), 0, st, A, g.tri_recL, g.n_tri_lane);
   if (counts[0] > 0)
     hipLaunchKernelGGL((k_tri_wave<T, 256, 64, 4>), dim3(cap_blocks_tri((counts[0] + 3) / 4, 1 << 20)),
                        dim3(256), 0, st, A, g.tri_rec0, counts[0]);
