@@ -78,6 +78,13 @@ static ef_status ws_ensure(Graph &g, int slot, size_t bytes, const char *what) {
   }
   size_t want = std::max<size_t>(bytes, 256);
   ef_status s = dev_alloc(g, &b.p, want, what);
+  if (s != EF_OK && g.score64) {
+    // the FP64 score table only saves time: workspace comes first
+    dev_free(g, g.score64, sizeof(double) * (size_t)g.n_score64);
+    g.score64 = nullptr;
+    g.n_score64 = 0;
+    s = dev_alloc(g, &b.p, want, what);
+  }
   if (s != EF_OK) return s;
   b.bytes = want;
   return EF_OK;
@@ -164,7 +171,7 @@ ef_status ef_graph_free(ef_graph *h) {
                     g.tri_rec0, g.tri_recL, g.tri_list[0], g.tri_list[1], g.tri_list[2], g.tri_list[3],
                     g.tri_recB[1], g.tri_recB[2], g.fin_list,
                     g.ps_list[0], g.ps_list[1], g.ps_list[2], g.ps_list[3], g.ps_list[4],
-                    g.d_counters};
+                    g.d_counters, g.score64};
   for (void *p : arrays)
     if (p) (void)hipFree(p);
   for (auto &b : g.ws)
@@ -654,6 +661,23 @@ ef_status graph_scratch(Graph &g, size_t bytes, void **out) {
   return s;
 }
 
+// The FP64 score table of the graph: built on the stream of the first FP64
+// call (not while that stream is captured) and kept. Without memory for it
+// the kernels compute every score.
+static ef_status score_table(Graph &g, hipStream_t st) {
+  if (g.score64) return EF_OK;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cap) != hipSuccess) (void)hipGetLastError();
+  if (cap != hipStreamCaptureStatusNone) return EF_OK;
+  const int32_t n = 3 * g.info.max_degree + 1;  // cluster degrees are at most 3 k_max - 4
+  if (dev_alloc(g, (void **)&g.score64, sizeof(double) * (size_t)n, "score table") != EF_OK) {
+    g.score64 = nullptr;
+    return EF_OK;
+  }
+  g.n_score64 = n;
+  return hip_status(launch_score_table(g.score64, n, st), "score table");
+}
+
 static void host_bins(const Graph &g, const int32_t *centres, int64_t count, Bins &b) {
   b.n_small = b.n_mid = b.n_big = b.n_tiles = 0;
   b.pairs_small = b.pairs_mid = b.pairs_big = 0;
@@ -946,6 +970,14 @@ extern "C" ef_status ef_compute(ef_graph *h, ef_algo algo, ef_prec prec, const i
   const bool reuse = whole && g.bins_kept && g.bins_buf == g.ws[WS_BINS].p &&
                      g.bins_thr.t8 == b.thr.t8 && g.bins_thr.t16 == b.thr.t16 &&
                      g.bins_thr.t32 == b.thr.t32;
+  if (!per_seed) {
+    if ((s = ws_ensure(g, WS_Y, sizeof(TriSlot) * 2 * (size_t)nup, "triangle slots")) != EF_OK)
+      return s;
+    if ((s = ws_ensure(g, WS_Z, tsz * (size_t)std::max(g.n, 1), "triangle node sums")) != EF_OK) return s;
+    if ((s = ws_ensure(g, WS_ZT, sizeof(int64_t) * (size_t)std::max(g.n, 1), "triangle node counts")) != EF_OK)
+      return s;
+  }
+  if (prec == EF_PREC_FP64 && (s = score_table(g, st)) != EF_OK) return s;
   prof.mark(0);
   if (!reuse) {
     e = launch_bin_centres(g, centres, n_work, b, st);
@@ -960,11 +992,6 @@ extern "C" ef_status ef_compute(ef_graph *h, ef_algo algo, ef_prec prec, const i
   if (e != hipSuccess) return hip_status(e, "pair loop");
   prof.mark(5);
   if (!per_seed) {
-    if ((s = ws_ensure(g, WS_Y, sizeof(TriSlot) * 2 * (size_t)nup, "triangle slots")) != EF_OK)
-      return s;
-    if ((s = ws_ensure(g, WS_Z, tsz * (size_t)std::max(g.n, 1), "triangle node sums")) != EF_OK) return s;
-    if ((s = ws_ensure(g, WS_ZT, sizeof(int64_t) * (size_t)std::max(g.n, 1), "triangle node counts")) != EF_OK)
-      return s;
     e = launch_triangles(g, prec, (TriSlot *)g.ws[WS_Y].p, g.ws[WS_Z].p,
                          (int64_t *)g.ws[WS_ZT].p, st);
     if (e != hipSuccess) return hip_status(e, "triangle pass");

@@ -23,6 +23,7 @@ namespace efi {
 //                            1024 x 1024 neighbours, one workgroup each
 // ---------------------------------------------------------------------------
 constexpr int kWave = 64;
+constexpr int kCUs = 256;             // compute units, for grids of one round of workgroups
 constexpr int kSmallMax = 64;
 constexpr int kSuper = 1024;          // neighbours per super-block
 constexpr int kBlocksPerSuper = 16;   // 64-wide blocks per super-block
@@ -210,6 +211,10 @@ struct Graph {
   int64_t all_sblocks = 0;  // sum of super-blocks over big centres
   int64_t owned_bytes = 0;  // device bytes held by this handle
   int32_t *d_counters = nullptr;  // persistent small counters (flag counts etc.)
+  // FP64 calls: d log d for every cluster degree d < n_score64 (built by the
+  // first one; null: no device memory for it, and the kernels take logs)
+  double *score64 = nullptr;
+  int32_t n_score64 = 0;
   ef_graph_info info{};
   ef_run_stats stats{};
   // workspace (grow-only, reused across calls)
@@ -309,6 +314,9 @@ hipError_t launch_bin_centres(const Graph &g, const int32_t *centres, int32_t n_
 hipError_t launch_pairs(const Graph &g, ef_prec prec, const Bins &b, void *R, void *records,
                         hipStream_t st, hipEvent_t ev_small, hipEvent_t ev_mid,
                         hipEvent_t ev_big, int32_t *agg_done = nullptr);
+
+// t[i] = i log i for i < n (0 at 0)
+hipError_t launch_score_table(double *t, int32_t n, hipStream_t st);
 
 // triangle pass (cluster-centric): Y, two TriSlots per up arc (upper end at
 // the up-arc slot, lower end at nup + slot), Z / ZT per node.

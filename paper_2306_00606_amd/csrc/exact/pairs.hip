@@ -197,44 +197,94 @@ __device__ __forceinline__ void tile(T cp, T kq, T &Rt, T &C) {
   }
 }
 
-// entries of a big centre's score table (FP32 path)
+// entries of the score tables in LDS
 constexpr int kGTab = 8192;
+
+// FP64: score(i) of every cluster degree i the graph can have, kept with the
+// graph (Graph::score64, n entries; null: none). d log d in double costs about
+// 90 VALU instructions, against one LDS read from a copy of the part a
+// workgroup needs; the entries are the same expression's values, so every
+// cluster keeps its score bits.
+struct ScoreTab {
+  const double *g = nullptr;
+  int32_t n = 0;
+};
+
+__global__ void k_score_table(double *__restrict__ t, int32_t n) {
+  for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
+    t[i] = score_masked((double)i);
+}
+
+// tab[i] = score(d0 + i), i < kGTab, on a whole workgroup (no barrier here)
+__device__ __forceinline__ void fill_tab(float *tab, int32_t d0, ScoreTab) {
+  for (int i = threadIdx.x; i < kGTab; i += blockDim.x) tab[i] = score((float)d0 + (float)i);
+}
+__device__ __forceinline__ void fill_tab(double *tab, int32_t d0, ScoreTab st) {
+  for (int i = threadIdx.x; i < kGTab; i += blockDim.x) {
+    const int32_t d = d0 + i;
+    tab[i] = d < st.n ? st.g[d] : score_masked((double)d);
+  }
+}
 
 // Full off-diagonal tile of a big centre with the scores read from the
 // centre's table: gt[i] = score(k_v - 2 + i), the same FP32 expression the
 // other tiles evaluate, so every cluster gets the same score bits. roff =
 // k_p - 2 for this lane's row, kq = degree of its column at step 0; every
 // index roff + kq of the tile must lie in the table (checked by the caller).
-// Same result layout as tile<T, false, false>; used by the FP32 path.
+// Same result layout as tile<T, false, false>.
 // The table is addressed by byte offsets idx_s(l) = 4 (roff(l) + kq(l + s)).
 // The lane that reads column q at step s reads q + 1 at step s + 1, so
 // idx_{s+1} = rot(idx_s) + 4 (roff - rot(roff)): one integer add with the
 // rotation folded in (v_add_u32_dpp), as for the cluster degree of tile().
 // The difference 4 (roff - rot(roff)) is formed in FP32 (exact: below 2^24):
 // folded into an integer v_subrev_u32_dpp it came out negated on the device.
+// FP64 tables hold doubles: the same with 8-byte steps.
 template <typename T>
-__device__ __forceinline__ void tile_tab(int32_t roff, int32_t kq, int32_t D, const float *gt,
-                                         T &Rt, T &C) {
+__device__ __forceinline__ void tile_tab(int32_t roff, int32_t kq, int32_t D, const T *gt, T &Rt,
+                                         T &C) {
   Rt = T(0);
   C = T(0);
   const char *base = reinterpret_cast<const char *>(gt);
-  int32_t idx = 4 * (roff + kq);
+  int32_t idx = (int32_t)sizeof(T) * (roff + kq);
 #pragma unroll 8
   for (int s = 0; s < 64; ++s) {
-    const T g = *reinterpret_cast<const float *>(base + idx);
+    const T g = *reinterpret_cast<const T *>(base + idx);
     Rt += g;
     C = rot1(C) + g;
     idx = rot1i(idx) + D;
   }
 }
-// the index step 4 (roff - rot(roff)) of tile_tab for this lane's row
-__device__ __forceinline__ int32_t tab_step(int32_t roff) {
-  const float r4 = (float)(4 * roff);
-  return (int32_t)(r4 - rot1(r4));
+// the index step of tile_tab for this lane's row: sizeof(T) (roff - rot(roff))
+template <typename T> __device__ __forceinline__ int32_t tab_step(int32_t roff) {
+  const float r = (float)((int32_t)sizeof(T) * roff);
+  return (int32_t)(r - rot1(r));
 }
-template <typename T>
-__device__ __forceinline__ void tile_tab(int32_t roff, int32_t kq, const float *gt, T &Rt, T &C) {
-  tile_tab<T>(roff, kq, tab_step(roff), gt, Rt, C);
+static_assert(8LL * kMaxDegree < (1 << 24), "table offsets must be exact in FP32");
+
+// The diagonal and masked forms of tile() with FP64 scores from a table:
+// tab[i] = score(off + i), read at every cluster degree d >= 1 of the tile
+// (the caller checks that the largest lies in it); cp = k_v + k_p - 4 or kNegI,
+// kq = this lane's column degree at step 0 or kNegI, as integers. The row step
+// is formed in FP32 for the reason given at tile_tab.
+template <bool DIAG>
+__device__ __forceinline__ void tile_tab_masked(int32_t cp, int32_t kq, int32_t off,
+                                                const double *tab, double &Rt, double &C) {
+  const int lane = threadIdx.x & 63;
+  Rt = 0.0;
+  C = 0.0;
+  int32_t d = cp + kq;
+  const int32_t D = (int32_t)((float)cp - rot1((float)cp));
+#pragma unroll 4
+  for (int s = DIAG ? 1 : 0; s < (DIAG ? 33 : 64); ++s) {
+    if (DIAG) d = rot1i(d) + D;
+    const double t = tab[max(d - off, 0)];
+    bool on = d >= 1;
+    if (DIAG && s == 32) on = on && lane < 32;
+    const double g = on ? t : 0.0;
+    Rt += g;
+    C = rot1(C) + g;
+    if (!DIAG) d = rot1i(d) + D;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -265,13 +315,16 @@ template <int S> __device__ __forceinline__ double rot_seg(double x) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-// one group of 64/S centres (list positions gi*PER ..) on a wavefront
+// one group of 64/S centres (list positions gi*PER ..) on a wavefront. tab
+// (FP64, or null): score(d) for d < ntab in LDS; a group whose cluster degrees
+// all lie below ntab reads it.
 template <typename T, int S>
 __device__ __forceinline__ void pairs_seg_group(const int32_t *__restrict__ row_ptr,
                                                 const int32_t *__restrict__ deg,
                                                 const int2 *__restrict__ adj2,
                                                 const int32_t *__restrict__ list, int64_t count,
-                                                int64_t gi, void *__restrict__ R) {
+                                                int64_t gi, void *__restrict__ R,
+                                                const T *tab = nullptr, int32_t ntab = 0) {
   constexpr int PER = 64 / S;
   const int lane = threadIdx.x & 63;
   const int seg = lane / S, j = lane & (S - 1);
@@ -281,17 +334,41 @@ __device__ __forceinline__ void pairs_seg_group(const int32_t *__restrict__ row_
   const int32_t k = have ? deg[v] : 0;
   const int32_t base = have ? row_ptr[v] : 0;
   const bool valid = j < k;
-  const T kp = valid ? (T)adj2[base + j].y : T(0);
-  const T cp = valid ? (T)(k - 4) + kp : (T)kNegF;
-  T kq = valid ? kp : (T)kNegF;
+  const int32_t kpi = valid ? adj2[base + j].y : 0;
   T Rt = T(0), C = T(0);
+  bool fits = false;
+  if (tab) {
+    // the largest row term plus the largest column degree of the wavefront
+    int32_t mr = valid ? k - 4 + kpi : 0, mc = kpi;
+    for (int o = 32; o > 0; o >>= 1) {
+      mr = max(mr, __shfl_xor(mr, o, 64));
+      mc = max(mc, __shfl_xor(mc, o, 64));
+    }
+    fits = __builtin_amdgcn_readfirstlane(mr + mc) < ntab;
+  }
+  if (fits) {
+    const int32_t cp = valid ? k - 4 + kpi : kNegI;
+    int32_t kq = valid ? kpi : kNegI;
 #pragma unroll 4
-  for (int s = 1; s <= S / 2; ++s) {
-    kq = rot_seg<S>(kq);
-    T g = score_masked(cp + kq);
-    if (s == S / 2) g = j < S / 2 ? g : T(0);
-    Rt += g;
-    C = rot_seg<S>(C) + g;
+    for (int s = 1; s <= S / 2; ++s) {
+      kq = rot_seg_i<S>(kq);
+      T g = tab[max(cp + kq, 0)];  // entry 0 is 0: masked rows and columns
+      if (s == S / 2) g = j < S / 2 ? g : T(0);
+      Rt += g;
+      C = rot_seg<S>(C) + g;
+    }
+  } else {
+    const T kp = (T)kpi;
+    const T cp = valid ? (T)(k - 4) + kp : (T)kNegF;
+    T kq = valid ? kp : (T)kNegF;
+#pragma unroll 4
+    for (int s = 1; s <= S / 2; ++s) {
+      kq = rot_seg<S>(kq);
+      T g = score_masked(cp + kq);
+      if (s == S / 2) g = j < S / 2 ? g : T(0);
+      Rt += g;
+      C = rot_seg<S>(C) + g;
+    }
   }
   // column (j + S/2) mod S is in C of this lane; bring column j home
   const T Cl = __shfl_xor(C, S / 2, 64);
@@ -303,47 +380,53 @@ __device__ __forceinline__ void pairs_seg_group(const int32_t *__restrict__ row_
   }
 }
 
-template <typename T, int S>
-__global__ __launch_bounds__(256) void k_pairs_small(const int32_t *__restrict__ row_ptr,
-                                                     const int32_t *__restrict__ deg,
-                                                     const int2 *__restrict__ adj2,
-                                                     const int32_t *__restrict__ list,
-                                                     int64_t count, void *__restrict__ R) {
-  constexpr int PER = 64 / S;
-  const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
-  const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-  const int64_t groups = (count + PER - 1) / PER;
-  for (int64_t gi = wave; gi < groups; gi += nwaves)
-    pairs_seg_group<T, S>(row_ptr, deg, adj2, list, count, gi, R);
-}
-
 // ---------------------------------------------------------------------------
 // tiny centres (k <= 8): one lane per centre, all C(k, 2) pairs in registers.
 // With a few pairs per centre, a segment per centre would spend its time on
 // the dependent loads of every centre; a lane keeps 64 centres in flight per
 // wavefront. Rows past k are clamped to valid neighbours and masked.
 // ---------------------------------------------------------------------------
+// tab (FP64, or null): score(d) for d < ntab in LDS, read when the lane's
+// cluster degrees all lie below ntab.
 template <typename T>
 __device__ __forceinline__ void pairs_lane_one(const int32_t *__restrict__ row_ptr,
                                                const int32_t *__restrict__ deg,
                                                const int2 *__restrict__ adj2, int32_t v,
-                                               void *__restrict__ R) {
+                                               void *__restrict__ R, const T *tab = nullptr,
+                                               int32_t ntab = 0) {
   constexpr int K = kSmallLaneMax;
   const int32_t k = deg[v], base = row_ptr[v];  // 2 <= k <= K
-  T kp[K];
+  int32_t kp[K];
+  int32_t mx = 0;
 #pragma unroll
-  for (int p = 0; p < K; ++p) kp[p] = (T)adj2[base + (p < k ? p : k - 1)].y;
-  const T c = (T)(k - 4);
+  for (int p = 0; p < K; ++p) {
+    kp[p] = adj2[base + (p < k ? p : k - 1)].y;
+    mx = max(mx, kp[p]);
+  }
   T r[K];
 #pragma unroll
   for (int p = 0; p < K; ++p) r[p] = T(0);
+  if (tab && k - 4 + 2 * mx < ntab) {
+    // (every member has degree >= 1 and k >= 2, so no degree is negative)
 #pragma unroll
-  for (int p = 0; p < K; ++p) {
+    for (int p = 0; p < K; ++p) {
 #pragma unroll
-    for (int q = p + 1; q < K; ++q) {
-      const T g = q < k ? score_masked(c + kp[p] + kp[q]) : T(0);
-      r[p] += g;
-      r[q] += g;
+      for (int q = p + 1; q < K; ++q) {
+        const T g = q < k ? tab[k - 4 + kp[p] + kp[q]] : T(0);
+        r[p] += g;
+        r[q] += g;
+      }
+    }
+  } else {
+    const T c = (T)(k - 4);
+#pragma unroll
+    for (int p = 0; p < K; ++p) {
+#pragma unroll
+      for (int q = p + 1; q < K; ++q) {
+        const T g = q < k ? score_masked(c + (T)kp[p] + (T)kp[q]) : T(0);
+        r[p] += g;
+        r[q] += g;
+      }
     }
   }
 #pragma unroll
@@ -356,15 +439,52 @@ __device__ __forceinline__ void pairs_lane_one(const int32_t *__restrict__ row_p
   }
 }
 
+// Centres of degree <= 64, all bins in one launch (they are short: a launch
+// each left the device half empty and cost more than the work on small
+// graphs). Work is handed out by wavefront: segments of 64, 32, 16 lanes, then
+// 64 tiny centres. FP64 keeps scores of the first cluster degrees in LDS
+// (64 KB), so its grid is a round of workgroups that each load the table once:
+// BA n = 1M, m = 5 in FP64 135 us, 345 with logs and a launch per bin (with
+// registers held to 64 for twice the wavefronts: 160).
+struct SmallArgs {
+  const int32_t *row_ptr, *deg;
+  const int2 *adj2;
+  const int32_t *list[4];  // tiny, 16, 32, 64 lanes
+  int64_t n[4];
+  void *R;
+};
+template <typename T> constexpr int kSmallThreads = std::is_same<T, float>::value ? 256 : 1024;
+
 template <typename T>
-__global__ __launch_bounds__(256) void k_pairs_lane(const int32_t *__restrict__ row_ptr,
-                                                    const int32_t *__restrict__ deg,
-                                                    const int2 *__restrict__ adj2,
-                                                    const int32_t *__restrict__ list,
-                                                    int64_t count, void *__restrict__ R) {
-  for (int64_t it = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; it < count;
-       it += (int64_t)gridDim.x * blockDim.x)
-    pairs_lane_one<T>(row_ptr, deg, adj2, list[it], R);
+__global__ __launch_bounds__(kSmallThreads<T>) void k_pairs_small(SmallArgs A, const ScoreTab st) {
+  constexpr bool kTab = std::is_same<T, double>::value;
+  __shared__ T tab_s[kTab ? kGTab : 1];
+  const T *tab = nullptr;
+  int32_t ntab = 0;
+  if constexpr (kTab) {
+    if (st.g) {
+      ntab = min(st.n, (int32_t)kGTab);
+      for (int i = threadIdx.x; i < ntab; i += kSmallThreads<T>) tab_s[i] = st.g[i];
+      tab = tab_s;
+      __syncthreads();
+    }
+  }
+  const int64_t u3 = A.n[3], u2 = u3 + (A.n[2] + 1) / 2, u1 = u2 + (A.n[1] + 3) / 4,
+                u0 = u1 + (A.n[0] + 63) / 64;
+  const int64_t nwaves = (int64_t)gridDim.x * (kSmallThreads<T> / 64);
+  for (int64_t u = ((int64_t)blockIdx.x * kSmallThreads<T> + threadIdx.x) >> 6; u < u0;
+       u += nwaves) {
+    if (u < u3) {
+      pairs_seg_group<T, 64>(A.row_ptr, A.deg, A.adj2, A.list[3], A.n[3], u, A.R, tab, ntab);
+    } else if (u < u2) {
+      pairs_seg_group<T, 32>(A.row_ptr, A.deg, A.adj2, A.list[2], A.n[2], u - u3, A.R, tab, ntab);
+    } else if (u < u1) {
+      pairs_seg_group<T, 16>(A.row_ptr, A.deg, A.adj2, A.list[1], A.n[1], u - u2, A.R, tab, ntab);
+    } else {
+      const int64_t i = (u - u1) * 64 + (threadIdx.x & 63);
+      if (i < A.n[0]) pairs_lane_one<T>(A.row_ptr, A.deg, A.adj2, A.list[0][i], A.R, tab, ntab);
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -384,12 +504,13 @@ __device__ __forceinline__ T col_degree(const int2 *adj2, int32_t base, int32_t 
 // the nb x 64 degrees of the blocks (filled here, behind a barrier).
 // On return (after the final barrier), wavefront w's lanes hold in `out` the
 // complete sum for index 64*(blk0+w)+lane over all pairs inside this range.
-// gtab (FP32, rows in ascending degree order, or null): the centre's score
-// table; full off-diagonal tiles whose largest degrees fit read it.
+// gtab (rows in ascending degree order, or null): the centre's scores from
+// cluster degree k_v - 2 on, glim of them; full off-diagonal tiles whose
+// largest degrees fit read it.
 template <typename T>
 __device__ void diag_super(const int2 *adj2, int32_t base, int32_t k, T kv4, int blk0, int nb,
                            T (*parts)[9][64], int w, Acc<T> &out, int32_t *colk,
-                           const float *gtab = nullptr) {
+                           const T *gtab = nullptr, int32_t glim = kGTab) {
   const int lane = threadIdx.x & 63;
   const int ws = __builtin_amdgcn_readfirstlane(w);
   const int32_t p = 64 * (blk0 + ws) + lane;
@@ -409,23 +530,48 @@ __device__ void diag_super(const int2 *adj2, int32_t base, int32_t k, T kv4, int
     if (gtab) {
       const int32_t kp_max = __builtin_amdgcn_readlane(kpi, 63);
       bool fit = false;
-      if (lane < nb && 64 * (blk0 + lane + 1) <= k) fit = kp_max + colk[64 * lane + 63] - 2 < kGTab;
+      if (lane < nb && 64 * (blk0 + lane + 1) <= k) fit = kp_max + colk[64 * lane + 63] - 2 < glim;
       nfit = __popcll(__ballot(fit));
     }
-    const int32_t Dt = gtab ? tab_step((rvalid ? kpi : 0) - 2) : 0;
+    const int32_t Dt = gtab ? tab_step<T>((rvalid ? kpi : 0) - 2) : 0;
+    // FP64: diagonal and masked tiles that fit read the table too (the last
+    // valid row and column have the largest degrees; kNegI where none is)
+    constexpr bool kTabAll = std::is_same<T, double>::value;
+    const int32_t kv = (int32_t)kv4 + 4, cpi = rvalid ? kv - 4 + kpi : kNegI;
+    int32_t kr_max = kpi;
+    if (kTabAll && gtab)
+      for (int o = 32; o > 0; o >>= 1) kr_max = max(kr_max, __shfl_xor(kr_max, o, 64));
     const T Dd = cp - rot1(cp);
     int c = ws;  // column block of round dl: (w + dl) mod nb
     for (int dl = 0; dl <= half; ++dl) {
       if (dl > 0 && dl == half && (nb & 1) == 0 && ws >= half) break;
       T Rt, C;
       if (dl == 0) {
-        const T kq = rvalid ? kp : (T)kNegF;
-        tile<T, true, true>(cp, kq, Rt, C);
+        bool tabbed = false;
+        if constexpr (kTabAll) {
+          if (gtab && __builtin_amdgcn_readfirstlane(2 * kr_max - 2) < glim) {
+            tabbed = true;
+            tile_tab_masked<true>(cpi, kpi, kv - 2, gtab, Rt, C);
+          }
+        }
+        if (!tabbed) tile<T, true, true>(cp, rvalid ? kp : (T)kNegF, Rt, C);
         parts[c][0][(lane + 32) & 63] = C;
       } else {
         const int32_t kq = colk[64 * c + lane];
         const bool masked = ragged && (c == nb - 1 || ws == nb - 1) && (blk0 + nb) * 64 > k;
-        if (masked) {
+        bool tabbed = false;
+        if constexpr (kTabAll) {
+          if (masked && gtab) {
+            int32_t kc_max = kq;
+            for (int o = 32; o > 0; o >>= 1) kc_max = max(kc_max, __shfl_xor(kc_max, o, 64));
+            if (__builtin_amdgcn_readfirstlane(kr_max + kc_max - 2) < glim) {
+              tabbed = true;
+              tile_tab_masked<false>(cpi, kq, kv - 2, gtab, Rt, C);
+            }
+          }
+        }
+        if (tabbed) {
+        } else if (masked) {
           tile<T, false, true>(cp, (T)kq, Rt, C);
         } else if (c < nfit) {
           tile_tab<T>((rvalid ? kpi : 0) - 2, kq, Dt, gtab, Rt, C);
@@ -539,7 +685,8 @@ __device__ __forceinline__ void pairs_mid_group(const int32_t *__restrict__ row_
                                                 const int2 *__restrict__ adj2,
                                                 const int32_t *__restrict__ list, int64_t count,
                                                 int64_t gi, void *__restrict__ R,
-                                                MidLds<T, G, WPG> &lds) {
+                                                MidLds<T, G, WPG> &lds,
+                                                const T *tab = nullptr, int32_t ntab = 0) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int grp = w / WPG, wl = w % WPG;
   const int64_t it = gi * G + grp;
@@ -557,7 +704,8 @@ __device__ __forceinline__ void pairs_mid_group(const int32_t *__restrict__ row_
                         out, lds.colk + 64 * WPG * grp);
   else
     diag_super<T>(adj2, base, k, (T)(k - 4), 0, nb, lds.parts[grp], wl, out,
-                  lds.colk + 64 * WPG * grp);
+                  lds.colk + 64 * WPG * grp, tab && have ? tab + (k - 2) : nullptr,
+                  ntab - (k - 2));
   const int32_t p = 64 * wl + lane;
   if (wl < nb && p < k) out.store_arc(R, base + p);
   __syncthreads();
@@ -573,6 +721,39 @@ __global__ __launch_bounds__(64 * WPG) void k_pairs_mid(const int32_t *__restric
   __shared__ MidLds<T, 1, WPG> lds;
   for (int64_t gi = blockIdx.x; gi < count; gi += gridDim.x)
     pairs_mid_group<T, 1, WPG>(row_ptr, deg, adj2, list, count, gi, R, lds);
+}
+
+// FP64: every class in one launch of 16-wavefront workgroups, 1, 2 or 4
+// centres each by class, that take items in turn (largest first) and keep
+// score(d) of the first kGTab cluster degrees in LDS (64 KB; 140 KB in all,
+// one workgroup per CU). Full tiles that fit read it, a workgroup loads it
+// once. BA n = 1M, m = 5: 118 us for the three classes, 733 with logs and
+// a launch per class.
+__global__ __launch_bounds__(1024) void k_pairs_mid_tab(
+    const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ deg,
+    const int2 *__restrict__ adjs, const int32_t *__restrict__ l0, int64_t n0,
+    const int32_t *__restrict__ l1, int64_t n1, const int32_t *__restrict__ l2, int64_t n2,
+    void *__restrict__ R, const ScoreTab st) {
+  __shared__ double tab[kGTab];
+  __shared__ __align__(16) unsigned char pool[sizeof(MidLds<double, 1>)];
+  static_assert(sizeof(MidLds<double, 2>) <= sizeof(pool) && sizeof(MidLds<double, 4>) <= sizeof(pool),
+                "one pool for every class");
+  const int32_t ntab = st.g ? min(st.n, (int32_t)kGTab) : 0;
+  for (int i = threadIdx.x; i < ntab; i += 1024) tab[i] = st.g[i];
+  __syncthreads();
+  const double *t = ntab > 0 ? tab : nullptr;
+  const int64_t i1 = n2 + (n1 + 1) / 2, i0 = i1 + (n0 + 3) / 4;
+  for (int64_t it = blockIdx.x; it < i0; it += gridDim.x) {
+    if (it < n2)
+      pairs_mid_group<double, 1>(row_ptr, deg, adjs, l2, n2, it, R,
+                                 *reinterpret_cast<MidLds<double, 1> *>(pool), t, ntab);
+    else if (it < i1)
+      pairs_mid_group<double, 2>(row_ptr, deg, adjs, l1, n1, it - n2, R,
+                                 *reinterpret_cast<MidLds<double, 2> *>(pool), t, ntab);
+    else
+      pairs_mid_group<double, 4>(row_ptr, deg, adjs, l0, n0, it - i1, R,
+                                 *reinterpret_cast<MidLds<double, 4> *>(pool), t, ntab);
+  }
 }
 
 // mid centres into their classes (order within a class is not fixed; every
@@ -610,19 +791,20 @@ __global__ __launch_bounds__(256) void k_mid_split(const int32_t *__restrict__ d
 // degree)). record layout, by sorted position:
 //                [0, 1024) row part (for P == Q: complete in-range sums),
 //                [1024, 2048) column part (P < Q only).
-// In the FP32 path a full off-diagonal 64 x 64 tile whose largest row and
-// column degrees satisfy k_p + k_q - 2 < kGTab reads its scores from an LDS
-// table of score(k_v - 2 + i), i < kGTab, built once per centre and
-// workgroup: one LDS read in place of a v_log_f32 and a multiply. In
+// A full off-diagonal 64 x 64 tile whose largest row and column degrees
+// satisfy k_p + k_q - 2 < kGTab reads its scores from an LDS table of
+// score(k_v - 2 + i), i < kGTab, built once per centre and workgroup: one LDS
+// read in place of a v_log_f32 and a multiply, or of the some 90 instructions
+// of d log d in FP64 (BA n = 1M, m = 5 in FP64: 49 us, 650 with logs). In
 // degree order that holds for most tiles; the others take the log.
 // Column partials of an off-diagonal super-tile: in round dl wavefront w
 // takes column block c = (w + dl) mod nbQ, so within a window of kColWin
 // rounds the partial of (c, round, w / nbQ) has one writer; a barrier
 // between windows orders the adds into the same accumulator, and the
 // column sum adds the accumulators in a fixed order (reproducible).
-// LDS: table (32 KB), the larger of the diagonal partials (36 KB) and the
-// column accumulators (at most 30 KB), and the super-tile's column degrees
-// (4 KB), so that two workgroups fit on a compute unit.
+// LDS (FP32): table (32 KB), the larger of the diagonal partials (36 KB) and
+// the column accumulators (at most 30 KB), and the super-tile's column degrees
+// (4 KB), so that two workgroups fit on a compute unit; FP64: 140 KB, one.
 // ---------------------------------------------------------------------------
 constexpr int kColWin = 4;  // rounds between the barriers of the column adds
 
@@ -638,8 +820,7 @@ __host__ __device__ constexpr int col_groups_max() {
 }
 
 template <typename T> struct BigLds {
-  static constexpr bool kTab = std::is_same<T, float>::value;
-  static constexpr int kTabBytes = kTab ? kGTab * 4 : 0;
+  static constexpr int kTabBytes = kGTab * (int)sizeof(T);
   static constexpr int kDiagBytes = kBlocksPerSuper * 9 * 64 * (int)sizeof(T);
   static constexpr int kColBytes = col_groups_max() * kColWin * 64 * (int)sizeof(T);
   static constexpr int kPartBytes = kDiagBytes > kColBytes ? kDiagBytes : kColBytes;
@@ -650,7 +831,7 @@ template <typename T> struct BigLds {
 
 // One super-tile on a 16-wavefront workgroup (every thread calls it: it holds
 // workgroup barriers). lds: BigLds<T>::kBytes, the scores of the current
-// centre (FP32 path) first, at address 0, so that a table read needs no base
+// centre first, at address 0, so that a table read needs no base
 // added; then the partials. tab_v: the centre whose scores lds holds (-1:
 // none), kept by the caller across calls.
 template <typename T>
@@ -659,9 +840,9 @@ __device__ __forceinline__ void pairs_big_tile(const int32_t *__restrict__ row_p
                                                const int2 *__restrict__ adjs,
                                                const BigCentre *__restrict__ big,
                                                const TileItem ti, void *__restrict__ rec,
-                                               unsigned char *lds, int32_t &tab_v) {
-  constexpr bool kTab = BigLds<T>::kTab;
-  float *gtab = reinterpret_cast<float *>(lds);
+                                               unsigned char *lds, int32_t &tab_v,
+                                               const ScoreTab st = ScoreTab()) {
+  T *gtab = reinterpret_cast<T *>(lds);
   T(*parts)[9][64] = reinterpret_cast<T(*)[9][64]>(lds + BigLds<T>::kTabBytes);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int2 *adj2 = adjs;
@@ -673,9 +854,8 @@ __device__ __forceinline__ void pairs_big_tile(const int32_t *__restrict__ row_p
   const int nbQ = min(kBlocksPerSuper, (k - kSuper * Q + 63) >> 6);
   const T kv4 = (T)(k - 4);
   if (P == Q) {
-    if (kTab && v != tab_v) {  // uniform: one centre per work item
-      const float d0 = (float)(k - 2);
-      for (int i = threadIdx.x; i < kGTab; i += blockDim.x) gtab[i] = score(d0 + (float)i);
+    if (v != tab_v) {  // uniform: one centre per work item
+      fill_tab(gtab, k - 2, st);
       tab_v = v;
     }
     zero_parts(&parts[0][0][0], kBlocksPerSuper * 9 * 64);
@@ -686,7 +866,7 @@ __device__ __forceinline__ void pairs_big_tile(const int32_t *__restrict__ row_p
     diag_super<T>(adj2, base, k, kv4, kBlocksPerSuper * P, nbQ,
                   reinterpret_cast<T(*)[9][64]>(&parts[0][0][0]), w, out,
                   reinterpret_cast<int32_t *>(lds + BigLds<T>::kTabBytes + BigLds<T>::kPartBytes),
-                  kTab ? gtab : nullptr);
+                  gtab);
     if (w < nbQ) out.store_rec(rec, rbase + 64 * w + lane);
   } else {
     // P < Q: all 16 row blocks of P are full
@@ -704,9 +884,8 @@ __device__ __forceinline__ void pairs_big_tile(const int32_t *__restrict__ row_p
       const int32_t q = kSuper * Q + i;
       colk[i] = q < k ? adj2[base + q].y : kNegI;
     }
-    if (kTab && v != tab_v) {  // uniform: one centre per work item
-      const float d0 = (float)(k - 2);
-      for (int i = threadIdx.x; i < kGTab; i += blockDim.x) gtab[i] = score(d0 + (float)i);
+    if (v != tab_v) {  // uniform: one centre per work item
+      fill_tab(gtab, k - 2, st);
       tab_v = v;
     }
     __syncthreads();
@@ -714,15 +893,12 @@ __device__ __forceinline__ void pairs_big_tile(const int32_t *__restrict__ row_p
     // k_p + k_q - 2 < kGTab at the largest row and column degrees (the last
     // lane of each block, as degrees ascend, so the blocks that fit are a
     // prefix)
-    int nfit = 0;
-    if (kTab) {
-      const int32_t kp_max = __shfl(kp, 63, 64);
-      const int nfull = ragged_q ? nbQ - 1 : nbQ;
-      bool fit = false;
-      if (lane < nfull) fit = kp_max + colk[64 * lane + 63] - 2 < kGTab;
-      nfit = __popcll(__ballot(fit));
-    }
-    const int32_t Dt = kTab ? tab_step(kp - 2) : 0;
+    const int32_t kp_max = __shfl(kp, 63, 64);
+    const int nfull = ragged_q ? nbQ - 1 : nbQ;
+    bool fit = false;
+    if (lane < nfull) fit = kp_max + colk[64 * lane + 63] - 2 < kGTab;
+    const int nfit = __popcll(__ballot(fit));
+    const int32_t Dt = tab_step<T>(kp - 2);
     const T Dd = cp - rot1(cp);
     Acc<T> out;
     T *mine = cacc + ((w / nbQ) * kColWin) * 64 + ((lane + 63) & 63);
@@ -730,7 +906,19 @@ __device__ __forceinline__ void pairs_big_tile(const int32_t *__restrict__ row_p
     for (int dl = 0; dl < nbQ; ++dl) {
       const int32_t kq = colk[64 * c + lane];
       T Rt, C;
-      if (ragged_q && c == nbQ - 1) {
+      bool tabbed = false;
+      if constexpr (std::is_same<T, double>::value) {
+        if (ragged_q && c == nbQ - 1) {
+          int32_t kc_max = kq;
+          for (int o = 32; o > 0; o >>= 1) kc_max = max(kc_max, __shfl_xor(kc_max, o, 64));
+          if (__builtin_amdgcn_readfirstlane(kp_max + kc_max - 2) < kGTab) {
+            tabbed = true;
+            tile_tab_masked<false>(k - 4 + kp, kq, k - 2, gtab, Rt, C);
+          }
+        }
+      }
+      if (tabbed) {
+      } else if (ragged_q && c == nbQ - 1) {
         tile<T, false, true>(cp, (T)kq, Rt, C);
       } else if (c < nfit) {
         tile_tab<T>(kp - 2, kq, Dt, gtab, Rt, C);
@@ -765,13 +953,14 @@ __global__ __launch_bounds__(1024) void k_pairs_big(const int32_t *__restrict__ 
                                                     const BigCentre *__restrict__ big,
                                                     const TileItem *__restrict__ tiles,
                                                     int64_t count, void *__restrict__ rec,
-                                                    const int32_t *__restrict__ agg_done) {
+                                                    const int32_t *__restrict__ agg_done,
+                                                    const ScoreTab st) {
   __shared__ __align__(16) unsigned char lds[BigLds<T>::kBytes];
   int32_t tab_v = -1;  // centre whose scores the table holds
   for (int64_t it = blockIdx.x; it < count; it += gridDim.x) {
     const TileItem ti = tiles[it];
     if (agg_done && agg_done[ti.big]) continue;  // uniform per workgroup
-    pairs_big_tile<T>(row_ptr, deg, adjs, big, ti, rec, lds, tab_v);
+    pairs_big_tile<T>(row_ptr, deg, adjs, big, ti, rec, lds, tab_v, st);
   }
 }
 
@@ -1141,22 +1330,32 @@ static hipError_t pairs_impl(const Graph &g, const Bins &b, void *R, void *recor
                              hipStream_t st, hipEvent_t ev_small, hipEvent_t ev_mid,
                              hipEvent_t ev_big, int32_t *agg_done) {
   static_assert(kSmallLaneMax == 8, "bin 0 holds centres of degree <= 8, one lane each");
-  if (b.n_smallb[0] > 0)
-    hipLaunchKernelGGL(k_pairs_lane<T>, dim3(capped((b.n_smallb[0] + 255) / 256, 1 << 16)),
-                       dim3(256), 0, st, g.row_ptr, g.deg, g.adj2, b.small[0], b.n_smallb[0], R);
-  if (b.n_smallb[1] > 0)
-    hipLaunchKernelGGL((k_pairs_small<T, 16>), dim3(capped((b.n_smallb[1] + 15) / 16, 1 << 20)),
-                       dim3(256), 0, st, g.row_ptr, g.deg, g.adj2, b.small[1], b.n_smallb[1], R);
-  if (b.n_smallb[2] > 0)
-    hipLaunchKernelGGL((k_pairs_small<T, 32>), dim3(capped((b.n_smallb[2] + 7) / 8, 1 << 20)),
-                       dim3(256), 0, st, g.row_ptr, g.deg, g.adj2, b.small[2], b.n_smallb[2], R);
-  if (b.n_smallb[3] > 0)
-    hipLaunchKernelGGL((k_pairs_small<T, 64>), dim3(capped((b.n_smallb[3] + 3) / 4, 1 << 20)),
-                       dim3(256), 0, st, g.row_ptr, g.deg, g.adj2, b.small[3], b.n_smallb[3], R);
+  constexpr bool kFp64 = std::is_same<T, double>::value;
+  const ScoreTab st64 = kFp64 ? ScoreTab{g.score64, g.n_score64} : ScoreTab{};
+  const int64_t waves = b.n_smallb[3] + (b.n_smallb[2] + 1) / 2 + (b.n_smallb[1] + 3) / 4 +
+                        (b.n_smallb[0] + 63) / 64;
+  if (waves > 0) {
+    SmallArgs A{g.row_ptr, g.deg, g.adj2, {}, {}, R};
+    for (int q = 0; q < 4; ++q) {
+      A.list[q] = b.small[q];
+      A.n[q] = b.n_smallb[q];
+    }
+    constexpr int kPer = kSmallThreads<T> / 64;
+    hipLaunchKernelGGL(k_pairs_small<T>,
+                       dim3(capped((waves + kPer - 1) / kPer, kFp64 ? 2 * kCUs : 1 << 20)),
+                       dim3(kSmallThreads<T>), 0, st, A, st64);
+  }
   if (ev_small) (void)hipEventRecord(ev_small, st);
   // class c holds centres of up to 4 << c blocks: one workgroup of that
   // many wavefronts each, over the degree-ordered rows (adjs), so that the
   // per-arc sums go out by sorted position like a big centre's
+  if constexpr (kFp64) {
+    const int64_t items = b.n_midc[2] + (b.n_midc[1] + 1) / 2 + (b.n_midc[0] + 3) / 4;
+    if (items > 0)
+      hipLaunchKernelGGL(k_pairs_mid_tab, dim3(capped(items, kCUs)), dim3(1024), 0, st, g.row_ptr,
+                         g.deg, g.adjs, b.midc[0], b.n_midc[0], b.midc[1], b.n_midc[1], b.midc[2],
+                         b.n_midc[2], R, st64);
+  } else {
   if (b.n_midc[0] > 0)
     hipLaunchKernelGGL((k_pairs_mid<T, 4>), dim3(capped(b.n_midc[0], 1 << 20)), dim3(256), 0,
                        st, g.row_ptr, g.deg, g.adjs, b.midc[0], b.n_midc[0], R);
@@ -1166,18 +1365,24 @@ static hipError_t pairs_impl(const Graph &g, const Bins &b, void *R, void *recor
   if (b.n_midc[2] > 0)
     hipLaunchKernelGGL((k_pairs_mid<T, 16>), dim3(capped(b.n_midc[2], 1 << 20)), dim3(1024), 0,
                        st, g.row_ptr, g.deg, g.adjs, b.midc[2], b.n_midc[2], R);
+  }
   if (ev_mid) (void)hipEventRecord(ev_mid, st);
   if (agg_done && b.n_big > 0)
     hipLaunchKernelGGL(k_pairs_agg<T>, dim3(capped(b.n_big, 1 << 16)), dim3(1024), 0, st,
                        g.row_ptr, g.deg, g.adjs, b.big, b.counters, agg_done, R);
   if (b.n_tiles > 0)
     hipLaunchKernelGGL(k_pairs_big<T>, dim3(capped(b.n_tiles, 1 << 20)), dim3(1024), 0, st,
-                       g.row_ptr, g.deg, g.adjs, b.big, b.tiles, b.n_tiles, records, agg_done);
+                       g.row_ptr, g.deg, g.adjs, b.big, b.tiles, b.n_tiles, records, agg_done, st64);
   if (ev_big) (void)hipEventRecord(ev_big, st);
   if (b.n_sblocks > 0)
     hipLaunchKernelGGL(k_arc_reduce<T>, dim3(capped(b.n_sblocks, 1 << 20)), dim3(256), 0, st,
                        g.row_ptr, g.deg, g.adjs, b.big, b.sblocks, b.n_sblocks, records, R,
                        agg_done);
+  return hipGetLastError();
+}
+
+hipError_t launch_score_table(double *t, int32_t n, hipStream_t st) {
+  hipLaunchKernelGGL(k_score_table, dim3(capped((n + 255) / 256, 4096)), dim3(256), 0, st, t, n);
   return hipGetLastError();
 }
 
