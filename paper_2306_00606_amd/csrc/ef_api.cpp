@@ -43,11 +43,14 @@ static int64_t max_device_bytes() {
   return v > 0 ? (int64_t)v : INT64_MAX;
 }
 
-// allocation accounted against EF_MAX_DEVICE_BYTES
-static ef_status dev_alloc(Graph &g, void **p, size_t bytes, const char *what) {
+// allocation accounted against EF_MAX_DEVICE_BYTES (`counted` bytes where given:
+// a block of several arrays counts them without the padding between)
+static ef_status dev_alloc(Graph &g, void **p, size_t bytes, const char *what,
+                           size_t counted = 0) {
   *p = nullptr;
   if (bytes == 0) bytes = 8;
-  if (g.owned_bytes + (int64_t)bytes > max_device_bytes()) {
+  if (counted == 0) counted = bytes;
+  if (g.owned_bytes + (int64_t)counted > max_device_bytes()) {
     set_error("%s: %zu bytes would exceed EF_MAX_DEVICE_BYTES", what, bytes);
     return EF_ERR_NOMEM;
   }
@@ -58,7 +61,7 @@ static ef_status dev_alloc(Graph &g, void **p, size_t bytes, const char *what) {
     set_error("%s: device allocation of %zu bytes failed", what, bytes);
     return EF_ERR_NOMEM;
   }
-  g.owned_bytes += (int64_t)bytes;
+  g.owned_bytes += (int64_t)counted;
   return EF_OK;
 }
 
@@ -66,6 +69,45 @@ static void dev_free(Graph &g, void *p, size_t bytes) {
   if (!p) return;
   (void)hipFree(p);
   g.owned_bytes -= (int64_t)(bytes ? bytes : 8);
+}
+
+// workspace slots
+enum {
+  WS_MAIN = 0,  // ef_compute's sums and records (ComputeWs), and the load's scratch
+  WS_FLAG, WS_BINS, WS_OUT, WS_BITMAP, WS_SEEDS, WS_UOUT, WS_TOPK, WS_SURR, WS_J3, WS_J3P, WS_J3L
+};
+
+// Byte offsets in WS_MAIN of one ef_compute call: per-arc sums, super-tile
+// records, flag list and bytes, output staging, triangle records and node sums
+// (cluster-centric only). One block: an allocation and a free of tens of
+// megabytes cost some 0.3 ms each.
+struct ComputeWs {
+  size_t R = 0, rec = 0, flag = 0, out = 0, Y = 0, Z = 0, ZT = 0, bytes = 0;
+};
+static ComputeWs compute_ws(const Graph &g, bool fp64, int64_t n_tiles, int64_t n_work,
+                            bool triangles) {
+  const size_t nnz = (size_t)std::max<int64_t>(g.nnz, 1), n = (size_t)std::max(g.n, 1),
+               nup = (size_t)std::max<int64_t>(g.nnz / 2, 1),
+               w = (size_t)std::max<int64_t>(n_work, 1);
+  const size_t sz = fp64 ? sizeof(double) : sizeof(float);  // a sum, and a record entry
+  ComputeWs L;
+  size_t p = 0;
+  auto take = [&](size_t b) {
+    const size_t r = p;
+    p += (b + 15) & ~(size_t)15;
+    return r;
+  };
+  L.R = take(sz * nnz);
+  L.rec = take(sz * kRecEntries * (size_t)std::max<int64_t>(n_tiles, 1));
+  L.flag = take((sizeof(int32_t) + 1) * w);
+  L.out = take((sizeof(double) + 2 * sizeof(int64_t)) * w);
+  if (triangles) {
+    L.Y = take(sizeof(TriSlot) * 2 * nup);
+    L.Z = take(sizeof(double) * n);  // FP32C: a float pair
+    L.ZT = take(sizeof(int64_t) * n);
+  }
+  L.bytes = p;
+  return L;
 }
 
 static ef_status ws_ensure(Graph &g, int slot, size_t bytes, const char *what) {
@@ -83,6 +125,13 @@ static ef_status ws_ensure(Graph &g, int slot, size_t bytes, const char *what) {
     dev_free(g, g.score64, sizeof(double) * (size_t)g.n_score64);
     g.score64 = nullptr;
     g.n_score64 = 0;
+    s = dev_alloc(g, &b.p, want, what);
+  }
+  if (s != EF_OK && slot != WS_MAIN && g.main_reserved && g.ws[WS_MAIN].p) {
+    // workspace that the load kept for a later ef_compute and nothing used yet
+    dev_free(g, g.ws[WS_MAIN].p, g.ws[WS_MAIN].bytes);
+    g.ws[WS_MAIN] = DevBuf{};
+    g.main_reserved = false;
     s = dev_alloc(g, &b.p, want, what);
   }
   if (s != EF_OK) return s;
@@ -162,17 +211,9 @@ ef_status ef_graph_free(ef_graph *h) {
     return EF_ERR_ARG;
   }
   Graph &g = h->g;
-  if (!g.borrowed) {
-    (void)hipFree(g.row_ptr);
-    (void)hipFree(g.col_idx);
-  }
-  void *arrays[] = {g.deg, g.src, g.rev, g.rrev, g.adj2, g.adjs, g.asum, g.qa, g.nbm, g.up_ptr, g.up_col, g.trec,
-                    g.up_deg, g.dn_ptr, g.dn, g.tri_zero, g.j3_seeds, g.j3_off,
-                    g.tri_rec0, g.tri_recL, g.tri_list[0], g.tri_list[1], g.tri_list[2], g.tri_list[3],
-                    g.tri_recB[1], g.tri_recB[2], g.fin_list,
-                    g.ps_list[0], g.ps_list[1], g.ps_list[2], g.ps_list[3], g.ps_list[4],
-                    g.d_counters, g.score64};
-  for (void *p : arrays)
+  void *blocks[] = {g.arena, g.lists, g.tri_zero, g.j3_seeds, g.j3_off, g.ps_list[0], g.ps_list[1],
+                    g.ps_list[2], g.ps_list[3], g.ps_list[4], g.score64};
+  for (void *p : blocks)
     if (p) (void)hipFree(p);
   for (auto &b : g.ws)
     if (b.p) (void)hipFree(b.p);
@@ -213,13 +254,13 @@ ef_status graph_load(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32
     return EF_ERR_OVERFLOW;
   }
   hipStream_t stream = (hipStream_t)hip_stream;
-  const bool devptr = (flags & EF_DEVICE_PTRS) != 0;
+  const bool devptr = (flags & EF_DEVICE_PTRS) != 0, validate = (flags & EF_VALIDATE) != 0;
   int dev = 0;
   ef_status st = EF_OK;
 
-  // host view of the CSR (needed for validation and for sizing work lists)
-  std::vector<int32_t> h_rp, h_ci;
-  const int32_t *hrp = row_ptr, *hci = col_idx;
+  // host view of the row offsets (bounds, and sizing of work lists)
+  std::vector<int32_t> h_rp;
+  const int32_t *hrp = row_ptr;
   if (devptr) {
     if ((st = check_device(&dev)) != EF_OK) return st;
     h_rp.resize((size_t)n + 1);
@@ -227,34 +268,65 @@ ef_status graph_load(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32
                              hipMemcpyDeviceToHost);
     if (e != hipSuccess) return hip_status(e, "copy row_ptr to host");
     hrp = h_rp.data();
-    if (flags & EF_VALIDATE) {
+  }
+  // The neighbour ids are checked by the preparation kernels (range always;
+  // with EF_VALIDATE order, self-loops and reverse arcs). host_check is the
+  // same check on the host, which names the first violation: run when the
+  // device finds one, and before any other error is returned, so that a bad
+  // CSR is reported as such whatever else fails.
+  auto host_check = [&]() -> ef_status {
+    std::vector<int32_t> h_ci;
+    const int32_t *hci = col_idx;
+    if (devptr) {
+      if (!validate) return EF_OK;
       h_ci.resize((size_t)std::max<int64_t>(nnz, 1));
       if (nnz > 0) {
-        e = hipMemcpy(h_ci.data(), col_idx, sizeof(int32_t) * (size_t)nnz, hipMemcpyDeviceToHost);
+        hipError_t e = hipMemcpy(h_ci.data(), col_idx, sizeof(int32_t) * (size_t)nnz,
+                                 hipMemcpyDeviceToHost);
         if (e != hipSuccess) return hip_status(e, "copy col_idx to host");
       }
       hci = h_ci.data();
     }
-  }
-  if (flags & EF_VALIDATE) {
-    st = ef_validate_csr(n, nnz, hrp, hci);
-    if (st != EF_OK) return st;
-  } else {
-    // Without the full validation the arrays must still be safe to index
-    // before any kernel reads them: offsets are checked here, neighbour ids
-    // here for host input and by a device pass for device input.
+    if (validate) return ef_validate_csr(n, nnz, hrp, hci);
     char msg[256] = "";
-    st = csr_check_bounds(n, nnz, hrp, devptr ? nullptr : hci, msg, sizeof(msg));
+    const ef_status s = csr_check_bounds(n, nnz, hrp, hci, msg, sizeof(msg));
+    if (s != EF_OK) set_error("ef_graph_load_csr: %s", msg);
+    return s;
+  };
+  // an error other than the CSR's own: the CSR's comes first
+  auto after_check = [&](auto report) -> ef_status {
+    const ef_status s = host_check();
+    return s != EF_OK ? s : report();
+  };
+  {
+    char msg[256] = "";
+    st = csr_check_bounds(n, nnz, hrp, nullptr, msg, sizeof(msg));
     if (st != EF_OK) {
-      set_error("ef_graph_load_csr: %s", msg);
+      set_error("%s: %s", validate ? "ef_validate_csr" : "ef_graph_load_csr", msg);
       return st;
     }
   }
+  ef_graph *h = new (std::nothrow) ef_graph();
+  if (!h) {
+    set_error("host allocation failed");
+    return EF_ERR_NOMEM;
+  }
+  Graph &g = h->g;
+  g.h_deg.resize((size_t)n);
   int32_t kmax = 0;
-  for (int32_t v = 0; v < n; ++v) kmax = std::max(kmax, hrp[v + 1] - hrp[v]);
+  int64_t n_over = 0;  // centres of degree > kSmallMax
+  for (int32_t v = 0; v < n; ++v) {
+    const int32_t k = hrp[v + 1] - hrp[v];
+    g.h_deg[(size_t)v] = k;
+    kmax = std::max(kmax, k);
+    n_over += k > kSmallMax;
+  }
   if (kmax > kMaxDegree) {
-    set_error("max degree %d exceeds %d (exact cluster degrees / int64 sums)", kmax, kMaxDegree);
-    return EF_ERR_OVERFLOW;
+    delete h;
+    return after_check([&] {
+      set_error("max degree %d exceeds %d (exact cluster degrees / int64 sums)", kmax, kMaxDegree);
+      return EF_ERR_OVERFLOW;
+    });
   }
   // the arrays every graph holds, against EF_MAX_DEVICE_BYTES, before the
   // device is touched (graph-dependent arrays are accounted as allocated)
@@ -264,201 +336,199 @@ ef_status graph_load(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32
     const int64_t need = (devptr ? 0 : 4 * n1 + 4 * m) + 4 * nn + (4 + 4 + 8 + 4) * m +
                          (8 + 16) * nn + 2 * 4 * n1 + (4 + 4 + 16) * mu + 256;
     if (need > max_device_bytes()) {
-      set_error("ef_graph_load_csr: the graph's %lld device bytes would exceed "
-                "EF_MAX_DEVICE_BYTES", (long long)need);
-      return EF_ERR_NOMEM;
+      delete h;
+      return after_check([&] {
+        set_error("ef_graph_load_csr: the graph's %lld device bytes would exceed "
+                  "EF_MAX_DEVICE_BYTES", (long long)need);
+        return EF_ERR_NOMEM;
+      });
     }
   }
-  if (!devptr && (st = check_device(&dev)) != EF_OK) return st;
-
-  ef_graph *h = new (std::nothrow) ef_graph();
-  if (!h) {
-    set_error("host allocation failed");
-    return EF_ERR_NOMEM;
+  if (!devptr && check_device(&dev) != EF_OK) {
+    delete h;
+    return after_check([&] { return check_device(&dev); });
   }
-  Graph &g = h->g;
   g.dev = dev;
   g.n = n;
   g.nnz = nnz;
-  g.borrowed = devptr;
-  const size_t N1 = (size_t)n + 1, NNZ = (size_t)std::max<int64_t>(nnz, 1);
-  const size_t NUP = (size_t)std::max<int64_t>(nnz / 2, 1);
-#define ALLOC(ptr, bytes, what)                                   \
-  do {                                                            \
-    st = dev_alloc(g, (void **)&(ptr), (bytes), what);            \
-    if (st != EF_OK) { ef_graph_free(h); return st; }             \
-  } while (0)
-  if (devptr) {
-    g.row_ptr = const_cast<int32_t *>(row_ptr);
-    g.col_idx = const_cast<int32_t *>(col_idx);
-  } else {
-    ALLOC(g.row_ptr, sizeof(int32_t) * N1, "row_ptr");
-    ALLOC(g.col_idx, sizeof(int32_t) * NNZ, "col_idx");
-    hipError_t e = hipMemcpyAsync(g.row_ptr, row_ptr, sizeof(int32_t) * N1,
-                                  hipMemcpyHostToDevice, stream);
-    if (e == hipSuccess && nnz > 0)
-      e = hipMemcpyAsync(g.col_idx, col_idx, sizeof(int32_t) * (size_t)nnz,
-                         hipMemcpyHostToDevice, stream);
-    if (e != hipSuccess) {
-      ef_graph_free(h);
-      return hip_status(e, "copy CSR to device");
-    }
-  }
-  ALLOC(g.deg, sizeof(int32_t) * std::max<size_t>(n, 1), "deg");
-  ALLOC(g.src, sizeof(int32_t) * NNZ, "src");
-  ALLOC(g.rev, sizeof(int32_t) * NNZ, "rev");
-  ALLOC(g.rrev, sizeof(int32_t) * NNZ, "reverse sum index");
-  ALLOC(g.adj2, sizeof(int2) * NNZ, "adj2");
-  ALLOC(g.asum, sizeof(int64_t) * std::max<size_t>(n, 1), "asum");
-  ALLOC(g.qa, sizeof(longlong2) * std::max<size_t>(n, 1), "qa");
-  ALLOC(g.nbm, sizeof(NbrMoments) * std::max<size_t>(n, 1), "neighbour degree moments");
-  ALLOC(g.up_ptr, sizeof(int32_t) * N1, "up_ptr");
-  ALLOC(g.up_col, sizeof(int32_t) * NUP, "up_col");
-  ALLOC(g.up_deg, sizeof(int32_t) * NUP, "up_deg");
-  ALLOC(g.trec, sizeof(int32_t) * NNZ, "triangle record index");
-  ALLOC(g.dn_ptr, sizeof(int32_t) * N1, "dn_ptr");
-  ALLOC(g.dn, sizeof(int4) * NUP, "triangle segments");
-  ALLOC(g.d_counters, sizeof(int32_t) * 64, "counters");
-  if (devptr && !(flags & EF_VALIDATE) && nnz > 0) {
-    // neighbour ids of borrowed device arrays: in range before any kernel
-    // indexes with them
-    int32_t bad = 0;
-    hipError_t e = launch_check_cols(g.col_idx, nnz, n, g.d_counters, stream);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(&bad, g.d_counters, sizeof(int32_t), hipMemcpyDeviceToHost, stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(stream);
-    if (e != hipSuccess) {
-      ef_graph_free(h);
-      return hip_status(e, "check neighbour ids");
-    }
-    if (bad) {
-      ef_graph_free(h);
-      set_error("ef_graph_load_csr: a neighbour id is outside [0, %d)", n);
-      return EF_ERR_RANGE;
-    }
-  }
-  // tail entries walked at each node by the triangle pass (binning)
-  std::vector<int64_t> h_work((size_t)n);
-  {
-    int32_t *tmp = nullptr;
-    int64_t *work = nullptr;
-    const size_t tmp_bytes = sizeof(int32_t) * (size_t)graph_prep_tmp_len((int64_t)NNZ);
-    const size_t work_bytes = sizeof(int64_t) * std::max<size_t>(n, 1);
-    ALLOC(tmp, tmp_bytes, "preprocessing scratch");
-    st = dev_alloc(g, (void **)&work, work_bytes, "preprocessing scratch");
-    if (st != EF_OK) {
-      dev_free(g, tmp, tmp_bytes);
-      ef_graph_free(h);
-      return st;
-    }
-    bool not_symmetric = false;
-    hipError_t e = launch_graph_prep(g, tmp, work, not_symmetric, stream);
-    // the reverse-sum index starts as rev; big centres' rows remap it below
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(g.rrev, g.rev, sizeof(int32_t) * (size_t)nnz, hipMemcpyDeviceToDevice,
-                         stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(stream);
-    if (e == hipSuccess && not_symmetric) {
-      dev_free(g, work, work_bytes);
-      dev_free(g, tmp, tmp_bytes);
-      ef_graph_free(h);
-      set_error("the CSR is not simple and symmetric (load with EF_VALIDATE for details)");
-      return EF_ERR_NOT_SYMMETRIC;
-    }
-    if (e == hipSuccess) e = graph_zero_count(g, tmp, g.n_tri_zero);
-    if (e == hipSuccess) {
-      st = dev_alloc(g, (void **)&g.tri_zero,
-                     sizeof(int32_t) * (size_t)std::max<int64_t>(g.n_tri_zero, 1), "zero slots");
-      if (st == EF_OK) {
-        e = launch_zero_list(g, tmp, stream);
-        if (e == hipSuccess && n > 0)
-          e = hipMemcpyAsync(h_work.data(), work, sizeof(int64_t) * (size_t)n,
-                             hipMemcpyDeviceToHost, stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(stream);
-      }
-    }
-    dev_free(g, work, work_bytes);
-    dev_free(g, tmp, tmp_bytes);
-    if (st != EF_OK) {
-      ef_graph_free(h);
-      return st;
-    }
-    if (e != hipSuccess) {
-      ef_graph_free(h);
-      return hip_status(e, "graph preprocessing");
-    }
-  }
-  std::vector<int32_t> h_dn_ptr(N1);
-  {
-    hipError_t e = hipMemcpy(h_dn_ptr.data(), g.dn_ptr, sizeof(int32_t) * N1,
-                             hipMemcpyDeviceToHost);
-    if (e != hipSuccess) {
-      ef_graph_free(h);
-      return hip_status(e, "copy dn_ptr to host");
-    }
-  }
-  // host copies: degrees and |up(u)|
-  g.h_deg.resize((size_t)n);
-  for (int32_t v = 0; v < n; ++v) g.h_deg[v] = hrp[v + 1] - hrp[v];
-  std::vector<int32_t> h_up_ptr(N1);
-  {
-    hipError_t e = hipMemcpy(h_up_ptr.data(), g.up_ptr, sizeof(int32_t) * N1,
-                             hipMemcpyDeviceToHost);
-    if (e != hipSuccess) {
-      ef_graph_free(h);
-      return hip_status(e, "copy up_ptr to host");
-    }
-  }
-  g.h_up_len.resize((size_t)n);
   ef_graph_info &inf = g.info;
   inf.n = n;
   inf.nnz = nnz;
   inf.max_degree = kmax;
   inf.up_arcs = nnz / 2;
-  // degree-ordered rows of the mid and big centres (the tile pair loops,
-  // which store their per-arc sums by sorted position)
+  const size_t N1 = (size_t)n + 1, NN = (size_t)std::max(n, 1),
+               NNZ = (size_t)std::max<int64_t>(nnz, 1),
+               NUP = (size_t)std::max<int64_t>(nnz / 2, 1);
+  // every array of known size in one block; first what the host reads back
   {
-    std::vector<int32_t> hb;
-    for (int32_t v = 0; v < n; ++v)
-      if (g.h_deg[v] > kSmallMax) hb.push_back(v);
-    if (!hb.empty()) {
-      ALLOC(g.adjs, sizeof(int2) * NNZ, "degree-ordered rows");
-      const int32_t nbig = (int32_t)hb.size();
-      const size_t sb = sizeof(int32_t) * 4 * NNZ, gb = sizeof(int32_t) * 2 * (size_t)nbig,
-                   bb = sizeof(int32_t) * (size_t)nbig;
-      int32_t *scratch = nullptr, *seg = nullptr, *d_big = nullptr;
-      void *temp = nullptr;
-      size_t temp_bytes = 0;
-      st = dev_alloc(g, (void **)&scratch, sb, "sort scratch");
-      if (st == EF_OK) st = dev_alloc(g, (void **)&seg, gb, "sort segments");
-      if (st == EF_OK) st = dev_alloc(g, (void **)&d_big, bb, "big centres");
-      hipError_t e = hipSuccess;
-      if (st == EF_OK) {
-        e = hipMemcpyAsync(d_big, hb.data(), bb, hipMemcpyHostToDevice, stream);
-        if (e == hipSuccess)
-          e = launch_big_sort(g, d_big, nbig, scratch, seg, nullptr, temp_bytes, stream);
-        if (e == hipSuccess) st = dev_alloc(g, &temp, temp_bytes, "sort scratch");
-        if (e == hipSuccess && st == EF_OK)
-          e = launch_big_sort(g, d_big, nbig, scratch, seg, temp, temp_bytes, stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(stream);
-      }
-      dev_free(g, temp, temp_bytes);
-      dev_free(g, d_big, bb);
-      dev_free(g, seg, gb);
-      dev_free(g, scratch, sb);
-      if (st == EF_OK && e != hipSuccess) st = hip_status(e, "degree-ordered rows");
-      if (st != EF_OK) {
-        ef_graph_free(h);
-        return st;
+    struct Piece {
+      void **p;
+      size_t bytes;
+    };
+    std::vector<Piece> pieces = {
+        {(void **)&g.d_counters, sizeof(int32_t) * 64},
+        {(void **)&g.up_ptr, sizeof(int32_t) * N1},
+        {(void **)&g.dn_ptr, sizeof(int32_t) * N1},
+        {(void **)&g.deg, sizeof(int32_t) * NN},
+        {(void **)&g.src, sizeof(int32_t) * NNZ},
+        {(void **)&g.rev, sizeof(int32_t) * NNZ},
+        {(void **)&g.rrev, sizeof(int32_t) * NNZ},
+        {(void **)&g.adj2, sizeof(int2) * NNZ},
+        {(void **)&g.asum, sizeof(int64_t) * NN},
+        {(void **)&g.qa, sizeof(longlong2) * NN},
+        {(void **)&g.nbm, sizeof(NbrMoments) * NN},
+        {(void **)&g.up_col, sizeof(int32_t) * NUP},
+        {(void **)&g.up_deg, sizeof(int32_t) * NUP},
+        {(void **)&g.trec, sizeof(int32_t) * NNZ},
+        {(void **)&g.dn, sizeof(int4) * NUP},
+    };
+    if (!devptr) {
+      pieces.push_back({(void **)&g.row_ptr, sizeof(int32_t) * N1});
+      pieces.push_back({(void **)&g.col_idx, sizeof(int32_t) * NNZ});
+    }
+    // degree-ordered rows of the mid and big centres (the tile pair loops,
+    // which store their per-arc sums by sorted position)
+    if (n_over > 0) pieces.push_back({(void **)&g.adjs, sizeof(int2) * NNZ});
+    size_t total = 0, sum = 0;
+    for (const Piece &q : pieces) {
+      total += (q.bytes + 255) & ~(size_t)255;
+      sum += q.bytes;
+    }
+    st = dev_alloc(g, &g.arena, total, "graph arrays", sum);
+    if (st == EF_OK) {
+      char *p = (char *)g.arena;
+      for (const Piece &q : pieces) {
+        *q.p = p;
+        p += (q.bytes + 255) & ~(size_t)255;
       }
     }
+  }
+  if (devptr) {
+    g.row_ptr = const_cast<int32_t *>(row_ptr);
+    g.col_idx = const_cast<int32_t *>(col_idx);
+  }
+  // Scratch of the preparation: WS_MAIN, at the size a cluster-centric call
+  // will want (kept for it; FP64's too where that is small), or what the
+  // preparation needs if there is no memory for more.
+  const int64_t nn_tiles = [&] {
+    int64_t t = 0;
+    for (int32_t v = 0; v < n && kmax > kSuper; ++v)
+      if (g.h_deg[(size_t)v] > kSuper) {
+        const int64_t ns = ((int64_t)g.h_deg[(size_t)v] + kSuper - 1) / kSuper;
+        t += ns * (ns + 1) / 2;
+      }
+    return t;
+  }();
+  const size_t prep_bytes = (sizeof(int32_t) * (size_t)graph_prep_tmp_len((int64_t)NNZ) + 15) &
+                            ~(size_t)15;
+  size_t sort_temp = 0;
+  if (st == EF_OK && n_over > 0) {
+    const hipError_t e = launch_big_sort(g, nullptr, (int32_t)n_over, nullptr, nullptr, nullptr,
+                                         sort_temp, stream);
+    if (e != hipSuccess) st = hip_status(e, "degree-ordered rows");
+  }
+  const size_t sort_bytes =
+      n_over > 0 ? ((sizeof(int32_t) * 4 * NNZ + 255) & ~(size_t)255) +
+                       ((sizeof(int32_t) * 3 * (size_t)n_over + 255) & ~(size_t)255) + sort_temp
+                 : 0;
+  const size_t scratch_bytes = std::max(prep_bytes + sizeof(int64_t) * NN, sort_bytes);
+  if (st == EF_OK) {
+    constexpr size_t kReserveFp64 = (size_t)64 << 20;
+    const size_t w32 = compute_ws(g, false, nn_tiles, n, true).bytes,
+                 w64 = compute_ws(g, true, nn_tiles, n, true).bytes;
+    const size_t want = std::max(scratch_bytes, w64 <= kReserveFp64 ? w64 : w32);
+    st = ws_ensure(g, WS_MAIN, want, "preprocessing scratch");
+    g.main_reserved = true;
+    if (st != EF_OK && want > scratch_bytes)
+      st = ws_ensure(g, WS_MAIN, scratch_bytes, "preprocessing scratch");
+  }
+  if (st != EF_OK) {
+    const std::string text = t_err;
+    ef_graph_free(h);
+    return after_check([&] {
+      set_error("%s", text.c_str());
+      return st;
+    });
+  }
+  int32_t *tmp = (int32_t *)g.ws[WS_MAIN].p;
+  int64_t *work = (int64_t *)((char *)g.ws[WS_MAIN].p + prep_bytes);
+  hipError_t e = hipSuccess;
+  if (!devptr) {
+    e = hipMemcpyAsync(g.row_ptr, row_ptr, sizeof(int32_t) * N1, hipMemcpyHostToDevice, stream);
+    if (e == hipSuccess && nnz > 0)
+      e = hipMemcpyAsync(g.col_idx, col_idx, sizeof(int32_t) * (size_t)nnz,
+                         hipMemcpyHostToDevice, stream);
+  }
+  if (e == hipSuccess) e = launch_graph_prep(g, tmp, work, validate, stream);
+  // the reverse-sum index starts as rev; the rows of mid and big centres remap
+  // it below
+  if (e == hipSuccess && nnz > 0)
+    e = hipMemcpyAsync(g.rrev, g.rev, sizeof(int32_t) * (size_t)nnz, hipMemcpyDeviceToDevice,
+                       stream);
+  // one read-back of the control record and the list offsets, one of the tail
+  // entries walked at each node by the triangle pass (binning)
+  const size_t ptr_stride = (sizeof(int32_t) * N1 + 255) & ~(size_t)255;
+  std::vector<char> h_back(256 + 2 * ptr_stride);
+  std::vector<int64_t> h_work((size_t)n);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(h_back.data(), g.d_counters, 256 + ptr_stride + sizeof(int32_t) * N1,
+                       hipMemcpyDeviceToHost, stream);
+  if (e == hipSuccess && n > 0)
+    e = hipMemcpyAsync(h_work.data(), work, sizeof(int64_t) * (size_t)n, hipMemcpyDeviceToHost,
+                       stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(stream);
+  if (e != hipSuccess) {
+    ef_graph_free(h);
+    return after_check([&] { return hip_status(e, "graph preprocessing"); });
+  }
+  const int32_t *h_ctl = (const int32_t *)h_back.data();
+  const int32_t *h_up_ptr = (const int32_t *)(h_back.data() + 256);
+  const int32_t *h_dn_ptr = (const int32_t *)(h_back.data() + 256 + ptr_stride);
+  if (nnz > 0 && (h_ctl[kCtlStop] || h_ctl[kCtlCol])) {
+    const bool col_bad = h_ctl[kCtlCol] != 0;
+    ef_graph_free(h);
+    return after_check([&] {
+      if (col_bad) {
+        set_error("ef_graph_load_csr: a neighbour id is outside [0, %d)", n);
+        return EF_ERR_RANGE;
+      }
+      set_error("the CSR is not simple and symmetric (load with EF_VALIDATE for details)");
+      return EF_ERR_NOT_SYMMETRIC;
+    });
+  }
+  g.n_tri_zero = nnz > 0 ? h_ctl[kCtlZero] : 0;
+  if (g.n_tri_zero > 0) {
+    st = dev_alloc(g, (void **)&g.tri_zero, sizeof(int32_t) * (size_t)g.n_tri_zero, "zero slots");
+    if (st != EF_OK) {
+      ef_graph_free(h);
+      return st;
+    }
+    e = launch_zero_list(g, tmp, stream);
+  }
+  // degree-ordered rows, sorted while the host builds the node lists
+  std::vector<int32_t> hb;
+  if (e == hipSuccess && n_over > 0) {
+    hb.reserve((size_t)n_over);
+    for (int32_t v = 0; v < n; ++v)
+      if (g.h_deg[(size_t)v] > kSmallMax) hb.push_back(v);
+    int32_t *scratch = tmp;
+    int32_t *d_big = (int32_t *)((char *)tmp + ((sizeof(int32_t) * 4 * NNZ + 255) & ~(size_t)255));
+    int32_t *seg = d_big + n_over;
+    void *temp = (char *)d_big + ((sizeof(int32_t) * 3 * (size_t)n_over + 255) & ~(size_t)255);
+    e = hipMemcpyAsync(d_big, hb.data(), sizeof(int32_t) * (size_t)n_over, hipMemcpyHostToDevice,
+                       stream);
+    if (e == hipSuccess)
+      e = launch_big_sort(g, d_big, (int32_t)n_over, scratch, seg, temp, sort_temp, stream);
+  }
+  if (e != hipSuccess) {
+    ef_graph_free(h);
+    return hip_status(e, "degree-ordered rows");
   }
   std::vector<int32_t> tri[4], fin, fin_group;
   std::vector<int4> recL;
   for (int32_t v = 0; v < n; ++v) {
     const int64_t k = g.h_deg[v];
     const int32_t up = h_up_ptr[v + 1] - h_up_ptr[v];
-    g.h_up_len[v] = up;
     inf.clusters += k * (k - 1) / 2;
     inf.sum_sq_degree += k * k;
     inf.wedge_checks += h_work[v];
@@ -507,9 +577,6 @@ ef_status graph_load(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32
   for (int bin = 0; bin < 4; ++bin) {
     std::sort(tri[bin].begin(), tri[bin].end(), by_work);
     g.n_tri[bin] = (int64_t)tri[bin].size();
-    if (bin > 0)
-      ALLOC(g.tri_list[bin], sizeof(int32_t) * std::max<size_t>(tri[bin].size(), 1),
-            "triangle list");
   }
   std::vector<int4> rec0(tri[0].size());
   for (size_t i = 0; i < tri[0].size(); ++i) {
@@ -517,7 +584,6 @@ ef_status graph_load(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32
     const int32_t m = h_up_ptr[v + 1] - h_up_ptr[v], nd = h_dn_ptr[v + 1] - h_dn_ptr[v];
     rec0[i] = make_int4(v, h_up_ptr[v], h_dn_ptr[v], m | (nd << 16));
   }
-  ALLOC(g.tri_rec0, sizeof(int4) * std::max<size_t>(rec0.size(), 1), "triangle records");
   // workgroup bins: |up(w)| <= kTriBin2 < 2^12, segments <= degree < 2^20
   static_assert(kTriBin2 < (1 << 12) && kMaxDegree < (1 << 20), "workgroup-bin record packing");
   std::vector<int4> recB[3];
@@ -528,11 +594,8 @@ ef_status graph_load(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32
       const int32_t m = h_up_ptr[v + 1] - h_up_ptr[v], nd = h_dn_ptr[v + 1] - h_dn_ptr[v];
       recB[bin][i] = make_int4(v, h_up_ptr[v], h_dn_ptr[v], m | (nd << 12));
     }
-    ALLOC(g.tri_recB[bin], sizeof(int4) * std::max<size_t>(recB[bin].size(), 1),
-          "triangle records");
   }
   g.n_tri_lane = (int64_t)recL.size();
-  ALLOC(g.tri_recL, sizeof(int4) * std::max<size_t>(recL.size(), 1), "triangle lane records");
   // tiers by degree (descending), each graph by graph
   auto fin_tier = [&](int32_t v) {
     return g.h_deg[v] > kFinBlockMin ? 0 : g.h_deg[v] > kFinHalfMax ? 1 : 2;
@@ -555,26 +618,56 @@ ef_status graph_load(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32
     g.h_tri_lane.resize(recL.size());
     for (size_t i = 0; i < recL.size(); ++i) g.h_tri_lane[i] = recL[i].x;
   }
-  ALLOC(g.fin_list, sizeof(int32_t) * std::max<size_t>(fin.size(), 1), "finalize list");
-#undef ALLOC
-  hipError_t e = hipSuccess;
-  for (int bin = 1; bin < 4 && e == hipSuccess; ++bin)
-    if (!tri[bin].empty())
-      e = hipMemcpy(g.tri_list[bin], tri[bin].data(), sizeof(int32_t) * tri[bin].size(),
-                    hipMemcpyHostToDevice);
-  if (e == hipSuccess && !rec0.empty())
-    e = hipMemcpy(g.tri_rec0, rec0.data(), sizeof(int4) * rec0.size(), hipMemcpyHostToDevice);
-  for (int bin = 1; bin <= 2 && e == hipSuccess; ++bin)
-    if (!recB[bin].empty())
-      e = hipMemcpy(g.tri_recB[bin], recB[bin].data(), sizeof(int4) * recB[bin].size(),
-                    hipMemcpyHostToDevice);
-  if (e == hipSuccess && !recL.empty())
-    e = hipMemcpy(g.tri_recL, recL.data(), sizeof(int4) * recL.size(), hipMemcpyHostToDevice);
-  if (e == hipSuccess && !fin.empty())
-    e = hipMemcpy(g.fin_list, fin.data(), sizeof(int32_t) * fin.size(), hipMemcpyHostToDevice);
-  if (e != hipSuccess) {
-    ef_graph_free(h);
-    return hip_status(e, "upload node lists");
+  // every list in one block, uploaded by one copy
+  {
+    struct Piece {
+      void **p;
+      const void *src;
+      size_t bytes;
+    };
+    const Piece pieces[] = {
+        {(void **)&g.tri_rec0, rec0.data(), sizeof(int4) * rec0.size()},
+        {(void **)&g.tri_recB[1], recB[1].data(), sizeof(int4) * recB[1].size()},
+        {(void **)&g.tri_recB[2], recB[2].data(), sizeof(int4) * recB[2].size()},
+        {(void **)&g.tri_recL, recL.data(), sizeof(int4) * recL.size()},
+        {(void **)&g.tri_list[1], tri[1].data(), sizeof(int32_t) * tri[1].size()},
+        {(void **)&g.tri_list[3], tri[3].data(), sizeof(int32_t) * tri[3].size()},
+        {(void **)&g.fin_list, fin.data(), sizeof(int32_t) * fin.size()},
+    };
+    size_t total = 0, sum = 0;
+    for (const Piece &q : pieces) {
+      total += (q.bytes + 255) & ~(size_t)255;
+      sum += q.bytes;
+    }
+    std::vector<char> all(total);
+    st = dev_alloc(g, &g.lists, total, "node lists", sum);
+    if (st != EF_OK) {
+      // room after all when the scratch goes (its work has to end first)
+      e = hipStreamSynchronize(stream);
+      dev_free(g, g.ws[WS_MAIN].p, g.ws[WS_MAIN].bytes);
+      g.ws[WS_MAIN] = DevBuf{};
+      g.main_reserved = false;
+      st = e == hipSuccess ? dev_alloc(g, &g.lists, total, "node lists", sum)
+                           : hip_status(e, "degree-ordered rows");
+    }
+    size_t at = 0;
+    for (const Piece &q : pieces) {
+      if (st == EF_OK) *q.p = (char *)g.lists + at;
+      if (q.bytes) std::memcpy(all.data() + at, q.src, q.bytes);
+      at += (q.bytes + 255) & ~(size_t)255;
+    }
+    if (st == EF_OK) {
+      if (total > 0)
+        e = hipMemcpyAsync(g.lists, all.data(), total, hipMemcpyHostToDevice, stream);
+      // (the load is complete when it returns; the host vectors go)
+      if (e == hipSuccess) e = hipStreamSynchronize(stream);
+      if (e != hipSuccess) st = hip_status(e, "upload node lists");
+    }
+    if (st != EF_OK) {
+      (void)hipStreamSynchronize(stream);
+      ef_graph_free(h);
+      return st;
+    }
   }
   *out = h;
   return EF_OK;
@@ -647,12 +740,6 @@ ef_status ef_stats(const ef_graph *h, ef_run_stats *out) {
 }  // extern "C"
 
 namespace efi {
-
-// workspace slots
-enum {
-  WS_R = 0, WS_REC, WS_Y, WS_Z, WS_ZT, WS_FLAG, WS_BINS, WS_OUT, WS_BITMAP,
-  WS_SEEDS, WS_UOUT, WS_TOPK, WS_SURR, WS_J3, WS_J3P, WS_J3L
-};
 
 // scratch for other translation units (kept in the handle, grow-only)
 ef_status graph_scratch(Graph &g, size_t bytes, void **out) {
@@ -801,8 +888,6 @@ extern "C" ef_status ef_compute(ef_graph *h, ef_algo algo, ef_prec prec, const i
   ef_status s = prof.init();
   if (s != EF_OK) return s;
   g.stats = ef_run_stats{};
-  const size_t tsz = prec == EF_PREC_FP64 ? sizeof(double) : sizeof(float2);
-  const int64_t nnz = std::max<int64_t>(g.nnz, 1), nup = std::max<int64_t>(g.nnz / 2, 1);
 
   // seeds: unique sorted list + inverse map
   const bool all = seeds == nullptr;
@@ -838,38 +923,26 @@ extern "C" ef_status ef_compute(ef_graph *h, ef_algo algo, ef_prec prec, const i
     host_bins(g, useeds.data(), (int64_t)useeds.size(), b);
   }
   if ((s = alloc_bins(g, b)) != EF_OK) return s;
-  // per-arc sums: one float (FP32C) or double each
-  const size_t asz = prec == EF_PREC_FP64 ? sizeof(double) : sizeof(float);
-  if ((s = ws_ensure(g, WS_R, asz * (size_t)nnz, "arc sums")) != EF_OK) return s;
-  // super-tile record entries: one float (FP32C) or double each
-  const size_t rsz = prec == EF_PREC_FP64 ? sizeof(double) : sizeof(float);
-  if ((s = ws_ensure(g, WS_REC, rsz * (size_t)kRecEntries * (size_t)std::max<int64_t>(b.n_tiles, 1),
-                     "super-tile records")) != EF_OK)
-    return s;
-  if ((s = ws_ensure(g, WS_FLAG, (sizeof(int32_t) + 1) * (size_t)std::max<int32_t>(n_work, 1),
-                     "flag list")) != EF_OK)
-    return s;
+  const ComputeWs L = compute_ws(g, prec == EF_PREC_FP64, b.n_tiles, n_work, !per_seed);
+  g.main_reserved = false;
+  if ((s = ws_ensure(g, WS_MAIN, L.bytes, "workspace")) != EF_OK) return s;
+  char *const ws = (char *)g.ws[WS_MAIN].p;
+  void *const ws_R = ws + L.R, *const ws_Z = ws + L.Z;
+  TriSlot *const ws_Y = (TriSlot *)(ws + L.Y);
+  int64_t *const ws_ZT = (int64_t *)(ws + L.ZT);
   // outputs of the unique work list: straight into the caller's device arrays
   // when possible, else into staging
-  double *ef_w = nullptr;
-  int64_t *D_w = nullptr, *N_w = nullptr;
-  const size_t out_bytes = (sizeof(double) + 2 * sizeof(int64_t)) * (size_t)std::max(n_work, 1);
-  if ((s = ws_ensure(g, WS_UOUT, out_bytes, "output staging")) != EF_OK) return s;
-  {
-    char *p = (char *)g.ws[WS_UOUT].p;
-    ef_w = (double *)p;
-    D_w = (int64_t *)(p + sizeof(double) * (size_t)std::max(n_work, 1));
-    N_w = D_w + std::max(n_work, 1);
-    if (all && out_dev) {
-      ef_w = ef;
-      if (D) D_w = D;
-      if (N) N_w = N;
-    }
+  double *ef_w = (double *)(ws + L.out);
+  int64_t *D_w = (int64_t *)(ef_w + std::max(n_work, 1)), *N_w = D_w + std::max(n_work, 1);
+  if (all && out_dev) {
+    ef_w = ef;
+    if (D) D_w = D;
+    if (N) N_w = N;
   }
   int32_t *cnt = g.d_counters;  // [0] flagged, [1] fp64-finalised
   hipError_t e = launch_zero_i32(cnt, 4, st);
   if (e != hipSuccess) return hip_status(e, "clear counters");
-  int32_t *flagged = (int32_t *)g.ws[WS_FLAG].p;
+  int32_t *flagged = (int32_t *)(ws + L.flag);
   uint8_t *flag_bytes = (uint8_t *)(flagged + std::max<int32_t>(n_work, 1));
 
   // device seed arrays: the unique work list (all nodes: none, position =
@@ -970,13 +1043,6 @@ extern "C" ef_status ef_compute(ef_graph *h, ef_algo algo, ef_prec prec, const i
   const bool reuse = whole && g.bins_kept && g.bins_buf == g.ws[WS_BINS].p &&
                      g.bins_thr.t8 == b.thr.t8 && g.bins_thr.t16 == b.thr.t16 &&
                      g.bins_thr.t32 == b.thr.t32;
-  if (!per_seed) {
-    if ((s = ws_ensure(g, WS_Y, sizeof(TriSlot) * 2 * (size_t)nup, "triangle slots")) != EF_OK)
-      return s;
-    if ((s = ws_ensure(g, WS_Z, tsz * (size_t)std::max(g.n, 1), "triangle node sums")) != EF_OK) return s;
-    if ((s = ws_ensure(g, WS_ZT, sizeof(int64_t) * (size_t)std::max(g.n, 1), "triangle node counts")) != EF_OK)
-      return s;
-  }
   if (prec == EF_PREC_FP64 && (s = score_table(g, st)) != EF_OK) return s;
   prof.mark(0);
   if (!reuse) {
@@ -987,23 +1053,20 @@ extern "C" ef_status ef_compute(ef_graph *h, ef_algo algo, ef_prec prec, const i
   g.bins_thr = b.thr;
   g.bins_buf = g.ws[WS_BINS].p;
   prof.mark(1);
-  e = launch_pairs(g, prec, b, g.ws[WS_R].p, g.ws[WS_REC].p, st, prof.ev(2), prof.ev(3),
+  e = launch_pairs(g, prec, b, ws_R, ws + L.rec, st, prof.ev(2), prof.ev(3),
                    prof.ev(4), algo == EF_ALGO_CLUSTER_AGG ? b.agg_done : nullptr);
   if (e != hipSuccess) return hip_status(e, "pair loop");
   prof.mark(5);
   if (!per_seed) {
-    e = launch_triangles(g, prec, (TriSlot *)g.ws[WS_Y].p, g.ws[WS_Z].p,
-                         (int64_t *)g.ws[WS_ZT].p, st);
+    e = launch_triangles(g, prec, ws_Y, ws_Z, ws_ZT, st);
     if (e != hipSuccess) return hip_status(e, "triangle pass");
     prof.mark(6);
-    e = launch_finalize_cluster(g, prec, g.ws[WS_R].p, (const TriSlot *)g.ws[WS_Y].p,
-                                g.ws[WS_Z].p, (int64_t *)g.ws[WS_ZT].p, ef_w, D_w, N_w,
-                                flag_bytes, st);
+    e = launch_finalize_cluster(g, prec, ws_R, ws_Y, ws_Z, ws_ZT, ef_w, D_w, N_w, flag_bytes, st);
     if (e == hipSuccess) e = launch_flag_compact(flag_bytes, n_work, flagged, cnt, st);
     if (e != hipSuccess) return hip_status(e, "finalize");
     prof.mark(7);
   } else {
-    e = launch_per_seed(g, prec, d_useeds, ps_lists, ps_counts, g.ws[WS_R].p,
+    e = launch_per_seed(g, prec, d_useeds, ps_lists, ps_counts, ws_R,
                         (uint32_t *)g.ws[WS_BITMAP].p, ef_w, D_w, N_w, flag_bytes, st,
                         prof.ev(6));
     if (e == hipSuccess) e = launch_flag_compact(flag_bytes, n_work, flagged, cnt, st);

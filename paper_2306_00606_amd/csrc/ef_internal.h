@@ -132,7 +132,9 @@ struct Graph {
   int dev = 0;
   int32_t n = 0;
   int64_t nnz = 0;
-  bool borrowed = false;
+  // device memory behind the arrays below, which the load takes as two blocks:
+  // the arrays of known size, and the node lists
+  void *arena = nullptr, *lists = nullptr;
   // device arrays
   int32_t *row_ptr = nullptr;
   int32_t *col_idx = nullptr;
@@ -164,7 +166,6 @@ struct Graph {
   int64_t n_tri_zero = 0;
   // host copies used for sizing work lists
   std::vector<int32_t> h_deg;
-  std::vector<int32_t> h_up_len;
   // triangle-pass node lists (device): see kTriBin*. Bin 0 as records
   // {w, up_ptr[w], dn_ptr[w], |up(w)| | segments << 16}, bins 1-3 as ids.
   int4 *tri_rec0 = nullptr;
@@ -219,6 +220,7 @@ struct Graph {
   ef_run_stats stats{};
   // workspace (grow-only, reused across calls)
   DevBuf ws[16];
+  bool main_reserved = false;  // WS_MAIN holds the load's scratch, kept for the first ef_compute
   // events for EF_PROFILE
   hipEvent_t ev[16] = {};
   bool ev_ready = false;
@@ -250,7 +252,9 @@ ef_status hip_status(hipError_t e, const char *what);
 
 // graph preprocessing
 int64_t graph_prep_tmp_len(int64_t nnz);
-hipError_t launch_graph_prep(Graph &g, int32_t *tmp, int64_t *work, bool &not_symmetric,
+// words of the control record the preparation leaves in Graph::d_counters
+enum { kCtlCol = 0, kCtlArc, kCtlStop, kCtlUp, kCtlZero, kCtlWords };
+hipError_t launch_graph_prep(Graph &g, int32_t *tmp, int64_t *work, bool validate,
                              hipStream_t st);
 // Degree-ordered view of the rows of the big centres big[0..nbig) (device
 // list): fills g.adjs with a stable segmented sort by neighbour degree.
@@ -259,16 +263,10 @@ hipError_t launch_graph_prep(Graph &g, int32_t *tmp, int64_t *work, bool &not_sy
 // temp_bytes).
 hipError_t launch_big_sort(Graph &g, const int32_t *big, int32_t nbig, int32_t *scratch,
                            int32_t *seg, void *temp, size_t &temp_bytes, hipStream_t st);
-hipError_t graph_zero_count(const Graph &g, const int32_t *tmp, int64_t &count);
 hipError_t launch_zero_list(Graph &g, const int32_t *tmp, hipStream_t st);
 hipError_t launch_exclusive_scan_i32(const int32_t *in, int32_t *out, int64_t count,
                                      int32_t *block_tmp, int64_t block_tmp_len, hipStream_t st);
 int64_t scan_tmp_len(int64_t count);
-
-// flag[0] = 1 if some col[0 .. nnz) lies outside [0, n), else 0 (clears it
-// first)
-hipError_t launch_check_cols(const int32_t *col, int64_t nnz, int32_t n, int32_t *flag,
-                             hipStream_t st);
 
 // zero a small int32 array with a kernel (usable under stream capture)
 hipError_t launch_zero_i32(int32_t *p, int32_t count, hipStream_t st);

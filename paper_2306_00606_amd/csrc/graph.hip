@@ -23,31 +23,36 @@ __device__ __forceinline__ bool rank_less(int32_t a, int32_t ka, int32_t b, int3
   return ka < kb || (ka == kb && a < b);
 }
 
-// flag[0] = 1 when a neighbour id lies outside [0, n); launch_check_cols
-// clears the flag first
-__global__ void k_check_clear(int32_t *__restrict__ flag) {
-  if (threadIdx.x == 0) flag[0] = 0;
-}
+// Checks on the device while the graph is prepared (ctl, 64 ints, cleared
+// first): [kCtlCol] a neighbour id lies outside [0, n), [kCtlArc] a row with a
+// self-loop, not ascending, or an arc without its reverse, [kCtlStop] set by
+// k_gate when the arrays cannot be filled, [kCtlUp] up-arcs found, [kCtlZero]
+// triangle slots to clear. Kernels that index by neighbour ids leave when
+// kCtlCol is set, those after the gate when kCtlStop is, so the host reads the
+// outcome once, at the end.
+__global__ void k_ctl_clear(int32_t *__restrict__ ctl) { ctl[threadIdx.x] = 0; }
 
 __global__ void k_check_cols(const int32_t *__restrict__ col, int64_t nnz, int32_t n,
-                             int32_t *__restrict__ flag) {
+                             int32_t *__restrict__ ctl) {
   bool bad = false;
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < nnz;
        e += (int64_t)gridDim.x * blockDim.x)
     bad |= (uint32_t)col[e] >= (uint32_t)n;
-  // one store per wavefront that saw a bad id
-  if (__ballot(bad) && (threadIdx.x & 63) == 0) atomicOr(flag, 1);
+  // one atomic per wavefront that saw a bad id
+  if (__ballot(bad) && (threadIdx.x & 63) == 0) atomicOr(&ctl[kCtlCol], 1);
 }
 
-hipError_t launch_check_cols(const int32_t *col, int64_t nnz, int32_t n, int32_t *flag,
-                             hipStream_t st) {
-  hipLaunchKernelGGL(k_check_clear, dim3(1), dim3(64), 0, st, flag);
-  if (nnz > 0) {
-    int64_t blocks = (nnz + 1023) / 1024;
-    if (blocks > 8192) blocks = 8192;
-    hipLaunchKernelGGL(k_check_cols, dim3((unsigned)blocks), dim3(256), 0, st, col, nnz, n, flag);
-  }
-  return hipGetLastError();
+// a simple symmetric graph has exactly nnz / 2 up-arcs: the up-arc arrays are
+// sized for that many
+__global__ void k_gate(int32_t *__restrict__ ctl, const int32_t *__restrict__ up_total,
+                       int64_t nnz, bool validate) {
+  const int32_t up = *up_total;
+  ctl[kCtlUp] = up;
+  ctl[kCtlStop] = (ctl[kCtlCol] || (validate && ctl[kCtlArc]) || 2 * (int64_t)up != nnz) ? 1 : 0;
+}
+
+__global__ void k_ctl_zero_total(int32_t *__restrict__ ctl, const int32_t *__restrict__ total) {
+  ctl[kCtlZero] = *total;
 }
 
 __global__ void k_degree(const int32_t *__restrict__ row_ptr, int32_t n,
@@ -74,7 +79,10 @@ __global__ void k_arc_src(const int32_t *__restrict__ row_ptr, int32_t n, int64_
 __global__ void k_arc_rev(const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
                           const int32_t *__restrict__ src, const int32_t *__restrict__ deg,
                           int64_t nnz, int32_t *__restrict__ rev, int2 *__restrict__ adj2,
-                          int32_t *__restrict__ upflag) {
+                          int32_t *__restrict__ upflag, int32_t *__restrict__ ctl,
+                          bool validate) {
+  if (ctl[kCtlCol]) return;
+  bool bad = false;
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < nnz;
        e += (int64_t)gridDim.x * blockDim.x) {
     const int32_t s = src[e], a = col[e];
@@ -85,18 +93,25 @@ __global__ void k_arc_rev(const int32_t *__restrict__ row_ptr, const int32_t *__
     }
     // on a valid (symmetric) graph the reverse arc is always found; keep the
     // index inside the row otherwise
-    rev[e] = (lo < row_ptr[a + 1] && col[lo] == s) ? lo : (int32_t)e;
+    const bool found = lo < row_ptr[a + 1] && col[lo] == s;
+    rev[e] = found ? lo : (int32_t)e;
+    // (in ascending rows the search finds every reverse arc there is; a row
+    // out of order is bad by itself)
+    bad |= !found || a == s || (e > row_ptr[s] && col[e - 1] >= a);
     const int32_t ka = deg[a];
     adj2[e] = make_int2(a, ka);
     upflag[e] = rank_less(s, deg[s], a, ka) ? 1 : 0;
   }
+  if (validate && __ballot(bad) && (threadIdx.x & 63) == 0) atomicOr(&ctl[kCtlArc], 1);
 }
 
 __global__ void k_up_fill(const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
                           const int32_t *__restrict__ rev, const int32_t *__restrict__ upflag,
                           const int32_t *__restrict__ upidx, int32_t n, int64_t nnz,
                           int32_t *__restrict__ up_ptr, int32_t *__restrict__ up_col,
-                          int32_t *__restrict__ tslot) {
+                          int32_t *__restrict__ tslot,
+    const int32_t *__restrict__ ctl) {
+  if (ctl[kCtlStop]) return;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < nnz; e += stride) {
     if (upflag[e]) {
@@ -116,7 +131,9 @@ __global__ void k_up_fill(const int32_t *__restrict__ row_ptr, const int32_t *__
 // Rank order inside every up(u) (rows are in id order after k_up_fill).
 // ---------------------------------------------------------------------------
 __global__ void k_up_keys(const int32_t *__restrict__ up_col, const int32_t *__restrict__ deg,
-                          int64_t nup, int32_t *__restrict__ upk) {
+                          int64_t nup, int32_t *__restrict__ upk,
+    const int32_t *__restrict__ ctl) {
+  if (ctl[kCtlStop]) return;
   for (int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; s < nup;
        s += (int64_t)gridDim.x * blockDim.x)
     upk[s] = deg[up_col[s]];
@@ -130,7 +147,9 @@ __global__ void k_up_sort(const int32_t *__restrict__ src, const int2 *__restric
                           int64_t nnz, const int32_t *__restrict__ up_ptr,
                           const int32_t *__restrict__ up_col, const int32_t *__restrict__ upk,
                           int32_t *__restrict__ newcol, int32_t *__restrict__ newdeg,
-                          int32_t *__restrict__ perm) {
+                          int32_t *__restrict__ perm,
+    const int32_t *__restrict__ ctl) {
+  if (ctl[kCtlStop]) return;
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < nnz;
        e += (int64_t)gridDim.x * blockDim.x) {
     if (!upflag[e]) continue;
@@ -146,7 +165,9 @@ __global__ void k_up_sort(const int32_t *__restrict__ src, const int2 *__restric
 }
 
 __global__ void k_tslot_remap(int32_t *__restrict__ tslot, const int32_t *__restrict__ perm,
-                              int64_t nnz) {
+                              int64_t nnz,
+    const int32_t *__restrict__ ctl) {
+  if (ctl[kCtlStop]) return;
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < nnz;
        e += (int64_t)gridDim.x * blockDim.x)
     tslot[e] = perm[tslot[e]];
@@ -158,7 +179,9 @@ __global__ void k_tslot_remap(int32_t *__restrict__ tslot, const int32_t *__rest
 __global__ void k_dn_flag(const int32_t *__restrict__ src, const int32_t *__restrict__ col,
                           const int32_t *__restrict__ upflag, const int32_t *__restrict__ tslot,
                           const int32_t *__restrict__ up_ptr, int64_t nnz,
-                          int32_t *__restrict__ dnflag) {
+                          int32_t *__restrict__ dnflag,
+    const int32_t *__restrict__ ctl) {
+  if (ctl[kCtlStop]) return;
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < nnz;
        e += (int64_t)gridDim.x * blockDim.x) {
     int32_t f = 0;
@@ -176,7 +199,9 @@ __global__ void k_dn_fill(const int32_t *__restrict__ row_ptr, const int32_t *__
                           const int32_t *__restrict__ deg, const int32_t *__restrict__ tslot,
                           const int32_t *__restrict__ up_ptr, const int32_t *__restrict__ dnflag,
                           const int32_t *__restrict__ dnidx, int32_t n, int64_t nnz,
-                          int4 *__restrict__ dn, int32_t *__restrict__ dn_ptr) {
+                          int4 *__restrict__ dn, int32_t *__restrict__ dn_ptr,
+    const int32_t *__restrict__ ctl) {
+  if (ctl[kCtlStop]) return;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   const int32_t ndn = nnz > 0 ? dnidx[nnz - 1] + dnflag[nnz - 1] : 0;
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < nnz; e += stride) {
@@ -194,7 +219,9 @@ __global__ void k_dn_fill(const int32_t *__restrict__ row_ptr, const int32_t *__
 __global__ void k_zero_flag(const int32_t *__restrict__ src, const int32_t *__restrict__ upflag,
                             const int32_t *__restrict__ tslot, const int32_t *__restrict__ up_ptr,
                             const int32_t *__restrict__ dn_ptr, int64_t nnz,
-                            int32_t *__restrict__ zf) {
+                            int32_t *__restrict__ zf,
+    const int32_t *__restrict__ ctl) {
+  if (ctl[kCtlStop]) return;
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < nnz;
        e += (int64_t)gridDim.x * blockDim.x) {
     if (!upflag[e]) continue;
@@ -212,7 +239,9 @@ __global__ void k_zero_flag(const int32_t *__restrict__ src, const int32_t *__re
 __global__ void k_trec(const int32_t *__restrict__ col, const int32_t *__restrict__ rev,
                        const int32_t *__restrict__ upflag, const int32_t *__restrict__ dn_ptr,
                        const int32_t *__restrict__ dnflag, int64_t nnz, int64_t nup,
-                       int32_t *__restrict__ tslot) {
+                       int32_t *__restrict__ tslot,
+    const int32_t *__restrict__ ctl) {
+  if (ctl[kCtlStop]) return;
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < nnz;
        e += (int64_t)gridDim.x * blockDim.x) {
     const int32_t s = tslot[e];
@@ -234,65 +263,96 @@ __global__ void k_zero_fill(const int32_t *__restrict__ zf, const int32_t *__res
     if (zf[i]) list[zidx[i]] = (int32_t)i;
 }
 
-// One wavefront per node: tail entries walked at w (sum of its segment lengths).
-__global__ void k_dn_work(const int32_t *__restrict__ dn_ptr, const int4 *__restrict__ dn,
-                          int32_t n, int64_t *__restrict__ work) {
+// Per-node sums over a row of entries [ptr[v], ptr[v+1]): 8 lanes per node for
+// rows of up to kRowShort, then a wavefront per longer row, which the
+// wavefronts of the same launch find by a ballot over 64 nodes at a time (a
+// wavefront per node left most lanes without an entry on sparse graphs:
+// sums of BA n = 200k, m = 5 in 36 and 105 us). sum(v, first, stride, lanes)
+// adds its lanes' entries; put(v, lanes) reduces and stores.
+constexpr int32_t kRowShort = 128;
+
+template <typename Sum>
+__device__ __forceinline__ void for_rows(const int32_t *__restrict__ ptr, int32_t n, Sum sum) {
+  const int64_t tid = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  const int64_t nth = (int64_t)gridDim.x * blockDim.x;
+  const int sub = threadIdx.x & 7;
+  const int64_t rounds = (n + nth / 8 - 1) / (nth / 8);
+  for (int64_t r = 0; r < rounds; ++r) {
+    const int64_t v = r * (nth / 8) + tid / 8;
+    const int32_t len = v < n ? ptr[v + 1] - ptr[v] : kRowShort + 1;
+    sum((int32_t)(v < n ? v : 0), len <= kRowShort, sub, 8);
+  }
   const int lane = threadIdx.x & 63;
-  const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
-  const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-  for (int64_t v = wave; v < n; v += nwaves) {
-    int64_t acc = 0;
-    for (int32_t i = dn_ptr[v] + lane; i < dn_ptr[v + 1]; i += 64) acc += dn[i].y;
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-    if (lane == 0) work[v] = acc;
+  for (int64_t v0 = (tid >> 6) * 64; v0 < n; v0 += nth) {
+    const int64_t v = v0 + lane;
+    unsigned long long m = __ballot(v < n && ptr[v + 1] - ptr[v] > kRowShort);
+    while (m != 0ull) {
+      const int j = __builtin_ctzll(m);
+      m &= m - 1ull;
+      sum((int32_t)(v0 + j), true, lane, 64);
+    }
   }
 }
+template <typename V> __device__ __forceinline__ V lanes_sum(V x, int lanes) {
+  for (int off = lanes / 2; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+  return x;
+}
 
-// One wavefront per node: sum of squared neighbour degrees and sum of the
-// neighbours' neighbour-degree sums (with k and asum, they give N and D of
-// the node in closed form).
+// tail entries walked at w (sum of its segment lengths)
+__global__ void k_dn_work(const int32_t *__restrict__ dn_ptr, const int4 *__restrict__ dn,
+                          int32_t n, int64_t *__restrict__ work,
+                          const int32_t *__restrict__ ctl) {
+  if (ctl[kCtlStop]) return;
+  for_rows(dn_ptr, n, [&](int32_t v, bool on, int first, int lanes) {
+    int64_t acc = 0;
+    if (on)
+      for (int32_t i = dn_ptr[v] + first; i < dn_ptr[v + 1]; i += lanes) acc += dn[i].y;
+    acc = lanes_sum(acc, lanes);
+    if (on && first == 0) work[v] = acc;
+  });
+}
+
+// sum of squared neighbour degrees and sum of the neighbours'
+// neighbour-degree sums (with k and asum, they give N and D of the node in
+// closed form)
 __global__ void k_qa(const int32_t *__restrict__ row_ptr, const int2 *__restrict__ adj2,
                      const int64_t *__restrict__ asum, int32_t n, longlong2 *__restrict__ qa,
-                     NbrMoments *__restrict__ nbm) {
-  const int lane = threadIdx.x & 63;
-  const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
-  const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-  for (int64_t v = wave; v < n; v += nwaves) {
+                     NbrMoments *__restrict__ nbm, const int32_t *__restrict__ ctl) {
+  if (ctl[kCtlStop]) return;
+  for_rows(row_ptr, n, [&](int32_t v, bool on, int first, int lanes) {
     int64_t q = 0, a2 = 0;
     double c3 = 0.0, c4 = 0.0;
-    for (int32_t e = row_ptr[v] + lane; e < row_ptr[v + 1]; e += 64) {
-      const int2 ad = adj2[e];
-      q += (int64_t)ad.y * ad.y;
-      a2 += asum[ad.x];
-      const double kb = (double)ad.y, kb2 = kb * kb;
-      c3 += kb2 * kb;
-      c4 += kb2 * kb2;
-    }
-    for (int off = 32; off > 0; off >>= 1) {
-      q += __shfl_xor(q, off, 64);
-      a2 += __shfl_xor(a2, off, 64);
-      c3 += __shfl_xor(c3, off, 64);
-      c4 += __shfl_xor(c4, off, 64);
-    }
-    if (lane == 0) {
+    if (on)
+      for (int32_t e = row_ptr[v] + first; e < row_ptr[v + 1]; e += lanes) {
+        const int2 ad = adj2[e];
+        q += (int64_t)ad.y * ad.y;
+        a2 += asum[ad.x];
+        const double kb = (double)ad.y, kb2 = kb * kb;
+        c3 += kb2 * kb;
+        c4 += kb2 * kb2;
+      }
+    q = lanes_sum(q, lanes);
+    a2 = lanes_sum(a2, lanes);
+    c3 = lanes_sum(c3, lanes);
+    c4 = lanes_sum(c4, lanes);
+    if (on && first == 0) {
       qa[v] = make_longlong2(q, a2);
       nbm[v] = NbrMoments{asum[v], q, c3, c4};
     }
-  }
+  });
 }
 
-// One wavefront per node: sum of neighbour degrees.
+// sum of neighbour degrees
 __global__ void k_asum(const int32_t *__restrict__ row_ptr, const int2 *__restrict__ adj2,
-                       int32_t n, int64_t *__restrict__ asum) {
-  const int lane = threadIdx.x & 63;
-  const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
-  const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
-  for (int64_t v = wave; v < n; v += nwaves) {
+                       int32_t n, int64_t *__restrict__ asum, const int32_t *__restrict__ ctl) {
+  if (ctl[kCtlStop]) return;
+  for_rows(row_ptr, n, [&](int32_t v, bool on, int first, int lanes) {
     int64_t acc = 0;
-    for (int32_t e = row_ptr[v] + lane; e < row_ptr[v + 1]; e += 64) acc += adj2[e].y;
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-    if (lane == 0) asum[v] = acc;
-  }
+    if (on)
+      for (int32_t e = row_ptr[v] + first; e < row_ptr[v + 1]; e += lanes) acc += adj2[e].y;
+    acc = lanes_sum(acc, lanes);
+    if (on && first == 0) asum[v] = acc;
+  });
 }
 
 // ---------------------------------------------------------------------------
@@ -304,6 +364,8 @@ constexpr int kScanItems = 8;
 constexpr int kScanTile = kScanThreads * kScanItems;
 
 int64_t scan_tmp_len(int64_t count) { return (count + kScanTile - 1) / kScanTile + 1; }
+// the scan leaves the total after its block offsets
+static int64_t scan_blocks(int64_t count) { return (count + kScanTile - 1) / kScanTile; }
 
 __device__ int32_t block_exclusive_scan(int32_t x, int32_t *sh, int32_t &total) {
   // sh: kScanThreads / 64 ints
@@ -403,101 +465,83 @@ int64_t graph_prep_tmp_len(int64_t nnz) {
   return 4 * nnz + nnz / 2 + scan_tmp_len(nnz);
 }
 
-// Everything but the zero-slot list, whose length the caller reads back
-// (graph_zero_count) to size it; work[v] = tail entries walked at v.
-// A simple symmetric graph has exactly nnz / 2 up-arcs; anything else is
-// reported through not_symmetric before any array is filled by them.
-hipError_t launch_graph_prep(Graph &g, int32_t *tmp, int64_t *work, bool &not_symmetric,
+// Everything but the zero-slot list, whose length (ctl[kCtlZero]) the caller
+// reads back to size it; work[v] = tail entries walked at v. Asynchronous: the
+// caller reads ctl when it has all run.
+hipError_t launch_graph_prep(Graph &g, int32_t *tmp, int64_t *work, bool validate,
                              hipStream_t st) {
-  not_symmetric = false;
   const int T = 256;
+  int32_t *ctl = g.d_counters;
+  hipLaunchKernelGGL(k_ctl_clear, dim3(1), dim3(64), 0, st, ctl);
   hipLaunchKernelGGL(k_degree, dim3(grid_for(g.n, T)), dim3(T), 0, st, g.row_ptr, g.n, g.deg);
   if (g.nnz > 0) {
     const int64_t nnz = g.nnz, nup = nnz / 2;
     int32_t *upflag = tmp, *upidx = tmp + nnz, *G = tmp + 2 * nnz, *dnflag = tmp + 3 * nnz,
             *perm = tmp + 4 * nnz, *scan_tmp = tmp + 4 * nnz + nup;
     const int64_t sl = scan_tmp_len(nnz);
+    hipLaunchKernelGGL(k_check_cols, dim3(grid_for((nnz + 3) / 4, T)), dim3(T), 0, st, g.col_idx,
+                       nnz, g.n, ctl);
     hipLaunchKernelGGL(k_arc_src, dim3(grid_for(nnz, T)), dim3(T), 0, st, g.row_ptr, g.n, nnz,
                        g.src);
     hipLaunchKernelGGL(k_arc_rev, dim3(grid_for(nnz, T)), dim3(T), 0, st, g.row_ptr,
-                       g.col_idx, g.src, g.deg, nnz, g.rev, g.adj2, upflag);
+                       g.col_idx, g.src, g.deg, nnz, g.rev, g.adj2, upflag, ctl, validate);
     hipError_t e = launch_exclusive_scan_i32(upflag, upidx, nnz, scan_tmp, sl, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    int32_t last_idx = 0, last_flag = 0;
-    if (e == hipSuccess)
-      e = hipMemcpy(&last_idx, upidx + nnz - 1, sizeof(int32_t), hipMemcpyDeviceToHost);
-    if (e == hipSuccess)
-      e = hipMemcpy(&last_flag, upflag + nnz - 1, sizeof(int32_t), hipMemcpyDeviceToHost);
     if (e != hipSuccess) return e;
-    if ((int64_t)last_idx + last_flag != nup || 2 * nup != nnz) {
-      not_symmetric = true;
-      return hipSuccess;
-    }
+    hipLaunchKernelGGL(k_gate, dim3(1), dim3(1), 0, st, ctl, scan_tmp + scan_blocks(nnz), nnz,
+                       validate);
     hipLaunchKernelGGL(k_up_fill, dim3(grid_for(nnz, T)), dim3(T), 0, st, g.row_ptr,
                        g.col_idx, g.rev, upflag, upidx, g.n, nnz, g.up_ptr, g.up_col,
-                       g.trec);
+                       g.trec, ctl);
     // rank order inside each up(u)
     int32_t *upk = G, *newcol = G + nup;
     hipLaunchKernelGGL(k_up_keys, dim3(grid_for(nup, T)), dim3(T), 0, st, g.up_col, g.deg, nup,
-                       upk);
+                       upk, ctl);
     hipLaunchKernelGGL(k_up_sort, dim3(grid_for(nnz, T)), dim3(T), 0, st, g.src, g.adj2,
-                       upflag, upidx, nnz, g.up_ptr, g.up_col, upk, newcol, g.up_deg, perm);
+                       upflag, upidx, nnz, g.up_ptr, g.up_col, upk, newcol, g.up_deg, perm, ctl);
     e = hipMemcpyAsync(g.up_col, newcol, sizeof(int32_t) * (size_t)nup, hipMemcpyDeviceToDevice,
                        st);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_tslot_remap, dim3(grid_for(nnz, T)), dim3(T), 0, st, g.trec, perm,
-                       nnz);
+                       nnz, ctl);
     // segments of the triangle pass
     int32_t *dnidx = G;
     hipLaunchKernelGGL(k_dn_flag, dim3(grid_for(nnz, T)), dim3(T), 0, st, g.src, g.col_idx,
-                       upflag, g.trec, g.up_ptr, nnz, dnflag);
+                       upflag, g.trec, g.up_ptr, nnz, dnflag, ctl);
     e = launch_exclusive_scan_i32(dnflag, dnidx, nnz, scan_tmp, sl, st);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_dn_fill, dim3(grid_for(nnz, T)), dim3(T), 0, st, g.row_ptr, g.src,
                        g.col_idx, g.deg, g.trec, g.up_ptr, dnflag, dnidx, g.n, nnz, g.dn,
-                       g.dn_ptr);
-    hipLaunchKernelGGL(k_dn_work, dim3(grid_for((int64_t)g.n * 64, T)), dim3(T), 0, st,
-                       g.dn_ptr, g.dn, g.n, work);
+                       g.dn_ptr, ctl);
+    hipLaunchKernelGGL(k_dn_work, dim3(grid_for((int64_t)g.n * 8, T)), dim3(T), 0, st,
+                       g.dn_ptr, g.dn, g.n, work, ctl);
     // slots cleared before each pass (long lists), then their scan
     int32_t *zf = G, *zidx = upidx;
     hipLaunchKernelGGL(k_zero_flag, dim3(grid_for(nnz, T)), dim3(T), 0, st, g.src, upflag,
-                       g.trec, g.up_ptr, g.dn_ptr, nnz, zf);
+                       g.trec, g.up_ptr, g.dn_ptr, nnz, zf, ctl);
     e = launch_exclusive_scan_i32(zf, zidx, nup, scan_tmp, sl, st);
     if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_ctl_zero_total, dim3(1), dim3(1), 0, st, ctl,
+                       scan_tmp + scan_blocks(nup));
     // tslot becomes the per-arc triangle record index
     hipLaunchKernelGGL(k_trec, dim3(grid_for(nnz, T)), dim3(T), 0, st, g.col_idx, g.rev, upflag,
-                       g.dn_ptr, dnflag, nnz, nup, g.trec);
-    hipLaunchKernelGGL(k_asum, dim3(grid_for((int64_t)g.n * 64, T)), dim3(T), 0, st,
-                       g.row_ptr, g.adj2, g.n, g.asum);
-    hipLaunchKernelGGL(k_qa, dim3(grid_for((int64_t)g.n * 64, T)), dim3(T), 0, st, g.row_ptr,
-                       g.adj2, g.asum, g.n, g.qa, g.nbm);
+                       g.dn_ptr, dnflag, nnz, nup, g.trec, ctl);
+    hipLaunchKernelGGL(k_asum, dim3(grid_for((int64_t)g.n * 8, T)), dim3(T), 0, st,
+                       g.row_ptr, g.adj2, g.n, g.asum, ctl);
+    hipLaunchKernelGGL(k_qa, dim3(grid_for((int64_t)g.n * 8, T)), dim3(T), 0, st, g.row_ptr,
+                       g.adj2, g.asum, g.n, g.qa, g.nbm, ctl);
   } else {
     hipLaunchKernelGGL(k_up_fill, dim3(grid_for(g.n + 1, T)), dim3(T), 0, st, g.row_ptr,
                        g.col_idx, g.rev, tmp, tmp, g.n, (int64_t)0, g.up_ptr, g.up_col,
-                       g.trec);
+                       g.trec, ctl);
     hipLaunchKernelGGL(k_dn_fill, dim3(grid_for(g.n + 1, T)), dim3(T), 0, st, g.row_ptr, g.src,
                        g.col_idx, g.deg, g.trec, g.up_ptr, tmp, tmp, g.n, (int64_t)0, g.dn,
-                       g.dn_ptr);
+                       g.dn_ptr, ctl);
     (void)hipMemsetAsync(g.asum, 0, sizeof(int64_t) * (size_t)g.n, st);
     (void)hipMemsetAsync(g.qa, 0, sizeof(longlong2) * (size_t)g.n, st);
     (void)hipMemsetAsync(g.nbm, 0, sizeof(NbrMoments) * (size_t)g.n, st);
     (void)hipMemsetAsync(work, 0, sizeof(int64_t) * (size_t)g.n, st);
   }
   return hipGetLastError();
-}
-
-// Length of the zero-slot list (after launch_graph_prep has completed).
-hipError_t graph_zero_count(const Graph &g, const int32_t *tmp, int64_t &count) {
-  count = 0;
-  const int64_t nnz = g.nnz, nup = nnz / 2;
-  if (nup <= 0) return hipSuccess;
-  int32_t last_idx = 0, last_flag = 0;
-  hipError_t e = hipMemcpy(&last_idx, tmp + nnz + nup - 1, sizeof(int32_t),
-                           hipMemcpyDeviceToHost);
-  if (e == hipSuccess)
-    e = hipMemcpy(&last_flag, tmp + 2 * nnz + nup - 1, sizeof(int32_t), hipMemcpyDeviceToHost);
-  count = (int64_t)last_idx + last_flag;
-  return e;
 }
 
 hipError_t launch_zero_list(Graph &g, const int32_t *tmp, hipStream_t st) {
