@@ -314,23 +314,20 @@ __device__ __forceinline__ bf16x8 wpack(const __bf16 *pack, int block) {
   return reinterpret_cast<const bf16x8 *>(pack)[block * 64 + (threadIdx.x & 63)];
 }
 
-// Forward of one tile. Rows r0 .. r0+31 of X (row index through `perm` when
-// given); rows at or past `rows` are zero. Leaves z1, z2 (pre-activations,
-// C layout) in registers and x, h1, h2 (bf16) in LDS; returns y for the rows
+// Forward of one tile on one wavefront. Rows r0 .. r0+31 of X; rows at or past
+// `rows` are zero. x, h1, h2 (bf16) pass through LDS; returns y for the rows
 // held by lanes 0 and 32 (C layout of column 0) in yv.
-__device__ void tile_forward(const float *__restrict__ X, const int32_t *__restrict__ perm,
-                             int64_t r0, int64_t rows, const float *__restrict__ P,
-                             const __bf16 *__restrict__ pack, TileLds &t, f32x16 z1[2],
-                             f32x16 z2[2], f32x16 &yv) {
+__device__ void tile_forward(const float *__restrict__ X, int64_t r0, int64_t rows,
+                             const float *__restrict__ P, const __bf16 *__restrict__ pack,
+                             TileLds &t, f32x16 &yv) {
   const int lane = threadIdx.x & 63;
   {
     const int i = lane & 31, c0 = (lane >> 5) * 8;
     const int64_t row = r0 + i;
     float xv[8];
     if (row < rows) {
-      const int64_t src = perm ? perm[row] : row;
-      const float4 a = *reinterpret_cast<const float4 *>(X + src * kF + c0);
-      const float4 b = *reinterpret_cast<const float4 *>(X + src * kF + c0 + 4);
+      const float4 a = *reinterpret_cast<const float4 *>(X + row * kF + c0);
+      const float4 b = *reinterpret_cast<const float4 *>(X + row * kF + c0 + 4);
       xv[0] = a.x; xv[1] = a.y; xv[2] = a.z; xv[3] = a.w;
       xv[4] = b.x; xv[5] = b.y; xv[6] = b.z; xv[7] = b.w;
     } else {
@@ -352,7 +349,6 @@ __device__ void tile_forward(const float *__restrict__ X, const int32_t *__restr
       c[r] += b1;
       t.h1[c_row(r, lane)][nb * 32 + (lane & 31)] = (__bf16)gelu(c[r]);
     }
-    z1[nb] = c;
   }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   __builtin_amdgcn_wave_barrier();
@@ -369,7 +365,6 @@ __device__ void tile_forward(const float *__restrict__ X, const int32_t *__restr
       c[r] += b2;
       t.h2[c_row(r, lane)][nb * 32 + (lane & 31)] = (__bf16)gelu(c[r]);
     }
-    z2[nb] = c;
   }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   __builtin_amdgcn_wave_barrier();
@@ -394,8 +389,8 @@ __global__ __launch_bounds__(256) void k_mlp_forward(const float *__restrict__ X
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int64_t tiles = (rows + 31) / 32;
   for (int64_t tile = (int64_t)blockIdx.x * 4 + wv; tile < tiles; tile += (int64_t)gridDim.x * 4) {
-    f32x16 z1[2], z2[2], yv;
-    tile_forward(X, nullptr, tile * 32, rows, P, pack, tl[wv], z1, z2, yv);
+    f32x16 yv;
+    tile_forward(X, tile * 32, rows, P, pack, tl[wv], yv);
     if ((lane & 31) == 0) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
@@ -413,152 +408,287 @@ __global__ __launch_bounds__(256) void k_mlp_forward(const float *__restrict__ X
 }
 
 // Training: gradients of the mean squared error over the rows perm[b0 .. b0+nb)
-// (scale = 2 / nb), accumulated per wavefront into part[wave][kParams]; the
-// squared-error sum per wavefront into part_loss[wave].
-__global__ __launch_bounds__(256) void k_mlp_grad(const float *__restrict__ X,
+// (scale = 2 / nb), one workgroup per tile slot (tiles slot, slot + grid, ...),
+// accumulated into part[slot][kParams]; the squared-error sum into
+// part_loss[slot]. A tile is shared by two wavefronts, each with one half of
+// the 64 hidden columns: a training step has one tile per slot and as many
+// slots as fill half the CUs, so its time is the tile's serial chain, and the
+// halves run the same products and sums (the same bits) with half the GELUs
+// each (4096 rows: 12.8 us, 22.9 with one wavefront per tile).
+__global__ __launch_bounds__(128) void k_mlp_grad(const float *__restrict__ X,
                                                   const float *__restrict__ Yt,
                                                   const int32_t *__restrict__ perm, int64_t b0,
                                                   int64_t nrows, const float *__restrict__ P,
                                                   const __bf16 *__restrict__ pack,
                                                   float *__restrict__ part,
                                                   float *__restrict__ part_loss) {
-  __shared__ TileLds tl[4];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  TileLds &t = tl[wv];
-  const int64_t wave = (int64_t)blockIdx.x * 4 + wv;
-  const int64_t nwaves = (int64_t)gridDim.x * 4;
+  __shared__ TileLds t;
+  const int lane = threadIdx.x & 63, nb = threadIdx.x >> 6;  // nb: this wavefront's column half
   const int64_t tiles = (nrows + 31) / 32;
   const float scale = 2.0f / (float)nrows;
-  const int col = lane & 31;
-  f32x16 gW2[2][2] = {}, gW1[2] = {};
-  float gb1[2] = {0.f, 0.f}, gb2[2] = {0.f, 0.f}, gw3[2] = {0.f, 0.f}, gb3 = 0.f, lsum = 0.f;
-  float w3b[2];
-  for (int nb = 0; nb < 2; ++nb) w3b[nb] = bf(P[kOffW3 + nb * 32 + col]);
-  const int32_t *pr = perm + b0;
-  for (int64_t tile = wave; tile < tiles; tile += nwaves) {
-    f32x16 z1[2], z2[2], yv;
-    tile_forward(X, pr, tile * 32, nrows, P, pack, t, z1, z2, yv);
-    if (col == 0) {
+  const int col = lane & 31, hc = nb * 32 + col;
+  f32x16 gW2[2] = {}, gW1 = {};
+  float gb1 = 0.f, gb2 = 0.f, gw3 = 0.f, gb3 = 0.f, lsum = 0.f;
+  const float w3b = bf(P[kOffW3 + hc]), b1 = P[kOffB1 + hc], b2 = P[kOffB2 + hc], b3 = P[kOffB3];
+  // this half's weights stay in registers over the tiles
+  const bf16x8 w1 = wpack(pack, kPackW1 + nb);
+  bf16x8 w2[4], w2t[4], w3[4];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int i = c_row(r, lane);
-        const int64_t row = tile * 32 + i;
-        float d = 0.f;
-        if (row < nrows) {
-          const float res = yv[r] - Yt[pr[row]];
-          lsum += res * res;
-          d = scale * res;
+  for (int kb = 0; kb < 4; ++kb) {
+    w2[kb] = wpack(pack, kPackW2 + kb * 2 + nb);
+    w2t[kb] = wpack(pack, kPackW2T + kb * 2 + nb);
+    w3[kb] = wpack(pack, kPackW3 + kb);
+  }
+  const int32_t *pr = perm + b0;
+  for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    {
+      const int i = threadIdx.x & 31, c0 = (threadIdx.x >> 5) * 4;
+      const int64_t row = tile * 32 + i;
+      float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (row < nrows) a = *reinterpret_cast<const float4 *>(X + (int64_t)pr[row] * kF + c0);
+      t.x[i][c0] = (__bf16)a.x;
+      t.x[i][c0 + 1] = (__bf16)a.y;
+      t.x[i][c0 + 2] = (__bf16)a.z;
+      t.x[i][c0 + 3] = (__bf16)a.w;
+    }
+    __syncthreads();
+    f32x16 z1 = {}, z2 = {}, yv = {};
+    z1 = mfma(lds_a(&t.x[0][0], kF, 0), w1, z1);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      z1[r] += b1;
+      t.h1[c_row(r, lane)][hc] = (__bf16)gelu(z1[r]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) z2 = mfma(lds_a(&t.h1[0][0], kH, kb), w2[kb], z2);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      z2[r] += b2;
+      t.h2[c_row(r, lane)][hc] = (__bf16)gelu(z2[r]);
+    }
+    __syncthreads();
+    if (nb == 0) {
+#pragma unroll
+      for (int kb = 0; kb < 4; ++kb) yv = mfma(lds_a(&t.h2[0][0], kH, kb), w3[kb], yv);
+      if (col == 0) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int i = c_row(r, lane);
+          const int64_t row = tile * 32 + i;
+          float d = 0.f;
+          if (row < nrows) {
+            const float res = yv[r] + b3 - Yt[pr[row]];
+            lsum += res * res;
+            d = scale * res;
+          }
+          t.dy[i] = d;
+          gb3 += d;
         }
-        t.dy[i] = d;
-        gb3 += d;
       }
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    __syncthreads();
     // layer 3 and dz2 = dy w3 * gelu'(z2)
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int i = c_row(r, lane);
-        const float d = t.dy[i];
-        gw3[nb] += (float)t.h2[i][nb * 32 + col] * d;
-        const float dz = d * w3b[nb] * gelu_grad(z2[nb][r]);
-        gb2[nb] += dz;
-        t.dz[i][nb * 32 + col] = (__bf16)dz;
-      }
+    for (int r = 0; r < 16; ++r) {
+      const int i = c_row(r, lane);
+      const float d = t.dy[i];
+      gw3 += (float)t.h2[i][hc] * d;
+      const float dz = d * w3b * gelu_grad(z2[r]);
+      gb2 += dz;
+      t.dz[i][hc] = (__bf16)dz;
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    __syncthreads();
     // dW2 += h1^T dz2 ; dh1 = dz2 W2^T
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
+      const bf16x8 dzb = lds_b(&t.dz[0][0], kH, kb, nb);
 #pragma unroll
-      for (int mb = 0; mb < 2; ++mb) {
-        const bf16x8 a = lds_at(&t.h1[0][0], kH, kb, mb, kH);
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb) gW2[mb][nb] = mfma(a, lds_b(&t.dz[0][0], kH, kb, nb), gW2[mb][nb]);
-      }
+      for (int mb = 0; mb < 2; ++mb)
+        gW2[mb] = mfma(lds_at(&t.h1[0][0], kH, kb, mb, kH), dzb, gW2[mb]);
     }
-    f32x16 dh1[2];
+    f32x16 dh1 = {};
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-      f32x16 c = {};
-#pragma unroll
-      for (int kb = 0; kb < 4; ++kb)
-        c = mfma(lds_a(&t.dz[0][0], kH, kb), wpack(pack, kPackW2T + kb * 2 + nb), c);
-      dh1[nb] = c;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    for (int kb = 0; kb < 4; ++kb) dh1 = mfma(lds_a(&t.dz[0][0], kH, kb), w2t[kb], dh1);
+    __syncthreads();
     // dz1 = dh1 * gelu'(z1)
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float dz = dh1[nb][r] * gelu_grad(z1[nb][r]);
-        gb1[nb] += dz;
-        t.dz[c_row(r, lane)][nb * 32 + col] = (__bf16)dz;
-      }
+    for (int r = 0; r < 16; ++r) {
+      const float dz = dh1[r] * gelu_grad(z1[r]);
+      gb1 += dz;
+      t.dz[c_row(r, lane)][hc] = (__bf16)dz;
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    __syncthreads();
     // dW1 += x^T dz1 (rows 16..31 of the A operand are zero)
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-      const bf16x8 a = lds_at(&t.x[0][0], kF, kb, 0, kF);
-#pragma unroll
-      for (int nb = 0; nb < 2; ++nb) gW1[nb] = mfma(a, lds_b(&t.dz[0][0], kH, kb, nb), gW1[nb]);
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    for (int kb = 0; kb < 2; ++kb)
+      gW1 = mfma(lds_at(&t.x[0][0], kF, kb, 0, kF), lds_b(&t.dz[0][0], kH, kb, nb), gW1);
+    __syncthreads();
   }
-  // write this wavefront's partial gradient
-  float *g = part + wave * kParams;
+  // write this slot's partial gradient
+  float *g = part + (int64_t)blockIdx.x * kParams;
 #pragma unroll
-  for (int nb = 0; nb < 2; ++nb) {
+  for (int r = 0; r < 16; ++r) {
+    const int m = c_row(r, lane);
+    if (m < kF) g[kOffW1 + m * kH + hc] = gW1[r];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int m = c_row(r, lane);
-      if (m < kF) g[kOffW1 + m * kH + nb * 32 + col] = gW1[nb][r];
-#pragma unroll
-      for (int mb = 0; mb < 2; ++mb) g[kOffW2 + (mb * 32 + m) * kH + nb * 32 + col] = gW2[mb][nb][r];
-    }
-    const float b1 = gb1[nb] + __shfl_xor(gb1[nb], 32, 64);
-    const float b2 = gb2[nb] + __shfl_xor(gb2[nb], 32, 64);
-    const float w3 = gw3[nb] + __shfl_xor(gw3[nb], 32, 64);
-    if (lane < 32) {
-      g[kOffB1 + nb * 32 + col] = b1;
-      g[kOffB2 + nb * 32 + col] = b2;
-      g[kOffW3 + nb * 32 + col] = w3;
-    }
+    for (int mb = 0; mb < 2; ++mb) g[kOffW2 + (mb * 32 + m) * kH + hc] = gW2[mb][r];
   }
-  const float b3 = gb3 + __shfl_xor(gb3, 32, 64);
+  const float s1 = gb1 + __shfl_xor(gb1, 32, 64);
+  const float s2 = gb2 + __shfl_xor(gb2, 32, 64);
+  const float s3 = gw3 + __shfl_xor(gw3, 32, 64);
+  if (lane < 32) {
+    g[kOffB1 + hc] = s1;
+    g[kOffB2 + hc] = s2;
+    g[kOffW3 + hc] = s3;
+  }
+  const float sb = gb3 + __shfl_xor(gb3, 32, 64);
   const float ls = lsum + __shfl_xor(lsum, 32, 64);
-  if (lane == 0) {
-    g[kOffB3] = b3;
-    part_loss[wave] = ls;
+  if (threadIdx.x == 0) {
+    g[kOffB3] = sb;
+    part_loss[blockIdx.x] = ls;
   }
 }
 
-// grad[p] = sum over wavefronts (fixed order); loss = sum of part_loss
-__global__ void k_grad_reduce(const float *__restrict__ part, const float *__restrict__ part_loss,
-                              int32_t nwaves, float *__restrict__ grad, float *__restrict__ loss) {
-  for (int p = blockIdx.x * blockDim.x + threadIdx.x; p <= kParams; p += gridDim.x * blockDim.x) {
-    if (p < kParams) {
-      double s = 0.0;
-      for (int w = 0; w < nwaves; ++w) s += part[(int64_t)w * kParams + p];
-      grad[p] = (float)s;
-    } else {
-      double s = 0.0;
-      for (int w = 0; w < nwaves; ++w) s += part_loss[w];
-      *loss = (float)s;
+// Sum of parameter p's partials over the slots (a workgroup of 256: 64
+// parameters, a quarter of the slots per wavefront, eight loads in flight, in
+// double), valid on wavefront 0; p = kParams: the squared-error sums. One
+// thread per parameter walked every slot in turn (128 slots: 35 us).
+__device__ __forceinline__ double grad_sum(const float *__restrict__ part,
+                                           const float *__restrict__ part_loss, int32_t slots,
+                                           int p) {
+  __shared__ double sh[4][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int32_t per = (slots + 3) / 4, lo = w * per, hi = min(slots, lo + per);
+  const float *src = p < kParams ? part + p : part_loss;
+  const int64_t stride = p < kParams ? kParams : 1;
+  double s = 0.0;
+  if (p <= kParams) {
+    int32_t i = lo;
+    for (; i + 8 <= hi; i += 8) {
+      float v[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v[q] = src[(i + q) * stride];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) s += v[q];
     }
+    for (; i < hi; ++i) s += src[i * stride];
+  }
+  sh[w][lane] = s;
+  __syncthreads();
+  return sh[0][lane] + sh[1][lane] + sh[2][lane] + sh[3][lane];
+}
+
+// grad[p] = sum over the slots (fixed order); loss = sum of part_loss
+__global__ __launch_bounds__(256) void k_grad_reduce(const float *__restrict__ part,
+                                                     const float *__restrict__ part_loss,
+                                                     int32_t slots, float *__restrict__ grad,
+                                                     float *__restrict__ loss) {
+  const int p = blockIdx.x * 64 + (threadIdx.x & 63);
+  const double s = grad_sum(part, part_loss, slots, p);
+  if (threadIdx.x >= 64) return;
+  if (p < kParams) grad[p] = (float)s;
+  else if (p == kParams) *loss = (float)s;
+}
+
+// place of element (row k of the K dimension, column n) in packed block `block`
+__device__ __forceinline__ int pack_at(int block, int k, int n) {
+  return (block * 64 + (((k & 15) >> 3) << 5) + n) * 8 + (k & 7);
+}
+
+// One training step's update: the gradient's sum over the slots, Adam (Kingma
+// and Ba, 2015) on the FP32 masters, step t (1-based), and the new weights'
+// places in the BF16 operand blocks (the zero columns of the last layer's
+// block stay as k_pack wrote them).
+__global__ __launch_bounds__(256) void k_grad_step(const float *__restrict__ part, int32_t slots,
+                                                   float *__restrict__ P, float *__restrict__ M,
+                                                   float *__restrict__ V,
+                                                   __bf16 *__restrict__ pack, float lr, float b1,
+                                                   float b2, float eps, float wd, int32_t t) {
+  const int p = blockIdx.x * 64 + (threadIdx.x & 63);
+  const double s = grad_sum(part, nullptr, slots, p < kParams ? p : kParams + 1);
+  if (threadIdx.x >= 64 || p >= kParams) return;
+  const float c1 = 1.0f - powf(b1, (float)t), c2 = 1.0f - powf(b2, (float)t);
+  const float g = (float)s;
+  // (fused multiply-adds written out: which product is rounded decides bits)
+  const float m = fmaf(1.0f - b1, g, b1 * M[p]);
+  const float v = fmaf(g, (1.0f - b2) * g, b2 * V[p]);
+  M[p] = m;
+  V[p] = v;
+  const float x = fmaf(-lr, fmaf(wd, P[p], (m / c1) / (sqrtf(v / c2) + eps)), P[p]);
+  P[p] = x;
+  const __bf16 w = (__bf16)x;
+  if (p < kOffB1) {
+    const int k = p / kH, n = p % kH;
+    pack[pack_at(kPackW1 + n / 32, k, n % 32)] = w;
+  } else if (p >= kOffW2 && p < kOffB2) {
+    const int k = (p - kOffW2) / kH, n = (p - kOffW2) % kH;
+    pack[pack_at(kPackW2 + (k / 16) * 2 + n / 32, k, n % 32)] = w;
+    pack[pack_at(kPackW2T + (n / 16) * 2 + k / 32, n, k % 32)] = w;
+  } else if (p >= kOffW3 && p < kOffB3) {
+    const int k = p - kOffW3;
+    pack[pack_at(kPackW3 + k / 16, k, 0)] = w;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// standardisation of training rows: column means and spreads in double (two
+// passes, per-workgroup sums added in a fixed order), then (x - mean) inv_std
+// ---------------------------------------------------------------------------
+constexpr int kStatBlocks = 256;
+
+// part[block][c] = sum over the block's rows of x, or of (x - mean)^2
+__global__ __launch_bounds__(256) void k_col_sums(const float *__restrict__ X, int64_t rows,
+                                                  const double *__restrict__ mean,
+                                                  double *__restrict__ part) {
+  __shared__ double sh[16][kF];
+  const int c = threadIdx.x & (kF - 1), r0 = threadIdx.x / kF;
+  const double m = mean ? mean[c] : 0.0;
+  double s = 0.0;
+  for (int64_t i = (int64_t)blockIdx.x * 16 + r0; i < rows; i += (int64_t)gridDim.x * 16) {
+    const double d = (double)X[i * kF + c] - m;
+    s += mean ? d * d : d;
+  }
+  sh[r0][c] = s;
+  __syncthreads();
+  if (threadIdx.x < kF) {
+    double a = 0.0;
+    for (int j = 0; j < 16; ++j) a += sh[j][c];
+    part[blockIdx.x * kF + c] = a;
+  }
+}
+
+// mean[c], or (spread) the float mean and 1 / standard deviation: 16 threads
+// per column add the workgroups' sums
+__global__ __launch_bounds__(256) void k_col_stats(const double *__restrict__ part,
+                                                   int32_t blocks, int64_t rows,
+                                                   double *__restrict__ mean, bool spread,
+                                                   float *__restrict__ mean_f,
+                                                   float *__restrict__ inv_f) {
+  __shared__ double sh[16][kF];
+  const int c = threadIdx.x & (kF - 1), j = threadIdx.x / kF;
+  double s = 0.0;
+  for (int32_t b = j; b < blocks; b += 16) s += part[b * kF + c];
+  sh[j][c] = s;
+  __syncthreads();
+  if (j > 0) return;
+  for (int q = 1; q < 16; ++q) s += sh[q][c];
+  s /= (double)rows;
+  if (!spread) {
+    mean[c] = s;
+    return;
+  }
+  const double sd = sqrt(s);
+  mean_f[c] = (float)mean[c];
+  inv_f[c] = (float)(sd > 1e-6 ? 1.0 / sd : 1.0);
+}
+
+__global__ __launch_bounds__(256) void k_standardise(float *__restrict__ X, int64_t count,
+                                                     const float *__restrict__ mean,
+                                                     const float *__restrict__ inv) {
+  for (int64_t i = blockIdx.x * 256ll + threadIdx.x; i < count; i += (int64_t)gridDim.x * 256) {
+    const int c = (int)(i & (kF - 1));
+    X[i] = (X[i] - mean[c]) * inv[c];
   }
 }
 
@@ -585,21 +715,6 @@ __global__ void k_pack(const float *__restrict__ P, __bf16 *__restrict__ pack) {
   }
 }
 
-// Adam (Kingma and Ba, 2015) on the FP32 masters: step t (1-based)
-__global__ void k_adam(float *__restrict__ P, float *__restrict__ M, float *__restrict__ V,
-                       const float *__restrict__ grad, float lr, float b1, float b2, float eps,
-                       float wd, int32_t t) {
-  const float c1 = 1.0f - powf(b1, (float)t), c2 = 1.0f - powf(b2, (float)t);
-  for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < kParams; p += gridDim.x * blockDim.x) {
-    const float g = grad[p];
-    const float m = b1 * M[p] + (1.0f - b1) * g;
-    const float v = b2 * V[p] + (1.0f - b2) * g * g;
-    M[p] = m;
-    V[p] = v;
-    P[p] -= lr * ((m / c1) / (sqrtf(v / c2) + eps) + wd * P[p]);
-  }
-}
-
 hipError_t launch_mlp_pack(const float *P, __bf16 *pack, hipStream_t st) {
   hipLaunchKernelGGL(k_pack, dim3(22), dim3(512), 0, st, P, pack);
   return hipGetLastError();
@@ -614,23 +729,49 @@ hipError_t launch_mlp_forward(const float *X, int64_t rows, const float *P, cons
   return hipGetLastError();
 }
 
-// gradient of the mean squared error over perm[b0 .. b0+nrows) with `nblocks`
-// workgroups of 4 wavefronts; part has room for nblocks*4 partials
-hipError_t launch_mlp_grad(const float *X, const float *Yt, const int32_t *perm, int64_t b0,
-                           int64_t nrows, const float *P, const __bf16 *pack, float *part,
-                           float *part_loss, int32_t nblocks, float *grad, float *loss,
-                           hipStream_t st) {
-  hipLaunchKernelGGL(k_mlp_grad, dim3(nblocks), dim3(256), 0, st, X, Yt, perm, b0, nrows, P, pack,
+// partial gradients of the mean squared error over perm[b0 .. b0+nrows) in
+// `slots` tile slots; part has room for as many
+hipError_t launch_mlp_partials(const float *X, const float *Yt, const int32_t *perm, int64_t b0,
+                               int64_t nrows, const float *P, const __bf16 *pack, float *part,
+                               float *part_loss, int32_t slots, hipStream_t st) {
+  hipLaunchKernelGGL(k_mlp_grad, dim3(slots), dim3(128), 0, st, X, Yt, perm, b0, nrows, P, pack,
                      part, part_loss);
-  hipLaunchKernelGGL(k_grad_reduce, dim3((kParams + 256) / 256), dim3(256), 0, st, part,
-                     part_loss, nblocks * 4, grad, loss);
   return hipGetLastError();
 }
 
-hipError_t launch_adam(float *P, float *M, float *V, const float *grad, float lr, float b1,
-                       float b2, float eps, float wd, int32_t t, hipStream_t st) {
-  hipLaunchKernelGGL(k_adam, dim3((kParams + 255) / 256), dim3(256), 0, st, P, M, V, grad, lr, b1,
-                     b2, eps, wd, t);
+// the gradient and the sum of squared errors from the partials
+hipError_t launch_grad_reduce(const float *part, const float *part_loss, int32_t slots,
+                              float *grad, float *loss, hipStream_t st) {
+  hipLaunchKernelGGL(k_grad_reduce, dim3(kParams / 64 + 1), dim3(256), 0, st, part, part_loss,
+                     slots, grad, loss);
+  return hipGetLastError();
+}
+
+// one optimiser step from the partials: P, M, V and the packed weights
+hipError_t launch_grad_step(const float *part, int32_t slots, float *P, float *M, float *V,
+                            __bf16 *pack, float lr, float b1, float b2, float eps, float wd,
+                            int32_t t, hipStream_t st) {
+  hipLaunchKernelGGL(k_grad_step, dim3((kParams + 63) / 64), dim3(256), 0, st, part, slots, P, M,
+                     V, pack, lr, b1, b2, eps, wd, t);
+  return hipGetLastError();
+}
+
+// X (rows x 16, device) standardised in place; mean / inv: 16 floats each.
+// scratch: standardise_scratch() doubles.
+int64_t standardise_scratch() { return (int64_t)kStatBlocks * kF + kF; }
+hipError_t launch_standardise(float *X, int64_t rows, double *scratch, float *mean, float *inv,
+                              hipStream_t st) {
+  const int32_t blocks = (int32_t)std::min<int64_t>(kStatBlocks, (rows + 15) / 16);
+  double *m = scratch + (int64_t)kStatBlocks * kF;
+  hipLaunchKernelGGL(k_col_sums, dim3(blocks), dim3(256), 0, st, X, rows, nullptr, scratch);
+  hipLaunchKernelGGL(k_col_stats, dim3(1), dim3(256), 0, st, scratch, blocks, rows, m, false,
+                     nullptr, nullptr);
+  hipLaunchKernelGGL(k_col_sums, dim3(blocks), dim3(256), 0, st, X, rows, m, scratch);
+  hipLaunchKernelGGL(k_col_stats, dim3(1), dim3(256), 0, st, scratch, blocks, rows, m, true, mean,
+                     inv);
+  hipLaunchKernelGGL(k_standardise,
+                     dim3((unsigned)std::min<int64_t>((rows * kF + 255) / 256, 8192)), dim3(256),
+                     0, st, X, rows * kF, mean, inv);
   return hipGetLastError();
 }
 

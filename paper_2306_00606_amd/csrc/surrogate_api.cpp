@@ -18,12 +18,17 @@ hipError_t launch_features(const Graph &g, const float *mean, const float *inv_s
 hipError_t launch_mlp_pack(const float *P, __bf16 *pack, hipStream_t st);
 hipError_t launch_mlp_forward(const float *X, int64_t rows, const float *P, const __bf16 *pack,
                               const float *lnN, float *y, double *ef, hipStream_t st);
-hipError_t launch_mlp_grad(const float *X, const float *Yt, const int32_t *perm, int64_t b0,
-                           int64_t nrows, const float *P, const __bf16 *pack, float *part,
-                           float *part_loss, int32_t nblocks, float *grad, float *loss,
-                           hipStream_t st);
-hipError_t launch_adam(float *P, float *M, float *V, const float *grad, float lr, float b1,
-                       float b2, float eps, float wd, int32_t t, hipStream_t st);
+hipError_t launch_mlp_partials(const float *X, const float *Yt, const int32_t *perm, int64_t b0,
+                               int64_t nrows, const float *P, const __bf16 *pack, float *part,
+                               float *part_loss, int32_t slots, hipStream_t st);
+hipError_t launch_grad_reduce(const float *part, const float *part_loss, int32_t slots,
+                              float *grad, float *loss, hipStream_t st);
+hipError_t launch_grad_step(const float *part, int32_t slots, float *P, float *M, float *V,
+                            __bf16 *pack, float lr, float b1, float b2, float eps, float wd,
+                            int32_t t, hipStream_t st);
+int64_t standardise_scratch();
+hipError_t launch_standardise(float *X, int64_t rows, double *scratch, float *mean, float *inv,
+                              hipStream_t st);
 int32_t mlp_param_count();
 int32_t mlp_pack_count();
 }  // namespace efi
@@ -37,7 +42,13 @@ extern "C" ef_status ef_topk(ef_graph *g, ef_algo algo, ef_prec prec, int32_t k,
                              double *ef, uint32_t flags, void *hip_stream);
 
 constexpr int kNF = 16;
-constexpr int kMaxGradBlocks = 64;
+constexpr int kMaxGradSlots = 256;  // tile slots of a gradient
+
+// slots of a gradient over `rows` rows: a tile of 32 each, in multiples of 4
+static int32_t grad_slots(int64_t rows) {
+  const int64_t tiles = (rows + 31) / 32;
+  return (int32_t)std::min<int64_t>((tiles + 3) / 4 * 4, kMaxGradSlots);
+}
 
 struct ef_surrogate {
   std::vector<float> P, M, V;  // FP32 masters and Adam moments (host copies)
@@ -59,8 +70,8 @@ static ef_status sg_device(ef_surrogate *s) {
   if (e == hipSuccess) e = hipMalloc(&s->dV, sizeof(float) * np);
   if (e == hipSuccess) e = hipMalloc(&s->dgrad, sizeof(float) * np);
   if (e == hipSuccess) e = hipMalloc(&s->dloss, sizeof(float) * 4);
-  if (e == hipSuccess) e = hipMalloc(&s->dpart, sizeof(float) * np * kMaxGradBlocks * 4);
-  if (e == hipSuccess) e = hipMalloc(&s->dpart_loss, sizeof(float) * kMaxGradBlocks * 4);
+  if (e == hipSuccess) e = hipMalloc(&s->dpart, sizeof(float) * np * kMaxGradSlots);
+  if (e == hipSuccess) e = hipMalloc(&s->dpart_loss, sizeof(float) * kMaxGradSlots);
   if (e == hipSuccess) e = hipMalloc(&s->dmean, sizeof(float) * kNF);
   if (e == hipSuccess) e = hipMalloc(&s->dinv, sizeof(float) * kNF);
   if (e == hipSuccess) e = hipMalloc(&s->dpack, sizeof(__bf16) * (size_t)mlp_pack_count());
@@ -293,11 +304,12 @@ ef_status ef_surrogate_gradients(ef_surrogate *s, const float *X, const float *y
   if (e == hipSuccess) e = hipMemcpyAsync(dX, X, sizeof(float) * kNF * rows, hipMemcpyHostToDevice, st);
   if (e == hipSuccess) e = hipMemcpyAsync(dy, y, sizeof(float) * rows, hipMemcpyHostToDevice, st);
   if (e == hipSuccess) e = hipMemcpyAsync(dperm, perm.data(), sizeof(int32_t) * rows, hipMemcpyHostToDevice, st);
-  const int64_t tiles = (rows + 31) / 32;
-  const int32_t nblocks = (int32_t)std::min<int64_t>((tiles + 3) / 4, kMaxGradBlocks);
+  const int32_t slots = grad_slots(rows);
   if (e == hipSuccess)
-    e = launch_mlp_grad(dX, dy, dperm, 0, rows, s->dP, s->dpack, s->dpart, s->dpart_loss, nblocks,
-                        s->dgrad, s->dloss, st);
+    e = launch_mlp_partials(dX, dy, dperm, 0, rows, s->dP, s->dpack, s->dpart, s->dpart_loss,
+                            slots, st);
+  if (e == hipSuccess)
+    e = launch_grad_reduce(s->dpart, s->dpart_loss, slots, s->dgrad, s->dloss, st);
   float hl = 0.f;
   if (e == hipSuccess)
     e = hipMemcpyAsync(grad, s->dgrad, sizeof(float) * mlp_param_count(), hipMemcpyDeviceToHost, st);
@@ -351,41 +363,45 @@ ef_status ef_surrogate_train(ef_surrogate *s, const float *X, const float *y, in
   hipStream_t st = (hipStream_t)hip_stream;
   ef_status r = sg_download(s, st);
   if (r != EF_OK) return r;
-  // standardisation from the data (FP64 sums on the host)
-  for (int f = 0; f < kNF; ++f) {
-    double m = 0.0, q = 0.0;
-    for (int64_t i = 0; i < rows; ++i) m += X[i * kNF + f];
-    m /= (double)rows;
-    for (int64_t i = 0; i < rows; ++i) {
-      const double d = X[i * kNF + f] - m;
-      q += d * d;
-    }
-    const double sd = std::sqrt(q / (double)rows);
-    s->mean[f] = (float)m;
-    s->inv_std[f] = (float)(sd > 1e-6 ? 1.0 / sd : 1.0);
-  }
-  std::vector<float> Xs((size_t)rows * kNF);
-  for (int64_t i = 0; i < rows; ++i)
-    for (int f = 0; f < kNF; ++f)
-      Xs[i * kNF + f] = (X[i * kNF + f] - s->mean[f]) * s->inv_std[f];
-  // split
-  std::mt19937_64 rng(cfg->seed);
-  std::vector<int32_t> idx((size_t)rows);
-  std::iota(idx.begin(), idx.end(), 0);
-  std::shuffle(idx.begin(), idx.end(), rng);
-  const int64_t nval = (int64_t)(cfg->val_fraction * (double)rows);
-  const int64_t ntr = rows - nval;
-  if ((r = sg_upload(s, st)) != EF_OK) return r;
+  // rows to the device, standardised there from the data (FP64 sums); the
+  // shuffles run meanwhile
   float *dX = nullptr, *dy = nullptr, *dbest = nullptr;
+  double *dstat = nullptr;
   int32_t *dperm = nullptr, *dval = nullptr;
   const size_t np = (size_t)mlp_param_count();
+  const int64_t nval = (int64_t)(cfg->val_fraction * (double)rows);
+  const int64_t ntr = rows - nval;
   hipError_t e = hipMalloc(&dX, sizeof(float) * kNF * rows);
   if (e == hipSuccess) e = hipMalloc(&dy, sizeof(float) * rows);
   if (e == hipSuccess) e = hipMalloc(&dperm, sizeof(int32_t) * std::max<int64_t>(ntr, 1));
   if (e == hipSuccess) e = hipMalloc(&dval, sizeof(int32_t) * std::max<int64_t>(nval, 1));
   if (e == hipSuccess) e = hipMalloc(&dbest, sizeof(float) * np);
-  if (e == hipSuccess) e = hipMemcpyAsync(dX, Xs.data(), sizeof(float) * kNF * rows, hipMemcpyHostToDevice, st);
-  if (e == hipSuccess) e = hipMemcpyAsync(dy, y, sizeof(float) * rows, hipMemcpyHostToDevice, st);
+  if (e == hipSuccess)
+    e = hipMalloc(&dstat, sizeof(double) * (size_t)standardise_scratch() + sizeof(float) * 2 * kNF);
+  float *dms = e == hipSuccess ? (float *)(dstat + standardise_scratch()) : nullptr;
+  if (e == hipSuccess) e = hipMemcpyAsync(dX, X, sizeof(float) * kNF * rows, hipMemcpyHostToDevice, st);
+  if (e == hipSuccess) e = launch_standardise(dX, rows, dstat, dms, dms + kNF, st);
+  float h_ms[2 * kNF];
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(dy, y, sizeof(float) * rows, hipMemcpyHostToDevice, st);
+  // split
+  std::mt19937_64 rng(cfg->seed);
+  std::vector<int32_t> idx((size_t)rows);
+  std::iota(idx.begin(), idx.end(), 0);
+  std::shuffle(idx.begin(), idx.end(), rng);
+  std::vector<int32_t> tr(idx.begin(), idx.begin() + ntr), tr_next;
+  if (cfg->epochs > 0) {
+    tr_next = tr;
+    std::shuffle(tr_next.begin(), tr_next.end(), rng);
+  }
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(h_ms, dms, sizeof(h_ms), hipMemcpyDeviceToHost, st);
+  if (e == hipSuccess) e = hipStreamSynchronize(st);
+  if (e == hipSuccess) {
+    std::memcpy(s->mean, h_ms, sizeof(s->mean));
+    std::memcpy(s->inv_std, h_ms + kNF, sizeof(s->inv_std));
+    if ((r = sg_upload(s, st)) != EF_OK) e = hipErrorUnknown;
+  }
   if (e == hipSuccess && nval > 0)
     e = hipMemcpyAsync(dval, idx.data() + ntr, sizeof(int32_t) * nval, hipMemcpyHostToDevice, st);
   if (e == hipSuccess) e = hipMemcpyAsync(dbest, s->dP, sizeof(float) * np, hipMemcpyDeviceToDevice, st);
@@ -393,7 +409,6 @@ ef_status ef_surrogate_train(ef_surrogate *s, const float *X, const float *y, in
   if (e == hipSuccess) e = hipEventCreate(&t0);
   if (e == hipSuccess) e = hipEventCreate(&t1);
   if (e == hipSuccess) e = hipEventRecord(t0, st);
-  std::vector<int32_t> tr(idx.begin(), idx.begin() + ntr);
   float best = INFINITY, last_train = 0.f, last_val = 0.f;
   int32_t since_best = 0, epochs_run = 0;
   const int64_t batch = cfg->batch;
@@ -407,32 +422,36 @@ ef_status ef_surrogate_train(ef_surrogate *s, const float *X, const float *y, in
     return (float)(cfg->lr * f);
   };
   for (int32_t ep = 0; ep < cfg->epochs && e == hipSuccess; ++ep) {
-    std::shuffle(tr.begin(), tr.end(), rng);
+    tr.swap(tr_next);
     e = hipMemcpyAsync(dperm, tr.data(), sizeof(int32_t) * ntr, hipMemcpyHostToDevice, st);
-    double tl = 0.0;
     for (int64_t b0 = 0; b0 < ntr && e == hipSuccess; b0 += batch) {
       const int64_t nb = std::min(batch, ntr - b0);
-      const int64_t tiles = (nb + 31) / 32;
-      const int32_t nblocks = (int32_t)std::min<int64_t>((tiles + 3) / 4, kMaxGradBlocks);
-      e = launch_mlp_grad(dX, dy, dperm, b0, nb, s->dP, s->dpack, s->dpart, s->dpart_loss,
-                          nblocks, s->dgrad, s->dloss, st);
+      const int32_t slots = grad_slots(nb);
+      e = launch_mlp_partials(dX, dy, dperm, b0, nb, s->dP, s->dpack, s->dpart, s->dpart_loss,
+                              slots, st);
       if (e == hipSuccess)
-        e = launch_adam(s->dP, s->dM, s->dV, s->dgrad, step_lr(t_step++), 0.9f, 0.999f, 1e-8f,
-                        cfg->weight_decay, ++s->step, st);
-      if (e == hipSuccess) e = launch_mlp_pack(s->dP, s->dpack, st);
+        e = launch_grad_step(s->dpart, slots, s->dP, s->dM, s->dV, s->dpack, step_lr(t_step++),
+                             0.9f, 0.999f, 1e-8f, cfg->weight_decay, ++s->step, st);
     }
-    // training loss of the epoch's last state and validation loss
+    // validation loss
     float hl = 0.f;
     if (e == hipSuccess && nval > 0) {
-      const int64_t tiles = (nval + 31) / 32;
-      const int32_t nblocks = (int32_t)std::min<int64_t>((tiles + 3) / 4, kMaxGradBlocks);
-      e = launch_mlp_grad(dX, dy, dval, 0, nval, s->dP, s->dpack, s->dpart, s->dpart_loss,
-                          nblocks, s->dgrad, s->dloss, st);
-      if (e == hipSuccess) e = hipMemcpyAsync(&hl, s->dloss, sizeof(float), hipMemcpyDeviceToHost, st);
+      const int32_t slots = grad_slots(nval);
+      e = launch_mlp_partials(dX, dy, dval, 0, nval, s->dP, s->dpack, s->dpart, s->dpart_loss,
+                              slots, st);
+      if (e == hipSuccess)
+        e = launch_grad_reduce(s->dpart, s->dpart_loss, slots, s->dgrad, s->dloss, st);
+    }
+    // the next epoch's order, while this one runs
+    if (ep + 1 < cfg->epochs) {
+      tr_next = tr;
+      std::shuffle(tr_next.begin(), tr_next.end(), rng);
+    }
+    if (e == hipSuccess && nval > 0) {
+      e = hipMemcpyAsync(&hl, s->dloss, sizeof(float), hipMemcpyDeviceToHost, st);
       if (e == hipSuccess) e = hipStreamSynchronize(st);
       last_val = hl / (float)nval;
     }
-    (void)tl;
     ++epochs_run;
     const float score = nval > 0 ? last_val : (float)ep;
     if (nval > 0 && score < best) {
@@ -450,14 +469,14 @@ ef_status ef_surrogate_train(ef_surrogate *s, const float *X, const float *y, in
     if (e == hipSuccess) e = launch_mlp_pack(s->dP, s->dpack, st);
   }
   if (e == hipSuccess) {
-    const int64_t tiles = (ntr + 31) / 32;
-    const int32_t nblocks = (int32_t)std::min<int64_t>((tiles + 3) / 4, kMaxGradBlocks);
-    std::vector<int32_t> ordered(tr);
-    e = hipMemcpyAsync(dperm, ordered.data(), sizeof(int32_t) * ntr, hipMemcpyHostToDevice, st);
+    const int32_t slots = grad_slots(ntr);
+    e = hipMemcpyAsync(dperm, tr.data(), sizeof(int32_t) * ntr, hipMemcpyHostToDevice, st);
     float hl = 0.f;
     if (e == hipSuccess)
-      e = launch_mlp_grad(dX, dy, dperm, 0, ntr, s->dP, s->dpack, s->dpart, s->dpart_loss,
-                          nblocks, s->dgrad, s->dloss, st);
+      e = launch_mlp_partials(dX, dy, dperm, 0, ntr, s->dP, s->dpack, s->dpart, s->dpart_loss,
+                              slots, st);
+    if (e == hipSuccess)
+      e = launch_grad_reduce(s->dpart, s->dpart_loss, slots, s->dgrad, s->dloss, st);
     if (e == hipSuccess) e = hipMemcpyAsync(&hl, s->dloss, sizeof(float), hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipEventRecord(t1, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
@@ -472,6 +491,8 @@ ef_status ef_surrogate_train(ef_surrogate *s, const float *X, const float *y, in
   (void)hipFree(dperm);
   (void)hipFree(dval);
   (void)hipFree(dbest);
+  (void)hipFree(dstat);
+  if (r != EF_OK) return r;
   if (e != hipSuccess) return hip_status(e, "surrogate training");
   s->host_dirty = true;
   if (rep) {
