@@ -756,7 +756,8 @@ static ef_status score_table(Graph &g, hipStream_t st) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(st, &cap) != hipSuccess) (void)hipGetLastError();
   if (cap != hipStreamCaptureStatusNone) return EF_OK;
-  const int32_t n = 3 * g.info.max_degree + 1;  // cluster degrees are at most 3 k_max - 4
+  // cluster degrees are below 3 k_max, with three events below 4 k_max
+  const int32_t n = 4 * g.info.max_degree + 1;
   if (dev_alloc(g, (void **)&g.score64, sizeof(double) * (size_t)n, "score table") != EF_OK) {
     g.score64 = nullptr;
     return EF_OK;
@@ -1305,8 +1306,9 @@ extern "C" ef_status ef_compute_j3(ef_graph *h, ef_prec prec, const int32_t *see
   int32_t *j3_lists = (int32_t *)g.ws[WS_J3L].p;
   int32_t *j3_counts = j3_lists + 5 * std::max<int64_t>(n_items, 1);
   const bool fp64 = prec == EF_PREC_FP64;
+  if (fp64 && (s = score_table(g, st)) != EF_OK) return s;
   prof.mark(0);
-  e = launch_j3_items(g, fp64, d_ord, d_off, n_work, n_items, j3_lists, j3_counts, PN, PD, PS,
+  e = launch_j3_items(g, fp64, all, d_ord, d_off, n_work, n_items, j3_lists, j3_counts, PN, PD, PS,
                       st);
   if (e != hipSuccess) return hip_status(e, "three-event items");
   prof.mark(1);
@@ -1344,7 +1346,7 @@ extern "C" ef_status ef_compute_j3(ef_graph *h, ef_prec prec, const int32_t *see
         e = hipMemcpyAsync(fpos, fpos_h.data(), sizeof(int32_t) * fpos_h.size(),
                            hipMemcpyHostToDevice, st);
       if (e == hipSuccess)
-        e = launch_j3_items(g, true, pord, po, n_flag, foff.back(), j3_lists, j3_counts, PN, PD,
+        e = launch_j3_items(g, true, false, pord, po, n_flag, foff.back(), j3_lists, j3_counts, PN, PD,
                             PS, st);
       if (e == hipSuccess)
         e = launch_j3_finish(g, true, PN, PD, PS, d_useeds, fpos, n_flag, ef_w, D_w, N_w,

@@ -345,7 +345,9 @@ hipError_t launch_per_seed(const Graph &g, ef_prec prec, const int32_t *seeds,
 // Expected Force with three transmission events (j3.hip): items are the arcs
 // of seeds[0 .. nseeds), seed i owning items off[i] .. off[i+1]; per-arc
 // partial sums in PN / PD / PS. lists: 5 * n_items ints of scratch, counts: 5.
-hipError_t launch_j3_items(const Graph &g, bool fp64, const int32_t *seeds, const int64_t *off,
+// both: the seeds are all nodes, and an edge's two arcs share one item.
+hipError_t launch_j3_items(const Graph &g, bool fp64, bool both, const int32_t *seeds,
+                           const int64_t *off,
                            int32_t nseeds, int64_t n_items, int32_t *lists, int32_t *counts,
                            long long *PN, long long *PD, double *PS, hipStream_t st);
 // N, D, EF of output positions (all of 0 .. count-1, or the count listed in

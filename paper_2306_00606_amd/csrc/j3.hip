@@ -30,7 +30,9 @@
 // lane per prefix walks a three-way merge of the sorted rows N(s), N(y),
 // N(z), which meets every w exactly c_w times in a row.
 // Item sums (event count, sum of d_J, sum of g(d_J)) are stored per arc and
-// summed per seed.
+// summed per seed. They belong to the infected set {s, y}, whichever of the two
+// was the seed: when every node is a seed (`both`), an edge is one item, stored
+// for both its arcs.
 //
 // Precision: FP64 scores d ln d in double. FP32C scores d log2 d with
 // v_log_f32 and sums them in double; the seed's EF is taken in double.
@@ -86,12 +88,13 @@ __device__ __forceinline__ int j3_bin(int32_t L) {
   return L <= kJ3LmaxW ? 0 : L <= kJ3Lmax0 ? 1 : L <= kJ3Lmax1 ? 2 : L <= kJ3Lmax2 ? 3 : 4;
 }
 
-// Sort the items into per-bin lists of arcs (lists + b * cap), counts[b]
-// advanced with one atomic per workgroup and bin (counts cleared before).
+// Sort the items (both: the arcs below their reverse) into per-bin lists of
+// arcs (lists + b * cap), counts[b] advanced with one atomic per workgroup and bin (counts cleared before).
 __global__ __launch_bounds__(256) void k_j3_bins(const int32_t *__restrict__ row_ptr,
                                                  const int2 *__restrict__ adj2,
                                                  const int32_t *__restrict__ seeds,
                                                  const int64_t *__restrict__ off, int32_t nseeds,
+                                                 const int32_t *__restrict__ rev, bool both,
                                                  int32_t *__restrict__ lists, int64_t cap,
                                                  int32_t *__restrict__ counts) {
   __shared__ int32_t wcnt[4][kJ3Bins];
@@ -106,7 +109,7 @@ __global__ __launch_bounds__(256) void k_j3_bins(const int32_t *__restrict__ row
       const int32_t i = j3_item_seed(off, nseeds, it);
       const int32_t sd = seeds[i];
       e = row_ptr[sd] + (int32_t)(it - off[i]);
-      bin = j3_bin(row_ptr[sd + 1] - row_ptr[sd] + adj2[e].y - 2);
+      if (!both || e < rev[e]) bin = j3_bin(row_ptr[sd + 1] - row_ptr[sd] + adj2[e].y - 2);
     }
     int32_t rank = 0;
     for (int b = 0; b < kJ3Bins; ++b) {
@@ -132,6 +135,21 @@ __global__ __launch_bounds__(256) void k_j3_bins(const int32_t *__restrict__ row
   }
 }
 
+// the sums of the item of arc e
+__device__ __forceinline__ void j3_store(long long *PN, long long *PD, double *PS,
+                                         const int32_t *rev, int32_t e, bool both, long long n,
+                                         long long d, double s) {
+  PN[e] = n;
+  PD[e] = d;
+  PS[e] = s;
+  if (both) {
+    const int32_t r = rev[e];
+    PN[r] = n;
+    PD[r] = d;
+    PS[r] = s;
+  }
+}
+
 // Merge path: one wavefront per item (arc e of the list), one lane per prefix.
 template <typename T>
 __global__ __launch_bounds__(256) void k_j3_merge(const int32_t *__restrict__ row_ptr,
@@ -142,7 +160,7 @@ __global__ __launch_bounds__(256) void k_j3_merge(const int32_t *__restrict__ ro
                                                   const int32_t *__restrict__ count_p,
                                                   long long *__restrict__ PN,
                                                   long long *__restrict__ PD,
-                                                  double *__restrict__ PS) {
+                                                  double *__restrict__ PS, bool both) {
   const int lane = threadIdx.x & 63;
   const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
@@ -197,11 +215,7 @@ __global__ __launch_bounds__(256) void k_j3_merge(const int32_t *__restrict__ ro
     cn = wave_sum_i64(cn);
     cd = wave_sum_i64(cd);
     cs = wave_sum_f64(cs);
-    if (lane == 0) {
-      PN[e] = cn;
-      PD[e] = cd;
-      PS[e] = cs;
-    }
+    if (lane == 0) j3_store(PN, PD, PS, rev, e, both, cn, cd, cs);
   }
 }
 
@@ -217,19 +231,33 @@ __device__ __forceinline__ int32_t j3_find_or_insert(int32_t *keys, int32_t x) {
   }
 }
 
-// Union path: one workgroup of WPB wavefronts per item (arc e of the list,
-// list length L <= SLOTS / 2), prefixes in chunks of PCH. Within a chunk the
-// M part depends on a prefix only through d_T: it is evaluated once per
-// distinct d_T and weighted by the number of prefixes that share it.
+// The score of a cluster degree as it enters the sums: FP32C from v_log_f32;
+// FP64 from the graph's table (Graph::score64; one gather in place of some 90
+// instructions), or computed for degrees past its end.
+struct J3Tab {
+  const double *g;
+  int32_t n;
+};
 template <typename T> struct J3Acc;
 template <> struct J3Acc<float> {
   using type = float;
-  __device__ static float g(int32_t d) { return score_t<float>(d); }
+  __device__ static float g(int32_t d, J3Tab) { return score_t<float>(d); }
 };
 template <> struct J3Acc<double> {
   using type = double;
-  __device__ static double g(int32_t d) { return score_t<double>(d); }
+  __device__ static double g(int32_t d, J3Tab t) {
+    return (uint32_t)d < (uint32_t)t.n ? t.g[d] : score_t<double>(d);
+  }
 };
+
+// Union path: one workgroup of WPB wavefronts per item (arc e of the list,
+// list length L <= SLOTS / 2), prefixes in chunks of PCH. Within a chunk the
+// M part depends on a prefix only through d_T and on a member w only through
+// kappa = k_w - 2 c_w: it is evaluated once per pair of distinct values and
+// weighted by the number of prefixes and the c_w that share them. (Every
+// member against every distinct d_T took most of the kernel: BA n = 100k,
+// m = 5, lists of 257-2048: 5.35 ms, 4.61 now, and 2.24 with an item per edge.)
+// An item with more than PCH distinct kappa takes its members one by one.
 
 template <typename T, int SLOTS, int WPB, int PCH>
 __global__ __launch_bounds__(64 * WPB) void k_j3_block(const int32_t *__restrict__ row_ptr,
@@ -240,7 +268,8 @@ __global__ __launch_bounds__(64 * WPB) void k_j3_block(const int32_t *__restrict
                                                         const int32_t *__restrict__ count_p,
                                                         long long *__restrict__ PN,
                                                         long long *__restrict__ PD,
-                                                        double *__restrict__ PS) {
+                                                        double *__restrict__ PS,
+                                                        const J3Tab tab, bool both) {
   constexpr int NT = 64 * WPB;
   constexpr int LMAX = SLOTS / 2;
   constexpr int MR = (LMAX + NT - 1) / NT;  // list entries per thread
@@ -255,6 +284,8 @@ __global__ __launch_bounds__(64 * WPB) void k_j3_block(const int32_t *__restrict
   __shared__ int32_t dkey[DS];
   __shared__ int32_t dcnt[DS];
   __shared__ int2 uniq[PCH];  // {d_T, number of prefixes}
+  __shared__ int2 kcls[PCH];  // {kappa, sum of c_w}
+  __shared__ int32_t kcount;  // distinct kappa inserted (past PCH: gave up)
   __shared__ int32_t flg_s[WPB][kFlg];
   __shared__ int32_t part[WPB];
   __shared__ long long red_a[WPB], red_b[WPB];
@@ -357,7 +388,7 @@ __global__ __launch_bounds__(64 * WPB) void k_j3_block(const int32_t *__restrict
         dT[r] = ks + ky + kz[r] - 2 * (1 + c);
         cn += dT[r];
         cd += (long long)dT[r] * (M1 - c) + M2 - (long long)c * (kz[r] - 2 * c);
-        cs -= (double)c * (double)G::g(dT[r] + kz[r] - 2 * c);
+        cs -= (double)c * (double)G::g(dT[r] + kz[r] - 2 * c, tab);
       }
     }
     // rounds of list entries this item uses (uniform)
@@ -370,6 +401,36 @@ __global__ __launch_bounds__(64 * WPB) void k_j3_block(const int32_t *__restrict
       wgt[r] = (tid + r * NT < L && !dup[r]) ? (V)cz[r] : (V)0;
       kap[r] = kz[r] - 2 * cz[r];
     }
+    // distinct kappa (keys kappa + 4 > 0), through the table of the d_T below:
+    // each thread looks at the count before an insertion, so at most PCH + NT
+    // of its 2 PCH slots fill
+    static_assert(PCH + NT <= DS, "the class table must keep a free slot");
+    if (tid == 0) kcount = 0;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < MR; ++r) {
+      if (tid + r * NT < L && !dup[r] && *(volatile int32_t *)&kcount <= PCH) {
+        const int32_t sl = j3_find_or_insert<DS>(dkey, kap[r] + 4);
+        if (atomicAdd(&dcnt[sl], cz[r]) == 0) atomicAdd(&kcount, 1);
+      }
+    }
+    __syncthreads();
+    const bool classed = kcount <= PCH;
+    int32_t nk = 0;
+#pragma unroll
+    for (int rr = 0; rr < DS / NT; ++rr) {
+      const int32_t sl = tid + rr * NT;
+      const int32_t key = dkey[sl], c = dcnt[sl];
+      int32_t tot;
+      const int32_t at = nk + group_excl_scan<NT>(key >= 0 ? 1 : 0, part, tot);
+      if (key >= 0) {
+        if (classed) kcls[at] = make_int2(key - 4, c);
+        dkey[sl] = -1;
+        dcnt[sl] = 0;
+      }
+      nk += tot;
+    }
+    __syncthreads();
     for (int32_t p0 = 0; p0 < L; p0 += PCH) {
       const int32_t nseg = L - p0 < PCH ? L - p0 : PCH;
       // segment table of the chunk, in prefix order
@@ -414,14 +475,25 @@ __global__ __launch_bounds__(64 * WPB) void k_j3_block(const int32_t *__restrict
         nuniq += tot;
       }
       __syncthreads();
-      // M part: every distinct d_T against this thread's M entries
-      for (int32_t u = 0; u < nuniq; ++u) {
-        const int2 dc = uniq[u];
-        V acc = 0;
+      // M part: a lane per distinct kappa, the distinct d_T dealt over the
+      // wavefronts
+      if (classed) {
+        for (int32_t j = lane; j < nk; j += 64) {
+          const int2 kw = kcls[j];
+          for (int32_t u = wv; u < nuniq; u += WPB) {
+            const int2 dc = uniq[u];
+            cs += (double)(dc.y * kw.y) * (double)G::g(dc.x + kw.x, tab);
+          }
+        }
+      } else {
+        for (int32_t u = 0; u < nuniq; ++u) {
+          const int2 dc = uniq[u];
+          V acc = 0;
 #pragma unroll
-        for (int r = 0; r < MR; ++r)
-          if (r < rmax) acc += wgt[r] * G::g(dc.x + kap[r]);
-        cs += (double)dc.y * (double)acc;
+          for (int r = 0; r < MR; ++r)
+            if (r < rmax) acc += wgt[r] * G::g(dc.x + kap[r], tab);
+          cs += (double)dc.y * (double)acc;
+        }
       }
       // z's neighbours: one walk over the chunk's rows N(z), wavefronts
       // taking contiguous shares
@@ -437,10 +509,11 @@ __global__ __launch_bounds__(64 * WPB) void k_j3_block(const int32_t *__restrict
             const int32_t f = LdsHash<SLOTS>::find(hkey, w.x);
             if (f >= 0) {
               const int32_t c = hc[f];
-              cs += (double)((c + 1) * G::g(d + w.y - 2 * c - 2) - c * G::g(d + w.y - 2 * c));
+              cs += (double)((c + 1) * G::g(d + w.y - 2 * c - 2, tab) -
+                             c * G::g(d + w.y - 2 * c, tab));
               cd += d + w.y - 4 * c - 2;
             } else {
-              cs += (double)G::g(d + w.y - 2);
+              cs += (double)G::g(d + w.y - 2, tab);
               cd += d + w.y - 2;
             }
           });
@@ -463,9 +536,7 @@ __global__ __launch_bounds__(64 * WPB) void k_j3_block(const int32_t *__restrict
         b += red_b[w];
         c += red_c[w];
       }
-      PN[e] = a;
-      PD[e] = b;
-      PS[e] = c;
+      j3_store(PN, PD, PS, rev, e, both, a, b, c);
     }
     // empty the hash slots this thread filled
 #pragma unroll
@@ -543,7 +614,8 @@ __global__ __launch_bounds__(64 * WPB) void k_j3_wave(const int32_t *__restrict_
                                                        const int32_t *__restrict__ count_p,
                                                        long long *__restrict__ PN,
                                                        long long *__restrict__ PD,
-                                                       double *__restrict__ PS) {
+                                                       double *__restrict__ PS,
+                                                       const J3Tab tab, bool both) {
   constexpr int SL = 2 * kJ3LmaxW;
   using G = J3Acc<T>;
   using V = typename G::type;
@@ -605,14 +677,17 @@ __global__ __launch_bounds__(64 * WPB) void k_j3_wave(const int32_t *__restrict_
     double cs = 0.0;
     if (i < L) {
       cd = (long long)dT * (M1 - c) + M2 - (long long)c * (kz - 2 * c);
-      cs = -(double)c * (double)G::g(dT + kz - 2 * c);
+      cs = -(double)c * (double)G::g(dT + kz - 2 * c, tab);
     }
-    // M part: every prefix's d_T (read from its lane) against this lane's entry
+    // M part: every distinct d_T (read from a lane that holds it), weighted by
+    // the prefixes that share it, against this lane's entry
     const V wgt = (i < L && !dup) ? (V)c : (V)0;
     const int32_t kap = kz - 2 * c;
-    for (int32_t j = 0; j < L; ++j) {
-      const int32_t d = __builtin_amdgcn_readlane(dT, j);
-      cs += (double)(wgt * G::g(d + kap));
+    for (unsigned long long left = __ballot(i < L); left != 0ull;) {
+      const int32_t d = __builtin_amdgcn_readlane(dT, __builtin_ctzll(left));
+      const unsigned long long same = __ballot(dT == d) & left;
+      left &= ~same;
+      cs += (double)__popcll(same) * (double)(wgt * G::g(d + kap, tab));
     }
     // segments: the rows N(z) of the prefixes
     int32_t tot = 0;
@@ -640,21 +715,18 @@ __global__ __launch_bounds__(64 * WPB) void k_j3_wave(const int32_t *__restrict_
           const int32_t f = LdsHash<SL>::find(hkey, w.x);
           if (f >= 0) {
             const int32_t cw = hc[f];
-            cs += (double)((cw + 1) * G::g(d + w.y - 2 * cw - 2) - cw * G::g(d + w.y - 2 * cw));
+            cs += (double)((cw + 1) * G::g(d + w.y - 2 * cw - 2, tab) -
+                           cw * G::g(d + w.y - 2 * cw, tab));
             cd += d + w.y - 4 * cw - 2;
           } else {
-            cs += (double)G::g(d + w.y - 2);
+            cs += (double)G::g(d + w.y - 2, tab);
             cd += d + w.y - 2;
           }
         });
     cn = wave_sum_i64(cn);
     cd = wave_sum_i64(cd);
     cs = wave_sum_f64(cs);
-    if (lane == 0) {
-      PN[e] = cn;
-      PD[e] = cd;
-      PS[e] = cs;
-    }
+    if (lane == 0) j3_store(PN, PD, PS, rev, e, both, cn, cd, cs);
     if (slot >= 0) hkey[slot] = -1;
   }
 }
@@ -669,38 +741,40 @@ static unsigned j3_blocks(int64_t threads) {
 // The items of seeds[0 .. nseeds) (off: item offsets), binned by list length,
 // each bin run by its kernel; lists: kJ3Bins * n_items ints, counts: kJ3Bins.
 static_assert(kJ3Bins == 5, "list and count scratch sized for five bins");
-hipError_t launch_j3_items(const Graph &g, bool fp64, const int32_t *seeds, const int64_t *off,
+hipError_t launch_j3_items(const Graph &g, bool fp64, bool both, const int32_t *seeds,
+                           const int64_t *off,
                            int32_t nseeds, int64_t n_items, int32_t *lists, int32_t *counts,
                            long long *PN, long long *PD, double *PS, hipStream_t st) {
   if (n_items <= 0) return hipSuccess;
   hipError_t e = launch_zero_i32(counts, kJ3Bins, st);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_j3_bins, dim3(j3_blocks(n_items)), dim3(256), 0, st, g.row_ptr, g.adj2,
-                     seeds, off, nseeds, lists, n_items, counts);
+                     seeds, off, nseeds, g.rev, both, lists, n_items, counts);
+  const J3Tab tab{g.score64, g.score64 ? g.n_score64 : 0};
   const int32_t *l[kJ3Bins];
   for (int b = 0; b < kJ3Bins; ++b) l[b] = lists + b * n_items;
   if (fp64) {
     hipLaunchKernelGGL((k_j3_wave<double, 4>), dim3(8192), dim3(256), 0, st, g.row_ptr, g.adj2,
-                       g.rev, g.src, l[0], counts + 0, PN, PD, PS);
+                       g.rev, g.src, l[0], counts + 0, PN, PD, PS, tab, both);
     hipLaunchKernelGGL((k_j3_block<double, 2 * kJ3Lmax0, 4, 256>), dim3(4096), dim3(256), 0, st,
-                       g.row_ptr, g.adj2, g.rev, g.src, l[1], counts + 1, PN, PD, PS);
+                       g.row_ptr, g.adj2, g.rev, g.src, l[1], counts + 1, PN, PD, PS, tab, both);
     hipLaunchKernelGGL((k_j3_block<double, 2 * kJ3Lmax1, 8, 1024>), dim3(1024), dim3(512), 0, st,
-                       g.row_ptr, g.adj2, g.rev, g.src, l[2], counts + 2, PN, PD, PS);
+                       g.row_ptr, g.adj2, g.rev, g.src, l[2], counts + 2, PN, PD, PS, tab, both);
     hipLaunchKernelGGL((k_j3_block<double, 2 * kJ3Lmax2, 8, 1024>), dim3(256), dim3(512), 0, st,
-                       g.row_ptr, g.adj2, g.rev, g.src, l[3], counts + 3, PN, PD, PS);
+                       g.row_ptr, g.adj2, g.rev, g.src, l[3], counts + 3, PN, PD, PS, tab, both);
     hipLaunchKernelGGL(k_j3_merge<double>, dim3(2048), dim3(256), 0, st, g.row_ptr, g.adj2,
-                       g.rev, g.src, l[4], counts + 4, PN, PD, PS);
+                       g.rev, g.src, l[4], counts + 4, PN, PD, PS, both);
   } else {
     hipLaunchKernelGGL((k_j3_wave<float, 4>), dim3(8192), dim3(256), 0, st, g.row_ptr, g.adj2,
-                       g.rev, g.src, l[0], counts + 0, PN, PD, PS);
+                       g.rev, g.src, l[0], counts + 0, PN, PD, PS, tab, both);
     hipLaunchKernelGGL((k_j3_block<float, 2 * kJ3Lmax0, 4, 256>), dim3(4096), dim3(256), 0, st,
-                       g.row_ptr, g.adj2, g.rev, g.src, l[1], counts + 1, PN, PD, PS);
+                       g.row_ptr, g.adj2, g.rev, g.src, l[1], counts + 1, PN, PD, PS, tab, both);
     hipLaunchKernelGGL((k_j3_block<float, 2 * kJ3Lmax1, 8, 1024>), dim3(1024), dim3(512), 0, st,
-                       g.row_ptr, g.adj2, g.rev, g.src, l[2], counts + 2, PN, PD, PS);
+                       g.row_ptr, g.adj2, g.rev, g.src, l[2], counts + 2, PN, PD, PS, tab, both);
     hipLaunchKernelGGL((k_j3_block<float, 2 * kJ3Lmax2, 8, 1024>), dim3(256), dim3(512), 0, st,
-                       g.row_ptr, g.adj2, g.rev, g.src, l[3], counts + 3, PN, PD, PS);
+                       g.row_ptr, g.adj2, g.rev, g.src, l[3], counts + 3, PN, PD, PS, tab, both);
     hipLaunchKernelGGL(k_j3_merge<float>, dim3(2048), dim3(256), 0, st, g.row_ptr, g.adj2,
-                       g.rev, g.src, l[4], counts + 4, PN, PD, PS);
+                       g.rev, g.src, l[4], counts + 4, PN, PD, PS, both);
   }
   return hipGetLastError();
 }
