@@ -74,7 +74,8 @@ static void dev_free(Graph &g, void *p, size_t bytes) {
 // workspace slots
 enum {
   WS_MAIN = 0,  // ef_compute's sums and records (ComputeWs), and the load's scratch
-  WS_FLAG, WS_BINS, WS_OUT, WS_BITMAP, WS_SEEDS, WS_UOUT, WS_TOPK, WS_SURR, WS_J3, WS_J3P, WS_J3L
+  WS_FLAG, WS_BINS, WS_OUT, WS_BITMAP, WS_SEEDS, WS_UOUT, WS_TOPK, WS_SURR, WS_J3, WS_J3P, WS_J3L,
+  WS_SPLIT  // pieces of the seeds of per-seed calls and their sums
 };
 
 // Byte offsets in WS_MAIN of one ef_compute call: per-arc sums, super-tile
@@ -125,6 +126,13 @@ static ef_status ws_ensure(Graph &g, int slot, size_t bytes, const char *what) {
     dev_free(g, g.score64, sizeof(double) * (size_t)g.n_score64);
     g.score64 = nullptr;
     g.n_score64 = 0;
+    s = dev_alloc(g, &b.p, want, what);
+  }
+  if (s != EF_OK && slot != WS_SPLIT && g.ws[WS_SPLIT].p) {
+    // so do the pieces that the largest seeds are cut into
+    dev_free(g, g.ws[WS_SPLIT].p, g.ws[WS_SPLIT].bytes);
+    g.ws[WS_SPLIT] = DevBuf{};
+    g.split_kept = false;
     s = dev_alloc(g, &b.p, want, what);
   }
   if (s != EF_OK && slot != WS_MAIN && g.main_reserved && g.ws[WS_MAIN].p) {
@@ -766,6 +774,60 @@ static ef_status score_table(Graph &g, hipStream_t st) {
   return hip_status(launch_score_table(g.score64, n, st), "score table");
 }
 
+// Cuts the seeds of bins 1-4 whose 2-hop work is above a piece's (the leading
+// ones: lst is by work, descending) into pieces: their number depends on the
+// seeds alone, and is at most 2 * kSeedPieces and a chunk's rounding per seed.
+static void seed_pieces(const Graph &g, const int32_t *useeds,
+                        const std::vector<int32_t> (&lst)[kSeedBins], std::vector<int4> &items,
+                        int64_t (&split)[kSeedBins], int64_t (&first)[kSeedBins + 1]) {
+  items.clear();
+  int64_t total = 0;
+  auto node = [&](int32_t pos) { return useeds ? useeds[pos] : pos; };
+  for (int b = 1; b < kSeedBins; ++b)
+    for (int32_t pos : lst[b]) total += g.h_asum[node(pos)];
+  split[0] = first[0] = first[1] = 0;
+  for (int b = 1; b < kSeedBins; ++b) {
+    const int64_t piece = std::max<int64_t>(kSeedPiece * seed_waves(b), total / kSeedPieces);
+    split[b] = 0;
+    for (int32_t pos : lst[b]) {
+      const int64_t work = g.h_asum[node(pos)];
+      if (work <= piece) break;
+      const int64_t chunks = (g.h_deg[node(pos)] + seed_chunk(b) - 1) / seed_chunk(b);
+      const int64_t want = (work + piece - 1) / piece;
+      const int32_t pieces = (int32_t)((want + chunks - 1) / chunks * chunks);
+      for (int32_t p = 0; p < pieces; ++p)
+        items.push_back(make_int4(pos, (int32_t)split[b], p, pieces));
+      split[b]++;
+    }
+    first[b + 1] = (int64_t)items.size();
+  }
+}
+
+// WS_SPLIT with the pieces and room for their sums; without memory the slot
+// stays empty. The pieces of whole-graph calls are kept there until others are
+// needed.
+static ef_status split_buffer(Graph &g, const std::vector<int4> &items, bool all, hipStream_t st) {
+  if (items.empty()) return EF_OK;
+  DevBuf &b = g.ws[WS_SPLIT];
+  const size_t bytes = (sizeof(int4) + kSeedPart) * items.size();
+  if (b.bytes < bytes) {
+    dev_free(g, b.p, b.bytes);
+    b = DevBuf{};
+    g.split_kept = false;
+    if (dev_alloc(g, &b.p, bytes, "seed pieces") != EF_OK) {
+      b.p = nullptr;
+      return EF_OK;
+    }
+    b.bytes = bytes;
+  }
+  if (all && g.split_kept) return EF_OK;
+  hipError_t e = hipMemcpyAsync(b.p, items.data(), sizeof(int4) * items.size(),
+                                hipMemcpyHostToDevice, st);
+  if (e == hipSuccess) e = hipStreamSynchronize(st);  // a call's items go out of scope
+  g.split_kept = all && e == hipSuccess;
+  return hip_status(e, "upload seed pieces");
+}
+
 static void host_bins(const Graph &g, const int32_t *centres, int64_t count, Bins &b) {
   b.n_small = b.n_mid = b.n_big = b.n_tiles = 0;
   b.pairs_small = b.pairs_mid = b.pairs_big = 0;
@@ -949,8 +1011,9 @@ extern "C" ef_status ef_compute(ef_graph *h, ef_algo algo, ef_prec prec, const i
   // device seed arrays: the unique work list (all nodes: none, position =
   // node id), the inverse map, and output positions by seed degree bin
   int32_t *d_useeds = nullptr, *d_inv = nullptr;
-  const int32_t *ps_lists[kSeedBins] = {nullptr, nullptr, nullptr, nullptr, nullptr};
-  int64_t ps_counts[kSeedBins] = {0, 0, 0, 0, 0};
+  SeedLists ls;
+  std::vector<int4> items;  // pieces of a call with seeds
+  int64_t split[kSeedBins], first[kSeedBins + 1];
   if (per_seed && g.h_asum.empty() && g.n > 0) {
     g.h_asum.resize((size_t)g.n);
     e = hipMemcpy(g.h_asum.data(), g.asum, sizeof(int64_t) * (size_t)g.n, hipMemcpyDeviceToHost);
@@ -986,11 +1049,12 @@ extern "C" ef_status ef_compute(ef_graph *h, ef_algo algo, ef_prec prec, const i
           if (e != hipSuccess) return hip_status(e, "upload seed lists");
         }
       }
+      seed_pieces(g, nullptr, lst, g.h_ps_items, g.ps_split, g.ps_first);
       g.ps_ready = true;
     }
     for (int bin = 0; bin < kSeedBins; ++bin) {
-      ps_lists[bin] = g.ps_list[bin];
-      ps_counts[bin] = g.n_ps[bin];
+      ls.list[bin] = g.ps_list[bin];
+      ls.count[bin] = g.n_ps[bin];
     }
   } else if (per_seed) {
     std::vector<int32_t> lst[kSeedBins];
@@ -999,30 +1063,29 @@ extern "C" ef_status ef_compute(ef_graph *h, ef_algo algo, ef_prec prec, const i
     std::sort(order.begin(), order.end(),
               [&](int32_t a, int32_t c) { return by_work(useeds[a], useeds[c]); });
     for (int32_t i : order) lst[seed_bin(useeds[i])].push_back(i);
-    const size_t cnt_all = useeds.size() * 2 + inv.size() + 4;
-    if ((s = ws_ensure(g, WS_SEEDS, sizeof(int32_t) * cnt_all, "seed lists")) != EF_OK) return s;
+    // one upload: the seeds, the bins' lists, the inverse map
+    std::vector<int32_t> up = useeds;
+    up.reserve(useeds.size() * 2 + inv.size());
+    for (int bin = 0; bin < kSeedBins; ++bin) up.insert(up.end(), lst[bin].begin(), lst[bin].end());
+    up.insert(up.end(), inv.begin(), inv.end());
+    if ((s = ws_ensure(g, WS_SEEDS, sizeof(int32_t) * (up.size() + 4), "seed lists")) != EF_OK)
+      return s;
     d_useeds = (int32_t *)g.ws[WS_SEEDS].p;
     int32_t *p = d_useeds + useeds.size();
-    e = hipMemcpyAsync(d_useeds, useeds.data(), sizeof(int32_t) * useeds.size(),
-                       hipMemcpyHostToDevice, st);
     for (int bin = 0; bin < kSeedBins; ++bin) {
-      ps_lists[bin] = p;
-      ps_counts[bin] = (int64_t)lst[bin].size();
-      if (e == hipSuccess && !lst[bin].empty())
-        e = hipMemcpyAsync(p, lst[bin].data(), sizeof(int32_t) * lst[bin].size(),
-                           hipMemcpyHostToDevice, st);
+      ls.list[bin] = p;
+      ls.count[bin] = (int64_t)lst[bin].size();
       p += lst[bin].size();
     }
     d_inv = p;
-    if (e == hipSuccess && !inv.empty())
-      e = hipMemcpyAsync(d_inv, inv.data(), sizeof(int32_t) * inv.size(), hipMemcpyHostToDevice,
-                         st);
+    e = hipMemcpyAsync(d_useeds, up.data(), sizeof(int32_t) * up.size(), hipMemcpyHostToDevice, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);  // host vectors go out of scope
     if (e != hipSuccess) return hip_status(e, "upload seeds");
+    seed_pieces(g, useeds.data(), lst, items, split, first);
   }
-  if (per_seed && ps_counts[kSeedBins - 1] > 0) {
+  if (per_seed && ls.count[kSeedBins - 1] > 0) {
     const size_t words = ((size_t)g.n + 31) / 32;
-    const size_t need = sizeof(uint32_t) * words * (size_t)ps_counts[kSeedBins - 1];
+    const size_t need = sizeof(uint32_t) * words * (size_t)ls.count[kSeedBins - 1];
     const bool fresh = g.ws[WS_BITMAP].bytes < need;
     if ((s = ws_ensure(g, WS_BITMAP, need, "membership bitmaps")) != EF_OK) return s;
     if (fresh) {
@@ -1039,6 +1102,18 @@ extern "C" ef_status ef_compute(ef_graph *h, ef_algo algo, ef_prec prec, const i
   if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
     (void)hipGetLastError();
     cap = hipStreamCaptureStatusActive;
+  }
+  // (the pieces only save time: without memory for them, or in a captured
+  // call, whose replays must not depend on them, no seed is cut)
+  if (per_seed && cap == hipStreamCaptureStatusNone) {
+    const std::vector<int4> &pc = all ? g.h_ps_items : items;
+    if ((s = split_buffer(g, pc, all, st)) != EF_OK) return s;
+    if (!pc.empty() && g.ws[WS_SPLIT].p) {
+      std::copy_n(all ? g.ps_split : split, kSeedBins, ls.split);
+      std::copy_n(all ? g.ps_first : first, kSeedBins + 1, ls.first);
+      ls.items = (const int4 *)g.ws[WS_SPLIT].p;
+      ls.parts = (char *)g.ws[WS_SPLIT].p + sizeof(int4) * pc.size();
+    }
   }
   const bool whole = centres == nullptr && cap == hipStreamCaptureStatusNone;
   const bool reuse = whole && g.bins_kept && g.bins_buf == g.ws[WS_BINS].p &&
@@ -1067,9 +1142,8 @@ extern "C" ef_status ef_compute(ef_graph *h, ef_algo algo, ef_prec prec, const i
     if (e != hipSuccess) return hip_status(e, "finalize");
     prof.mark(7);
   } else {
-    e = launch_per_seed(g, prec, d_useeds, ps_lists, ps_counts, ws_R,
-                        (uint32_t *)g.ws[WS_BITMAP].p, ef_w, D_w, N_w, flag_bytes, st,
-                        prof.ev(6));
+    e = launch_per_seed(g, prec, d_useeds, ls, ws_R, (uint32_t *)g.ws[WS_BITMAP].p, ef_w, D_w, N_w,
+                        flag_bytes, st, prof.ev(6));
     if (e == hipSuccess) e = launch_flag_compact(flag_bytes, n_work, flagged, cnt, st);
     if (e != hipSuccess) return hip_status(e, "per-seed stream");
     prof.mark(7);
@@ -1086,14 +1160,12 @@ extern "C" ef_status ef_compute(ef_graph *h, ef_algo algo, ef_prec prec, const i
       e = launch_gather_outputs(d_inv, n_seeds, ef_w, D_w, N_w, ef, D, N, st);
       if (e != hipSuccess) return hip_status(e, "scatter outputs");
     } else {
-      std::vector<double> hef((size_t)n_work);
-      std::vector<int64_t> hD((size_t)n_work), hN((size_t)n_work);
-      e = hipMemcpyAsync(hef.data(), ef_w, sizeof(double) * n_work, hipMemcpyDeviceToHost, st);
-      if (e == hipSuccess)
-        e = hipMemcpyAsync(hD.data(), D_w, sizeof(int64_t) * n_work, hipMemcpyDeviceToHost, st);
-      if (e == hipSuccess)
-        e = hipMemcpyAsync(hN.data(), N_w, sizeof(int64_t) * n_work, hipMemcpyDeviceToHost, st);
+      // the staged EF, D and N lie one after the other: one copy
+      std::vector<int64_t> h(3 * (size_t)n_work);
+      e = hipMemcpyAsync(h.data(), ef_w, 3 * sizeof(int64_t) * n_work, hipMemcpyDeviceToHost, st);
       if (e == hipSuccess) e = hipStreamSynchronize(st);
+      const double *hef = (const double *)h.data();
+      const int64_t *hD = h.data() + n_work, *hN = hD + n_work;
       if (e != hipSuccess) return hip_status(e, "copy outputs");
       for (int32_t i = 0; i < n_seeds; ++i) {
         ef[i] = hef[inv[i]];

@@ -76,6 +76,11 @@ constexpr int kSeedBin0 = 64, kSeedBin1 = 512, kSeedBin2 = 2048, kSeedBin3 = 819
 constexpr int64_t kSeedWaveWork = 4096;
 constexpr int kSeedChunk = 2048;
 
+// Seeds of bins 1-4 with much 2-hop work are cut into pieces, a workgroup each:
+// of kSeedPiece entries per wavefront, or (when that makes too many) of a
+// 1/kSeedPieces share of all the work of these bins.
+constexpr int64_t kSeedPiece = 2048, kSeedPieces = 8192;
+
 // FP32C: seeds whose estimated cancellation factor (S/D)/EF exceeds this are
 // recomputed from non-negative terms.
 constexpr float kKappaMax = 16.0f;
@@ -187,6 +192,9 @@ struct Graph {
   int32_t *ps_list[kSeedBins] = {nullptr, nullptr, nullptr, nullptr, nullptr};
   int64_t n_ps[kSeedBins] = {0, 0, 0, 0, 0};
   bool ps_ready = false;
+  std::vector<int4> h_ps_items;  // pieces of its seeds (SeedLists::items)
+  int64_t ps_split[kSeedBins] = {0, 0, 0, 0, 0}, ps_first[kSeedBins + 1] = {0, 0, 0, 0, 0, 0};
+  bool split_kept = false;      // WS_SPLIT holds h_ps_items
   std::vector<int64_t> h_asum;  // host copy of asum (built on first per-seed use)
   // graphs loaded as a union of parts (batches): node ids of the triangle
   // lane bin, of triangle bins 0-3 and of fin_list, in list order
@@ -332,15 +340,30 @@ hipError_t launch_finalize_cluster(const Graph &g, ef_prec prec, const void *R, 
 hipError_t launch_flag_compact(const uint8_t *fl, int64_t n, int32_t *flagged, int32_t *counts,
                                hipStream_t st);
 
+// Output positions by seed bin (kSeedBins bins, see above), by 2-hop work
+// descending. The first split[b] of bin b are cut into pieces: items first[b]
+// .. first[b+1] - 1, each {position, index in list, piece, pieces of the seed},
+// a seed's pieces together and in order; parts: kSeedPart bytes per item for
+// their sums.
+constexpr size_t kSeedPart = 24;
+struct SeedLists {
+  const int32_t *list[kSeedBins] = {};
+  int64_t count[kSeedBins] = {};
+  int64_t split[kSeedBins] = {}, first[kSeedBins + 1] = {};
+  const int4 *items = nullptr;
+  void *parts = nullptr;
+};
 // per-seed formulation: star sums from R of the seed's own arcs, 2-hop walk,
-// then Eq. 1. seeds: the unique work list (NULL: position = node id);
-// lists[b] / counts[b]: output positions by seed bin (kSeedBins bins, see
-// above); the last bin's membership comes from bitmaps, counts[last] of n
-// bits each, in list order.
+// then Eq. 1. seeds: the unique work list (NULL: position = node id); the last
+// bin's membership comes from bitmaps, count[last] of n bits each, in list
+// order.
 hipError_t launch_per_seed(const Graph &g, ef_prec prec, const int32_t *seeds,
-                           const int32_t *const *lists, const int64_t *counts, const void *R,
-                           uint32_t *bitmaps, double *ef, int64_t *D, int64_t *N, uint8_t *fl,
-                           hipStream_t st, hipEvent_t ev_stream_done);
+                           const SeedLists &ls, const void *R, uint32_t *bitmaps, double *ef,
+                           int64_t *D, int64_t *N, uint8_t *fl, hipStream_t st,
+                           hipEvent_t ev_stream_done);
+// wavefronts of a workgroup of bin b >= 1, and the neighbours of one chunk
+inline int seed_waves(int b) { return b == 1 ? 8 : 16; }
+inline int seed_chunk(int b) { return b == 1 ? kSeedBin1 : kSeedChunk; }
 
 // Expected Force with three transmission events (j3.hip): items are the arcs
 // of seeds[0 .. nseeds), seed i owning items off[i] .. off[i+1]; per-arc

@@ -527,6 +527,8 @@ __device__ __forceinline__ int32_t hash_insert(int32_t *hkey, int32_t x) {
   return LdsHash<SLOTS>::insert(hkey, x);
 }
 
+constexpr int kSeedUnroll = 4;  // steps of 64 entries per round of a walk
+
 // one wavefront walks entries [beg, end) of the current chunk
 template <typename T, int SLOTS, bool BITMAP>
 __device__ __forceinline__ void seed_walk(const int2 *__restrict__ adj2, const int2 *seg,
@@ -536,12 +538,12 @@ __device__ __forceinline__ void seed_walk(const int2 *__restrict__ adj2, const i
                                           typename SumT<T>::type &sacc, int64_t &Dd,
                                           int64_t &Nn) {
   using S = SumT<T>;
-  // per-round partials: at most 4 terms per lane, folded into the compensated
-  // and 64-bit sums after each round (d < 3 * kMaxDegree, so 4 fit in int32)
-  static_assert(4LL * 3 * kMaxDegree < (1LL << 31), "per-round degree sum overflows");
+  // per-round partials: kSeedUnroll terms per lane at most, folded into the compensated
+  // and 64-bit sums after each round (d < 3 * kMaxDegree: they fit in int32)
+  static_assert(3LL * kSeedUnroll * kMaxDegree < (1LL << 31), "per-round degree sum overflows");
   T rs = T(0);
   int32_t rd = 0, rn = 0;
-  seg_walk<4>(
+  seg_walk<kSeedUnroll>(
       segp, nseg, beg, end, flg,
       [&](int32_t sg, int32_t idx) {
         const int2 sv = seg[sg];
@@ -644,9 +646,23 @@ __global__ __launch_bounds__(64 * WPB) void k_seed_wave(
   }
 }
 
+template <typename T> struct SeedPart {
+  typename SumT<T>::type s;
+  int64_t D, N;
+};
+static_assert(sizeof(SeedPart<float>) == kSeedPart && sizeof(SeedPart<double>) == kSeedPart,
+              "launch_per_seed's callers size the parts");
+
 // one workgroup of WPB wavefronts per seed; neighbours in chunks of MAXK,
 // each wavefront walking a contiguous share of a chunk's sequence. BITMAP:
-// membership from bm + slot * words, slot = index in the list.
+// membership from bm + slot * words, slot = index in the list. The first
+// n_items workgroups take pieces of the n_split seeds that lead the list: a
+// piece is one chunk, or an even part of every wavefront's share of it, cut at
+// the walk's rounds, so the FP32 sums of a round keep their terms. A seed walks
+// at some 0.5 us per step of its workgroup whatever else the chip does: on
+// R-MAT scale 18 the one seed of 722k entries among 1000 took 412 us and the
+// others, up to 347k entries, 367 us; in pieces 32 and 38 us (of half and of
+// twice the size: 23 and 42 us, 49 and 45 us).
 // Minimum wavefronts per SIMD asked of the compiler for a per-seed bin: 8
 // (64 VGPRs, a few spilled) for the 2048- and 8192-slot hashes, which then
 // fit four 8-wavefront or two 16-wavefront workgroups on a compute unit. The
@@ -661,9 +677,10 @@ __global__ __launch_bounds__(64 * WPB, seed_block_min_waves(SLOTS)) void k_seed_
     const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ deg,
     const int2 *__restrict__ adj2, const int64_t *__restrict__ asum,
     const int32_t *__restrict__ seeds, const int32_t *__restrict__ list, int64_t count,
-    const void *__restrict__ R, const uint32_t *__restrict__ bm, int64_t words,
-    double *__restrict__ ef, int64_t *__restrict__ Dout, int64_t *__restrict__ Nout,
-    uint8_t *__restrict__ fl) {
+    const int4 *__restrict__ items, int64_t n_items, int64_t n_split,
+    SeedPart<T> *__restrict__ parts, const void *__restrict__ R,
+    const uint32_t *__restrict__ bm, int64_t words, double *__restrict__ ef,
+    int64_t *__restrict__ Dout, int64_t *__restrict__ Nout, uint8_t *__restrict__ fl) {
   using S = SumT<T>;
   using Acc = typename S::type;
   constexpr int NT = 64 * WPB;
@@ -677,11 +694,18 @@ __global__ __launch_bounds__(64 * WPB, seed_block_min_waves(SLOTS)) void k_seed_
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   int32_t *flg = flg_s[wv];
   flg[lane] = 0;
-  for (int64_t it = blockIdx.x; it < count; it += gridDim.x) {
-    const int32_t pos = list[it];
+  for (int64_t it = blockIdx.x; it < n_items + count - n_split; it += gridDim.x) {
+    const bool cut = it < n_items;
+    int64_t li = n_split + it - n_items;
+    const int4 item = cut ? items[it] : make_int4(list[li], 0, 0, 1);
+    if (cut) li = item.y;
+    const int32_t pos = item.x;
     const int32_t s = seeds ? seeds[pos] : pos;
     const int32_t k = deg[s], base = row_ptr[s];
-    const uint32_t *mybm = BITMAP ? bm + it * words : nullptr;
+    const uint32_t *mybm = BITMAP ? bm + li * words : nullptr;
+    // piece item.z of item.w: part `sub` of `per` of chunk `chunk`
+    const int32_t per = cut ? item.w / ((k + MAXK - 1) / MAXK) : 1;
+    const int32_t chunk = cut ? item.z / per : 0, sub = cut ? item.z % per : 0;
     if constexpr (!BITMAP) {
       for (int i = tid; i < SLOTS; i += NT) hkey[i] = -1;
       __syncthreads();
@@ -690,17 +714,25 @@ __global__ __launch_bounds__(64 * WPB, seed_block_min_waves(SLOTS)) void k_seed_
     int64_t Dd = 0, Nn = 0;
     for (int32_t j = tid; j < k; j += NT) {
       if constexpr (!BITMAP) hash_insert<SLOTS>(hkey, adj2[base + j].x);
-      if (k >= 2) S::add_arc(sacc, R, base + j);
+      if (k >= 2 && item.z == 0) S::add_arc(sacc, R, base + j);
     }
-    for (int32_t c0 = 0; c0 < k; c0 += MAXK) {
+    for (int32_t c0 = chunk * MAXK; c0 < (cut ? min(k, (chunk + 1) * MAXK) : k); c0 += MAXK) {
       const int32_t cnt = min(MAXK, k - c0);
       const int32_t total = seed_chunk_setup<NT>(row_ptr, adj2, base, c0, cnt, tid, seg, segp, part);
       __syncthreads();
       const int32_t steps = (total + 63) >> 6;
-      const int32_t beg = (int32_t)(((int64_t)steps * wv / WPB) << 6);
-      const int32_t fin = (int32_t)(((int64_t)steps * (wv + 1) / WPB) << 6);
-      seed_walk<T, SLOTS, BITMAP>(adj2, seg, segp, cnt, beg, fin < total ? fin : total, s, k, hkey,
-                                  mybm, flg, sacc, Dd, Nn);
+      int32_t beg = (int32_t)(((int64_t)steps * wv / WPB) << 6);
+      int32_t fin = (int32_t)(((int64_t)steps * (wv + 1) / WPB) << 6);
+      fin = fin < total ? fin : total;
+      if (cut) {
+        constexpr int32_t kRound = 64 * kSeedUnroll;
+        const int64_t rounds = (fin - beg + kRound - 1) / kRound;
+        const int32_t b0 = beg;
+        beg = b0 + kRound * (int32_t)(rounds * sub / per);
+        fin = min(fin, b0 + kRound * (int32_t)(rounds * (sub + 1) / per));
+      }
+      seed_walk<T, SLOTS, BITMAP>(adj2, seg, segp, cnt, beg, fin, s, k, hkey, mybm, flg, sacc, Dd,
+                                  Nn);
       __syncthreads();
     }
     sacc = wave_sum(sacc);
@@ -720,9 +752,40 @@ __global__ __launch_bounds__(64 * WPB, seed_block_min_waves(SLOTS)) void k_seed_
         dsum += shD[w];
         nsum += shN[w];
       }
-      seed_finish<T>(pos, k, asum[s], a, nsum, dsum, ef, Dout, Nout, fl);
+      if (cut) parts[it] = SeedPart<T>{a, dsum, nsum};
+      else seed_finish<T>(pos, k, asum[s], a, nsum, dsum, ef, Dout, Nout, fl);
     }
     __syncthreads();
+  }
+}
+
+// the sums of the seeds that were cut: a wavefront per item, of which a seed's
+// first one adds up its pieces
+template <typename T>
+__global__ __launch_bounds__(256) void k_seed_merge(
+    const int32_t *__restrict__ deg, const int64_t *__restrict__ asum,
+    const int32_t *__restrict__ seeds, const int4 *__restrict__ items, int64_t n_items,
+    const SeedPart<T> *__restrict__ parts, double *__restrict__ ef, int64_t *__restrict__ Dout,
+    int64_t *__restrict__ Nout, uint8_t *__restrict__ fl) {
+  using Acc = typename SumT<T>::type;
+  const int lane = threadIdx.x & 63;
+  const int64_t it = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (it >= n_items || items[it].z != 0) return;
+  const int4 item = items[it];
+  Acc a = Acc();
+  int64_t Dd = 0, Nn = 0;
+  for (int32_t p = lane; p < item.w; p += 64) {
+    const SeedPart<T> x = parts[it + p];
+    acc_merge(a, x.s);
+    Dd += x.D;
+    Nn += x.N;
+  }
+  a = wave_sum(a);
+  Dd = wave_sum_i64(Dd);
+  Nn = wave_sum_i64(Nn);
+  if (lane == 0) {
+    const int32_t s = seeds ? seeds[item.x] : item.x;
+    seed_finish<T>(item.x, deg[s], asum[s], a, Nn, Dd, ef, Dout, Nout, fl);
   }
 }
 
@@ -733,55 +796,61 @@ static_assert(kSeedSlots[0] >= 2 * kSeedBin0 && kSeedSlots[1] >= 2 * kSeedBin1 &
                   kSeedSlots[2] >= 2 * kSeedBin2 && kSeedSlots[3] >= 2 * kSeedBin3,
               "per-seed hash sets must stay at most half full");
 
+template <typename T, int B>
+static void seed_block_bin(const Graph &g, const int32_t *seeds, const SeedLists &ls,
+                           const void *R, const uint32_t *bitmaps, int64_t words, double *ef,
+                           int64_t *D, int64_t *N, uint8_t *fl, hipStream_t st) {
+  constexpr bool kBitmap = B == kSeedBins - 1;
+  constexpr int kWaves = B == 1 ? 8 : 16;
+  const int64_t items = ls.first[B + 1] - ls.first[B];
+  const int64_t blocks = items + ls.count[B] - ls.split[B];
+  if (blocks <= 0) return;
+  hipLaunchKernelGGL((k_seed_block<T, kBitmap ? 1 : kSeedSlots[kBitmap ? 0 : B],
+                                   B == 1 ? kSeedBin1 : kSeedChunk, kWaves, kBitmap>),
+                     dim3(cap_blocks(blocks, 1 << 20)), dim3(64 * kWaves), 0, st, g.row_ptr, g.deg,
+                     g.adj2, g.asum, seeds, ls.list[B], ls.count[B],
+                     ls.items ? ls.items + ls.first[B] : nullptr, items, ls.split[B],
+                     ls.parts ? (SeedPart<T> *)ls.parts + ls.first[B] : nullptr, R, bitmaps, words,
+                     ef, D, N, fl);
+}
+
 template <typename T>
-static void per_seed_impl(const Graph &g, const int32_t *seeds, const int32_t *const *lists,
-                          const int64_t *counts, const void *R, const uint32_t *bitmaps,
-                          int64_t words, double *ef, int64_t *D, int64_t *N, uint8_t *fl,
-                          hipStream_t st) {
-  if (counts[0] > 0)
+static void per_seed_impl(const Graph &g, const int32_t *seeds, const SeedLists &ls, const void *R,
+                          const uint32_t *bitmaps, int64_t words, double *ef, int64_t *D,
+                          int64_t *N, uint8_t *fl, hipStream_t st) {
+  if (ls.count[0] > 0)
     hipLaunchKernelGGL((k_seed_wave<T, kSeedSlots[0], kSeedBin0, 4>),
-                       dim3(cap_blocks((counts[0] + 3) / 4, 1 << 20)), dim3(256), 0, st,
-                       g.row_ptr, g.deg, g.adj2, g.asum, seeds, lists[0], counts[0], R, ef, D, N,
-                       fl);
-  if (counts[1] > 0)
-    hipLaunchKernelGGL((k_seed_block<T, kSeedSlots[1], kSeedBin1, 8, false>),
-                       dim3(cap_blocks(counts[1], 1 << 20)), dim3(512), 0, st, g.row_ptr, g.deg,
-                       g.adj2, g.asum, seeds, lists[1], counts[1], R, nullptr, words, ef, D, N,
-                       fl);
-  if (counts[2] > 0)
-    hipLaunchKernelGGL((k_seed_block<T, kSeedSlots[2], kSeedChunk, 16, false>),
-                       dim3(cap_blocks(counts[2], 1 << 20)), dim3(1024), 0, st, g.row_ptr,
-                       g.deg, g.adj2, g.asum, seeds, lists[2], counts[2], R, nullptr, words, ef,
-                       D, N, fl);
-  if (counts[3] > 0)
-    hipLaunchKernelGGL((k_seed_block<T, kSeedSlots[3], kSeedChunk, 16, false>),
-                       dim3(cap_blocks(counts[3], 1 << 20)), dim3(1024), 0, st, g.row_ptr,
-                       g.deg, g.adj2, g.asum, seeds, lists[3], counts[3], R, nullptr, words, ef,
-                       D, N, fl);
-  if (counts[4] > 0)
-    hipLaunchKernelGGL((k_seed_block<T, 1, kSeedChunk, 16, true>),
-                       dim3(cap_blocks(counts[4], 1 << 20)), dim3(1024), 0, st, g.row_ptr,
-                       g.deg, g.adj2, g.asum, seeds, lists[4], counts[4], R, bitmaps, words, ef,
-                       D, N, fl);
+                       dim3(cap_blocks((ls.count[0] + 3) / 4, 1 << 20)), dim3(256), 0, st,
+                       g.row_ptr, g.deg, g.adj2, g.asum, seeds, ls.list[0], ls.count[0], R, ef, D,
+                       N, fl);
+  seed_block_bin<T, 1>(g, seeds, ls, R, bitmaps, words, ef, D, N, fl, st);
+  seed_block_bin<T, 2>(g, seeds, ls, R, bitmaps, words, ef, D, N, fl, st);
+  seed_block_bin<T, 3>(g, seeds, ls, R, bitmaps, words, ef, D, N, fl, st);
+  seed_block_bin<T, 4>(g, seeds, ls, R, bitmaps, words, ef, D, N, fl, st);
+  const int64_t items = ls.first[kSeedBins];
+  if (items > 0)
+    hipLaunchKernelGGL((k_seed_merge<T>), dim3((unsigned)((items + 3) / 4)), dim3(256), 0, st,
+                       g.deg, g.asum, seeds, ls.items, items, (const SeedPart<T> *)ls.parts, ef, D,
+                       N, fl);
 }
 
 hipError_t launch_per_seed(const Graph &g, ef_prec prec, const int32_t *seeds,
-                           const int32_t *const *lists, const int64_t *counts, const void *R,
-                           uint32_t *bitmaps, double *ef, int64_t *D, int64_t *N, uint8_t *fl,
-                           hipStream_t st, hipEvent_t ev_stream_done) {
+                           const SeedLists &ls, const void *R, uint32_t *bitmaps, double *ef,
+                           int64_t *D, int64_t *N, uint8_t *fl, hipStream_t st,
+                           hipEvent_t ev_stream_done) {
   const int64_t words = ((int64_t)g.n + 31) / 32;
   constexpr int L = kSeedBins - 1;
-  if (counts[L] > 0)
-    hipLaunchKernelGGL(k_bitmap_set, dim3(cap_blocks(counts[L], 65536)), dim3(256), 0, st,
-                       g.row_ptr, g.col_idx, seeds, lists[L], counts[L], bitmaps, words, 1);
+  if (ls.count[L] > 0)
+    hipLaunchKernelGGL(k_bitmap_set, dim3(cap_blocks(ls.count[L], 65536)), dim3(256), 0, st,
+                       g.row_ptr, g.col_idx, seeds, ls.list[L], ls.count[L], bitmaps, words, 1);
   if (prec == EF_PREC_FP64)
-    per_seed_impl<double>(g, seeds, lists, counts, R, bitmaps, words, ef, D, N, fl, st);
+    per_seed_impl<double>(g, seeds, ls, R, bitmaps, words, ef, D, N, fl, st);
   else
-    per_seed_impl<float>(g, seeds, lists, counts, R, bitmaps, words, ef, D, N, fl, st);
+    per_seed_impl<float>(g, seeds, ls, R, bitmaps, words, ef, D, N, fl, st);
   if (ev_stream_done) (void)hipEventRecord(ev_stream_done, st);
-  if (counts[L] > 0)
-    hipLaunchKernelGGL(k_bitmap_set, dim3(cap_blocks(counts[L], 65536)), dim3(256), 0, st,
-                       g.row_ptr, g.col_idx, seeds, lists[L], counts[L], bitmaps, words, 0);
+  if (ls.count[L] > 0)
+    hipLaunchKernelGGL(k_bitmap_set, dim3(cap_blocks(ls.count[L], 65536)), dim3(256), 0, st,
+                       g.row_ptr, g.col_idx, seeds, ls.list[L], ls.count[L], bitmaps, words, 0);
   return hipGetLastError();
 }
 
