@@ -302,18 +302,26 @@ __device__ __forceinline__ void fin_groups(const FinArgs &A, const int32_t *node
   }
 }
 
-// one lane per node of degree <= kFinLaneMax over node ids 0..n-1: the loads
-// of all of a node's arcs are issued together (indices clamped to its row,
-// contributions past k masked), so a node costs two dependent round trips
+// kFinShare lanes per node of degree <= kFinLaneMax over node ids lo..hi-1: the
+// loads of all of a node's arcs are issued together (indices clamped to its
+// row, contributions past k masked), so a node costs two dependent round trips.
+// Bound by those and by the random sectors of R and Y: two lanes halve a lane's
+// loads and the rows a load instruction touches (64 graphs, 580k such nodes:
+// 70 us for the kernel; one lane 78, four 76, eight 99 us. BA n = 200k, m = 5:
+// 53 us; 56, 53, 54).
+constexpr int kFinShare = 2;
 template <typename T>
 __device__ __forceinline__ void fin_lanes(const FinArgs &A, int64_t lo, int64_t hi, int64_t blk,
                                           int64_t nblk) {
   using Acc = typename SumT<T>::type;
-  constexpr int K = kFinLaneMax;
-  const int64_t stride = nblk * (int64_t)blockDim.x;
-  for (int64_t v = lo + blk * (int64_t)blockDim.x + threadIdx.x; v < hi; v += stride) {
+  constexpr int G = kFinShare, K = kFinLaneMax / G;
+  const int sub = threadIdx.x & (G - 1);
+  const int64_t stride = nblk * (int64_t)blockDim.x / G;
+  const int64_t v0 = lo + (blk * (int64_t)blockDim.x + threadIdx.x) / G;
+  // (a node's lanes leave the loop together: shuffles stay within them)
+  for (int64_t v = v0; v < hi; v += stride) {
     const int32_t k = A.deg[v];
-    if (k > K) continue;
+    if (k > kFinLaneMax) continue;
     Acc sacc = Acc();
     double tfix = 0.0;
     int64_t Tc = 0;
@@ -322,7 +330,7 @@ __device__ __forceinline__ void fin_lanes(const FinArgs &A, int64_t lo, int64_t 
       int32_t ka[K], rv[K], tr[K];
 #pragma unroll
       for (int i = 0; i < K; ++i) {
-        const int32_t e = base + (i < k ? i : k - 1);
+        const int32_t q = i * G + sub, e = base + (q < k ? q : k - 1);
         ka[i] = A.adj2[e].y;
         rv[i] = A.rrev[e];
         tr[i] = A.trec[e];
@@ -331,13 +339,14 @@ __device__ __forceinline__ void fin_lanes(const FinArgs &A, int64_t lo, int64_t 
       TriSlot ts[K];
 #pragma unroll
       for (int i = 0; i < K; ++i) {
-        own[i] = RVal<T>::load(A.R, base + (i < k ? i : k - 1));
+        const int32_t q = i * G + sub;
+        own[i] = RVal<T>::load(A.R, base + (q < k ? q : k - 1));
         back[i] = RVal<T>::load(A.R, rv[i]);
         ts[i] = A.Y[tr[i] >= 0 ? tr[i] : 0];
       }
 #pragma unroll
       for (int i = 0; i < K; ++i) {
-        const bool in = i < k;
+        const bool in = i * G + sub < k;
         // a centre of degree 1 has no pairs: its row sums were never written
         RVal<T>::add(sacc, own[i], in && k >= 2);
         RVal<T>::add(sacc, back[i], in && ka[i] >= 2);
@@ -346,8 +355,12 @@ __device__ __forceinline__ void fin_lanes(const FinArgs &A, int64_t lo, int64_t 
         Tc += hit ? ts[i].t : 0;
       }
     }
-    fin_store<T>((int32_t)v, k, A.asum[v], A.qa[v], A.dn_ptr[v + 1] > A.dn_ptr[v], sacc, tfix,
-                 Tc, A.Z, A.ZT, A.ef, A.D, A.N, A.fl);
+    sacc = group_sum<G>(sacc);
+    tfix = group_sum<G>(tfix);
+    Tc = group_sum<G>(Tc);
+    if (sub == 0)
+      fin_store<T>((int32_t)v, k, A.asum[v], A.qa[v], A.dn_ptr[v + 1] > A.dn_ptr[v], sacc, tfix,
+                   Tc, A.Z, A.ZT, A.ef, A.D, A.N, A.fl);
   }
 }
 
@@ -396,7 +409,7 @@ __device__ __forceinline__ void fin_hubs(const FinArgs &A, const int32_t *nodes,
 //   [b0, b1)       degree kFinHalfMax+1 .. kFinBlockMin, a wavefront each
 //   [b1, b2)       degree kFinGroupMax+1 .. kFinHalfMax, 32 lanes each
 //   [b2, b3)       degree kFinLaneMax+1 .. kFinGroupMax, 8 lanes each (list by id)
-//   [b3, grid)     degree <= kFinLaneMax, one lane each (node ids)
+//   [b3, grid)     degree <= kFinLaneMax, kFinShare lanes each (node ids)
 template <typename T>
 __global__ __launch_bounds__(256) void k_finalize_cluster(
     FinArgs A, const int32_t *l_hub, int64_t n_hub, const int32_t *l_wave, int64_t n_wave,
@@ -427,7 +440,7 @@ hipError_t launch_finalize_cluster(const Graph &g, ef_prec prec, const void *R, 
   const int64_t bw = n_wave > 0 ? cap_blocks((n_wave * 64 + 255) / 256, 1 << 18) : 0;
   const int64_t bc = g.n_fin_half > 0 ? cap_blocks((g.n_fin_half * 32 + 255) / 256, 1 << 18) : 0;
   const int64_t bg = g.n_fin_group > 0 ? cap_blocks((g.n_fin_group * 8 + 255) / 256, 1 << 18) : 0;
-  const int64_t bl = cap_blocks(((int64_t)g.n + 255) / 256, 1 << 17);
+  const int64_t bl = cap_blocks(((int64_t)g.n * kFinShare + 255) / 256, 1 << 17);
   const FinArgs A{g.row_ptr, g.deg, g.adj2, g.rrev, g.trec, g.dn_ptr, g.asum, g.qa,
                   R,         Y,     Z,      ZT,    ef,     D,      N,        fl};
   const unsigned grid = (unsigned)(bh + bw + bc + bg + bl);
