@@ -741,7 +741,7 @@ static unsigned j3_blocks(int64_t threads) {
 // The items of seeds[0 .. nseeds) (off: item offsets), binned by list length,
 // each bin run by its kernel; lists: kJ3Bins * n_items ints, counts: kJ3Bins.
 static_assert(kJ3Bins == 5, "list and count scratch sized for five bins");
-hipError_t launch_j3_items(const Graph &g, bool fp64, bool both, const int32_t *seeds,
+hipError_t launch_j3_items(const Graph &g, bool fp64, bool tab, bool both, const int32_t *seeds,
                            const int64_t *off,
                            int32_t nseeds, int64_t n_items, int32_t *lists, int32_t *counts,
                            long long *PN, long long *PD, double *PS, hipStream_t st) {
@@ -750,29 +750,29 @@ hipError_t launch_j3_items(const Graph &g, bool fp64, bool both, const int32_t *
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_j3_bins, dim3(j3_blocks(n_items)), dim3(256), 0, st, g.row_ptr, g.adj2,
                      seeds, off, nseeds, g.rev, both, lists, n_items, counts);
-  const J3Tab tab{g.score64, g.score64 ? g.n_score64 : 0};
+  const J3Tab jt{tab ? g.score64 : nullptr, tab && g.score64 ? g.n_score64 : 0};
   const int32_t *l[kJ3Bins];
   for (int b = 0; b < kJ3Bins; ++b) l[b] = lists + b * n_items;
   if (fp64) {
     hipLaunchKernelGGL((k_j3_wave<double, 4>), dim3(8192), dim3(256), 0, st, g.row_ptr, g.adj2,
-                       g.rev, g.src, l[0], counts + 0, PN, PD, PS, tab, both);
+                       g.rev, g.src, l[0], counts + 0, PN, PD, PS, jt, both);
     hipLaunchKernelGGL((k_j3_block<double, 2 * kJ3Lmax0, 4, 256>), dim3(4096), dim3(256), 0, st,
-                       g.row_ptr, g.adj2, g.rev, g.src, l[1], counts + 1, PN, PD, PS, tab, both);
+                       g.row_ptr, g.adj2, g.rev, g.src, l[1], counts + 1, PN, PD, PS, jt, both);
     hipLaunchKernelGGL((k_j3_block<double, 2 * kJ3Lmax1, 8, 1024>), dim3(1024), dim3(512), 0, st,
-                       g.row_ptr, g.adj2, g.rev, g.src, l[2], counts + 2, PN, PD, PS, tab, both);
+                       g.row_ptr, g.adj2, g.rev, g.src, l[2], counts + 2, PN, PD, PS, jt, both);
     hipLaunchKernelGGL((k_j3_block<double, 2 * kJ3Lmax2, 8, 1024>), dim3(256), dim3(512), 0, st,
-                       g.row_ptr, g.adj2, g.rev, g.src, l[3], counts + 3, PN, PD, PS, tab, both);
+                       g.row_ptr, g.adj2, g.rev, g.src, l[3], counts + 3, PN, PD, PS, jt, both);
     hipLaunchKernelGGL(k_j3_merge<double>, dim3(2048), dim3(256), 0, st, g.row_ptr, g.adj2,
                        g.rev, g.src, l[4], counts + 4, PN, PD, PS, both);
   } else {
     hipLaunchKernelGGL((k_j3_wave<float, 4>), dim3(8192), dim3(256), 0, st, g.row_ptr, g.adj2,
-                       g.rev, g.src, l[0], counts + 0, PN, PD, PS, tab, both);
+                       g.rev, g.src, l[0], counts + 0, PN, PD, PS, jt, both);
     hipLaunchKernelGGL((k_j3_block<float, 2 * kJ3Lmax0, 4, 256>), dim3(4096), dim3(256), 0, st,
-                       g.row_ptr, g.adj2, g.rev, g.src, l[1], counts + 1, PN, PD, PS, tab, both);
+                       g.row_ptr, g.adj2, g.rev, g.src, l[1], counts + 1, PN, PD, PS, jt, both);
     hipLaunchKernelGGL((k_j3_block<float, 2 * kJ3Lmax1, 8, 1024>), dim3(1024), dim3(512), 0, st,
-                       g.row_ptr, g.adj2, g.rev, g.src, l[2], counts + 2, PN, PD, PS, tab, both);
+                       g.row_ptr, g.adj2, g.rev, g.src, l[2], counts + 2, PN, PD, PS, jt, both);
     hipLaunchKernelGGL((k_j3_block<float, 2 * kJ3Lmax2, 8, 1024>), dim3(256), dim3(512), 0, st,
-                       g.row_ptr, g.adj2, g.rev, g.src, l[3], counts + 3, PN, PD, PS, tab, both);
+                       g.row_ptr, g.adj2, g.rev, g.src, l[3], counts + 3, PN, PD, PS, jt, both);
     hipLaunchKernelGGL(k_j3_merge<float>, dim3(2048), dim3(256), 0, st, g.row_ptr, g.adj2,
                        g.rev, g.src, l[4], counts + 4, PN, PD, PS, both);
   }
