@@ -74,7 +74,8 @@ __device__ __forceinline__ float bf(float x) { return (float)(__bf16)x; }
 // = m2 / 2 - m3 / 6 + m4 / 12 - ..., m_j = E[x^j]; the features carry m2,
 // m3 and m4. No triangle pass is needed.
 struct FeatAcc {  // POD (lives in LDS); start from feat_zero()
-  int64_t B, Q, c1;
+  int64_t B, Q;
+  int32_t c1;
   float mx, mn;
   double s1, s2, e2, e3, e4;
   __device__ void add(int2 ad, const NbrMoments &t, int64_t k, const NbrMoments &own) {
@@ -121,38 +122,76 @@ __device__ __forceinline__ FeatAcc feat_zero() {
   return a;
 }
 
-template <int G> __device__ __forceinline__ FeatAcc feat_reduce(FeatAcc a) {
-  for (int off = G / 2; off > 0; off >>= 1) {
-    FeatAcc o = feat_zero();
-    o.B = __shfl_xor(a.B, off, G);
-    o.Q = __shfl_xor(a.Q, off, G);
-    o.c1 = __shfl_xor(a.c1, off, G);
-    o.mx = __shfl_xor(a.mx, off, G);
-    o.mn = __shfl_xor(a.mn, off, G);
-    o.s1 = __shfl_xor(a.s1, off, G);
-    o.s2 = __shfl_xor(a.s2, off, G);
-    o.e2 = __shfl_xor(a.e2, off, G);
-    o.e3 = __shfl_xor(a.e3, off, G);
-    o.e4 = __shfl_xor(a.e4, off, G);
-    a.merge(o);
-  }
-  return a;
+// x of lane i ^ OFF, where the lanes of each group of OFF hold the same x
+template <int OFF> __device__ __forceinline__ int32_t lane_xor(int32_t x) {
+  // quad_perm [1,0,3,2] and [2,3,0,1], row_half_mirror, row_ror:8
+  constexpr int kCtl = OFF == 1 ? 0xB1 : OFF == 2 ? 0x4E : OFF == 4 ? 0x141 : 0x128;
+  if constexpr (OFF <= 8) return __builtin_amdgcn_update_dpp(0, x, kCtl, 0xF, 0xF, true);
+  return __shfl_xor(x, OFF, 64);
+}
+template <int OFF> __device__ __forceinline__ long long lane_xor(long long x) {
+  const int32_t lo = lane_xor<OFF>((int32_t)x), hi = lane_xor<OFF>((int32_t)(x >> 32));
+  return (long long)(((unsigned long long)(uint32_t)hi << 32) | (uint32_t)lo);
+}
+template <int OFF> __device__ __forceinline__ float lane_xor(float x) {
+  return __int_as_float(lane_xor<OFF>(__float_as_int(x)));
+}
+template <int OFF> __device__ __forceinline__ double lane_xor(double x) {
+  return __longlong_as_double(lane_xor<OFF>((long long)__double_as_longlong(x)));
 }
 
-// arcs first, first + stride, ... of node v (degree k, own sums own)
+// the sums over the G lanes of a group, on each of them
+template <int G, int OFF = 1> __device__ __forceinline__ void feat_reduce(FeatAcc &a) {
+  if constexpr (OFF < G) {
+    FeatAcc o;
+    o.B = lane_xor<OFF>((long long)a.B);
+    o.Q = lane_xor<OFF>((long long)a.Q);
+    o.c1 = lane_xor<OFF>(a.c1);
+    o.mx = lane_xor<OFF>(a.mx);
+    o.mn = lane_xor<OFF>(a.mn);
+    o.s1 = lane_xor<OFF>(a.s1);
+    o.s2 = lane_xor<OFF>(a.s2);
+    o.e2 = lane_xor<OFF>(a.e2);
+    o.e3 = lane_xor<OFF>(a.e3);
+    o.e4 = lane_xor<OFF>(a.e4);
+    a.merge(o);
+    feat_reduce<G, OFF * 2>(a);
+  }
+}
+
+// two arcs of a row at a time, i and i + stride; the second repeats the first
+// past the row's end, so that their loads are in flight together
+struct FeatPair {
+  int2 a0, a1;
+};
+__device__ __forceinline__ FeatPair feat_pair(const int2 *__restrict__ adj2, int32_t k,
+                                              int32_t base, int32_t i, int32_t stride) {
+  FeatPair p{{0, 0}, {0, 0}};
+  if (i < k) {
+    p.a0 = adj2[base + i];
+    p.a1 = adj2[base + (i + stride < k ? i + stride : i)];
+  }
+  return p;
+}
+// arcs first, first + stride, ... of a node (degree k, own sums own); p: the
+// first two
 __device__ __forceinline__ void feat_arcs(const int2 *__restrict__ adj2,
                                           const NbrMoments *__restrict__ nbm, int32_t k,
                                           int32_t base, const NbrMoments &own, int32_t first,
-                                          int32_t stride, FeatAcc &f) {
-  for (int32_t e = base + first; e < base + k; e += stride) {
-    const int2 ad = adj2[e];
-    f.add(ad, nbm[ad.x], k, own);
+                                          int32_t stride, FeatPair p, FeatAcc &f) {
+  for (int32_t i = first; i < k; i += 2 * stride) {
+    const NbrMoments m0 = nbm[p.a0.x], m1 = nbm[p.a1.x];
+    const FeatPair q = feat_pair(adj2, k, base, i + 2 * stride, stride);
+    f.add(p.a0, m0, k, own);
+    if (i + stride < k) f.add(p.a1, m1, k, own);
+    p = q;
   }
 }
 
-__device__ void feat_store(int32_t v, int32_t k, int64_t A, FeatAcc a,
-                           const float *__restrict__ mean, const float *__restrict__ inv_std,
-                           float *__restrict__ X, float *__restrict__ lnN) {
+// the features of a node, standardised where mean is given; returns ln N(s)
+__device__ __forceinline__ float feat_values(int32_t k, int64_t A, const FeatAcc &a,
+                                             const float *__restrict__ mean,
+                                             const float *__restrict__ inv_std, float (&f)[kF]) {
   const int64_t kk = k, B = a.B, Q = a.Q;
   const int64_t Ns = kk * kk - 2 * kk + A;
   // D without the triangle term
@@ -168,7 +207,6 @@ __device__ void feat_store(int32_t v, int32_t k, int64_t A, FeatAcc a,
     m3 = r3 - 3.0 * r2 + 2.0;
     m4 = r4 - 4.0 * r3 + 6.0 * r2 - 3.0;
   }
-  float f[kF];
   f[0] = logf(1.0f + (float)kk);
   f[1] = logf(1.0f + (float)A);
   f[2] = logf(1.0f + (float)B);
@@ -186,101 +224,30 @@ __device__ void feat_store(int32_t v, int32_t k, int64_t A, FeatAcc a,
   f[13] = logf(1.0f + (float)Q);
   f[14] = k > 0 ? (float)a.c1 / (float)k : 0.0f;
   f[15] = (float)log1p(fmax(m2, 0.0));
-  float *dst = X + (int64_t)v * kF;
+  if (mean) {
 #pragma unroll
-  for (int i = 0; i < kF; ++i) dst[i] = mean ? (f[i] - mean[i]) * inv_std[i] : f[i];
-  lnN[v] = Ns > 0 ? logf((float)Ns) : 0.0f;
-}
-
-// nodes == nullptr: nodes 0..count-1 of degree <= kmax; else the listed nodes
-template <int G>
-__global__ __launch_bounds__(256) void k_features(
-    const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ deg,
-    const int2 *__restrict__ adj2, const NbrMoments *__restrict__ nbm,
-    const int32_t *__restrict__ nodes, int64_t count, int32_t kmax,
-    const float *__restrict__ mean, const float *__restrict__ inv_std, float *__restrict__ X,
-    float *__restrict__ lnN) {
-  const int sub = threadIdx.x & (G - 1);
-  const int64_t grp = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / G;
-  const int64_t ngrp = ((int64_t)gridDim.x * blockDim.x) / G;
-  const int64_t rounds = (count + ngrp - 1) / ngrp;
-  for (int64_t r = 0; r < rounds; ++r) {
-    const int64_t it = r * ngrp + grp;
-    int32_t v = -1, k = 0;
-    if (it < count) {
-      v = nodes ? nodes[it] : (int32_t)it;
-      k = deg[v];
-      if (!nodes && k > kmax) v = -1;
-    }
-    if (v < 0) k = 0;
-    FeatAcc f = feat_zero();
-    NbrMoments own{0, 0, 0.0, 0.0};
-    if (v >= 0) {
-      own = nbm[v];
-      feat_arcs(adj2, nbm, k, row_ptr[v], own, sub, G, f);
-    }
-    f = feat_reduce<G>(f);
-    if (v >= 0 && sub == 0) feat_store(v, k, own.s1, f, mean, inv_std, X, lnN);
+    for (int i = 0; i < kF; ++i) f[i] = (f[i] - mean[i]) * inv_std[i];
   }
-}
-
-__global__ __launch_bounds__(1024) void k_features_hub(
-    const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ deg,
-    const int2 *__restrict__ adj2, const NbrMoments *__restrict__ nbm,
-    const int32_t *__restrict__ nodes, int64_t count, const float *__restrict__ mean,
-    const float *__restrict__ inv_std, float *__restrict__ X, float *__restrict__ lnN) {
-  __shared__ FeatAcc sh[16];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  for (int64_t it = blockIdx.x; it < count; it += gridDim.x) {
-    const int32_t v = nodes[it];
-    const int32_t k = deg[v];
-    FeatAcc f = feat_zero();
-    const NbrMoments own = nbm[v];
-    feat_arcs(adj2, nbm, k, row_ptr[v], own, tid, 1024, f);
-    f = feat_reduce<64>(f);
-    if (lane == 0) sh[wv] = f;
-    __syncthreads();
-    if (tid == 0) {
-      FeatAcc a = sh[0];
-      for (int w = 1; w < 16; ++w) a.merge(sh[w]);
-      feat_store(v, k, own.s1, a, mean, inv_std, X, lnN);
-    }
-    __syncthreads();
-  }
-}
-
-hipError_t launch_features(const Graph &g, const float *mean, const float *inv_std, float *X,
-                           float *lnN, hipStream_t st) {
-  auto cap = [](int64_t b, int64_t c) { return (unsigned)std::max<int64_t>(1, std::min(b, c)); };
-  const int64_t n_wave = g.n_fin - g.n_fin_hub - g.n_fin_half;
-  const int32_t *l_wave = g.fin_list + g.n_fin_hub, *l_half = l_wave + n_wave;
-  if (g.n_fin_hub > 0)
-    hipLaunchKernelGGL(k_features_hub, dim3(cap(g.n_fin_hub, 1 << 16)), dim3(1024), 0, st,
-                       g.row_ptr, g.deg, g.adj2, g.nbm, g.fin_list, g.n_fin_hub, mean, inv_std, X,
-                       lnN);
-  hipLaunchKernelGGL(k_features<8>, dim3(cap(((int64_t)g.n * 8 + 255) / 256, 1 << 20)), dim3(256),
-                     0, st, g.row_ptr, g.deg, g.adj2, g.nbm, nullptr, (int64_t)g.n, kFinGroupMax,
-                     mean, inv_std, X, lnN);
-  if (n_wave > 0)
-    hipLaunchKernelGGL(k_features<64>, dim3(cap((n_wave * 64 + 255) / 256, 1 << 20)), dim3(256),
-                       0, st, g.row_ptr, g.deg, g.adj2, g.nbm, l_wave, n_wave, 0, mean, inv_std,
-                       X, lnN);
-  if (g.n_fin_half > 0)
-    hipLaunchKernelGGL(k_features<32>, dim3(cap((g.n_fin_half * 32 + 255) / 256, 1 << 20)),
-                       dim3(256), 0, st, g.row_ptr, g.deg, g.adj2, g.nbm, l_half, g.n_fin_half, 0,
-                       mean, inv_std, X, lnN);
-  return hipGetLastError();
+  return Ns > 0 ? logf((float)Ns) : 0.0f;
 }
 
 // ---------------------------------------------------------------------------
 // MLP on one 32-row tile per wavefront
 // ---------------------------------------------------------------------------
-struct TileLds {
+struct TileLds {  // training: one tile, shared by two wavefronts
   __bf16 x[32][kF];
   __bf16 h1[32][kH];
   __bf16 h2[32][kH];
   __bf16 dz[32][kH];
   float dy[32];
+};
+// inference: a wavefront's rows and one hidden layer at a time. Rows are 16
+// bytes longer than their values, so that the A fragments of neighbouring rows
+// lie in different banks.
+constexpr int kXPad = kF + 8, kHPad = kH + 8;
+struct __align__(16) FwdLds {
+  __bf16 x[64][kXPad];
+  __bf16 h[32][kHPad];
 };
 
 __device__ __forceinline__ bf16x8 lds_a(const __bf16 *rowmajor, int ld, int kb) {
@@ -314,31 +281,15 @@ __device__ __forceinline__ bf16x8 wpack(const __bf16 *pack, int block) {
   return reinterpret_cast<const bf16x8 *>(pack)[block * 64 + (threadIdx.x & 63)];
 }
 
-// Forward of one tile on one wavefront. Rows r0 .. r0+31 of X; rows at or past
-// `rows` are zero. x, h1, h2 (bf16) pass through LDS; returns y for the rows
-// held by lanes 0 and 32 (C layout of column 0) in yv.
-__device__ void tile_forward(const float *__restrict__ X, int64_t r0, int64_t rows,
-                             const float *__restrict__ P, const __bf16 *__restrict__ pack,
-                             TileLds &t, f32x16 &yv) {
+// Forward of the 32 rows x on one wavefront; h: LDS for the hidden layers (the
+// first is in registers, as A fragments, before the second takes its place).
+// Returns y for the rows held by lanes 0 and 32 (C layout of column 0).
+__device__ __forceinline__ f32x16 tile_forward(const __bf16 (*x)[kXPad], __bf16 (*h)[kHPad],
+                                               const float *__restrict__ P,
+                                               const __bf16 *__restrict__ pack) {
   const int lane = threadIdx.x & 63;
-  {
-    const int i = lane & 31, c0 = (lane >> 5) * 8;
-    const int64_t row = r0 + i;
-    float xv[8];
-    if (row < rows) {
-      const float4 a = *reinterpret_cast<const float4 *>(X + row * kF + c0);
-      const float4 b = *reinterpret_cast<const float4 *>(X + row * kF + c0 + 4);
-      xv[0] = a.x; xv[1] = a.y; xv[2] = a.z; xv[3] = a.w;
-      xv[4] = b.x; xv[5] = b.y; xv[6] = b.z; xv[7] = b.w;
-    } else {
-      for (int j = 0; j < 8; ++j) xv[j] = 0.0f;
-    }
-    for (int j = 0; j < 8; ++j) t.x[i][c0 + j] = (__bf16)xv[j];
-  }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-  const bf16x8 ax = lds_a(&t.x[0][0], kF, 0);
+  wave_sync();
+  const bf16x8 ax = lds_a(&x[0][0], kXPad, 0);
 #pragma unroll
   for (int nb = 0; nb < 2; ++nb) {
     f32x16 c = {};
@@ -347,64 +298,253 @@ __device__ void tile_forward(const float *__restrict__ X, int64_t r0, int64_t ro
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       c[r] += b1;
-      t.h1[c_row(r, lane)][nb * 32 + (lane & 31)] = (__bf16)gelu(c[r]);
+      h[c_row(r, lane)][nb * 32 + (lane & 31)] = (__bf16)gelu(c[r]);
     }
   }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  wave_sync();
+  bf16x8 ah[4];
+#pragma unroll
+  for (int kb = 0; kb < 4; ++kb) ah[kb] = lds_a(&h[0][0], kHPad, kb);
+  wave_sync();
 #pragma unroll
   for (int nb = 0; nb < 2; ++nb) {
     f32x16 c = {};
 #pragma unroll
-    for (int kb = 0; kb < 4; ++kb)
-      c = mfma(lds_a(&t.h1[0][0], kH, kb), wpack(pack, kPackW2 + kb * 2 + nb), c);
+    for (int kb = 0; kb < 4; ++kb) c = mfma(ah[kb], wpack(pack, kPackW2 + kb * 2 + nb), c);
     const float b2 = P[kOffB2 + nb * 32 + (lane & 31)];
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       c[r] += b2;
-      t.h2[c_row(r, lane)][nb * 32 + (lane & 31)] = (__bf16)gelu(c[r]);
+      h[c_row(r, lane)][nb * 32 + (lane & 31)] = (__bf16)gelu(c[r]);
     }
   }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  wave_sync();
   f32x16 c = {};
 #pragma unroll
-  for (int kb = 0; kb < 4; ++kb) c = mfma(lds_a(&t.h2[0][0], kH, kb), wpack(pack, kPackW3 + kb), c);
+  for (int kb = 0; kb < 4; ++kb)
+    c = mfma(lds_a(&h[0][0], kHPad, kb), wpack(pack, kPackW3 + kb), c);
   const float b3 = P[kOffB3];
 #pragma unroll
   for (int r = 0; r < 16; ++r) c[r] += b3;
-  yv = c;
+  return c;
 }
 
-// inference: y for rows [0, rows); out_ef = max(0, lnN - y) when lnN given
+// y of rows [0, rows) of X (rows past the end are zero)
 __global__ __launch_bounds__(256) void k_mlp_forward(const float *__restrict__ X, int64_t rows,
                                                      const float *__restrict__ P,
                                                      const __bf16 *__restrict__ pack,
-                                                     const float *__restrict__ lnN,
-                                                     float *__restrict__ y_out,
-                                                     double *__restrict__ ef_out) {
-  __shared__ TileLds tl[4];
+                                                     float *__restrict__ y_out) {
+  __shared__ FwdLds lds[4];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  FwdLds &L = lds[wv];
   const int64_t tiles = (rows + 31) / 32;
   for (int64_t tile = (int64_t)blockIdx.x * 4 + wv; tile < tiles; tile += (int64_t)gridDim.x * 4) {
-    f32x16 yv;
-    tile_forward(X, tile * 32, rows, P, pack, tl[wv], yv);
+    const int i = lane & 31, c0 = (lane >> 5) * 8;
+    const int64_t row = tile * 32 + i;
+    float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
+    if (row < rows) {
+      a = *reinterpret_cast<const float4 *>(X + row * kF + c0);
+      b = *reinterpret_cast<const float4 *>(X + row * kF + c0 + 4);
+    }
+    const float xv[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+    for (int j = 0; j < 8; ++j) L.x[i][c0 + j] = (__bf16)xv[j];
+    const f32x16 y = tile_forward(L.x, L.h, P, pack);
     if ((lane & 31) == 0) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int64_t row = tile * 32 + c_row(r, lane);
-        if (row < rows) {
-          if (y_out) y_out[row] = yv[r];
-          if (ef_out) {
-            const float e = lnN[row] - yv[r];
-            ef_out[row] = e > 0.0f ? (double)e : 0.0;
-          }
-        }
+        const int64_t out = tile * 32 + c_row(r, lane);
+        if (out < rows) y_out[out] = y[r];
       }
     }
   }
+}
+
+struct FeatArgs {
+  const int32_t *row_ptr, *deg;
+  const int2 *adj2;
+  const NbrMoments *nbm;
+  const float *mean, *inv_std;
+  float *X, *lnN;         // features and ln N by node, or
+  const float *P;         // the network and its predictions
+  const __bf16 *pack;
+  double *ef;
+};
+struct FeatNode {  // a lane's node (v < 0: none) and its sums
+  FeatAcc f;
+  int32_t v, k;
+  int64_t s1;
+};
+
+// Item i0 of a wavefront: R rounds of 64 / G nodes of `nodes` (NULL: node ids
+// 0..count-1 of degree <= kmax), G lanes per node. Lane r of a group keeps the
+// node of round r, so that one pass over the features' formulas (some 900
+// instructions, most in FP64) and the network serves 64 R / G nodes.
+template <int G, int R>
+__device__ __forceinline__ FeatNode feat_groups(const FeatArgs &A, const int32_t *nodes,
+                                                int64_t count, int32_t kmax, int64_t i0) {
+  static_assert(R <= G, "a lane keeps one node");
+  constexpr int W = 64 / G;  // nodes per round
+  const int lane = threadIdx.x & 63, sub = lane & (G - 1), grp = lane / G;
+  FeatNode o{feat_zero(), -1, 0, 0};
+  const int64_t it = i0 + sub * W + grp;
+  int32_t bk = 0;
+  if (sub < R && it < count) {
+    o.v = nodes ? nodes[it] : (int32_t)it;
+    o.k = A.deg[o.v];
+    bk = A.row_ptr[o.v];
+    if (!nodes && o.k > kmax) o.v = -1;
+    if (o.v < 0) o.k = 0;
+  }
+  int32_t k = __shfl(o.k, 0, G), base = __shfl(bk, 0, G);
+  FeatPair p = feat_pair(A.adj2, k, base, sub, G);
+  for (int r = 0; r < R; ++r) {
+    const int32_t v = __shfl(o.v, r, G);
+    const int32_t kn = r + 1 < R ? __shfl(o.k, r + 1, G) : 0,
+                  bn = r + 1 < R ? __shfl(bk, r + 1, G) : 0;
+    const FeatPair q = feat_pair(A.adj2, kn, bn, sub, G);  // the next round's
+    FeatAcc f = feat_zero();
+    NbrMoments own{0, 0, 0.0, 0.0};
+    if (v >= 0) {
+      own = A.nbm[v];
+      feat_arcs(A.adj2, A.nbm, k, base, own, sub, G, p, f);
+    }
+    feat_reduce<G>(f);
+    if (sub == r) {
+      o.f = f;
+      o.s1 = own.s1;
+    }
+    k = kn;
+    base = bn;
+    p = q;
+  }
+  return o;
+}
+
+// hub v on the whole workgroup; thread 0 holds it
+__device__ __forceinline__ FeatNode feat_hub(const FeatArgs &A, int32_t v) {
+  __shared__ FeatAcc sh[4];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int32_t k = A.deg[v], base = A.row_ptr[v];
+  FeatNode o{feat_zero(), tid == 0 ? v : -1, k, 0};
+  const NbrMoments own = A.nbm[v];
+  o.s1 = own.s1;
+  feat_arcs(A.adj2, A.nbm, k, base, own, tid, 256, feat_pair(A.adj2, k, base, tid, 256), o.f);
+  feat_reduce<64>(o.f);
+  __syncthreads();  // the previous hub's sums have been read
+  if (lane == 0) sh[wv] = o.f;
+  __syncthreads();
+  if (tid == 0)
+    for (int w = 1; w < 4; ++w) o.f.merge(sh[w]);
+  return o;
+}
+
+// One launch for every node, the longest rows first: hubs, a workgroup each
+// (blocks [0, b0)), degree kFinHalfMax+1 .. kFinBlockMin, a wavefront each
+// ([b0, b1)), kFinGroupMax+1 .. kFinHalfMax, 32 lanes each ([b1, b2)), and the
+// rest, 8 lanes each (node ids). PREDICT: the wavefront that has the features
+// of its nodes runs the network on them and writes the predicted EF.
+// Bound by the gathers of the neighbours' moments: a 128-byte sector of the
+// memory-side cache for 32 bytes of each arc (BA n = 1M, m = 8: 15M of them,
+// 7 TB/s), with the formulas and the GELUs beside them. That graph: 303 us; with
+// the network in a launch of its own 355 us, and with a launch per tier and the
+// formulas on one lane of eight 563 us.
+template <int R, bool PREDICT>
+__global__ __launch_bounds__(256) void k_features(FeatArgs A, const int32_t *l_hub, int64_t n_hub,
+                                                  const int32_t *l_wave, int64_t n_wave,
+                                                  const int32_t *l_half, int64_t n_half, int64_t n,
+                                                  int64_t b0, int64_t b1, int64_t b2) {
+  __shared__ FwdLds lds[PREDICT ? 4 : 1];
+  const int64_t b = blockIdx.x;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  // this wavefront's items: first, step and end; and a lane's row in the tile
+  // (feat_groups: round sub, group grp)
+  int64_t i0, step, end;
+  int row, rows;
+  if (b < b0) {
+    i0 = b, step = b0, end = n_hub, row = 0, rows = wv == 0 ? 1 : 0;
+  } else if (b < b1) {
+    i0 = (b - b0) * 4 + wv, step = (b1 - b0) * 4, end = n_wave, row = lane, rows = 1;
+  } else if (b < b2) {
+    i0 = ((b - b1) * 4 + wv) * 2 * R, step = (b2 - b1) * 8 * R, end = n_half;
+    row = (lane & 31) * 2 + (lane >> 5), rows = 2 * R;
+  } else {
+    i0 = ((b - b2) * 4 + wv) * 8 * R, step = ((int64_t)gridDim.x - b2) * 32 * R, end = n;
+    row = (lane & 7) * 8 + (lane >> 3), rows = 8 * R;
+  }
+  for (; i0 < end; i0 += step) {
+    const FeatNode o = b < b0   ? feat_hub(A, l_hub[i0])
+                       : b < b1 ? feat_groups<64, 1>(A, l_wave, n_wave, 0, i0)
+                       : b < b2 ? feat_groups<32, R>(A, l_half, n_half, 0, i0)
+                                : feat_groups<8, R>(A, nullptr, n, kFinGroupMax, i0);
+    float f[kF], ln = 0.0f;
+    if (o.v >= 0) ln = feat_values(o.k, o.s1, o.f, A.mean, A.inv_std, f);
+    if constexpr (!PREDICT) {
+      if (o.v >= 0) {
+        float *dst = A.X + (int64_t)o.v * kF;
+#pragma unroll
+        for (int i = 0; i < kF; ++i) dst[i] = f[i];
+        A.lnN[o.v] = ln;
+      }
+    } else {
+      FwdLds &L = lds[wv];
+      wave_sync();  // the previous item's rows have been read
+      if (o.v >= 0) {
+#pragma unroll
+        for (int i = 0; i < kF; ++i) L.x[row][i] = (__bf16)f[i];
+      }
+      // (rows without a node hold what was there: a row's values reach no other)
+      for (int t = 0; t < rows; t += 32) {
+        const f32x16 y = tile_forward(&L.x[t], L.h, A.P, A.pack);
+        wave_sync();
+        float *ys = reinterpret_cast<float *>(&L.h[0][0]);
+        if ((lane & 31) == 0) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) ys[c_row(r, lane)] = y[r];
+        }
+        wave_sync();
+        if (o.v >= 0 && row >= t && row < t + 32) {
+          const float e = ln - ys[row - t];
+          A.ef[o.v] = e > 0.0f ? (double)e : 0.0;
+        }
+        wave_sync();
+      }
+    }
+  }
+}
+
+template <int R, bool PREDICT>
+static hipError_t features_impl(const Graph &g, const FeatArgs &A, hipStream_t st) {
+  auto blocks = [](int64_t count, int64_t per) {
+    return count > 0 ? std::min<int64_t>((count + per - 1) / per, 1 << 20) : 0;
+  };
+  const int64_t n_wave = g.n_fin - g.n_fin_hub - g.n_fin_half;
+  const int32_t *l_wave = g.fin_list + g.n_fin_hub, *l_half = l_wave + n_wave;
+  const int64_t b0 = blocks(g.n_fin_hub, 1), b1 = b0 + blocks(n_wave, 4),
+                b2 = b1 + blocks(g.n_fin_half, 8 * R), grid = b2 + blocks(g.n, 32 * R);
+  hipLaunchKernelGGL((k_features<R, PREDICT>), dim3((unsigned)grid), dim3(256), 0, st, A,
+                     g.fin_list, g.n_fin_hub, l_wave, n_wave, l_half, g.n_fin_half, (int64_t)g.n,
+                     b0, b1, b2);
+  return hipGetLastError();
+}
+
+// Eight rounds per wavefront from kFeatRounds nodes on: below, as many
+// wavefronts as one round gives are wanted (predictions on BA, m = 8, one and
+// eight rounds: 4000 nodes 12 and 27 us, 32000 30 and 41, 64000 52 and 46; a
+// million 816 and 303).
+constexpr int32_t kFeatRounds = 1 << 16;
+
+hipError_t launch_features(const Graph &g, const float *mean, const float *inv_std, float *X,
+                           float *lnN, hipStream_t st) {
+  const FeatArgs A{g.row_ptr, g.deg, g.adj2, g.nbm, mean, inv_std, X, lnN, nullptr, nullptr,
+                   nullptr};
+  return g.n >= kFeatRounds ? features_impl<8, false>(g, A, st) : features_impl<1, false>(g, A, st);
+}
+
+// predicted EF of every node: max(0, ln N - y)
+hipError_t launch_predict(const Graph &g, const float *mean, const float *inv_std, const float *P,
+                          const __bf16 *pack, double *ef, hipStream_t st) {
+  const FeatArgs A{g.row_ptr, g.deg, g.adj2, g.nbm, mean, inv_std, nullptr, nullptr, P, pack, ef};
+  return g.n >= kFeatRounds ? features_impl<8, true>(g, A, st) : features_impl<1, true>(g, A, st);
 }
 
 // Training: gradients of the mean squared error over the rows perm[b0 .. b0+nb)
@@ -721,11 +861,11 @@ hipError_t launch_mlp_pack(const float *P, __bf16 *pack, hipStream_t st) {
 }
 
 hipError_t launch_mlp_forward(const float *X, int64_t rows, const float *P, const __bf16 *pack,
-                              const float *lnN, float *y, double *ef, hipStream_t st) {
+                              float *y, hipStream_t st) {
   if (rows <= 0) return hipSuccess;
   const int64_t tiles = (rows + 31) / 32;
   const unsigned blocks = (unsigned)std::min<int64_t>((tiles + 3) / 4, 1 << 16);
-  hipLaunchKernelGGL(k_mlp_forward, dim3(blocks), dim3(256), 0, st, X, rows, P, pack, lnN, y, ef);
+  hipLaunchKernelGGL(k_mlp_forward, dim3(blocks), dim3(256), 0, st, X, rows, P, pack, y);
   return hipGetLastError();
 }
 

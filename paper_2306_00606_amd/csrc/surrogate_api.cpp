@@ -16,8 +16,10 @@ namespace efi {
 hipError_t launch_features(const Graph &g, const float *mean, const float *inv_std, float *X,
                            float *lnN, hipStream_t st);
 hipError_t launch_mlp_pack(const float *P, __bf16 *pack, hipStream_t st);
+hipError_t launch_predict(const Graph &g, const float *mean, const float *inv_std, const float *P,
+                          const __bf16 *pack, double *ef, hipStream_t st);
 hipError_t launch_mlp_forward(const float *X, int64_t rows, const float *P, const __bf16 *pack,
-                              const float *lnN, float *y, double *ef, hipStream_t st);
+                              float *y, hipStream_t st);
 hipError_t launch_mlp_partials(const float *X, const float *Yt, const int32_t *perm, int64_t b0,
                                int64_t nrows, const float *P, const __bf16 *pack, float *part,
                                float *part_loss, int32_t slots, hipStream_t st);
@@ -337,14 +339,14 @@ ef_status ef_surrogate_forward(ef_surrogate *s, const float *X, int64_t rows, fl
   ef_status r = s->device_ready ? EF_OK : sg_upload(s, st);
   if (r != EF_OK) return r;
   if (flags & EF_OUT_DEVICE)
-    return hip_status(launch_mlp_forward(X, rows, s->dP, s->dpack, nullptr, y, nullptr, st),
+    return hip_status(launch_mlp_forward(X, rows, s->dP, s->dpack, y, st),
                       "surrogate forward");
   float *dX = nullptr, *dy = nullptr;
   hipError_t e = hipMalloc(&dX, sizeof(float) * kNF * rows);
   if (e == hipSuccess) e = hipMalloc(&dy, sizeof(float) * rows);
   if (e == hipSuccess)
     e = hipMemcpyAsync(dX, X, sizeof(float) * kNF * rows, hipMemcpyHostToDevice, st);
-  if (e == hipSuccess) e = launch_mlp_forward(dX, rows, s->dP, s->dpack, nullptr, dy, nullptr, st);
+  if (e == hipSuccess) e = launch_mlp_forward(dX, rows, s->dP, s->dpack, dy, st);
   if (e == hipSuccess) e = hipMemcpyAsync(y, dy, sizeof(float) * rows, hipMemcpyDeviceToHost, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   (void)hipFree(dX);
@@ -522,27 +524,13 @@ ef_status ef_surrogate_predict(ef_surrogate *s, ef_graph *h, double *ef_pred, ui
   ef_status r = s->device_ready ? EF_OK : sg_upload(s, st);
   if (r != EF_OK) return r;
   const size_t n = (size_t)g.n;
-  char *p = nullptr;
-  const size_t need = (sizeof(float) * kNF + sizeof(float)) * n + sizeof(double) * n + 4096;
-  ef_status rs = graph_scratch(g, need, (void **)&p);
-  if (rs != EF_OK) return rs;
-  hipError_t e = hipSuccess;
-  char *base = p;
-  auto take = [&](size_t b) {
-    char *rr = p;
-    p += (b + 255) & ~(size_t)255;
-    return rr;
-  };
-  float *Xd = (float *)take(sizeof(float) * kNF * n);
-  float *Ld = (float *)take(sizeof(float) * n);
   const bool dev = (flags & EF_OUT_DEVICE) != 0;
-  double *Ed = dev ? ef_pred : (double *)take(sizeof(double) * n);
-  e = launch_features(g, s->dmean, s->dinv, Xd, Ld, st);
-  if (e == hipSuccess) e = launch_mlp_forward(Xd, (int64_t)n, s->dP, s->dpack, Ld, nullptr, Ed, st);
+  double *Ed = ef_pred;
+  if (!dev && (r = graph_scratch(g, sizeof(double) * n, (void **)&Ed)) != EF_OK) return r;
+  hipError_t e = launch_predict(g, s->dmean, s->dinv, s->dP, s->dpack, Ed, st);
   if (e == hipSuccess && !dev)
     e = hipMemcpyAsync(ef_pred, Ed, sizeof(double) * n, hipMemcpyDeviceToHost, st);
   if (e == hipSuccess && !dev) e = hipStreamSynchronize(st);
-  (void)base;
   return hip_status(e, "surrogate predict");
 }
 
