@@ -78,9 +78,14 @@ enum {
   WS_SPLIT  // pieces of the seeds of per-seed calls and their sums
 };
 
+// Host outputs of up to kOneCopy nodes come back in one copy, with the counters,
+// and are spread by the host: a copy to pageable memory costs some 15 us beside
+// its bytes, four of them as much as the host takes for these nodes.
+constexpr int32_t kOneCopy = 16384;
+
 // Byte offsets in WS_MAIN of one ef_compute call: per-arc sums, super-tile
-// records, flag list and bytes, output staging, triangle records and node sums
-// (cluster-centric only). One block: an allocation and a free of tens of
+// records, flag list and bytes, output staging and pass 2's counters, triangle records
+// and node sums (cluster-centric only). One block: an allocation and a free of tens of
 // megabytes cost some 0.3 ms each.
 struct ComputeWs {
   size_t R = 0, rec = 0, flag = 0, out = 0, Y = 0, Z = 0, ZT = 0, bytes = 0;
@@ -100,8 +105,8 @@ static ComputeWs compute_ws(const Graph &g, bool fp64, int64_t n_tiles, int64_t 
   };
   L.R = take(sz * nnz);
   L.rec = take(sz * kRecEntries * (size_t)std::max<int64_t>(n_tiles, 1));
-  L.flag = take((sizeof(int32_t) + 1) * w);
-  L.out = take((sizeof(double) + 2 * sizeof(int64_t)) * w);
+  L.flag = take((w > (size_t)kPass2Scan ? sizeof(int32_t) : 0) * w + w);
+  L.out = take((sizeof(double) + 2 * sizeof(int64_t)) * w + 2 * sizeof(int32_t));
   if (triangles) {
     L.Y = take(sizeof(TriSlot) * 2 * nup);
     L.Z = take(sizeof(double) * n);  // FP32C: a float pair
@@ -1009,11 +1014,11 @@ extern "C" ef_status ef_compute(ef_graph *h, ef_algo algo, ef_prec prec, const i
     if (D) D_w = D;
     if (N) N_w = N;
   }
-  int32_t *cnt = g.d_counters;  // [0] flagged, [1] fp64-finalised
-  hipError_t e = launch_zero_i32(cnt, 4, st);
-  if (e != hipSuccess) return hip_status(e, "clear counters");
-  int32_t *flagged = (int32_t *)(ws + L.flag);
-  uint8_t *flag_bytes = (uint8_t *)(flagged + std::max<int32_t>(n_work, 1));
+  // FP32C: [0] positions recomputed by pass 2, [1] finalised in FP64
+  int32_t *cnt = (int32_t *)(ws + L.out + 24 * (size_t)n_work);
+  hipError_t e = hipSuccess;
+  int32_t *listed = (int32_t *)(ws + L.flag);
+  uint8_t *flag_bytes = (uint8_t *)(listed + (n_work > kPass2Scan ? n_work : 0));
 
   // device seed arrays: the unique work list (all nodes: none, position =
   // node id), the inverse map, and output positions by seed degree bin
@@ -1167,42 +1172,59 @@ extern "C" ef_status ef_compute(ef_graph *h, ef_algo algo, ef_prec prec, const i
     e = fork ? join(0) : launch_triangles(g, prec, ws_Y, ws_Z, ws_ZT, st);
     if (e != hipSuccess) return hip_status(e, "triangle pass");
     prof.mark(6);
-    e = launch_finalize_cluster(g, prec, ws_R, ws_Y, ws_Z, ws_ZT, ef_w, D_w, N_w, flag_bytes, st);
-    if (e == hipSuccess) e = launch_flag_compact(flag_bytes, n_work, flagged, cnt, st);
+    e = launch_finalize_cluster(g, prec, ws_R, ws_Y, ws_Z, ws_ZT, ef_w, D_w, N_w, flag_bytes,
+                                prec == EF_PREC_FP32C ? cnt : nullptr, st);
     if (e != hipSuccess) return hip_status(e, "finalize");
     prof.mark(7);
   } else {
-    e = launch_per_seed(g, prec, d_useeds, ls, ws_R, (uint32_t *)g.ws[WS_BITMAP].p, ef_w, D_w, N_w,
-                        flag_bytes, st, prof.ev(6));
-    if (e == hipSuccess) e = launch_flag_compact(flag_bytes, n_work, flagged, cnt, st);
+    if (prec == EF_PREC_FP32C) e = launch_zero_i32(cnt, 2, st);
+    if (e == hipSuccess)
+      e = launch_per_seed(g, prec, d_useeds, ls, ws_R, (uint32_t *)g.ws[WS_BITMAP].p, ef_w, D_w,
+                          N_w, flag_bytes, st, prof.ev(6));
     if (e != hipSuccess) return hip_status(e, "per-seed stream");
     prof.mark(7);
   }
   if (prec == EF_PREC_FP32C) {
-    e = launch_pass2(g, per_seed ? d_useeds : nullptr, flagged, cnt, n_work, ef_w, D_w, st);
+    e = launch_pass2(g, per_seed ? d_useeds : nullptr, flag_bytes, n_work, listed, cnt, ef_w,
+                     D_w, st);
     if (e != hipSuccess) return hip_status(e, "pass 2");
   }
   prof.mark(8);
 
   // deliver outputs
+  int32_t hc[2] = {0, 0};
+  bool counted = false;
   if (!all) {
     if (out_dev) {
       e = launch_gather_outputs(d_inv, n_seeds, ef_w, D_w, N_w, ef, D, N, st);
       if (e != hipSuccess) return hip_status(e, "scatter outputs");
     } else {
-      // the staged EF, D and N lie one after the other: one copy
-      std::vector<int64_t> h(3 * (size_t)n_work);
-      e = hipMemcpyAsync(h.data(), ef_w, 3 * sizeof(int64_t) * n_work, hipMemcpyDeviceToHost, st);
+      // the staged EF, D and N and the counters lie one after the other: one copy
+      std::vector<int64_t> h(3 * (size_t)n_work + 1);
+      e = hipMemcpyAsync(h.data(), ef_w, sizeof(int64_t) * h.size(), hipMemcpyDeviceToHost, st);
       if (e == hipSuccess) e = hipStreamSynchronize(st);
+      if (e != hipSuccess) return hip_status(e, "copy outputs");
       const double *hef = (const double *)h.data();
       const int64_t *hD = h.data() + n_work, *hN = hD + n_work;
-      if (e != hipSuccess) return hip_status(e, "copy outputs");
+      std::memcpy(hc, hN + n_work, sizeof(hc));
+      counted = true;
       for (int32_t i = 0; i < n_seeds; ++i) {
         ef[i] = hef[inv[i]];
         if (D) D[i] = hD[inv[i]];
         if (N) N[i] = hN[inv[i]];
       }
     }
+  } else if (!out_dev && n_out <= kOneCopy) {
+    std::vector<int64_t> h(3 * (size_t)n_out + 1);
+    e = hipMemcpyAsync(h.data(), ef_w, sizeof(int64_t) * h.size(), hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e != hipSuccess) return hip_status(e, "copy outputs");
+    const size_t bytes = sizeof(int64_t) * (size_t)n_out;
+    std::memcpy(ef, h.data(), bytes);
+    if (D) std::memcpy(D, h.data() + n_out, bytes);
+    if (N) std::memcpy(N, h.data() + 2 * (size_t)n_out, bytes);
+    std::memcpy(hc, h.data() + 3 * (size_t)n_out, sizeof(hc));
+    counted = true;
   } else if (!out_dev) {
     e = hipMemcpyAsync(ef, ef_w, sizeof(double) * (size_t)n_out, hipMemcpyDeviceToHost, st);
     if (e == hipSuccess && D)
@@ -1218,10 +1240,11 @@ extern "C" ef_status ef_compute(ef_graph *h, ef_algo algo, ef_prec prec, const i
   g.stats.pairs_big = b.pairs_big;
   g.stats.seeds = n_work;
   if ((prof.on || !out_dev) && !(flags & kInternalNoReadback)) {
-    int32_t hc[2] = {0, 0};
-    e = hipMemcpyAsync(hc, cnt, sizeof(hc), hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (prec == EF_PREC_FP32C && !counted)
+      e = hipMemcpyAsync(hc, cnt, sizeof(hc), hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess && (prof.on || !counted)) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return hip_status(e, "read counters");
+    if (prec != EF_PREC_FP32C) hc[0] = hc[1] = 0;  // not written
     g.stats.promoted = hc[0];
     g.stats.fp64_finalized = hc[1];
   }

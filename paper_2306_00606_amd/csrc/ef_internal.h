@@ -338,13 +338,7 @@ hipError_t launch_triangles(const Graph &g, ef_prec prec, TriSlot *Y, void *Z, i
 // per-node sums + Eq. 1 (cluster-centric); per-node flag bytes in fl.
 hipError_t launch_finalize_cluster(const Graph &g, ef_prec prec, const void *R, const TriSlot *Y,
                                    const void *Z, const int64_t *ZT, double *ef, int64_t *D,
-                                   int64_t *N, uint8_t *fl, hipStream_t st);
-
-// flag bytes of positions 0..n-1 (written by the finalize and per-seed
-// kernels: bit 0 pass 2, bit 1 FP64-finalised) -> flagged list and
-// counts[0] (its length), counts[1] (FP64 count); counts are added to.
-hipError_t launch_flag_compact(const uint8_t *fl, int64_t n, int32_t *flagged, int32_t *counts,
-                               hipStream_t st);
+                                   int64_t *N, uint8_t *fl, int32_t *counts, hipStream_t st);
 
 // Output positions by seed bin (kSeedBins bins, see above), by 2-hop work
 // descending. The first split[b] of bin b are cut into pieces: items first[b]
@@ -387,11 +381,19 @@ hipError_t launch_j3_finish(const Graph &g, bool fp64, const long long *PN, cons
                             int32_t count, double *ef, int64_t *D, int64_t *N, uint8_t *fl,
                             hipStream_t st);
 
-// FP32C pass 2: recompute EF of flagged positions from non-negative terms.
-// seeds[pos] gives the node of output position pos (NULL: pos is the node).
-hipError_t launch_pass2(const Graph &g, const int32_t *seeds, const int32_t *flagged,
-                        const int32_t *flag_count, int32_t max_flagged, double *ef,
-                        const int64_t *D, hipStream_t st);
+// FP32C pass 2 over positions 0 .. n-1: recompute EF from non-negative terms
+// where bit 0 of the flag byte is set. seeds[pos] gives the node of output
+// position pos (NULL: pos is the node). counts[0] += positions recomputed,
+// counts[1] += positions whose bit 1 is set (finalised in FP64). listed: n ints
+// of scratch, for n > kPass2Scan: there a launch that lists the flagged
+// positions first pays (64 graphs of 716k nodes, 0.2% of them flagged: 21 us
+// against 35, since a workgroup that finds several takes them one by one; R-MAT
+// scale 22 44 us against 79), below it costs more than it saves (BA n = 200k 10
+// us against 4).
+constexpr int64_t kPass2Scan = 1 << 18;
+hipError_t launch_pass2(const Graph &g, const int32_t *seeds, const uint8_t *fl, int64_t n,
+                        int32_t *listed, int32_t *counts, double *ef, const int64_t *D,
+                        hipStream_t st);
 
 // top-k by EF (descending, ties by id ascending) over ef[0..n): device
 // values in, device nodes[0..k) and (nullable) ef_out[0..k) out; scratch of

@@ -19,8 +19,8 @@ constexpr double kLn2 = 0.69314718055994530942;
 
 // Eq. 1 from the sums. fl[pos] receives the position's flags: bit 0 the
 // FP32 result is cancellation-prone (recomputed by pass 2), bit 1 it was
-// finalised in FP64 (more than 2^24 clusters). Flags are bytes, compacted
-// afterwards by k_flag_compact: no contended atomics here.
+// finalised in FP64 (more than 2^24 clusters). Flags are bytes, looked through
+// afterwards by pass 2: no contended atomics here.
 template <typename T>
 __device__ __forceinline__ double finish_ef(int64_t Nn, int64_t Dd, double S, int32_t pos,
                                            uint8_t *fl);
@@ -118,16 +118,6 @@ __global__ __launch_bounds__(1024) void k_flag_compact(const uint8_t *__restrict
     run += tot;
     __syncthreads();
   }
-}
-
-hipError_t launch_flag_compact(const uint8_t *fl, int64_t n, int32_t *flagged, int32_t *counts,
-                               hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  int64_t blocks = (n + 4095) / 4096;
-  if (blocks > 256) blocks = 256;
-  hipLaunchKernelGGL(k_flag_compact, dim3((unsigned)blocks), dim3(1024), 0, st, fl, n, flagged,
-                     counts);
-  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
@@ -266,6 +256,7 @@ struct FinArgs {
   double *ef;
   int64_t *D, *N;
   uint8_t *fl;
+  int32_t *counts;  // pass 2's two counters, cleared here
 };
 
 // G lanes per node over `nodes` (NULL: node ids 0..count-1 of degree <= kmax),
@@ -416,6 +407,7 @@ __global__ __launch_bounds__(256) void k_finalize_cluster(
     const int32_t *l_half, int64_t n_half, const int32_t *l_group, int64_t n_group, int32_t n,
     int64_t b0, int64_t b1, int64_t b2, int64_t b3) {
   const int64_t b = blockIdx.x;
+  if (A.counts && b == 0 && threadIdx.x < 2) A.counts[threadIdx.x] = 0;
   if (b < b0) fin_hubs<T>(A, l_hub, n_hub, b, b0);
   else if (b < b1) fin_groups<T, 64>(A, l_wave, n_wave, 0, b - b0, b1 - b0);
   else if (b < b2) fin_groups<T, 32>(A, l_half, n_half, 0, b - b1, b2 - b1);
@@ -430,7 +422,7 @@ static unsigned cap_blocks(int64_t b, int64_t cap) {
 
 hipError_t launch_finalize_cluster(const Graph &g, ef_prec prec, const void *R, const TriSlot *Y,
                                    const void *Z, const int64_t *ZT, double *ef, int64_t *D,
-                                   int64_t *N, uint8_t *fl, hipStream_t st) {
+                                   int64_t *N, uint8_t *fl, int32_t *counts, hipStream_t st) {
   // fin_list = [hubs][wavefront tier][32-lane tier] (degree descending), then
   // the 8-lane tier (id order)
   const int64_t n_wave = g.n_fin - g.n_fin_hub - g.n_fin_half;
@@ -442,7 +434,7 @@ hipError_t launch_finalize_cluster(const Graph &g, ef_prec prec, const void *R, 
   const int64_t bg = g.n_fin_group > 0 ? cap_blocks((g.n_fin_group * 8 + 255) / 256, 1 << 18) : 0;
   const int64_t bl = cap_blocks(((int64_t)g.n * kFinShare + 255) / 256, 1 << 17);
   const FinArgs A{g.row_ptr, g.deg, g.adj2, g.rrev, g.trec, g.dn_ptr, g.asum, g.qa,
-                  R,         Y,     Z,      ZT,    ef,     D,      N,        fl};
+                  R,         Y,     Z,      ZT,    ef,     D,      N,        fl,    counts};
   const unsigned grid = (unsigned)(bh + bw + bc + bg + bl);
   if (prec == EF_PREC_FP64)
     hipLaunchKernelGGL(k_finalize_cluster<double>, dim3(grid), dim3(256), 0, st, A, g.fin_list,
@@ -956,29 +948,70 @@ __device__ __forceinline__ void pass2_seed(const int32_t *__restrict__ row_ptr,
   __syncthreads();
 }
 
+// Pass 2 of the flagged positions: those listed (counts[0] of them), or, without
+// a list, those that workgroup b finds among positions b, b + grid, ..., whose
+// flag bytes it reads 256 at a time (flagged positions are often neighbours:
+// this way they go to different workgroups), adding to counts as k_flag_compact
+// does.
 __global__ __launch_bounds__(256) void k_pass2(const int32_t *__restrict__ row_ptr,
                                                const int32_t *__restrict__ col,
                                                const int32_t *__restrict__ deg,
                                                const int2 *__restrict__ adj2,
                                                const int32_t *__restrict__ seeds,
-                                               const int32_t *__restrict__ flagged,
-                                               const int32_t *__restrict__ flag_count,
+                                               const uint8_t *__restrict__ fl, int64_t n,
+                                               const int32_t *__restrict__ listed,
+                                               int32_t *__restrict__ counts,
                                                double *__restrict__ ef,
                                                const int64_t *__restrict__ Dv) {
   __shared__ Pass2Lds L;
-  const int32_t count = *flag_count;
-  for (int32_t it = blockIdx.x; it < count; it += gridDim.x) {
-    const int32_t pos = flagged[it];
-    pass2_seed(row_ptr, col, deg, adj2, seeds ? seeds[pos] : pos, pos, ef, Dv, L);
+  __shared__ int32_t list[256], found;
+  const int tid = threadIdx.x, lane = tid & 63;
+  if (listed) {
+    const int32_t count = counts[0];
+    for (int32_t it = blockIdx.x; it < count; it += gridDim.x) {
+      const int32_t q = listed[it];
+      pass2_seed(row_ptr, col, deg, adj2, seeds ? seeds[q] : q, q, ef, Dv, L);
+    }
+    return;
+  }
+  int32_t flagged = 0, wide = 0;  // per wavefront
+  for (int64_t p0 = blockIdx.x; p0 < n; p0 += 256 * (int64_t)gridDim.x) {
+    const int64_t pos = p0 + tid * (int64_t)gridDim.x;
+    const int x = pos < n ? fl[pos] : 0;
+    const unsigned long long m = __ballot(x & 1);
+    flagged += __popcll(m);
+    wide += __popcll(__ballot(x & 2));
+    if (!__syncthreads_or(x & 1)) continue;
+    if (tid == 0) found = 0;
+    __syncthreads();
+    int32_t at = 0;
+    if (lane == 0 && m != 0ull) at = atomicAdd(&found, __popcll(m));
+    at = __shfl(at, 0, 64) + __popcll(m & ((1ull << lane) - 1));
+    if (x & 1) list[at] = (int32_t)pos;
+    __syncthreads();
+    const int32_t count = found;
+    for (int32_t i = 0; i < count; ++i) {
+      const int32_t q = list[i];
+      pass2_seed(row_ptr, col, deg, adj2, seeds ? seeds[q] : q, q, ef, Dv, L);
+    }
+  }
+  if (lane == 0) {
+    if (flagged) atomicAdd(&counts[0], flagged);
+    if (wide) atomicAdd(&counts[1], wide);
   }
 }
 
-hipError_t launch_pass2(const Graph &g, const int32_t *seeds, const int32_t *flagged,
-                        const int32_t *flag_count, int32_t max_flagged, double *ef,
-                        const int64_t *D, hipStream_t st) {
-  if (max_flagged <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_pass2, dim3(cap_blocks(max_flagged, 8192)), dim3(256), 0, st, g.row_ptr,
-                     g.col_idx, g.deg, g.adj2, seeds, flagged, flag_count, ef, D);
+hipError_t launch_pass2(const Graph &g, const int32_t *seeds, const uint8_t *fl, int64_t n,
+                        int32_t *listed, int32_t *counts, double *ef, const int64_t *D,
+                        hipStream_t st) {
+  if (n <= 0) return hipSuccess;
+  const bool list = n > kPass2Scan;
+  if (list)
+    hipLaunchKernelGGL(k_flag_compact, dim3(cap_blocks((n + 4095) / 4096, 256)), dim3(1024), 0, st,
+                       fl, n, listed, counts);
+  hipLaunchKernelGGL(k_pass2, dim3(cap_blocks(n, list ? 8192 : 2048)), dim3(256), 0, st, g.row_ptr,
+                     g.col_idx, g.deg, g.adj2, seeds, fl, n, list ? listed : nullptr, counts, ef,
+                     D);
   return hipGetLastError();
 }
 
