@@ -9,6 +9,7 @@
 #include <new>
 #include <numeric>
 #include <string>
+#include <memory>
 #include <vector>
 
 #include "csr_check.h"
@@ -481,22 +482,23 @@ ef_status graph_load(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32
   // one read-back of the control record and the list offsets, one of the tail
   // entries walked at each node by the triangle pass (binning)
   const size_t ptr_stride = (sizeof(int32_t) * N1 + 255) & ~(size_t)255;
-  std::vector<char> h_back(256 + 2 * ptr_stride);
-  std::vector<int64_t> h_work((size_t)n);
+  // (not cleared first: the copies fill them)
+  const std::unique_ptr<char[]> h_back(new char[256 + 2 * ptr_stride]);
+  const std::unique_ptr<int64_t[]> h_work(new int64_t[NN]);
   if (e == hipSuccess)
-    e = hipMemcpyAsync(h_back.data(), g.d_counters, 256 + ptr_stride + sizeof(int32_t) * N1,
+    e = hipMemcpyAsync(h_back.get(), g.d_counters, 256 + ptr_stride + sizeof(int32_t) * N1,
                        hipMemcpyDeviceToHost, stream);
   if (e == hipSuccess && n > 0)
-    e = hipMemcpyAsync(h_work.data(), work, sizeof(int64_t) * (size_t)n, hipMemcpyDeviceToHost,
+    e = hipMemcpyAsync(h_work.get(), work, sizeof(int64_t) * (size_t)n, hipMemcpyDeviceToHost,
                        stream);
   if (e == hipSuccess) e = hipStreamSynchronize(stream);
   if (e != hipSuccess) {
     ef_graph_free(h);
     return after_check([&] { return hip_status(e, "graph preprocessing"); });
   }
-  const int32_t *h_ctl = (const int32_t *)h_back.data();
-  const int32_t *h_up_ptr = (const int32_t *)(h_back.data() + 256);
-  const int32_t *h_dn_ptr = (const int32_t *)(h_back.data() + 256 + ptr_stride);
+  const int32_t *h_ctl = (const int32_t *)h_back.get();
+  const int32_t *h_up_ptr = (const int32_t *)(h_back.get() + 256);
+  const int32_t *h_dn_ptr = (const int32_t *)(h_back.get() + 256 + ptr_stride);
   if (nnz > 0 && (h_ctl[kCtlStop] || h_ctl[kCtlCol])) {
     const bool col_bad = h_ctl[kCtlCol] != 0;
     ef_graph_free(h);
@@ -518,6 +520,7 @@ ef_status graph_load(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32
     }
     e = launch_zero_list(g, tmp, stream);
   }
+  if (e == hipSuccess) e = launch_lane_counts(g, stream);
   // degree-ordered rows, sorted while the host builds the node lists
   std::vector<int32_t> hb;
   if (e == hipSuccess && n_over > 0) {
@@ -537,58 +540,81 @@ ef_status graph_load(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32
     ef_graph_free(h);
     return hip_status(e, "degree-ordered rows");
   }
-  std::vector<int32_t> tri[4], fin, fin_group;
-  std::vector<int4> recL;
+  // (what most nodes are is counted without branches, which their degrees, in
+  // no order, would mispredict: 1.0 ms for 200k nodes with them)
+  std::vector<int32_t> tri[4], fin_tier[3];
+  const std::unique_ptr<int32_t[]> fin_group(new int32_t[NN]);
+  const bool parts = part_off && n_parts > 0;
+  static_assert(kFinLaneMax < kFinGroupMax && kFinGroupMax <= kSmallMax, "tiers by degree");
+  int64_t by_deg[kSmallMax + 2] = {};
   for (int32_t v = 0; v < n; ++v) {
     const int64_t k = g.h_deg[v];
-    const int32_t up = h_up_ptr[v + 1] - h_up_ptr[v];
+    const int32_t up = h_up_ptr[v + 1] - h_up_ptr[v], nd = h_dn_ptr[v + 1] - h_dn_ptr[v];
     inf.clusters += k * (k - 1) / 2;
     inf.sum_sq_degree += k * k;
     inf.wedge_checks += h_work[v];
-    if (k >= 2 && k <= kSmallMax) {
-      g.all_small++;
-      g.all_small_deg[k]++;
-      g.all_pairs_small += k * (k - 1) / 2;
-    } else if (k > kSmallMax && k <= kSuper) {
-      g.all_mid++;
-      g.all_midc[mid_class((int32_t)k)]++;
-      g.all_pairs_mid += k * (k - 1) / 2;
-    } else if (k > kSuper) {
-      const int64_t ns = (k + kSuper - 1) / kSuper;
-      g.all_big++;
-      g.all_tiles += ns * (ns + 1) / 2;
-      g.all_pairs_big += k * (k - 1) / 2;
-      g.all_sblocks += ns;
-    }
-    const int32_t nd = h_dn_ptr[v + 1] - h_dn_ptr[v];
-    if (nd > 0 && up <= kTriLaneM && h_work[v] <= kTriLaneWork && nd <= kTriLaneSegs) {
-      recL.push_back(make_int4(v, h_up_ptr[v], h_dn_ptr[v],
-                               up | (nd << 8) | ((int32_t)h_work[v] << 16)));
-    } else if (nd > 0) {
+    by_deg[std::min<int64_t>(k, kSmallMax + 1)]++;
+    const bool lane = (nd > 0) & (up <= kTriLaneM) & (h_work[v] <= kTriLaneWork) &
+                      (nd <= kTriLaneSegs);  // tri_lane_bin
+    g.n_tri_lane += lane;
+    if ((nd > 0) & !lane) {
       const int bin = (up <= kTriBin0 && h_work[v] <= kTriWaveWork && nd <= kTriWaveSegs) ? 0
                       : up <= kTriBin1                                                  ? 1
                       : up <= kTriBin2                                                  ? 2
                                                                                         : 3;
       tri[bin].push_back(v);
     }
-    if (k > kFinGroupMax) fin.push_back(v);
-    else if (k > kFinLaneMax) fin_group.push_back(v);
+    if (parts && lane) g.h_tri_lane.push_back(v);
+    fin_group[(size_t)g.n_fin_group] = v;
+    g.n_fin_group += (k > kFinLaneMax) & (k <= kFinGroupMax);
+    if (k > kFinGroupMax) fin_tier[k > kFinBlockMin ? 0 : k > kFinHalfMax ? 1 : 2].push_back(v);
+  }
+  for (int64_t k = 2; k <= kSmallMax; ++k) {
+    g.all_small += by_deg[k];
+    g.all_small_deg[k] = by_deg[k];
+    g.all_pairs_small += by_deg[k] * (k * (k - 1) / 2);
+  }
+  for (int32_t v : hb) {  // the nodes of degree > kSmallMax
+    const int64_t k = g.h_deg[v];
+    if (k <= kSuper) {
+      g.all_mid++;
+      g.all_midc[mid_class((int32_t)k)]++;
+      g.all_pairs_mid += k * (k - 1) / 2;
+    } else {
+      const int64_t ns = (k + kSuper - 1) / kSuper;
+      g.all_big++;
+      g.all_tiles += ns * (ns + 1) / 2;
+      g.all_pairs_big += k * (k - 1) / 2;
+      g.all_sblocks += ns;
+    }
   }
   // graph by graph when the nodes are a union of parts (a batch), then
   // longest walks first
   std::vector<int32_t> part;
-  if (part_off && n_parts > 0) {
+  if (parts) {
     part.resize((size_t)n);
     for (int32_t q = 0; q < n_parts; ++q)
       for (int64_t v = part_off[q]; v < part_off[q + 1]; ++v) part[(size_t)v] = q;
   }
   auto part_of = [&](int32_t v) { return part.empty() ? 0 : part[(size_t)v]; };
-  auto by_work = [&](int32_t a, int32_t b) {
-    if (part_of(a) != part_of(b)) return part_of(a) < part_of(b);
-    return h_work[a] != h_work[b] ? h_work[a] > h_work[b] : a < b;
+  // (a list in id order, so part by part: each part by its value, descending,
+  // then by id, as 64-bit keys)
+  std::vector<uint64_t> keys;
+  auto sort_parts = [&](std::vector<int32_t> &l, size_t from, auto value) {
+    for (size_t i = from; i < l.size();) {
+      const int32_t q = part_of(l[i]);
+      keys.clear();
+      const size_t i0 = i;
+      for (; i < l.size() && part_of(l[i]) == q; ++i) {
+        const uint64_t x = (uint64_t)std::min<int64_t>(value(l[i]), UINT32_MAX);
+        keys.push_back((UINT32_MAX - x) << 32 | (uint32_t)l[i]);
+      }
+      std::sort(keys.begin(), keys.end());
+      for (size_t j = 0; j < keys.size(); ++j) l[i0 + j] = (int32_t)(uint32_t)keys[j];
+    }
   };
   for (int bin = 0; bin < 4; ++bin) {
-    std::sort(tri[bin].begin(), tri[bin].end(), by_work);
+    sort_parts(tri[bin], 0, [&](int32_t v) { return h_work[v]; });
     g.n_tri[bin] = (int64_t)tri[bin].size();
   }
   std::vector<int4> rec0(tri[0].size());
@@ -608,30 +634,26 @@ ef_status graph_load(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32
       recB[bin][i] = make_int4(v, h_up_ptr[v], h_dn_ptr[v], m | (nd << 12));
     }
   }
-  g.n_tri_lane = (int64_t)recL.size();
   // tiers by degree (descending), each graph by graph
-  auto fin_tier = [&](int32_t v) {
-    return g.h_deg[v] > kFinBlockMin ? 0 : g.h_deg[v] > kFinHalfMax ? 1 : 2;
-  };
-  std::sort(fin.begin(), fin.end(), [&](int32_t a, int32_t b) {
-    if (fin_tier(a) != fin_tier(b)) return fin_tier(a) < fin_tier(b);
-    if (part_of(a) != part_of(b)) return part_of(a) < part_of(b);
-    return g.h_deg[a] != g.h_deg[b] ? g.h_deg[a] > g.h_deg[b] : a < b;
-  });
+  auto by_degree = [&](int32_t v) { return (int64_t)g.h_deg[v]; };
+  std::vector<int32_t> &fin = fin_tier[0];
+  g.n_fin_hub = (int64_t)fin.size();
+  g.n_fin_half = (int64_t)fin_tier[2].size();
+  sort_parts(fin, 0, by_degree);
+  for (int t = 1; t < 3; ++t) {
+    const size_t from = fin.size();
+    fin.insert(fin.end(), fin_tier[t].begin(), fin_tier[t].end());
+    sort_parts(fin, from, by_degree);
+  }
   g.n_fin = (int64_t)fin.size();
-  for (int32_t v : fin)
-    if (g.h_deg[v] > kFinBlockMin) g.n_fin_hub++;
-    else if (g.h_deg[v] <= kFinHalfMax) g.n_fin_half++;
-  g.n_fin_group = (int64_t)fin_group.size();
-  fin.insert(fin.end(), fin_group.begin(), fin_group.end());
+  fin.insert(fin.end(), fin_group.get(), fin_group.get() + g.n_fin_group);
   if (!part.empty()) {
     // node ids of the lists, for schedules that split them by graph
     g.h_fin = fin;
     for (int bin = 0; bin < 4; ++bin) g.h_tri[bin] = tri[bin];
-    g.h_tri_lane.resize(recL.size());
-    for (size_t i = 0; i < recL.size(); ++i) g.h_tri_lane[i] = recL[i].x;
   }
-  // every list in one block, uploaded by one copy
+  // every list in one block, uploaded by one copy but for the last one, which
+  // the device fills
   {
     struct Piece {
       void **p;
@@ -642,17 +664,18 @@ ef_status graph_load(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32
         {(void **)&g.tri_rec0, rec0.data(), sizeof(int4) * rec0.size()},
         {(void **)&g.tri_recB[1], recB[1].data(), sizeof(int4) * recB[1].size()},
         {(void **)&g.tri_recB[2], recB[2].data(), sizeof(int4) * recB[2].size()},
-        {(void **)&g.tri_recL, recL.data(), sizeof(int4) * recL.size()},
         {(void **)&g.tri_list[1], tri[1].data(), sizeof(int32_t) * tri[1].size()},
         {(void **)&g.tri_list[3], tri[3].data(), sizeof(int32_t) * tri[3].size()},
         {(void **)&g.fin_list, fin.data(), sizeof(int32_t) * fin.size()},
     };
-    size_t total = 0, sum = 0;
+    const size_t lane_bytes = sizeof(int4) * (size_t)g.n_tri_lane;
+    size_t up_bytes = 0, sum = lane_bytes;
     for (const Piece &q : pieces) {
-      total += (q.bytes + 255) & ~(size_t)255;
+      up_bytes += (q.bytes + 255) & ~(size_t)255;
       sum += q.bytes;
     }
-    std::vector<char> all(total);
+    const size_t total = up_bytes + lane_bytes;
+    std::vector<char> all(up_bytes);
     st = dev_alloc(g, &g.lists, total, "node lists", sum);
     if (st != EF_OK) {
       // room after all when the scratch goes (its work has to end first)
@@ -670,8 +693,10 @@ ef_status graph_load(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32
       at += (q.bytes + 255) & ~(size_t)255;
     }
     if (st == EF_OK) {
-      if (total > 0)
-        e = hipMemcpyAsync(g.lists, all.data(), total, hipMemcpyHostToDevice, stream);
+      g.tri_recL = (int4 *)((char *)g.lists + up_bytes);
+      e = launch_lane_recs(g, stream);
+      if (e == hipSuccess && up_bytes > 0)
+        e = hipMemcpyAsync(g.lists, all.data(), up_bytes, hipMemcpyHostToDevice, stream);
       // (the load is complete when it returns; the host vectors go)
       if (e == hipSuccess) e = hipStreamSynchronize(stream);
       if (e != hipSuccess) st = hip_status(e, "upload node lists");

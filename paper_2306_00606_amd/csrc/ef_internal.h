@@ -56,6 +56,9 @@ constexpr int64_t kTriWaveWork = 4096;
 constexpr int kTriLaneM = 16;
 constexpr int64_t kTriLaneWork = 64;
 constexpr int32_t kTriLaneSegs = 64;
+__host__ __device__ inline bool tri_lane_bin(int32_t up, int32_t segments, int64_t walk) {
+  return segments > 0 && up <= kTriLaneM && walk <= kTriLaneWork && segments <= kTriLaneSegs;
+}
 static_assert(kTriLaneM < 256 && kTriLaneSegs < 256 && kTriLaneWork < 65536,
               "lane-bin record packing");
 constexpr int32_t kTriWaveSegs = 256;
@@ -276,6 +279,10 @@ hipError_t launch_graph_prep(Graph &g, int32_t *tmp, int64_t *work, bool validat
 hipError_t launch_big_sort(Graph &g, const int32_t *big, int32_t nbig, int32_t *scratch,
                            int32_t *seg, void *temp, size_t &temp_bytes, hipStream_t st);
 hipError_t launch_zero_list(Graph &g, const int32_t *tmp, hipStream_t st);
+// counts the lane bin's nodes by block of the second, which fills tri_recL
+// (n_tri_lane records)
+hipError_t launch_lane_counts(Graph &g, hipStream_t st);
+hipError_t launch_lane_recs(Graph &g, hipStream_t st);
 hipError_t launch_exclusive_scan_i32(const int32_t *in, int32_t *out, int64_t count,
                                      int32_t *block_tmp, int64_t block_tmp_len, hipStream_t st);
 int64_t scan_tmp_len(int64_t count);

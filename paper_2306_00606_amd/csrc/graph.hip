@@ -265,10 +265,12 @@ __global__ void k_zero_fill(const int32_t *__restrict__ zf, const int32_t *__res
 
 // Per-node sums over a row of entries [ptr[v], ptr[v+1]): 8 lanes per node for
 // rows of up to kRowShort, then a wavefront per longer row, which the
-// wavefronts of the same launch find by a ballot over 64 nodes at a time (a
-// wavefront per node left most lanes without an entry on sparse graphs:
-// sums of BA n = 200k, m = 5 in 36 and 105 us). sum(v, first, stride, lanes)
-// adds its lanes' entries; put(v, lanes) reduces and stores.
+// wavefronts of the same launch find by a ballot over up to 64 nodes at a time
+// (a wavefront per node left most lanes without an entry on sparse graphs:
+// sums of BA n = 200k, m = 5 in 36 and 105 us). The nodes of a ballot are as far
+// apart as there are wavefronts: hubs are often neighbours by id, and 64 of them
+// on one wavefront took that graph's k_asum to 170 us and k_qa to 272 (now 20).
+// sum(v, on, first, lanes) adds its lanes' entries, reduces and stores.
 constexpr int32_t kRowShort = 128;
 
 template <typename Sum>
@@ -283,13 +285,14 @@ __device__ __forceinline__ void for_rows(const int32_t *__restrict__ ptr, int32_
     sum((int32_t)(v < n ? v : 0), len <= kRowShort, sub, 8);
   }
   const int lane = threadIdx.x & 63;
-  for (int64_t v0 = (tid >> 6) * 64; v0 < n; v0 += nth) {
-    const int64_t v = v0 + lane;
+  const int64_t nw = nth >> 6;
+  for (int64_t v0 = tid >> 6; v0 < n; v0 += 64 * nw) {
+    const int64_t v = v0 + lane * nw;
     unsigned long long m = __ballot(v < n && ptr[v + 1] - ptr[v] > kRowShort);
     while (m != 0ull) {
       const int j = __builtin_ctzll(m);
       m &= m - 1ull;
-      sum((int32_t)(v0 + j), true, lane, 64);
+      sum((int32_t)(v0 + j * nw), true, lane, 64);
     }
   }
 }
@@ -306,6 +309,7 @@ __global__ void k_dn_work(const int32_t *__restrict__ dn_ptr, const int4 *__rest
   for_rows(dn_ptr, n, [&](int32_t v, bool on, int first, int lanes) {
     int64_t acc = 0;
     if (on)
+#pragma unroll 4
       for (int32_t i = dn_ptr[v] + first; i < dn_ptr[v + 1]; i += lanes) acc += dn[i].y;
     acc = lanes_sum(acc, lanes);
     if (on && first == 0) work[v] = acc;
@@ -323,6 +327,7 @@ __global__ void k_qa(const int32_t *__restrict__ row_ptr, const int2 *__restrict
     int64_t q = 0, a2 = 0;
     double c3 = 0.0, c4 = 0.0;
     if (on)
+#pragma unroll 4
       for (int32_t e = row_ptr[v] + first; e < row_ptr[v + 1]; e += lanes) {
         const int2 ad = adj2[e];
         q += (int64_t)ad.y * ad.y;
@@ -349,6 +354,7 @@ __global__ void k_asum(const int32_t *__restrict__ row_ptr, const int2 *__restri
   for_rows(row_ptr, n, [&](int32_t v, bool on, int first, int lanes) {
     int64_t acc = 0;
     if (on)
+#pragma unroll 4
       for (int32_t e = row_ptr[v] + first; e < row_ptr[v + 1]; e += lanes) acc += adj2[e].y;
     acc = lanes_sum(acc, lanes);
     if (on && first == 0) asum[v] = acc;
@@ -541,6 +547,74 @@ hipError_t launch_graph_prep(Graph &g, int32_t *tmp, int64_t *work, bool validat
     (void)hipMemsetAsync(g.nbm, 0, sizeof(NbrMoments) * (size_t)g.n, st);
     (void)hipMemsetAsync(work, 0, sizeof(int64_t) * (size_t)g.n, st);
   }
+  return hipGetLastError();
+}
+
+// Records of the triangle pass's lane bin, in id order (tri_lane_bin has the
+// rule). Each workgroup owns a contiguous range of nodes; pass 0 counts the
+// bin's nodes in it (more than one workgroup), pass 1 starts from the counts of
+// those before and writes. Bound by the walk's loads on 48 workgroups (BA n = 200k,
+// m = 5: 73 us each; the counts run while the host builds the other lists).
+// Built by the host and uploaded, the 190k records took 0.1 ms more.
+constexpr int kLaneBlocks = 48;  // counts fit the control record
+constexpr int kLaneOneBlock = 4096;
+template <int PASS>
+__global__ __launch_bounds__(1024) void k_lane_recs(const int32_t *__restrict__ up_ptr,
+                                                    const int32_t *__restrict__ dn_ptr,
+                                                    const int4 *__restrict__ dn, int32_t n,
+                                                    int32_t *__restrict__ counts,
+                                                    int4 *__restrict__ recs) {
+  __shared__ int32_t wsum[16];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int32_t per = (int32_t)(((int64_t)n + gridDim.x - 1) / gridDim.x);
+  const int64_t lo = blockIdx.x * (int64_t)per, hi = lo + per < n ? lo + per : n;
+  int32_t run = 0;
+  if constexpr (PASS == 1)
+    for (unsigned i = 0; i < blockIdx.x; ++i) run += counts[i];
+  for (int64_t v0 = lo; v0 < hi; v0 += 1024) {
+    const int64_t v = v0 + tid;
+    int32_t u0 = 0, d0 = 0, up = 0, nd = 0, walk = 0;
+    if (v < hi) {
+      u0 = up_ptr[v];
+      d0 = dn_ptr[v];
+      up = up_ptr[v + 1] - u0;
+      nd = dn_ptr[v + 1] - d0;
+      if (nd <= kTriLaneSegs && up <= kTriLaneM)
+#pragma unroll 4
+        for (int32_t i = 0; i < nd; ++i) walk += dn[d0 + i].y;
+    }
+    const bool in = v < hi && tri_lane_bin(up, nd, walk);
+    const unsigned long long m = __ballot(in);
+    if (lane == 0) wsum[wv] = __popcll(m);
+    __syncthreads();
+    int32_t pre = 0, tot = 0;
+    for (int i = 0; i < 16; ++i) {
+      if (i < wv) pre += wsum[i];
+      tot += wsum[i];
+    }
+    if (PASS == 1 && in)
+      recs[run + pre + __popcll(m & ((1ull << lane) - 1))] =
+          make_int4((int32_t)v, u0, d0, up | (nd << 8) | (walk << 16));
+    run += tot;
+    __syncthreads();
+  }
+  if (PASS == 0 && tid == 0) counts[blockIdx.x] = run;
+}
+
+static_assert(kCtlWords + kLaneBlocks <= 64, "the record and the counts share d_counters");
+static int lane_blocks(const Graph &g) { return g.n <= kLaneOneBlock ? 1 : kLaneBlocks; }
+
+hipError_t launch_lane_counts(Graph &g, hipStream_t st) {
+  if (g.nnz <= 0 || lane_blocks(g) == 1) return hipSuccess;
+  hipLaunchKernelGGL(k_lane_recs<0>, dim3(lane_blocks(g)), dim3(1024), 0, st, g.up_ptr, g.dn_ptr,
+                     g.dn, g.n, g.d_counters + kCtlWords, nullptr);
+  return hipGetLastError();
+}
+
+hipError_t launch_lane_recs(Graph &g, hipStream_t st) {
+  if (g.n_tri_lane <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_lane_recs<1>, dim3(lane_blocks(g)), dim3(1024), 0, st, g.up_ptr, g.dn_ptr,
+                     g.dn, g.n, g.d_counters + kCtlWords, g.tri_recL);
   return hipGetLastError();
 }
 
