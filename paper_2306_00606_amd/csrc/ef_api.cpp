@@ -474,11 +474,6 @@ ef_status graph_load(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32
                          hipMemcpyHostToDevice, stream);
   }
   if (e == hipSuccess) e = launch_graph_prep(g, tmp, work, validate, stream);
-  // the reverse-sum index starts as rev; the rows of mid and big centres remap
-  // it below
-  if (e == hipSuccess && nnz > 0)
-    e = hipMemcpyAsync(g.rrev, g.rev, sizeof(int32_t) * (size_t)nnz, hipMemcpyDeviceToDevice,
-                       stream);
   // one read-back of the control record and the list offsets, one of the tail
   // entries walked at each node by the triangle pass (binning)
   const size_t ptr_stride = (sizeof(int32_t) * N1 + 255) & ~(size_t)255;

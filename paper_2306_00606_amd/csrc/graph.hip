@@ -30,18 +30,6 @@ __device__ __forceinline__ bool rank_less(int32_t a, int32_t ka, int32_t b, int3
 // triangle slots to clear. Kernels that index by neighbour ids leave when
 // kCtlCol is set, those after the gate when kCtlStop is, so the host reads the
 // outcome once, at the end.
-__global__ void k_ctl_clear(int32_t *__restrict__ ctl) { ctl[threadIdx.x] = 0; }
-
-__global__ void k_check_cols(const int32_t *__restrict__ col, int64_t nnz, int32_t n,
-                             int32_t *__restrict__ ctl) {
-  bool bad = false;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < nnz;
-       e += (int64_t)gridDim.x * blockDim.x)
-    bad |= (uint32_t)col[e] >= (uint32_t)n;
-  // one atomic per wavefront that saw a bad id
-  if (__ballot(bad) && (threadIdx.x & 63) == 0) atomicOr(&ctl[kCtlCol], 1);
-}
-
 // a simple symmetric graph has exactly nnz / 2 up-arcs: the up-arc arrays are
 // sized for that many
 __global__ void k_gate(int32_t *__restrict__ ctl, const int32_t *__restrict__ up_total,
@@ -55,16 +43,21 @@ __global__ void k_ctl_zero_total(int32_t *__restrict__ ctl, const int32_t *__res
   ctl[kCtlZero] = *total;
 }
 
+// degrees; clears the control record
 __global__ void k_degree(const int32_t *__restrict__ row_ptr, int32_t n,
-                         int32_t *__restrict__ deg) {
+                         int32_t *__restrict__ deg, int32_t *__restrict__ ctl) {
+  if (blockIdx.x == 0 && threadIdx.x < 64) ctl[threadIdx.x] = 0;
   for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n;
        v += (int64_t)gridDim.x * blockDim.x)
     deg[v] = row_ptr[v + 1] - row_ptr[v];
 }
 
-// src[e] = the row that holds arc e (binary search over row_ptr).
-__global__ void k_arc_src(const int32_t *__restrict__ row_ptr, int32_t n, int64_t nnz,
-                          int32_t *__restrict__ src) {
+// src[e] = the row that holds arc e (binary search over row_ptr); checks the
+// neighbour ids.
+__global__ void k_arc_src(const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
+                          int32_t n, int64_t nnz, int32_t *__restrict__ src,
+                          int32_t *__restrict__ ctl) {
+  bool bad = false;
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < nnz;
        e += (int64_t)gridDim.x * blockDim.x) {
     int32_t lo = 0, hi = n;  // find largest v with row_ptr[v] <= e
@@ -73,14 +66,17 @@ __global__ void k_arc_src(const int32_t *__restrict__ row_ptr, int32_t n, int64_
       if (row_ptr[mid] <= e) lo = mid; else hi = mid;
     }
     src[e] = lo;
+    bad |= (uint32_t)col[e] >= (uint32_t)n;
   }
+  // one atomic per wavefront that saw a bad id
+  if (__ballot(bad) && (threadIdx.x & 63) == 0) atomicOr(&ctl[kCtlCol], 1);
 }
 
 __global__ void k_arc_rev(const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
                           const int32_t *__restrict__ src, const int32_t *__restrict__ deg,
-                          int64_t nnz, int32_t *__restrict__ rev, int2 *__restrict__ adj2,
-                          int32_t *__restrict__ upflag, int32_t *__restrict__ ctl,
-                          bool validate) {
+                          int64_t nnz, int32_t *__restrict__ rev, int32_t *__restrict__ rrev,
+                          int2 *__restrict__ adj2, int32_t *__restrict__ upflag,
+                          int32_t *__restrict__ ctl, bool validate) {
   if (ctl[kCtlCol]) return;
   bool bad = false;
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < nnz;
@@ -94,7 +90,9 @@ __global__ void k_arc_rev(const int32_t *__restrict__ row_ptr, const int32_t *__
     // on a valid (symmetric) graph the reverse arc is always found; keep the
     // index inside the row otherwise
     const bool found = lo < row_ptr[a + 1] && col[lo] == s;
-    rev[e] = found ? lo : (int32_t)e;
+    const int32_t r = found ? lo : (int32_t)e;
+    rev[e] = r;
+    rrev[e] = r;  // until the rows of mid and big centres remap it
     // (in ascending rows the search finds every reverse arc there is; a row
     // out of order is bad by itself)
     bad |= !found || a == s || (e > row_ptr[s] && col[e - 1] >= a);
@@ -164,13 +162,16 @@ __global__ void k_up_sort(const int32_t *__restrict__ src, const int2 *__restric
   }
 }
 
+// slots and up_col in the new order
 __global__ void k_tslot_remap(int32_t *__restrict__ tslot, const int32_t *__restrict__ perm,
-                              int64_t nnz,
-    const int32_t *__restrict__ ctl) {
+                              int64_t nnz, const int32_t *__restrict__ newcol,
+                              int32_t *__restrict__ up_col, const int32_t *__restrict__ ctl) {
   if (ctl[kCtlStop]) return;
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < nnz;
-       e += (int64_t)gridDim.x * blockDim.x)
+       e += (int64_t)gridDim.x * blockDim.x) {
     tslot[e] = perm[tslot[e]];
+    if (e < nnz / 2) up_col[e] = newcol[e];
+  }
 }
 
 // Segments: a down-arc w -> u (rank(u) < rank(w)) with a non-empty tail of
@@ -269,7 +270,8 @@ __global__ void k_zero_fill(const int32_t *__restrict__ zf, const int32_t *__res
 // (a wavefront per node left most lanes without an entry on sparse graphs:
 // sums of BA n = 200k, m = 5 in 36 and 105 us). The nodes of a ballot are as far
 // apart as there are wavefronts: hubs are often neighbours by id, and 64 of them
-// on one wavefront took that graph's k_asum to 170 us and k_qa to 272 (now 20).
+// on one wavefront took that graph's degree sums to 170 us and k_qa to 272 (now
+// 20 each).
 // sum(v, on, first, lanes) adds its lanes' entries, reduces and stores.
 constexpr int32_t kRowShort = 128;
 
@@ -301,9 +303,11 @@ template <typename V> __device__ __forceinline__ V lanes_sum(V x, int lanes) {
   return x;
 }
 
-// tail entries walked at w (sum of its segment lengths)
+// tail entries walked at w (sum of its segment lengths), and the sum of its
+// neighbours' degrees
 __global__ void k_dn_work(const int32_t *__restrict__ dn_ptr, const int4 *__restrict__ dn,
-                          int32_t n, int64_t *__restrict__ work,
+                          const int32_t *__restrict__ row_ptr, const int2 *__restrict__ adj2,
+                          int32_t n, int64_t *__restrict__ work, int64_t *__restrict__ asum,
                           const int32_t *__restrict__ ctl) {
   if (ctl[kCtlStop]) return;
   for_rows(dn_ptr, n, [&](int32_t v, bool on, int first, int lanes) {
@@ -313,6 +317,14 @@ __global__ void k_dn_work(const int32_t *__restrict__ dn_ptr, const int4 *__rest
       for (int32_t i = dn_ptr[v] + first; i < dn_ptr[v + 1]; i += lanes) acc += dn[i].y;
     acc = lanes_sum(acc, lanes);
     if (on && first == 0) work[v] = acc;
+  });
+  for_rows(row_ptr, n, [&](int32_t v, bool on, int first, int lanes) {
+    int64_t acc = 0;
+    if (on)
+#pragma unroll 4
+      for (int32_t e = row_ptr[v] + first; e < row_ptr[v + 1]; e += lanes) acc += adj2[e].y;
+    acc = lanes_sum(acc, lanes);
+    if (on && first == 0) asum[v] = acc;
   });
 }
 
@@ -344,20 +356,6 @@ __global__ void k_qa(const int32_t *__restrict__ row_ptr, const int2 *__restrict
       qa[v] = make_longlong2(q, a2);
       nbm[v] = NbrMoments{asum[v], q, c3, c4};
     }
-  });
-}
-
-// sum of neighbour degrees
-__global__ void k_asum(const int32_t *__restrict__ row_ptr, const int2 *__restrict__ adj2,
-                       int32_t n, int64_t *__restrict__ asum, const int32_t *__restrict__ ctl) {
-  if (ctl[kCtlStop]) return;
-  for_rows(row_ptr, n, [&](int32_t v, bool on, int first, int lanes) {
-    int64_t acc = 0;
-    if (on)
-#pragma unroll 4
-      for (int32_t e = row_ptr[v] + first; e < row_ptr[v + 1]; e += lanes) acc += adj2[e].y;
-    acc = lanes_sum(acc, lanes);
-    if (on && first == 0) asum[v] = acc;
   });
 }
 
@@ -441,12 +439,53 @@ __global__ void k_scan_apply(const int32_t *__restrict__ in, int64_t count,
   }
 }
 
+// The scan of up to kScanOne values by one workgroup: a launch in place of three
+// (a new graph of 8000 arcs runs three scans).
+constexpr int64_t kScanOne = 16 * kScanTile;
+__global__ __launch_bounds__(1024) void k_scan_one(const int32_t *__restrict__ in, int64_t count,
+                                                   int32_t *__restrict__ out,
+                                                   int32_t *__restrict__ total) {
+  __shared__ int32_t sh[16];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  int32_t carry = 0;
+  for (int64_t base = 0; base < count; base += 1024 * kScanItems) {
+    const int64_t i0 = base + (int64_t)threadIdx.x * kScanItems;
+    int32_t v[kScanItems], s = 0;
+    for (int i = 0; i < kScanItems; ++i) {
+      v[i] = i0 + i < count ? in[i0 + i] : 0;
+      s += v[i];
+    }
+    int32_t incl = s;
+    for (int off = 1; off < 64; off <<= 1) {
+      const int32_t y = __shfl_up(incl, off, 64);
+      if (lane >= off) incl += y;
+    }
+    if (lane == 63) sh[w] = incl;
+    __syncthreads();
+    int32_t run = carry + incl - s;
+    for (int i = 0; i < 16; ++i) {
+      if (i < w) run += sh[i];
+      carry += sh[i];
+    }
+    __syncthreads();
+    for (int i = 0; i < kScanItems; ++i) {
+      if (i0 + i < count) out[i0 + i] = run;
+      run += v[i];
+    }
+  }
+  if (threadIdx.x == 0) *total = carry;
+}
+
 hipError_t launch_exclusive_scan_i32(const int32_t *in, int32_t *out, int64_t count,
                                      int32_t *block_tmp, int64_t block_tmp_len,
                                      hipStream_t st) {
   if (count <= 0) return hipSuccess;
   const int64_t nb = (count + kScanTile - 1) / kScanTile;
   if (block_tmp_len < nb + 1) return hipErrorInvalidValue;
+  if (count <= kScanOne) {
+    hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(1024), 0, st, in, count, out, block_tmp + nb);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_scan_totals, dim3((unsigned)nb), dim3(kScanThreads), 0, st, in, count,
                      block_tmp);
   hipLaunchKernelGGL(k_scan_totals_single, dim3(1), dim3(kScanThreads), 0, st, block_tmp, nb);
@@ -478,19 +517,16 @@ hipError_t launch_graph_prep(Graph &g, int32_t *tmp, int64_t *work, bool validat
                              hipStream_t st) {
   const int T = 256;
   int32_t *ctl = g.d_counters;
-  hipLaunchKernelGGL(k_ctl_clear, dim3(1), dim3(64), 0, st, ctl);
-  hipLaunchKernelGGL(k_degree, dim3(grid_for(g.n, T)), dim3(T), 0, st, g.row_ptr, g.n, g.deg);
+  hipLaunchKernelGGL(k_degree, dim3(grid_for(g.n, T)), dim3(T), 0, st, g.row_ptr, g.n, g.deg, ctl);
   if (g.nnz > 0) {
     const int64_t nnz = g.nnz, nup = nnz / 2;
     int32_t *upflag = tmp, *upidx = tmp + nnz, *G = tmp + 2 * nnz, *dnflag = tmp + 3 * nnz,
             *perm = tmp + 4 * nnz, *scan_tmp = tmp + 4 * nnz + nup;
     const int64_t sl = scan_tmp_len(nnz);
-    hipLaunchKernelGGL(k_check_cols, dim3(grid_for((nnz + 3) / 4, T)), dim3(T), 0, st, g.col_idx,
-                       nnz, g.n, ctl);
-    hipLaunchKernelGGL(k_arc_src, dim3(grid_for(nnz, T)), dim3(T), 0, st, g.row_ptr, g.n, nnz,
-                       g.src);
+    hipLaunchKernelGGL(k_arc_src, dim3(grid_for(nnz, T)), dim3(T), 0, st, g.row_ptr, g.col_idx,
+                       g.n, nnz, g.src, ctl);
     hipLaunchKernelGGL(k_arc_rev, dim3(grid_for(nnz, T)), dim3(T), 0, st, g.row_ptr,
-                       g.col_idx, g.src, g.deg, nnz, g.rev, g.adj2, upflag, ctl, validate);
+                       g.col_idx, g.src, g.deg, nnz, g.rev, g.rrev, g.adj2, upflag, ctl, validate);
     hipError_t e = launch_exclusive_scan_i32(upflag, upidx, nnz, scan_tmp, sl, st);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_gate, dim3(1), dim3(1), 0, st, ctl, scan_tmp + scan_blocks(nnz), nnz,
@@ -504,11 +540,8 @@ hipError_t launch_graph_prep(Graph &g, int32_t *tmp, int64_t *work, bool validat
                        upk, ctl);
     hipLaunchKernelGGL(k_up_sort, dim3(grid_for(nnz, T)), dim3(T), 0, st, g.src, g.adj2,
                        upflag, upidx, nnz, g.up_ptr, g.up_col, upk, newcol, g.up_deg, perm, ctl);
-    e = hipMemcpyAsync(g.up_col, newcol, sizeof(int32_t) * (size_t)nup, hipMemcpyDeviceToDevice,
-                       st);
-    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_tslot_remap, dim3(grid_for(nnz, T)), dim3(T), 0, st, g.trec, perm,
-                       nnz, ctl);
+                       nnz, newcol, g.up_col, ctl);
     // segments of the triangle pass
     int32_t *dnidx = G;
     hipLaunchKernelGGL(k_dn_flag, dim3(grid_for(nnz, T)), dim3(T), 0, st, g.src, g.col_idx,
@@ -519,7 +552,7 @@ hipError_t launch_graph_prep(Graph &g, int32_t *tmp, int64_t *work, bool validat
                        g.col_idx, g.deg, g.trec, g.up_ptr, dnflag, dnidx, g.n, nnz, g.dn,
                        g.dn_ptr, ctl);
     hipLaunchKernelGGL(k_dn_work, dim3(grid_for((int64_t)g.n * 8, T)), dim3(T), 0, st,
-                       g.dn_ptr, g.dn, g.n, work, ctl);
+                       g.dn_ptr, g.dn, g.row_ptr, g.adj2, g.n, work, g.asum, ctl);
     // slots cleared before each pass (long lists), then their scan
     int32_t *zf = G, *zidx = upidx;
     hipLaunchKernelGGL(k_zero_flag, dim3(grid_for(nnz, T)), dim3(T), 0, st, g.src, upflag,
@@ -531,8 +564,6 @@ hipError_t launch_graph_prep(Graph &g, int32_t *tmp, int64_t *work, bool validat
     // tslot becomes the per-arc triangle record index
     hipLaunchKernelGGL(k_trec, dim3(grid_for(nnz, T)), dim3(T), 0, st, g.col_idx, g.rev, upflag,
                        g.dn_ptr, dnflag, nnz, nup, g.trec, ctl);
-    hipLaunchKernelGGL(k_asum, dim3(grid_for((int64_t)g.n * 8, T)), dim3(T), 0, st,
-                       g.row_ptr, g.adj2, g.n, g.asum, ctl);
     hipLaunchKernelGGL(k_qa, dim3(grid_for((int64_t)g.n * 8, T)), dim3(T), 0, st, g.row_ptr,
                        g.adj2, g.asum, g.n, g.qa, g.nbm, ctl);
   } else {
