@@ -151,13 +151,6 @@ extern "C" ef_status ef_batch_free(ef_batch *b) {
   for (hipEvent_t e : {b->ev_in, b->ev_out, b->t0, b->t1})
     if (e) (void)hipEventDestroy(e);
   if (b->own) (void)hipStreamDestroy(b->own);
-  if (b->g)
-    for (int i = 0; i < 2; ++i) {
-      Graph &g = b->g->g;
-      if (g.side[i]) (void)hipStreamDestroy(g.side[i]);
-      for (hipEvent_t e : {g.side_fork[i], g.side_join[i]})
-        if (e) (void)hipEventDestroy(e);
-    }
   if (b->g) ef_graph_free(b->g);
   delete b;
   return EF_OK;
@@ -211,11 +204,7 @@ extern "C" ef_status ef_batch_create(int32_t n_graphs, const int32_t *node_off, 
     return s;
   }
   hipError_t e = hipStreamCreateWithFlags(&b->own, hipStreamNonBlocking);
-  Graph &g = b->g->g;
-  for (hipStream_t *st : {&g.side[0], &g.side[1]})
-    if (e == hipSuccess) e = hipStreamCreateWithFlags(st, hipStreamNonBlocking);
-  for (hipEvent_t *ev : {&b->ev_in, &b->ev_out, &g.side_fork[0], &g.side_fork[1], &g.side_join[0],
-                         &g.side_join[1]})
+  for (hipEvent_t *ev : {&b->ev_in, &b->ev_out})
     if (e == hipSuccess) e = hipEventCreateWithFlags(ev, hipEventDisableTiming);
   for (hipEvent_t *ev : {&b->t0, &b->t1})
     if (e == hipSuccess) e = hipEventCreate(ev);
@@ -521,7 +510,7 @@ extern "C" ef_status ef_batch_autotune(ef_batch *b, ef_prec prec) {
   ef_status s = EF_OK;
   // phased design: small-bin thresholds. The candidates' centres share one
   // launch, so the best of them differ by no more than two timings of one do (on
-  // 64 graphs of 1000 to 20000 nodes 0 to 3%, the others 5 to 110%), and the last
+  // 64 graphs of 1000 to 20000 nodes 0 to 3%, the others 4 to 110%), and the last
   // bits of FP32C results follow the choice: kTuneFirst, unless one is clearly
   // faster
   TuneEntry best{g.thr, 0, 0, 0};

@@ -1153,26 +1153,6 @@ extern "C" ef_status ef_compute(ef_graph *h, ef_algo algo, ef_prec prec, const i
   if (prec == EF_PREC_FP64 && eager && (s = score_table(g, st)) != EF_OK) return s;
   const bool tab = eager || replay_own;
   prof.mark(0);
-  // On a batch's handle what does not need each other runs side by side: the
-  // triangle pass, the pairs of larger centres and those of the others. Each of
-  // these kernels leaves part of the chip idle (64 graphs of 1000 to 20000
-  // nodes: 225 us one after the other, 140 so). A profiled call times them one
-  // by one; other handles stay on the caller's stream: a stream of their own
-  // costs 0.5 ms at first use, and at R-MAT scale 22 takes 2% off a call.
-  const bool fork = g.side[0] && !per_seed && !prof.on;
-  auto branch = [&](int i) {
-    hipError_t r = hipEventRecord(g.side_fork[i], st);
-    return r == hipSuccess ? hipStreamWaitEvent(g.side[i], g.side_fork[i], 0) : r;
-  };
-  auto join = [&](int i) {
-    hipError_t r = hipEventRecord(g.side_join[i], g.side[i]);
-    return r == hipSuccess ? hipStreamWaitEvent(st, g.side_join[i], 0) : r;
-  };
-  if (fork) {
-    e = branch(0);
-    if (e == hipSuccess) e = launch_triangles(g, prec, ws_Y, ws_Z, ws_ZT, g.side[0]);
-    if (e != hipSuccess) return hip_status(e, "triangle pass");
-  }
   if (!reuse) {
     e = launch_bin_centres(g, centres, n_work, b, st);
     if (e != hipSuccess) return hip_status(e, "binning");
@@ -1181,15 +1161,12 @@ extern "C" ef_status ef_compute(ef_graph *h, ef_algo algo, ef_prec prec, const i
   g.bins_thr = b.thr;
   g.bins_buf = g.ws[WS_BINS].p;
   prof.mark(1);
-  e = fork ? branch(1) : hipSuccess;
-  if (e == hipSuccess)
-    e = launch_pairs(g, prec, b, ws_R, ws + L.rec, st, fork ? g.side[1] : st, tab, prof.ev(2),
-                     prof.ev(3), prof.ev(4), algo == EF_ALGO_CLUSTER_AGG ? b.agg_done : nullptr);
-  if (e == hipSuccess && fork) e = join(1);
+  e = launch_pairs(g, prec, b, ws_R, ws + L.rec, st, tab, prof.ev(2), prof.ev(3), prof.ev(4),
+                   algo == EF_ALGO_CLUSTER_AGG ? b.agg_done : nullptr);
   if (e != hipSuccess) return hip_status(e, "pair loop");
   prof.mark(5);
   if (!per_seed) {
-    e = fork ? join(0) : launch_triangles(g, prec, ws_Y, ws_Z, ws_ZT, st);
+    e = launch_triangles(g, prec, ws_Y, ws_Z, ws_ZT, st);
     if (e != hipSuccess) return hip_status(e, "triangle pass");
     prof.mark(6);
     e = launch_finalize_cluster(g, prec, ws_R, ws_Y, ws_Z, ws_ZT, ef_w, D_w, N_w, flag_bytes,

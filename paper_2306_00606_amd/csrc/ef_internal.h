@@ -232,10 +232,6 @@ struct Graph {
   // workspace (grow-only, reused across calls)
   DevBuf ws[16];
   bool main_reserved = false;  // WS_MAIN holds the load's scratch, kept for the first ef_compute
-  // batches: streams beside the caller's for the triangle pass [0] and for the
-  // larger centres' pairs [1], and the events that fork and join them
-  hipStream_t side[2] = {nullptr, nullptr};
-  hipEvent_t side_fork[2] = {nullptr, nullptr}, side_join[2] = {nullptr, nullptr};
   // events for EF_PROFILE
   hipEvent_t ev[16] = {};
   bool ev_ready = false;
@@ -323,15 +319,14 @@ hipError_t launch_bin_centres(const Graph &g, const int32_t *centres, int32_t n_
 // pair loop: writes R (per arc, base cluster scores without triangle
 // correction) for the arcs of every centre in the bins; big centres go via
 // super-tile records and a per-arc reduction.
-// st_large: the stream of the larger centres' kernels (degree > 256 and, in
-// FP64, > 64), st or a branch of it. tab: FP64 scores from the graph's table.
+// tab: FP64 scores from the graph's table.
 // ev_small / ev_mid / ev_big (nullable) are recorded after the small, mid and
 // super-tile kernels.
 // agg_done (nullable, one int per big centre): the degree-class aggregated
 // variant writes R of big centres directly (1), leaving centres with too many
 // distinct neighbour degrees (0) to the super-tile path.
 hipError_t launch_pairs(const Graph &g, ef_prec prec, const Bins &b, void *R, void *records,
-                        hipStream_t st, hipStream_t st_large, bool tab, hipEvent_t ev_small,
+                        hipStream_t st, bool tab, hipEvent_t ev_small,
                         hipEvent_t ev_mid, hipEvent_t ev_big, int32_t *agg_done = nullptr);
 
 // t[i] = i log i for i < n (0 at 0)

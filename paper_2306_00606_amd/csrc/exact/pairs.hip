@@ -1327,7 +1327,7 @@ hipError_t launch_bin_centres(const Graph &g, const int32_t *centres, int32_t n_
 
 template <typename T>
 static hipError_t pairs_impl(const Graph &g, const Bins &b, void *R, void *records,
-                             hipStream_t st, hipStream_t st_large, bool tab, hipEvent_t ev_small,
+                             hipStream_t st, bool tab, hipEvent_t ev_small,
                              hipEvent_t ev_mid, hipEvent_t ev_big, int32_t *agg_done) {
   static_assert(kSmallLaneMax == 8, "bin 0 holds centres of degree <= 8, one lane each");
   constexpr bool kFp64 = std::is_same<T, double>::value;
@@ -1352,7 +1352,7 @@ static hipError_t pairs_impl(const Graph &g, const Bins &b, void *R, void *recor
   if constexpr (kFp64) {
     const int64_t items = b.n_midc[2] + (b.n_midc[1] + 1) / 2 + (b.n_midc[0] + 3) / 4;
     if (items > 0)
-      hipLaunchKernelGGL(k_pairs_mid_tab, dim3(capped(items, kCUs)), dim3(1024), 0, st_large,
+      hipLaunchKernelGGL(k_pairs_mid_tab, dim3(capped(items, kCUs)), dim3(1024), 0, st,
                          g.row_ptr, g.deg, g.adjs, b.midc[0], b.n_midc[0], b.midc[1], b.n_midc[1],
                          b.midc[2], b.n_midc[2], R, st64);
   } else {
@@ -1364,18 +1364,18 @@ static hipError_t pairs_impl(const Graph &g, const Bins &b, void *R, void *recor
                        st, g.row_ptr, g.deg, g.adjs, b.midc[1], b.n_midc[1], R);
   if (b.n_midc[2] > 0)
     hipLaunchKernelGGL((k_pairs_mid<T, 16>), dim3(capped(b.n_midc[2], 1 << 20)), dim3(1024), 0,
-                       st_large, g.row_ptr, g.deg, g.adjs, b.midc[2], b.n_midc[2], R);
+                       st, g.row_ptr, g.deg, g.adjs, b.midc[2], b.n_midc[2], R);
   }
   if (ev_mid) (void)hipEventRecord(ev_mid, st);
   if (agg_done && b.n_big > 0)
-    hipLaunchKernelGGL(k_pairs_agg<T>, dim3(capped(b.n_big, 1 << 16)), dim3(1024), 0, st_large,
+    hipLaunchKernelGGL(k_pairs_agg<T>, dim3(capped(b.n_big, 1 << 16)), dim3(1024), 0, st,
                        g.row_ptr, g.deg, g.adjs, b.big, b.counters, agg_done, R);
   if (b.n_tiles > 0)
-    hipLaunchKernelGGL(k_pairs_big<T>, dim3(capped(b.n_tiles, 1 << 20)), dim3(1024), 0, st_large,
+    hipLaunchKernelGGL(k_pairs_big<T>, dim3(capped(b.n_tiles, 1 << 20)), dim3(1024), 0, st,
                        g.row_ptr, g.deg, g.adjs, b.big, b.tiles, b.n_tiles, records, agg_done, st64);
   if (ev_big) (void)hipEventRecord(ev_big, st);
   if (b.n_sblocks > 0)
-    hipLaunchKernelGGL(k_arc_reduce<T>, dim3(capped(b.n_sblocks, 1 << 20)), dim3(256), 0, st_large,
+    hipLaunchKernelGGL(k_arc_reduce<T>, dim3(capped(b.n_sblocks, 1 << 20)), dim3(256), 0, st,
                        g.row_ptr, g.deg, g.adjs, b.big, b.sblocks, b.n_sblocks, records, R,
                        agg_done);
   return hipGetLastError();
@@ -1387,12 +1387,12 @@ hipError_t launch_score_table(double *t, int32_t n, hipStream_t st) {
 }
 
 hipError_t launch_pairs(const Graph &g, ef_prec prec, const Bins &b, void *R, void *records,
-                        hipStream_t st, hipStream_t st_large, bool tab, hipEvent_t ev_small,
+                        hipStream_t st, bool tab, hipEvent_t ev_small,
                         hipEvent_t ev_mid, hipEvent_t ev_big, int32_t *agg_done) {
   if (prec == EF_PREC_FP64)
-    return pairs_impl<double>(g, b, R, records, st, st_large, tab, ev_small, ev_mid, ev_big,
+    return pairs_impl<double>(g, b, R, records, st, tab, ev_small, ev_mid, ev_big,
                               agg_done);
-  return pairs_impl<float>(g, b, R, records, st, st_large, tab, ev_small, ev_mid, ev_big,
+  return pairs_impl<float>(g, b, R, records, st, tab, ev_small, ev_mid, ev_big,
                            agg_done);
 }
 

@@ -1,5 +1,5 @@
 """Replays of captured whole-graph calls (needs an MI355X): a batch's own graph,
-whose triangle pass and larger centres run on branches, over graphs that have
+which reads the work lists kept before its capture, over graphs that have
 centres and triangle nodes of every bin; and a graph that the caller captures,
 which must not depend on what the handle builds or drops between replays."""
 import numpy as np
@@ -18,7 +18,7 @@ REL = {"fp64": 1e-9, "fp32c": 1e-5}
     [gen.rmat(12, 16, 3, perm_seed=1), gen.barabasi_albert(5000, 4, 2), gen.erdos_renyi(7, 0.5, 1)],
     [gen.erdos_renyi(400, 0.004, 5), gen.erdos_renyi(2, 0.9, 6)],  # no centre above the small bins
 ])
-def test_batch_branches(graphs, prec):
+def test_batch_kept_lists(graphs, prec):
     torch = pytest.importorskip("torch")
     want = [np.concatenate(x) for x in zip(*(oracle.ef(rp, ci, threads=4) for rp, ci in graphs))]
     with efgpu.Batch(graphs) as b:
