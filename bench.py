@@ -89,7 +89,7 @@ SIR_OPS_PER_ARC = 54
 # counter summaries sit with the other rocprofv3 summaries); None whenever
 # the kernel changes. Mostly whole lines fetched for the row bounds of each
 # frontier node and the column entry of each successful draw.
-SIR_ATTEMPT_TRAFFIC_BYTES = 25.1e9
+SIR_ATTEMPT_TRAFFIC_BYTES = 25.2e9
 
 
 def table_clusters(rp, ci):

@@ -141,10 +141,11 @@ ef_status ef_validate_csr(int32_t n, int64_t nnz, const int32_t *row_ptr,
 
 /* Load a graph (Algorithm 1's input, Sec. 4). Without EF_DEVICE_PTRS the
  * arrays are host memory and are copied; with it they are device memory and
- * are borrowed. EF_VALIDATE runs ef_validate_csr first (device inputs are
- * copied to the host for it). The library allocates its own device arrays
- * (degrees, arc sources, reverse arcs, the degree-oriented half adjacency)
- * and keeps them until ef_graph_free. */
+ * are borrowed. EF_VALIDATE checks what ef_validate_csr checks, on the device
+ * while the graph is prepared, and reports the same error (device inputs are
+ * copied to the host only to word one). The library allocates its own device
+ * arrays (degrees, arc sources, reverse arcs, the degree-oriented half
+ * adjacency) and keeps them until ef_graph_free. */
 ef_status ef_graph_load_csr(int32_t n, int64_t nnz, const int32_t *row_ptr,
                             const int32_t *col_idx, uint32_t flags, void *hip_stream,
                             ef_graph **out);
@@ -216,11 +217,12 @@ ef_status ef_compute_j3(ef_graph *g, ef_prec prec, const int32_t *seeds, int32_t
  * infection tree, d = 1..4 (divide by inf_count for the empirical spreading
  * power of order d). Nullable: work[0] = arcs walked by the attempts (one draw
  * each), work[1] = frontier node-steps (infected nodes summed over the steps
- * run); phase_ms[0..2] = kernel time of the attempts, of the updates with
- * their prefix kernels, and of the descendant counts, from HIP events on the
+ * run); phase_ms[0..2] = kernel time of the attempts, of the updates (each with
+ * the prefixes its last workgroup takes), and of the descendant counts, from HIP events on the
  * stream. Simulations run in batches of up to 1024 sharing about 3 GB of the
- * graph's scratch memory (13 bytes per node and simulation). The stream is
- * synchronised every 8 steps and at the end. EF_ERR_ARG for beta or mu
+ * graph's scratch memory (13 bytes per node and simulation). The host
+ * looks every few steps whether an outbreak is alive, with steps queued ahead,
+ * and the stream is synchronised at the end. EF_ERR_ARG for beta or mu
  * outside [0, 1], negative n_sims or t_max, null outputs, or simulations on
  * a graph without nodes. */
 ef_status ef_sir(ef_graph *g, double beta, double mu, uint64_t seed, int32_t n_sims,
