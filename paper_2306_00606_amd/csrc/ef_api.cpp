@@ -117,6 +117,15 @@ static ComputeWs compute_ws(const Graph &g, bool fp64, int64_t n_tiles, int64_t 
   return L;
 }
 
+// Gives up ef_compute's block when no call is using it (the free waits for work
+// in flight) and no captured graph refers to it.
+static bool drop_main(Graph &g) {
+  if (g.main_busy || g.main_captured || !g.ws[WS_MAIN].p) return false;
+  dev_free(g, g.ws[WS_MAIN].p, g.ws[WS_MAIN].bytes);
+  g.ws[WS_MAIN] = DevBuf{};
+  return true;
+}
+
 static ef_status ws_ensure(Graph &g, int slot, size_t bytes, const char *what) {
   DevBuf &b = g.ws[slot];
   if (b.bytes >= bytes && b.p) return EF_OK;
@@ -125,7 +134,7 @@ static ef_status ws_ensure(Graph &g, int slot, size_t bytes, const char *what) {
     b.p = nullptr;
     b.bytes = 0;
   }
-  size_t want = std::max<size_t>(bytes, 256);
+  size_t want = std::max<size_t>(bytes, slot == WS_MAIN ? 16 : 256);
   ef_status s = dev_alloc(g, &b.p, want, what);
   if (s != EF_OK && g.score64) {
     // the FP64 score table only saves time: workspace comes first
@@ -141,13 +150,7 @@ static ef_status ws_ensure(Graph &g, int slot, size_t bytes, const char *what) {
     g.split_kept = false;
     s = dev_alloc(g, &b.p, want, what);
   }
-  if (s != EF_OK && slot != WS_MAIN && g.main_reserved && g.ws[WS_MAIN].p) {
-    // workspace that the load kept for a later ef_compute and nothing used yet
-    dev_free(g, g.ws[WS_MAIN].p, g.ws[WS_MAIN].bytes);
-    g.ws[WS_MAIN] = DevBuf{};
-    g.main_reserved = false;
-    s = dev_alloc(g, &b.p, want, what);
-  }
+  if (s != EF_OK && slot != WS_MAIN && drop_main(g)) s = dev_alloc(g, &b.p, want, what);
   if (s != EF_OK) return s;
   b.bytes = want;
   return EF_OK;
@@ -433,26 +436,24 @@ ef_status graph_load(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32
       }
     return t;
   }();
-  const size_t prep_bytes = (sizeof(int32_t) * (size_t)graph_prep_tmp_len((int64_t)NNZ) + 15) &
-                            ~(size_t)15;
+  const size_t work_bytes = sizeof(int64_t) * NN;
+  const size_t prep_bytes = sizeof(int32_t) * (size_t)graph_prep_tmp_len((int64_t)NNZ);
   size_t sort_temp = 0;
   if (st == EF_OK && n_over > 0) {
     const hipError_t e = launch_big_sort(g, nullptr, (int32_t)n_over, nullptr, nullptr, nullptr,
                                          sort_temp, stream);
     if (e != hipSuccess) st = hip_status(e, "degree-ordered rows");
   }
+  sort_temp = (sort_temp + 15) & ~(size_t)15;
   const size_t sort_bytes =
-      n_over > 0 ? ((sizeof(int32_t) * 4 * NNZ + 255) & ~(size_t)255) +
-                       ((sizeof(int32_t) * 3 * (size_t)n_over + 255) & ~(size_t)255) + sort_temp
-                 : 0;
-  const size_t scratch_bytes = std::max(prep_bytes + sizeof(int64_t) * NN, sort_bytes);
+      n_over > 0 ? sort_temp + sizeof(int32_t) * (4 * NNZ + 3 * (size_t)n_over) : 0;
+  const size_t scratch_bytes = std::max(work_bytes + prep_bytes, sort_bytes);
   if (st == EF_OK) {
     constexpr size_t kReserveFp64 = (size_t)64 << 20;
     const size_t w32 = compute_ws(g, false, nn_tiles, n, true).bytes,
                  w64 = compute_ws(g, true, nn_tiles, n, true).bytes;
     const size_t want = std::max(scratch_bytes, w64 <= kReserveFp64 ? w64 : w32);
     st = ws_ensure(g, WS_MAIN, want, "preprocessing scratch");
-    g.main_reserved = true;
     if (st != EF_OK && want > scratch_bytes)
       st = ws_ensure(g, WS_MAIN, scratch_bytes, "preprocessing scratch");
   }
@@ -464,8 +465,8 @@ ef_status graph_load(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32
       return st;
     });
   }
-  int32_t *tmp = (int32_t *)g.ws[WS_MAIN].p;
-  int64_t *work = (int64_t *)((char *)g.ws[WS_MAIN].p + prep_bytes);
+  int64_t *work = (int64_t *)g.ws[WS_MAIN].p;
+  int32_t *tmp = (int32_t *)((char *)g.ws[WS_MAIN].p + work_bytes);
   hipError_t e = hipSuccess;
   if (!devptr) {
     e = hipMemcpyAsync(g.row_ptr, row_ptr, sizeof(int32_t) * N1, hipMemcpyHostToDevice, stream);
@@ -522,10 +523,10 @@ ef_status graph_load(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32
     hb.reserve((size_t)n_over);
     for (int32_t v = 0; v < n; ++v)
       if (g.h_deg[(size_t)v] > kSmallMax) hb.push_back(v);
-    int32_t *scratch = tmp;
-    int32_t *d_big = (int32_t *)((char *)tmp + ((sizeof(int32_t) * 4 * NNZ + 255) & ~(size_t)255));
+    void *temp = g.ws[WS_MAIN].p;
+    int32_t *scratch = (int32_t *)((char *)temp + sort_temp);
+    int32_t *d_big = scratch + 4 * NNZ;
     int32_t *seg = d_big + n_over;
-    void *temp = (char *)d_big + ((sizeof(int32_t) * 3 * (size_t)n_over + 255) & ~(size_t)255);
     e = hipMemcpyAsync(d_big, hb.data(), sizeof(int32_t) * (size_t)n_over, hipMemcpyHostToDevice,
                        stream);
     if (e == hipSuccess)
@@ -677,7 +678,6 @@ ef_status graph_load(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32
       e = hipStreamSynchronize(stream);
       dev_free(g, g.ws[WS_MAIN].p, g.ws[WS_MAIN].bytes);
       g.ws[WS_MAIN] = DevBuf{};
-      g.main_reserved = false;
       st = e == hipSuccess ? dev_alloc(g, &g.lists, total, "node lists", sum)
                            : hip_status(e, "degree-ordered rows");
     }
@@ -1019,27 +1019,7 @@ extern "C" ef_status ef_compute(ef_graph *h, ef_algo algo, ef_prec prec, const i
   }
   if ((s = alloc_bins(g, b)) != EF_OK) return s;
   const ComputeWs L = compute_ws(g, prec == EF_PREC_FP64, b.n_tiles, n_work, !per_seed);
-  g.main_reserved = false;
-  if ((s = ws_ensure(g, WS_MAIN, L.bytes, "workspace")) != EF_OK) return s;
-  char *const ws = (char *)g.ws[WS_MAIN].p;
-  void *const ws_R = ws + L.R, *const ws_Z = ws + L.Z;
-  TriSlot *const ws_Y = (TriSlot *)(ws + L.Y);
-  int64_t *const ws_ZT = (int64_t *)(ws + L.ZT);
-  // outputs of the unique work list: straight into the caller's device arrays
-  // when possible, else into staging
-  double *ef_w = (double *)(ws + L.out);
-  int64_t *D_w = (int64_t *)(ef_w + std::max(n_work, 1)), *N_w = D_w + std::max(n_work, 1);
-  if (all && out_dev) {
-    ef_w = ef;
-    if (D) D_w = D;
-    if (N) N_w = N;
-  }
-  // FP32C: [0] positions recomputed by pass 2, [1] finalised in FP64
-  int32_t *cnt = (int32_t *)(ws + L.out + 24 * (size_t)n_work);
   hipError_t e = hipSuccess;
-  int32_t *listed = (int32_t *)(ws + L.flag);
-  uint8_t *flag_bytes = (uint8_t *)(listed + (n_work > kPass2Scan ? n_work : 0));
-
   // device seed arrays: the unique work list (all nodes: none, position =
   // node id), the inverse map, and output positions by seed degree bin
   int32_t *d_useeds = nullptr, *d_inv = nullptr;
@@ -1071,10 +1051,11 @@ extern "C" ef_status ef_compute(ef_graph *h, ef_algo algo, ef_prec prec, const i
       for (int bin = 0; bin < kSeedBins; ++bin) {
         std::sort(lst[bin].begin(), lst[bin].end(), by_work);
         g.n_ps[bin] = (int64_t)lst[bin].size();
-        if ((s = dev_alloc(g, (void **)&g.ps_list[bin],
-                           sizeof(int32_t) * std::max<size_t>(lst[bin].size(), 1),
-                           "seed lists")) != EF_OK)
-          return s;
+        const size_t bytes = sizeof(int32_t) * std::max<size_t>(lst[bin].size(), 1);
+        s = dev_alloc(g, (void **)&g.ps_list[bin], bytes, "seed lists");
+        if (s != EF_OK && drop_main(g))
+          s = dev_alloc(g, (void **)&g.ps_list[bin], bytes, "seed lists");
+        if (s != EF_OK) return s;
         if (!lst[bin].empty()) {
           e = hipMemcpy(g.ps_list[bin], lst[bin].data(), sizeof(int32_t) * lst[bin].size(),
                         hipMemcpyHostToDevice);
@@ -1126,6 +1107,31 @@ extern "C" ef_status ef_compute(ef_graph *h, ef_algo algo, ef_prec prec, const i
     }
   }
 
+  // the block last: the buffers above may take the place of a larger one
+  if ((s = ws_ensure(g, WS_MAIN, L.bytes, "workspace")) != EF_OK) return s;
+  struct MainUse {
+    Graph &g;
+    explicit MainUse(Graph &gg) : g(gg) { g.main_busy = true; }
+    ~MainUse() { g.main_busy = false; }
+  } main_use(g);
+  char *const ws = (char *)g.ws[WS_MAIN].p;
+  void *const ws_R = ws + L.R, *const ws_Z = ws + L.Z;
+  TriSlot *const ws_Y = (TriSlot *)(ws + L.Y);
+  int64_t *const ws_ZT = (int64_t *)(ws + L.ZT);
+  // outputs of the unique work list: straight into the caller's device arrays
+  // when possible, else into staging
+  double *ef_w = (double *)(ws + L.out);
+  int64_t *D_w = (int64_t *)(ef_w + std::max(n_work, 1)), *N_w = D_w + std::max(n_work, 1);
+  if (all && out_dev) {
+    ef_w = ef;
+    if (D) D_w = D;
+    if (N) N_w = N;
+  }
+  // FP32C: [0] positions recomputed by pass 2, [1] finalised in FP64
+  int32_t *cnt = (int32_t *)(ws + L.out + 24 * (size_t)n_work);
+  int32_t *listed = (int32_t *)(ws + L.flag);
+  uint8_t *flag_bytes = (uint8_t *)(listed + (n_work > kPass2Scan ? n_work : 0));
+
   // whole-graph calls bin every node with the graph's thresholds: their
   // lists are kept and reused (not while the stream is being captured, so
   // that a captured graph bins by itself)
@@ -1133,6 +1139,7 @@ extern "C" ef_status ef_compute(ef_graph *h, ef_algo algo, ef_prec prec, const i
   // (the pieces only save time: without memory for them, or in a captured
   // call, whose replays must not depend on them, no seed is cut)
   const bool eager = !capturing(st);
+  g.main_captured |= !eager;
   if (per_seed && eager) {
     const std::vector<int4> &pc = all ? g.h_ps_items : items;
     if ((s = split_buffer(g, pc, all, st)) != EF_OK) return s;
@@ -1370,12 +1377,14 @@ extern "C" ef_status ef_compute_j3(ef_graph *h, ef_prec prec, const int32_t *see
       std::iota(ord.begin(), ord.end(), 0);
       std::vector<int64_t> off;
       order_of(ord, off);
-      if ((s = dev_alloc(g, (void **)&g.j3_seeds, sizeof(int32_t) * ord.size(), "j3 order")) !=
-          EF_OK)
-        return s;
-      if ((s = dev_alloc(g, (void **)&g.j3_off, sizeof(int64_t) * off.size(), "j3 offsets")) !=
-          EF_OK)
-        return s;
+      s = dev_alloc(g, (void **)&g.j3_seeds, sizeof(int32_t) * ord.size(), "j3 order");
+      if (s != EF_OK && drop_main(g))
+        s = dev_alloc(g, (void **)&g.j3_seeds, sizeof(int32_t) * ord.size(), "j3 order");
+      if (s != EF_OK) return s;
+      s = dev_alloc(g, (void **)&g.j3_off, sizeof(int64_t) * off.size(), "j3 offsets");
+      if (s != EF_OK && drop_main(g))
+        s = dev_alloc(g, (void **)&g.j3_off, sizeof(int64_t) * off.size(), "j3 offsets");
+      if (s != EF_OK) return s;
       e = hipMemcpy(g.j3_seeds, ord.data(), sizeof(int32_t) * ord.size(), hipMemcpyHostToDevice);
       if (e == hipSuccess)
         e = hipMemcpy(g.j3_off, off.data(), sizeof(int64_t) * off.size(), hipMemcpyHostToDevice);
@@ -1531,7 +1540,9 @@ extern "C" ef_status ef_compute_j3(ef_graph *h, ef_prec prec, const int32_t *see
 // host outputs go through a device staging area after the top-k scratch.
 static ef_status topk_device_values(Graph &g, const double *ef_all, int32_t k, int32_t *nodes,
                                     double *ef, bool out_dev, hipStream_t st) {
-  const size_t sort_bytes = (topk_scratch_bytes(g.n, k) + 255) & ~(size_t)255;
+  // (staged outputs lie apart from the values)
+  const bool direct = topk_direct(ef_all, g.n, k, out_dev ? nodes : nullptr, out_dev ? ef : nullptr);
+  const size_t sort_bytes = direct ? 0 : (topk_scratch_bytes(g.n, k) + 255) & ~(size_t)255;
   const size_t node_bytes = (sizeof(int32_t) * (size_t)k + 255) & ~(size_t)255;
   const size_t stage = out_dev ? 0 : node_bytes + sizeof(double) * (size_t)k;
   ef_status s = ws_ensure(g, WS_TOPK, sort_bytes + stage, "top-k scratch");

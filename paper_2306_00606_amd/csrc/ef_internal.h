@@ -231,7 +231,9 @@ struct Graph {
   ef_run_stats stats{};
   // workspace (grow-only, reused across calls)
   DevBuf ws[16];
-  bool main_reserved = false;  // WS_MAIN holds the load's scratch, kept for the first ef_compute
+  // the block of ef_compute (the load's scratch at first): in use by a running
+  // call, or referred to by a captured graph
+  bool main_busy = false, main_captured = false;
   // events for EF_PROFILE
   hipEvent_t ev[16] = {};
   bool ev_ready = false;
@@ -402,6 +404,9 @@ hipError_t launch_pass2(const Graph &g, const int32_t *seeds, const uint8_t *fl,
 // topk_scratch_bytes(n, k) device bytes, none of it needing prior clearing.
 // hipErrorInvalidValue when k > n or the scratch is too small.
 size_t topk_scratch_bytes(int32_t n, int32_t k);
+// whether launch_topk ranks all values in one launch, without scratch
+bool topk_direct(const double *vals, int32_t n, int32_t k, const int32_t *nodes,
+                 const double *ef_out);
 hipError_t launch_topk(const double *ef, int32_t n, int32_t k, void *scratch,
                        size_t scratch_bytes, int32_t *nodes, double *ef_out, hipStream_t st);
 // Schedule of the persistent batch kernel (one launch for the whole exact

@@ -397,7 +397,7 @@ __global__ __launch_bounds__(kSirThreads) void k_sir_attempt(
   }
   sir_flush(buf, nxc, nxt, n);
   // each wavefront owns one slot of the arc counts: no atomic needed
-  if (lane == 63) wk[blockIdx.x * 4 + wv] += arcs;
+  if (lane == 63) atomicAdd((unsigned long long *)&wk[blockIdx.x], (unsigned long long)arcs);
   if (!sir_last(ticket)) return;
   const int32_t tot = sir_scan(
       R, sh,
@@ -610,7 +610,7 @@ extern "C" ef_status ef_sir(ef_graph *h, double beta, double mu, uint64_t seed, 
   const size_t bytes = cells * 13 + sizeof(SirSim) * RB + sizeof(int32_t) * kSirPad * RB +
                        sizeof(int32_t) * (5 * (size_t)kSirTab + 2 + RB +
                                           (kSirTickets + 1) * kSirPad) +
-                       sizeof(int64_t) * (5 * (size_t)n + kSirGrid * 4) + 16 * 256;
+                       sizeof(int64_t) * (5 * (size_t)n + kSirGrid) + 16 * 256;
   char *p = nullptr;
   ef_status s = graph_scratch(g, bytes, (void **)&p);
   if (s != EF_OK) return s;
@@ -631,14 +631,14 @@ extern "C" ef_status ef_sir(ef_graph *h, double beta, double mu, uint64_t seed, 
   int32_t *d_ticket = (int32_t *)take(sizeof(int32_t) * (kSirTickets + 1) * kSirPad);
   int64_t *d_sp = (int64_t *)take(sizeof(int64_t) * 5 * (size_t)n);  // 4 orders, then counts
   int64_t *d_ic = d_sp + 4 * (int64_t)n;
-  int64_t *d_wk = (int64_t *)take(sizeof(int64_t) * kSirGrid * 4);  // arcs per attempt wavefront
+  int64_t *d_wk = (int64_t *)take(sizeof(int64_t) * kSirGrid);  // arcs per attempt workgroup
   const uint64_t tb = sir_threshold(beta), tm = sir_threshold(mu);
   const int64_t global_min = ((int64_t)n + 3) / 4;
   hipError_t e = hipSuccess;
   hipLaunchKernelGGL(k_sir_zero64, dim3(sir_blocks(5 * (int64_t)n)), dim3(256), 0, st,
                      5 * (int64_t)n, d_sp);
-  hipLaunchKernelGGL(k_sir_zero64, dim3(kSirGrid * 4 / 256), dim3(256), 0, st,
-                     (int64_t)kSirGrid * 4, d_wk);
+  hipLaunchKernelGGL(k_sir_zero64, dim3(kSirGrid / 256), dim3(256), 0, st,
+                     (int64_t)kSirGrid, d_wk);
   // a word of host memory per round of kSirCheck steps in flight (two), which
   // the device writes, and an event after each round
   int32_t *h_alive = nullptr;
@@ -745,7 +745,7 @@ extern "C" ef_status ef_sir(ef_graph *h, double beta, double mu, uint64_t seed, 
     e = hipMemcpyAsync(sp_sum, d_sp, sizeof(int64_t) * 4 * (size_t)n, hipMemcpyDeviceToHost, st);
   if (e == hipSuccess)
     e = hipMemcpyAsync(inf_count, d_ic, sizeof(int64_t) * (size_t)n, hipMemcpyDeviceToHost, st);
-  std::vector<int64_t> h_wk(work ? (size_t)kSirGrid * 4 : 0);
+  std::vector<int64_t> h_wk(work ? (size_t)kSirGrid : 0);
   if (e == hipSuccess && work)
     e = hipMemcpyAsync(h_wk.data(), d_wk, sizeof(int64_t) * h_wk.size(), hipMemcpyDeviceToHost, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);

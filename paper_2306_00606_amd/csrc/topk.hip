@@ -556,20 +556,25 @@ bool tk_overlap(const void *a, size_t na, const void *b, size_t nb) {
 
 size_t topk_scratch_bytes(int32_t n, int32_t k) { return tk_layout(n, k).bytes; }
 
+// the one-launch form writes outputs while other workgroups still read the
+// values: not for outputs placed over them
+bool topk_direct(const double *vals, int32_t n, int32_t k, const int32_t *nodes,
+                 const double *ef_out) {
+  return n <= kTkDirect && !tk_overlap(vals, sizeof(double) * n, nodes, sizeof(int32_t) * k) &&
+         !(ef_out && tk_overlap(vals, sizeof(double) * n, ef_out, sizeof(double) * k));
+}
+
 hipError_t launch_topk(const double *vals, int32_t n, int32_t k, void *scratch,
                        size_t scratch_bytes, int32_t *nodes, double *ef_out, hipStream_t st) {
   if (n <= 0 || k <= 0) return hipSuccess;
   if (k > n) return hipErrorInvalidValue;
-  const TkLayout L = tk_layout(n, k);
-  if (L.bytes > scratch_bytes) return hipErrorInvalidValue;
-  // the one-launch form writes outputs while other workgroups still read the
-  // values: not for outputs placed over them
-  if (n <= kTkDirect && !tk_overlap(vals, sizeof(double) * n, nodes, sizeof(int32_t) * k) &&
-      !(ef_out && tk_overlap(vals, sizeof(double) * n, ef_out, sizeof(double) * k))) {
+  if (topk_direct(vals, n, k, nodes, ef_out)) {
     hipLaunchKernelGGL((k_tk_rank<true, kTkDirect>), dim3((n + 63) / 64), dim3(kTkSelThreads), 0,
                        st, vals, nullptr, nullptr, n, k, true, nodes, ef_out, nullptr, nullptr);
     return hipGetLastError();
   }
+  const TkLayout L = tk_layout(n, k);
+  if (L.bytes > scratch_bytes) return hipErrorInvalidValue;
   char *p = (char *)scratch;
   auto *state = (TkState *)(p + L.state);
   auto *hist = (uint32_t *)(p + L.hist);
