@@ -126,6 +126,32 @@ static bool drop_main(Graph &g) {
   return true;
 }
 
+// Device arrays that a call builds on first use and its handle keeps: filled as
+// they are added, and freed again unless the call comes to keep() them, so that
+// after a failure the handle holds none of them.
+class KeptArrays {
+ public:
+  explicit KeptArrays(Graph &g) : g_(g) {}
+  ~KeptArrays() {
+    for (const DevBuf &b : held_) dev_free(g_, b.p, b.bytes);
+  }
+  ef_status add(void **out, const void *src, size_t bytes, const char *what) {
+    DevBuf b;
+    b.bytes = std::max<size_t>(bytes, 4);
+    ef_status s = dev_alloc(g_, &b.p, b.bytes, what);
+    if (s != EF_OK && drop_main(g_)) s = dev_alloc(g_, &b.p, b.bytes, what);
+    if (s != EF_OK) return s;
+    held_.push_back(b);
+    *out = b.p;
+    return bytes ? hip_status(hipMemcpy(b.p, src, bytes, hipMemcpyHostToDevice), what) : EF_OK;
+  }
+  void keep() { held_.clear(); }
+
+ private:
+  Graph &g_;
+  std::vector<DevBuf> held_;
+};
+
 static ef_status ws_ensure(Graph &g, int slot, size_t bytes, const char *what) {
   DevBuf &b = g.ws[slot];
   if (b.bytes >= bytes && b.p) return EF_OK;
@@ -1048,19 +1074,19 @@ extern "C" ef_status ef_compute(ef_graph *h, ef_algo algo, ef_prec prec, const i
     if (!g.ps_ready) {
       std::vector<int32_t> lst[kSeedBins];
       for (int32_t v = 0; v < g.n; ++v) lst[seed_bin(v)].push_back(v);
+      // (the handle gets the lists when all are there)
+      KeptArrays kept(g);
+      int32_t *list[kSeedBins];
       for (int bin = 0; bin < kSeedBins; ++bin) {
         std::sort(lst[bin].begin(), lst[bin].end(), by_work);
+        if ((s = kept.add((void **)&list[bin], lst[bin].data(),
+                          sizeof(int32_t) * lst[bin].size(), "seed lists")) != EF_OK)
+          return s;
+      }
+      kept.keep();
+      for (int bin = 0; bin < kSeedBins; ++bin) {
+        g.ps_list[bin] = list[bin];
         g.n_ps[bin] = (int64_t)lst[bin].size();
-        const size_t bytes = sizeof(int32_t) * std::max<size_t>(lst[bin].size(), 1);
-        s = dev_alloc(g, (void **)&g.ps_list[bin], bytes, "seed lists");
-        if (s != EF_OK && drop_main(g))
-          s = dev_alloc(g, (void **)&g.ps_list[bin], bytes, "seed lists");
-        if (s != EF_OK) return s;
-        if (!lst[bin].empty()) {
-          e = hipMemcpy(g.ps_list[bin], lst[bin].data(), sizeof(int32_t) * lst[bin].size(),
-                        hipMemcpyHostToDevice);
-          if (e != hipSuccess) return hip_status(e, "upload seed lists");
-        }
       }
       seed_pieces(g, nullptr, lst, g.h_ps_items, g.ps_split, g.ps_first);
       g.ps_ready = true;
@@ -1377,18 +1403,17 @@ extern "C" ef_status ef_compute_j3(ef_graph *h, ef_prec prec, const int32_t *see
       std::iota(ord.begin(), ord.end(), 0);
       std::vector<int64_t> off;
       order_of(ord, off);
-      s = dev_alloc(g, (void **)&g.j3_seeds, sizeof(int32_t) * ord.size(), "j3 order");
-      if (s != EF_OK && drop_main(g))
-        s = dev_alloc(g, (void **)&g.j3_seeds, sizeof(int32_t) * ord.size(), "j3 order");
-      if (s != EF_OK) return s;
-      s = dev_alloc(g, (void **)&g.j3_off, sizeof(int64_t) * off.size(), "j3 offsets");
-      if (s != EF_OK && drop_main(g))
-        s = dev_alloc(g, (void **)&g.j3_off, sizeof(int64_t) * off.size(), "j3 offsets");
-      if (s != EF_OK) return s;
-      e = hipMemcpy(g.j3_seeds, ord.data(), sizeof(int32_t) * ord.size(), hipMemcpyHostToDevice);
-      if (e == hipSuccess)
-        e = hipMemcpy(g.j3_off, off.data(), sizeof(int64_t) * off.size(), hipMemcpyHostToDevice);
-      if (e != hipSuccess) return hip_status(e, "upload j3 order");
+      KeptArrays kept(g);
+      int32_t *seeds_d;
+      int64_t *off_d;
+      if ((s = kept.add((void **)&seeds_d, ord.data(), sizeof(int32_t) * ord.size(),
+                        "j3 order")) != EF_OK ||
+          (s = kept.add((void **)&off_d, off.data(), sizeof(int64_t) * off.size(),
+                        "j3 offsets")) != EF_OK)
+        return s;
+      kept.keep();
+      g.j3_seeds = seeds_d;
+      g.j3_off = off_d;
     }
     d_ord = g.j3_seeds;
     d_off = g.j3_off;

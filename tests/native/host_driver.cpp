@@ -198,10 +198,36 @@ static void batches() {
   }
 }
 
+// a first use that runs out of memory half-way leaves nothing that a later call
+// takes for the whole
+static void first_use() {
+  const Csr c = hubby(3000, 6, 4);
+  ef_graph *h = load(c);
+  stub::fail_mallocs(8 * ((size_t)c.n() + 1));  // the item offsets
+  CHECK(whole_j3(h, EF_PREC_FP32C) == EF_ERR_NOMEM);
+  CHECK(!h->g.j3_seeds && !h->g.j3_off);
+  stub::fail_mallocs(0);
+  CHECK(whole_j3(h, EF_PREC_FP32C) == EF_OK);
+  std::vector<size_t> bins(efi::kSeedBins, 0);
+  CHECK(whole(h, EF_ALGO_PER_SEED, EF_PREC_FP32C) == EF_OK);
+  for (int b = 0; b < efi::kSeedBins; ++b) bins[(size_t)b] = 4 * (size_t)h->g.n_ps[b];
+  CHECK(ef_graph_free(h) == EF_OK);
+  h = load(c);
+  CHECK(bins[1] > 0);
+  stub::fail_mallocs(bins[1]);  // the second of the seed lists
+  CHECK(whole(h, EF_ALGO_PER_SEED, EF_PREC_FP32C) == EF_ERR_NOMEM);
+  CHECK(!h->g.ps_list[0] && !h->g.ps_ready);
+  stub::fail_mallocs(0);
+  CHECK(whole(h, EF_ALGO_PER_SEED, EF_PREC_FP32C) == EF_OK);
+  CHECK(ef_graph_free(h) == EF_OK);
+  CHECK(stub::live_blocks() == 0);
+}
+
 int main(int argc, char **argv) {
   const std::map<std::string, std::function<void()>> all = {
       {"calls", calls},
       {"batches", batches},
+      {"first_use", first_use},
   };
   const auto it = argc == 2 ? all.find(argv[1]) : all.end();
   if (it == all.end()) return 2;

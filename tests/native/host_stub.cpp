@@ -100,7 +100,7 @@ size_t live_bytes() {
   for (const auto &m : g_mem) s += m.second;
   return s;
 }
-void fail_next_malloc(size_t bytes) { g_fail_bytes = bytes; }
+void fail_mallocs(size_t bytes) { g_fail_bytes = bytes; }
 void begin_capture(hipStream_t st) { g_capture[st]; }
 void end_capture(hipStream_t st) {
   g_last = g_capture[st];
@@ -134,10 +134,7 @@ hipError_t hipGetLastError() { return hipSuccess; }
 
 hipError_t hipMalloc(void **p, size_t bytes) {
   if (!g_capture.empty()) fail("hipMalloc while a stream is captured");
-  if (g_fail_bytes && bytes >= g_fail_bytes) {
-    g_fail_bytes = 0;
-    return hipErrorOutOfMemory;
-  }
+  if (g_fail_bytes && bytes == g_fail_bytes) return hipErrorOutOfMemory;
   *p = std::malloc(bytes);  // exactly `bytes`: what follows is not readable
   if (!*p) return hipErrorOutOfMemory;
   std::memset(*p, 0xCD, bytes);

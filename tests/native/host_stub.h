@@ -16,8 +16,8 @@ size_t live_blocks();
 bool live(const void *p);
 // device bytes held now
 size_t live_bytes();
-// the next hipMalloc of at least `bytes` (and only that one) fails
-void fail_next_malloc(size_t bytes);
+// every hipMalloc of exactly `bytes` fails from now on (0: none)
+void fail_mallocs(size_t bytes);
 
 // a caller's capture of stream st: launches are kept instead of run; replay()
 // runs what the last capture kept
