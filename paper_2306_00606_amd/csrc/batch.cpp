@@ -130,6 +130,9 @@ static void drop_graph(ef_batch *b, int d) {
   if (b->graph[d]) (void)hipGraphDestroy(b->graph[d]);
   b->exec[d] = nullptr;
   b->graph[d] = nullptr;
+  // (only the phased design's graph refers to the handle's workspace, and only
+  // the batch captures calls of its handle)
+  if (d == 0 && b->g) b->g->g.main_captured = false;
 }
 
 static void drop_persist(ef_batch *b) {

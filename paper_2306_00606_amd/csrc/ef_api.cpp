@@ -155,11 +155,11 @@ class KeptArrays {
 static ef_status ws_ensure(Graph &g, int slot, size_t bytes, const char *what) {
   DevBuf &b = g.ws[slot];
   if (b.bytes >= bytes && b.p) return EF_OK;
-  if (b.p) {
-    dev_free(g, b.p, b.bytes);
-    b.p = nullptr;
-    b.bytes = 0;
-  }
+  // a replay writes to the block it was captured with, whatever the calls since
+  // have needed
+  const DevBuf captured = slot == WS_MAIN && g.main_captured ? b : DevBuf{};
+  if (b.p && !captured.p) dev_free(g, b.p, b.bytes);
+  b = DevBuf{};
   size_t want = std::max<size_t>(bytes, slot == WS_MAIN ? 16 : 256);
   ef_status s = dev_alloc(g, &b.p, want, what);
   if (s != EF_OK && g.score64) {
@@ -177,8 +177,15 @@ static ef_status ws_ensure(Graph &g, int slot, size_t bytes, const char *what) {
     s = dev_alloc(g, &b.p, want, what);
   }
   if (s != EF_OK && slot != WS_MAIN && drop_main(g)) s = dev_alloc(g, &b.p, want, what);
-  if (s != EF_OK) return s;
+  if (s != EF_OK) {
+    b = captured;
+    return s;
+  }
   b.bytes = want;
+  if (captured.p) {
+    g.main_old.push_back(captured);
+    g.main_captured = false;
+  }
   return EF_OK;
 }
 
@@ -260,6 +267,7 @@ ef_status ef_graph_free(ef_graph *h) {
     if (p) (void)hipFree(p);
   for (auto &b : g.ws)
     if (b.p) (void)hipFree(b.p);
+  for (auto &b : g.main_old) (void)hipFree(b.p);
   if (g.ev_ready)
     for (auto &e : g.ev) (void)hipEventDestroy(e);
   delete h;

@@ -234,6 +234,9 @@ struct Graph {
   // the block of ef_compute (the load's scratch at first): in use by a running
   // call, or referred to by a captured graph
   bool main_busy = false, main_captured = false;
+  // blocks that captured graphs refer to and that were outgrown: kept until the
+  // handle is freed
+  std::vector<DevBuf> main_old;
   // events for EF_PROFILE
   hipEvent_t ev[16] = {};
   bool ev_ready = false;

@@ -89,6 +89,31 @@ struct Out {
   explicit Out(size_t count)
       : ef(std::max<size_t>(count, 1)), D(ef.size()), N(ef.size()), n(count) {}
 };
+// outputs on the device
+struct DeviceOut {
+  double *ef = nullptr;
+  int64_t *D = nullptr, *N = nullptr;
+  size_t n;
+  explicit DeviceOut(size_t count) : n(count) {
+    (void)hipMalloc(&ef, 8 * n);
+    (void)hipMalloc(&D, 8 * n);
+    (void)hipMalloc(&N, 8 * n);
+  }
+  ~DeviceOut() {
+    (void)hipFree(ef);
+    (void)hipFree(D);
+    (void)hipFree(N);
+  }
+  ef_status call(ef_graph *h, ef_algo algo, ef_prec p, hipStream_t st) const {
+    return ef_compute(h, algo, p, nullptr, 0, ef, D, N, EF_OUT_DEVICE, st);
+  }
+  void clear() { std::memset(ef, 0, 8 * n); }
+  bool expected() const {
+    for (size_t v = 0; v < n; ++v)
+      if (ef[v] != (double)v + 0.5 || D[v] != 3 * (int64_t)v) return false;
+    return true;
+  }
+};
 static bool expected(const Out &o, const std::vector<int32_t> *seeds) {
   for (size_t i = 0; i < o.n; ++i) {
     const int32_t v = seeds ? (*seeds)[i] : (int32_t)i;
@@ -223,11 +248,58 @@ static void first_use() {
   CHECK(stub::live_blocks() == 0);
 }
 
+// a whole-graph call captured by the caller
+static void capture(ef_graph *h, ef_algo algo, ef_prec p, const DeviceOut &o) {
+  hipStream_t st;
+  (void)hipStreamCreateWithFlags(&st, 0);
+  CHECK(o.call(h, algo, p, st) == EF_OK);  // sizes the workspace
+  CHECK(hipStreamSynchronize(st) == hipSuccess);
+  stub::begin_capture(st);
+  CHECK(o.call(h, algo, p, st) == EF_OK);
+  stub::end_capture(st);
+  (void)hipStreamDestroy(st);
+}
+
+// a captured graph's block outlives calls that need a larger one
+static void captured() {
+  const Csr c = ring(300000, 8);  // FP64 needs more than the load sets aside
+  DeviceOut o((size_t)c.n());
+  for (int form = 0; form < 2; ++form) {
+    ef_graph *h = load(c);
+    if (form == 0) capture(h, EF_ALGO_CLUSTER, EF_PREC_FP32C, o);
+    else capture(h, EF_ALGO_PER_SEED, EF_PREC_FP64, o);
+    const size_t before = h->g.ws[0].bytes;
+    CHECK(whole(h, EF_ALGO_CLUSTER, EF_PREC_FP64) == EF_OK);
+    CHECK(h->g.ws[0].bytes > before);
+    o.clear();
+    stub::replay();
+    CHECK(o.expected());
+    CHECK(whole(h, EF_ALGO_CLUSTER, EF_PREC_FP64) == EF_OK);
+    stub::replay();
+    CHECK(ef_graph_free(h) == EF_OK);
+  }
+  // a batch's own graphs hold no block once they are replaced
+  const int32_t off[2] = {0, c.n()};
+  size_t held[2];
+  for (int first = 0; first < 2; ++first) {
+    ef_batch *b = nullptr;
+    CHECK(ef_batch_create(1, off, c.nnz(), c.rp.data(), c.ci.data(), 0, nullptr, &b) == EF_OK);
+    Out r((size_t)c.n());
+    for (int q = first; q < 2; ++q)
+      CHECK(ef_batch_compute(b, q == 0 ? EF_PREC_FP32C : EF_PREC_FP64, r.ef.data(), r.D.data(),
+                             r.N.data(), EF_BATCH_PHASED, nullptr) == EF_OK);
+    held[first] = stub::live_bytes();
+    CHECK(ef_batch_free(b) == EF_OK);
+  }
+  CHECK(held[0] == held[1]);
+}
+
 int main(int argc, char **argv) {
   const std::map<std::string, std::function<void()>> all = {
       {"calls", calls},
       {"batches", batches},
       {"first_use", first_use},
+      {"captured", captured},
   };
   const auto it = argc == 2 ? all.find(argv[1]) : all.end();
   if (it == all.end()) return 2;
