@@ -270,6 +270,7 @@ ef_status ef_graph_free(ef_graph *h) {
   for (auto &b : g.main_old) (void)hipFree(b.p);
   if (g.ev_ready)
     for (auto &e : g.ev) (void)hipEventDestroy(e);
+  if (g.score_ev) (void)hipEventDestroy(g.score_ev);
   delete h;
   return EF_OK;
 }
@@ -824,20 +825,36 @@ static bool capturing(hipStream_t st) {
   return cap != hipStreamCaptureStatusNone;
 }
 
+// Stream st follows the fill of the score table, which may have been queued on
+// another one.
+static ef_status score_follow(Graph &g, hipStream_t st) {
+  if (!g.score64 || !g.score_pending) return EF_OK;
+  return hip_status(hipStreamWaitEvent(st, g.score_ev, 0), "score table");
+}
+
 // The FP64 score table of the graph: built on the stream of the first FP64
 // call and kept until memory runs short. Without memory for it, and in a call
 // that a caller captures (whose replays it might not outlive), the kernels
 // compute every score.
 static ef_status score_table(Graph &g, hipStream_t st) {
-  if (g.score64) return EF_OK;
+  if (g.score64) return score_follow(g, st);
   // cluster degrees are below 3 k_max, with three events below 4 k_max
   const int32_t n = 4 * g.info.max_degree + 1;
-  if (dev_alloc(g, (void **)&g.score64, sizeof(double) * (size_t)n, "score table") != EF_OK) {
-    g.score64 = nullptr;
-    return EF_OK;
+  const size_t bytes = sizeof(double) * (size_t)n;
+  void *t = nullptr;
+  if (dev_alloc(g, &t, bytes, "score table") != EF_OK) return EF_OK;
+  hipError_t e = hipSuccess;
+  if (!g.score_ev) e = hipEventCreateWithFlags(&g.score_ev, hipEventDisableTiming);
+  if (e == hipSuccess) e = launch_score_table((double *)t, n, st);
+  if (e == hipSuccess) e = hipEventRecord(g.score_ev, st);
+  if (e != hipSuccess) {
+    dev_free(g, t, bytes);
+    return hip_status(e, "score table");
   }
+  g.score64 = (double *)t;
   g.n_score64 = n;
-  return hip_status(launch_score_table(g.score64, n, st), "score table");
+  g.score_pending = true;
+  return EF_OK;
 }
 
 // Cuts the seeds of bins 1-4 whose 2-hop work is above a piece's (the leading
@@ -1277,6 +1294,7 @@ extern "C" ef_status ef_compute(ef_graph *h, ef_algo algo, ef_prec prec, const i
   g.stats.pairs_mid = b.pairs_mid;
   g.stats.pairs_big = b.pairs_big;
   g.stats.seeds = n_work;
+  if (prec == EF_PREC_FP64 && !out_dev) g.score_pending = false;  // st has been waited for
   if ((prof.on || !out_dev) && !(flags & kInternalNoReadback)) {
     if (prec == EF_PREC_FP32C && !counted)
       e = hipMemcpyAsync(hc, cnt, sizeof(hc), hipMemcpyDeviceToHost, st);
@@ -1510,6 +1528,7 @@ extern "C" ef_status ef_compute_j3(ef_graph *h, ef_prec prec, const int32_t *see
       if (e == hipSuccess)
         e = hipMemcpyAsync(fpos, fpos_h.data(), sizeof(int32_t) * fpos_h.size(),
                            hipMemcpyHostToDevice, st);
+      if (e == hipSuccess && tab && (s = score_follow(g, st)) != EF_OK) return s;
       if (e == hipSuccess)
         e = launch_j3_items(g, true, tab, false, pord, po, n_flag, foff.back(), j3_lists, j3_counts,
                             PN, PD, PS, st);

@@ -227,6 +227,10 @@ struct Graph {
   // first one; null: no device memory for it, and the kernels take logs)
   double *score64 = nullptr;
   int32_t n_score64 = 0;
+  // recorded behind its fill; calls wait for it on their streams until the host
+  // has waited for one of them (score_pending)
+  hipEvent_t score_ev = nullptr;
+  bool score_pending = false;
   ef_graph_info info{};
   ef_run_stats stats{};
   // workspace (grow-only, reused across calls)

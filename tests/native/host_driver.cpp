@@ -294,12 +294,36 @@ static void captured() {
   CHECK(held[0] == held[1]);
 }
 
+// calls of one handle on different streams, without a wait between them, that
+// share nothing the first one fills
+static void streams() {
+  const Csr c = hubby(3000, 6, 5);
+  hipStream_t a, b;
+  (void)hipStreamCreateWithFlags(&a, 0);
+  (void)hipStreamCreateWithFlags(&b, 0);
+  DeviceOut o((size_t)c.n()), o3((size_t)c.n());
+  for (ef_prec p : {EF_PREC_FP64, EF_PREC_FP32C}) {  // FP32C recomputes some seeds in FP64
+    ef_graph *h = load(c);
+    for (int round = 0; round < 2; ++round) {
+      CHECK(o.call(h, EF_ALGO_CLUSTER, EF_PREC_FP64, a) == EF_OK);
+      CHECK(ef_compute_j3(h, p, nullptr, 0, o3.ef, o3.D, o3.N, EF_OUT_DEVICE, b) == EF_OK);
+      CHECK(o.expected() && o3.expected());
+    }
+    CHECK(whole(h, EF_ALGO_CLUSTER, EF_PREC_FP64) == EF_OK);
+    CHECK(!h->g.score_pending);
+    CHECK(ef_graph_free(h) == EF_OK);
+  }
+  (void)hipStreamDestroy(a);
+  (void)hipStreamDestroy(b);
+}
+
 int main(int argc, char **argv) {
   const std::map<std::string, std::function<void()>> all = {
       {"calls", calls},
       {"batches", batches},
       {"first_use", first_use},
       {"captured", captured},
+      {"streams", streams},
   };
   const auto it = argc == 2 ? all.find(argv[1]) : all.end();
   if (it == all.end()) return 2;
