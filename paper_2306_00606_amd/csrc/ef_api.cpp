@@ -117,6 +117,15 @@ static ComputeWs compute_ws(const Graph &g, bool fp64, int64_t n_tiles, int64_t 
   return L;
 }
 
+// Largest block that a load keeps for the first ef_compute. An allocation and a
+// free of tens of megabytes cost some 0.3 ms each, a tenth of a load of 2M arcs;
+// larger graphs load for longer, and idle handles would hold gigabytes. A graph
+// with slots for tri_zero has more than kTriBin2^2 arcs and so no such block:
+// that allocation never finds its place taken.
+constexpr size_t kMainKept = (size_t)64 << 20;
+static_assert(kMainKept < (sizeof(float) + sizeof(TriSlot)) * kTriBin2 * kTriBin2,
+              "a load that keeps its block clears no triangle slots");
+
 // Gives up ef_compute's block when no call is using it (the free waits for work
 // in flight) and no captured graph refers to it.
 static bool drop_main(Graph &g) {
@@ -459,9 +468,10 @@ ef_status graph_load(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32
     g.row_ptr = const_cast<int32_t *>(row_ptr);
     g.col_idx = const_cast<int32_t *>(col_idx);
   }
-  // Scratch of the preparation: WS_MAIN, at the size a cluster-centric call
-  // will want (kept for it; FP64's too where that is small), or what the
-  // preparation needs if there is no memory for more.
+  // Scratch of the preparation: WS_MAIN. Where a cluster-centric call (FP64's,
+  // or FP32C's) will want at most kMainKept and not much more than the scratch
+  // itself, it has that size and is kept for the call; otherwise it is freed at
+  // the end, since a handle need not ever score.
   const int64_t nn_tiles = [&] {
     int64_t t = 0;
     for (int32_t v = 0; v < n && kmax > kSuper; ++v)
@@ -483,11 +493,13 @@ ef_status graph_load(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32
   const size_t sort_bytes =
       n_over > 0 ? sort_temp + sizeof(int32_t) * (4 * NNZ + 3 * (size_t)n_over) : 0;
   const size_t scratch_bytes = std::max(work_bytes + prep_bytes, sort_bytes);
+  size_t kept_bytes = 0;
+  for (const bool fp64 : {false, true}) {
+    const size_t w = compute_ws(g, fp64, nn_tiles, n, true).bytes;
+    if (nnz > 0 && w <= kMainKept && w <= 2 * scratch_bytes) kept_bytes = w;
+  }
   if (st == EF_OK) {
-    constexpr size_t kReserveFp64 = (size_t)64 << 20;
-    const size_t w32 = compute_ws(g, false, nn_tiles, n, true).bytes,
-                 w64 = compute_ws(g, true, nn_tiles, n, true).bytes;
-    const size_t want = std::max(scratch_bytes, w64 <= kReserveFp64 ? w64 : w32);
+    const size_t want = std::max(scratch_bytes, kept_bytes);
     st = ws_ensure(g, WS_MAIN, want, "preprocessing scratch");
     if (st != EF_OK && want > scratch_bytes)
       st = ws_ensure(g, WS_MAIN, scratch_bytes, "preprocessing scratch");
@@ -730,6 +742,7 @@ ef_status graph_load(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32
       // (the load is complete when it returns; the host vectors go)
       if (e == hipSuccess) e = hipStreamSynchronize(stream);
       if (e != hipSuccess) st = hip_status(e, "upload node lists");
+      if (kept_bytes == 0) drop_main(g);
     }
     if (st != EF_OK) {
       (void)hipStreamSynchronize(stream);

@@ -317,6 +317,49 @@ static void streams() {
   (void)hipStreamDestroy(b);
 }
 
+// device bytes of a handle's node lists, without the padding between them
+static int64_t list_bytes(const efi::Graph &g) {
+  return 16 * (g.n_tri_lane + g.n_tri[0] + g.n_tri[1] + g.n_tri[2]) +
+         4 * (g.n_tri[1] + g.n_tri[3] + g.n_fin + g.n_fin_group);
+}
+// what a loaded handle holds for calls that may not come
+static void idle() {
+  const Csr graphs[] = {from_edges(40000, {}), ring(500000, 8), from_edges(3000, {{0, 1}}),
+                        hubby(3000, 6, 6), ring(100000, 8)};
+  for (const Csr &c : graphs) {
+    ef_graph *h = load(c);
+    const size_t bytes = h->g.ws[0].bytes;
+    CHECK(bytes <= (64u << 20) && bytes <= 40 * (size_t)c.nnz());
+    CHECK((bytes > 0) == (&c >= graphs + 3));
+    CHECK(whole(h, EF_ALGO_CLUSTER, EF_PREC_FP32C) == EF_OK);
+    CHECK(bytes == 0 || h->g.ws[0].bytes == bytes);
+    CHECK(ef_graph_free(h) == EF_OK);
+  }
+}
+// a load accepted under one limit is accepted under any larger one: here what is
+// left after a block for ef_compute has room for half of the triangle slots that
+// are cleared before each pass
+static void limits() {
+  const Csr c = complete(2200);
+  ef_graph *h = load(c);
+  const efi::Graph &g = h->g;
+  CHECK(g.n_tri_zero > 0);
+  CHECK(whole(h, EF_ALGO_CLUSTER, EF_PREC_FP32C) == EF_OK);
+  const int64_t main = (int64_t)h->g.ws[0].bytes, slots = 4 * g.n_tri_zero;
+  int64_t other = 0;  // the other workspace
+  for (int i = 1; i < 16; ++i) other += (int64_t)h->g.ws[i].bytes;
+  const int64_t arrays = g.owned_bytes - main - slots - list_bytes(g) - other;
+  CHECK(ef_graph_free(h) == EF_OK);
+  for (int64_t limit : {arrays + main - 4, arrays + main + slots / 2, arrays + main + 2 * slots}) {
+    setenv("EF_MAX_DEVICE_BYTES", std::to_string(limit).c_str(), 1);
+    h = load(c);
+    CHECK(h != nullptr);
+    if (h) CHECK(ef_graph_free(h) == EF_OK);
+  }
+  unsetenv("EF_MAX_DEVICE_BYTES");
+  CHECK(stub::live_blocks() == 0);
+}
+
 int main(int argc, char **argv) {
   const std::map<std::string, std::function<void()>> all = {
       {"calls", calls},
@@ -324,6 +367,8 @@ int main(int argc, char **argv) {
       {"first_use", first_use},
       {"captured", captured},
       {"streams", streams},
+      {"idle", idle},
+      {"limits", limits},
   };
   const auto it = argc == 2 ? all.find(argv[1]) : all.end();
   if (it == all.end()) return 2;
