@@ -838,28 +838,36 @@ static bool capturing(hipStream_t st) {
   return cap != hipStreamCaptureStatusNone;
 }
 
-// Stream st follows the fill of the score table, which may have been queued on
-// another one.
+// The score table is behind stream st from here on, whichever stream its fill
+// was queued on. (A pending fill without an event is one whose call failed
+// before it had waited for it: the table goes, and the free waits.)
 static ef_status score_follow(Graph &g, hipStream_t st) {
   if (!g.score64 || !g.score_pending) return EF_OK;
-  return hip_status(hipStreamWaitEvent(st, g.score_ev, 0), "score table");
+  if (g.score_recorded) return hip_status(hipStreamWaitEvent(st, g.score_ev, 0), "score table");
+  dev_free(g, g.score64, sizeof(double) * (size_t)g.n_score64);
+  g.score64 = nullptr;
+  g.n_score64 = 0;
+  return EF_OK;
 }
 
 // The FP64 score table of the graph: built on the stream of the first FP64
 // call and kept until memory runs short. Without memory for it, and in a call
 // that a caller captures (whose replays it might not outlive), the kernels
-// compute every score.
-static ef_status score_table(Graph &g, hipStream_t st) {
-  if (g.score64) return score_follow(g, st);
+// compute every score. waits: the call waits for its stream before it returns,
+// and no event has to follow the fill for later ones (in a new graph's one call
+// the event took 45 us of 350).
+static ef_status score_table(Graph &g, hipStream_t st, bool waits) {
+  const ef_status s = score_follow(g, st);
+  if (s != EF_OK || g.score64) return s;
   // cluster degrees are below 3 k_max, with three events below 4 k_max
   const int32_t n = 4 * g.info.max_degree + 1;
   const size_t bytes = sizeof(double) * (size_t)n;
   void *t = nullptr;
   if (dev_alloc(g, &t, bytes, "score table") != EF_OK) return EF_OK;
   hipError_t e = hipSuccess;
-  if (!g.score_ev) e = hipEventCreateWithFlags(&g.score_ev, hipEventDisableTiming);
+  if (!waits && !g.score_ev) e = hipEventCreateWithFlags(&g.score_ev, hipEventDisableTiming);
   if (e == hipSuccess) e = launch_score_table((double *)t, n, st);
-  if (e == hipSuccess) e = hipEventRecord(g.score_ev, st);
+  if (e == hipSuccess && !waits) e = hipEventRecord(g.score_ev, st);
   if (e != hipSuccess) {
     dev_free(g, t, bytes);
     return hip_status(e, "score table");
@@ -867,6 +875,7 @@ static ef_status score_table(Graph &g, hipStream_t st) {
   g.score64 = (double *)t;
   g.n_score64 = n;
   g.score_pending = true;
+  g.score_recorded = !waits;
   return EF_OK;
 }
 
@@ -1221,7 +1230,8 @@ extern "C" ef_status ef_compute(ef_graph *h, ef_algo algo, ef_prec prec, const i
   const bool reuse = whole && g.bins_kept && g.bins_buf == g.ws[WS_BINS].p &&
                      g.bins_thr.t8 == b.thr.t8 && g.bins_thr.t16 == b.thr.t16 &&
                      g.bins_thr.t32 == b.thr.t32;
-  if (prec == EF_PREC_FP64 && eager && (s = score_table(g, st)) != EF_OK) return s;
+  if (prec == EF_PREC_FP64 && eager && (s = score_table(g, st, !out_dev)) != EF_OK)
+    return s;
   const bool tab = eager || replay_own;
   prof.mark(0);
   if (!reuse) {
@@ -1502,7 +1512,7 @@ extern "C" ef_status ef_compute_j3(ef_graph *h, ef_prec prec, const int32_t *see
   int32_t *j3_counts = j3_lists + 5 * std::max<int64_t>(n_items, 1);
   const bool fp64 = prec == EF_PREC_FP64;
   const bool tab = !capturing(st);
-  if (fp64 && tab && (s = score_table(g, st)) != EF_OK) return s;
+  if (fp64 && tab && (s = score_table(g, st, !out_dev)) != EF_OK) return s;
   prof.mark(0);
   e = launch_j3_items(g, fp64, tab, all, d_ord, d_off, n_work, n_items, j3_lists, j3_counts, PN, PD,
                       PS, st);
@@ -1588,6 +1598,7 @@ extern "C" ef_status ef_compute_j3(ef_graph *h, ef_prec prec, const int32_t *see
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return hip_status(e, "copy outputs");
   }
+  if (fp64 && !out_dev) g.score_pending = false;  // st has been waited for
   g.stats.seeds = n_work;
   g.stats.promoted = n_flag;
   if (prof.on) {

@@ -227,10 +227,10 @@ struct Graph {
   // first one; null: no device memory for it, and the kernels take logs)
   double *score64 = nullptr;
   int32_t n_score64 = 0;
-  // recorded behind its fill; calls wait for it on their streams until the host
-  // has waited for one of them (score_pending)
+  // the host has not waited for its fill yet (score_pending): calls then wait on
+  // their streams for an event behind it (score_recorded: there is one)
   hipEvent_t score_ev = nullptr;
-  bool score_pending = false;
+  bool score_pending = false, score_recorded = false;
   ef_graph_info info{};
   ef_run_stats stats{};
   // workspace (grow-only, reused across calls)

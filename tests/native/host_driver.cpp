@@ -313,6 +313,19 @@ static void streams() {
     CHECK(!h->g.score_pending);
     CHECK(ef_graph_free(h) == EF_OK);
   }
+  // a call that waits by itself fills the table, or fails before it waits
+  for (bool fails : {false, true}) {
+    ef_graph *h = load(c);
+    if (fails) stub::fail_copies(8 * (size_t)c.n());  // of its results
+    Out r((size_t)c.n());
+    CHECK((ef_compute_j3(h, EF_PREC_FP64, nullptr, 0, r.ef.data(), r.D.data(), r.N.data(), 0, a) ==
+           EF_OK) == !fails);
+    stub::fail_copies(0);
+    CHECK(h->g.score64 && h->g.score_pending == fails);
+    CHECK(o.call(h, EF_ALGO_CLUSTER, EF_PREC_FP64, b) == EF_OK);
+    CHECK(o.call(h, EF_ALGO_CLUSTER, EF_PREC_FP64, a) == EF_OK);
+    CHECK(o.expected() && ef_graph_free(h) == EF_OK);
+  }
   (void)hipStreamDestroy(a);
   (void)hipStreamDestroy(b);
 }

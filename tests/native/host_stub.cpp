@@ -31,7 +31,7 @@ void fail(const char *fmt, ...) {
 }
 
 std::map<void *, size_t> g_mem;
-size_t g_fail_bytes = 0;
+size_t g_fail_bytes = 0, g_fail_copy = 0;
 
 // What has happened before what: per stream, the operations of every stream
 // that its next one follows; the host follows what it has waited for.
@@ -101,6 +101,7 @@ size_t live_bytes() {
   return s;
 }
 void fail_mallocs(size_t bytes) { g_fail_bytes = bytes; }
+void fail_copies(size_t bytes) { g_fail_copy = bytes; }
 void begin_capture(hipStream_t st) { g_capture[st]; }
 void end_capture(hipStream_t st) {
   g_last = g_capture[st];
@@ -154,6 +155,7 @@ hipError_t hipFree(void *p) {
   return hipSuccess;
 }
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t st) {
+  if (g_fail_copy && n == g_fail_copy) return hipErrorUnknown;
   return queue(st, [=] { if (n) std::memcpy(d, s, n); });
 }
 hipError_t hipStreamSynchronize(hipStream_t st) {

@@ -18,6 +18,8 @@ bool live(const void *p);
 size_t live_bytes();
 // every hipMalloc of exactly `bytes` fails from now on (0: none)
 void fail_mallocs(size_t bytes);
+// every hipMemcpyAsync of exactly `bytes` fails from now on (0: none)
+void fail_copies(size_t bytes);
 
 // a caller's capture of stream st: launches are kept instead of run; replay()
 // runs what the last capture kept
