@@ -868,6 +868,8 @@ __device__ __forceinline__ void tri_lane_node(const TriArgs &A, const int4 rc) {
 // against the whole row), the credits to x by row position in integer LDS
 // slots and those to u, whose segment is one lane's, in its registers (both
 // in the representation of the other bins, so the records are the same bits).
+// FP64 sums the credits to w in double: a lane those of its segment, then the
+// first lane of a node's those of the lanes behind it, in a fixed order.
 // Bound by the dependent loads of a chunk on small graphs and by the row
 // comparisons on large ones.
 // BA n = 200k, m = 5 (FP32C): 39.5 us, one lane per node 93; a graph of
@@ -884,9 +886,8 @@ template <typename T> struct TriPackLds {
   __align__(16) int32_t up[kRows];  // ids of up(w) by node and position, -1 past its end
   unsigned long long acc[kRows];    // credits to x
   int32_t cnt[Credit<T>::kPacked ? 1 : kRows];
-  long long z[Credit<T>::kPacked ? 1 : kPackNodes];  // FP64: credits to w, 2^-44 units
+  double z[Credit<T>::kPacked ? 1 : kPackNodes];  // FP64: credits to w
 };
-constexpr double kPackZFix = 17592186044416.0;  // 2^44: |sum| < 2^13, beyond the records' 2^-36
 
 template <typename T>
 __global__ __launch_bounds__(256) void k_tri_pack(TriArgs A, const int4 *__restrict__ recs,
@@ -944,13 +945,14 @@ __global__ __launch_bounds__(256) void k_tri_pack(TriArgs A, const int4 *__restr
       if constexpr (!Credit<T>::kPacked) L.cnt[r] = 0;
     }
     if constexpr (!Credit<T>::kPacked)
-      if (lane < kPackNodes) L.z[lane] = 0;
+      if (lane < kPackNodes) L.z[lane] = 0.0;
     wave_sync();
     for (int32_t c0 = 0; c0 < nseg; c0 += 64) {
       const bool live = c0 + lane < nseg;
       const int32_t len = live ? sg.y : 0, row = node * M, slot = sg.x, ks = sg.z;
       const int32_t e0 = slot + 1;
-      const int32_t znode = node;
+      [[maybe_unused]] const int32_t znode = node;
+      [[maybe_unused]] double zl = 0.0;
       if (c0 + 64 < nseg) sg = segment(min(c0 + 64 + lane, nseg - 1), node);
       LaneSlot<T> su;
       for (int32_t j = 0; __ballot(j < len) != 0ull; j += 4) {
@@ -980,12 +982,22 @@ __global__ __launch_bounds__(256) void k_tri_pack(TriArgs A, const int4 *__restr
           hits &= ~(0xFFu << q8);
           Credit<T>::add(L.acc, L.cnt, at, dl);
           su.add(dl);
-          if constexpr (!Credit<T>::kPacked)
-            atomicAdd((unsigned long long *)&L.z[znode],
-                      (unsigned long long)__double2ll_rn((double)dl * kPackZFix));
+          if constexpr (!Credit<T>::kPacked) zl += dl;
         }
       }
       if (live) A.Y[A.nup + slot] = su.slot();
+      if constexpr (!Credit<T>::kPacked) {
+        // (a node's segments are consecutive lanes; lanes past the last segment
+        // go with its node and add nothing)
+        for (int o = 1; o < 64; o <<= 1) {
+          const double y = __shfl_down(zl, o, 64);
+          const int32_t yn = __shfl_down(znode, o, 64);
+          if (lane + o < 64 && yn == znode) zl += y;
+        }
+        const int32_t before = __shfl_up(znode, 1, 64);
+        if (lane == 0 || before != znode) L.z[znode] += zl;
+        wave_sync();  // the next chunk's lanes may add to the same node
+      }
     }
     wave_sync();
     // the rows' upper-end records; a node's sum over its row of M lanes
@@ -1006,7 +1018,7 @@ __global__ __launch_bounds__(256) void k_tri_pack(TriArgs A, const int4 *__restr
       if (pos == 0 && mn > 0) {  // every listed node has up(w) non-empty
         typename S::type acc = typename S::type();
         if constexpr (kZFromSlots<T>) acc = dfv_from_fix(zs);
-        else acc = (double)L.z[nq] * (1.0 / kPackZFix);
+        else acc = L.z[nq];
         S::store(acc, A.Z, w);
         A.ZT[w] = zt;
       }
