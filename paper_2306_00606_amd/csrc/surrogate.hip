@@ -420,21 +420,22 @@ __device__ __forceinline__ FeatNode feat_groups(const FeatArgs &A, const int32_t
   return o;
 }
 
-// hub v on the whole workgroup; thread 0 holds it
+// hub v on the whole workgroup of NT threads; thread 0 holds it
+template <int NT>
 __device__ __forceinline__ FeatNode feat_hub(const FeatArgs &A, int32_t v) {
-  __shared__ FeatAcc sh[4];
+  __shared__ FeatAcc sh[NT / 64];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int32_t k = A.deg[v], base = A.row_ptr[v];
   FeatNode o{feat_zero(), tid == 0 ? v : -1, k, 0};
   const NbrMoments own = A.nbm[v];
   o.s1 = own.s1;
-  feat_arcs(A.adj2, A.nbm, k, base, own, tid, 256, feat_pair(A.adj2, k, base, tid, 256), o.f);
+  feat_arcs(A.adj2, A.nbm, k, base, own, tid, NT, feat_pair(A.adj2, k, base, tid, NT), o.f);
   feat_reduce<64>(o.f);
   __syncthreads();  // the previous hub's sums have been read
   if (lane == 0) sh[wv] = o.f;
   __syncthreads();
   if (tid == 0)
-    for (int w = 1; w < 4; ++w) o.f.merge(sh[w]);
+    for (int w = 1; w < NT / 64; ++w) o.f.merge(sh[w]);
   return o;
 }
 
@@ -448,12 +449,13 @@ __device__ __forceinline__ FeatNode feat_hub(const FeatArgs &A, int32_t v) {
 // 7 TB/s), with the formulas and the GELUs beside them. That graph: 303 us; with
 // the network in a launch of its own 355 us, and with a launch per tier and the
 // formulas on one lane of eight 563 us.
-template <int R, bool PREDICT>
-__global__ __launch_bounds__(256) void k_features(FeatArgs A, const int32_t *l_hub, int64_t n_hub,
+template <int R, bool PREDICT, int NT>
+__global__ __launch_bounds__(NT) void k_features(FeatArgs A, const int32_t *l_hub, int64_t n_hub,
                                                   const int32_t *l_wave, int64_t n_wave,
                                                   const int32_t *l_half, int64_t n_half, int64_t n,
                                                   int64_t b0, int64_t b1, int64_t b2) {
-  __shared__ FwdLds lds[PREDICT ? 4 : 1];
+  constexpr int W = NT / 64;
+  __shared__ FwdLds lds[PREDICT ? W : 1];
   const int64_t b = blockIdx.x;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   // this wavefront's items: first, step and end; and a lane's row in the tile
@@ -463,16 +465,16 @@ __global__ __launch_bounds__(256) void k_features(FeatArgs A, const int32_t *l_h
   if (b < b0) {
     i0 = b, step = b0, end = n_hub, row = 0, rows = wv == 0 ? 1 : 0;
   } else if (b < b1) {
-    i0 = (b - b0) * 4 + wv, step = (b1 - b0) * 4, end = n_wave, row = lane, rows = 1;
+    i0 = (b - b0) * W + wv, step = (b1 - b0) * W, end = n_wave, row = lane, rows = 1;
   } else if (b < b2) {
-    i0 = ((b - b1) * 4 + wv) * 2 * R, step = (b2 - b1) * 8 * R, end = n_half;
+    i0 = ((b - b1) * W + wv) * 2 * R, step = (b2 - b1) * W * 2 * R, end = n_half;
     row = (lane & 31) * 2 + (lane >> 5), rows = 2 * R;
   } else {
-    i0 = ((b - b2) * 4 + wv) * 8 * R, step = ((int64_t)gridDim.x - b2) * 32 * R, end = n;
+    i0 = ((b - b2) * W + wv) * 8 * R, step = ((int64_t)gridDim.x - b2) * W * 8 * R, end = n;
     row = (lane & 7) * 8 + (lane >> 3), rows = 8 * R;
   }
   for (; i0 < end; i0 += step) {
-    const FeatNode o = b < b0   ? feat_hub(A, l_hub[i0])
+    const FeatNode o = b < b0   ? feat_hub<NT>(A, l_hub[i0])
                        : b < b1 ? feat_groups<64, 1>(A, l_wave, n_wave, 0, i0)
                        : b < b2 ? feat_groups<32, R>(A, l_half, n_half, 0, i0)
                                 : feat_groups<8, R>(A, nullptr, n, kFinGroupMax, i0);
@@ -512,16 +514,17 @@ __global__ __launch_bounds__(256) void k_features(FeatArgs A, const int32_t *l_h
   }
 }
 
-template <int R, bool PREDICT>
+template <int R, bool PREDICT, int NT>
 static hipError_t features_impl(const Graph &g, const FeatArgs &A, hipStream_t st) {
+  constexpr int W = NT / 64;
   auto blocks = [](int64_t count, int64_t per) {
     return count > 0 ? std::min<int64_t>((count + per - 1) / per, 1 << 20) : 0;
   };
   const int64_t n_wave = g.n_fin - g.n_fin_hub - g.n_fin_half;
   const int32_t *l_wave = g.fin_list + g.n_fin_hub, *l_half = l_wave + n_wave;
-  const int64_t b0 = blocks(g.n_fin_hub, 1), b1 = b0 + blocks(n_wave, 4),
-                b2 = b1 + blocks(g.n_fin_half, 8 * R), grid = b2 + blocks(g.n, 32 * R);
-  hipLaunchKernelGGL((k_features<R, PREDICT>), dim3((unsigned)grid), dim3(256), 0, st, A,
+  const int64_t b0 = blocks(g.n_fin_hub, 1), b1 = b0 + blocks(n_wave, W),
+                b2 = b1 + blocks(g.n_fin_half, W * 2 * R), grid = b2 + blocks(g.n, W * 8 * R);
+  hipLaunchKernelGGL((k_features<R, PREDICT, NT>), dim3((unsigned)grid), dim3(NT), 0, st, A,
                      g.fin_list, g.n_fin_hub, l_wave, n_wave, l_half, g.n_fin_half, (int64_t)g.n,
                      b0, b1, b2);
   return hipGetLastError();
@@ -533,18 +536,37 @@ static hipError_t features_impl(const Graph &g, const FeatArgs &A, hipStream_t s
 // million 816 and 303).
 constexpr int32_t kFeatRounds = 1 << 16;
 
+// Workgroups of 512 threads, of which a hub takes one, where the largest hub
+// alone takes longer than the rest of the graph: it sums its arcs at some 0.77 a
+// nanosecond on 256 threads (bound by the formulas of one CU) and 1.2 on 512,
+// the rest at some 50. Elsewhere 256: more workgroups per CU (predictions on
+// stars of 50k, 200k and 1M arcs: 62, 191 and 830 us; 71, 282 and 1294 with 256
+// threads, 75, 182 and 747 with 1024; R-MAT scale 22 2034 us against 1814, BA
+// n = 1M, m = 8 361 against 340).
+constexpr int32_t kFeatWide = 32768;
+template <bool PREDICT>
+static hipError_t features_by_size(const Graph &g, const FeatArgs &A, hipStream_t st) {
+  const int32_t k = g.info.max_degree;
+  const bool wide = k > kFeatWide && k > g.nnz / 64;
+  if (g.n >= kFeatRounds)
+    return wide ? features_impl<8, PREDICT, 512>(g, A, st)
+                : features_impl<8, PREDICT, 256>(g, A, st);
+  return wide ? features_impl<1, PREDICT, 512>(g, A, st)
+              : features_impl<1, PREDICT, 256>(g, A, st);
+}
+
 hipError_t launch_features(const Graph &g, const float *mean, const float *inv_std, float *X,
                            float *lnN, hipStream_t st) {
   const FeatArgs A{g.row_ptr, g.deg, g.adj2, g.nbm, mean, inv_std, X, lnN, nullptr, nullptr,
                    nullptr};
-  return g.n >= kFeatRounds ? features_impl<8, false>(g, A, st) : features_impl<1, false>(g, A, st);
+  return features_by_size<false>(g, A, st);
 }
 
 // predicted EF of every node: max(0, ln N - y)
 hipError_t launch_predict(const Graph &g, const float *mean, const float *inv_std, const float *P,
                           const __bf16 *pack, double *ef, hipStream_t st) {
   const FeatArgs A{g.row_ptr, g.deg, g.adj2, g.nbm, mean, inv_std, nullptr, nullptr, P, pack, ef};
-  return g.n >= kFeatRounds ? features_impl<8, true>(g, A, st) : features_impl<1, true>(g, A, st);
+  return features_by_size<true>(g, A, st);
 }
 
 // Training: gradients of the mean squared error over the rows perm[b0 .. b0+nb)
