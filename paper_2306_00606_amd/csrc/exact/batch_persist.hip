@@ -175,19 +175,19 @@ __device__ inline void persist_item(const PersistArgs &P, const int4 it, unsigne
         arc_reduce_item<T>(P.row_ptr, P.deg, P.adjs, P.big, P.reduce[i], P.rec, P.R);
       break;
     case PI_FIN_LANE:
-      fin_lanes<T>(P.fin, a, b, 0, 1);
+      fin_lanes<T, 1>(P.fin, a, b, 0, 1);
       break;
     case PI_FIN_G8:
-      fin_groups<T, 8>(P.fin, P.fin_list[0] + a, cnt, 0, 0, 1);
+      fin_groups<T, 8, 1>(P.fin, P.fin_list[0] + a, cnt, 0, 0, 1);
       break;
     case PI_FIN_G32:
-      fin_groups<T, 32>(P.fin, P.fin_list[1] + a, cnt, 0, 0, 1);
+      fin_groups<T, 32, 1>(P.fin, P.fin_list[1] + a, cnt, 0, 0, 1);
       break;
     case PI_FIN_G64:
-      fin_groups<T, 64>(P.fin, P.fin_list[2] + a, cnt, 0, 0, 1);
+      fin_groups<T, 64, 1>(P.fin, P.fin_list[2] + a, cnt, 0, 0, 1);
       break;
     case PI_FIN_HUB:
-      fin_hubs<T>(P.fin, P.fin_list[3] + a, cnt, 0, 1);
+      fin_hubs<T, 1>(P.fin, P.fin_list[3] + a, cnt, 0, 1);
       break;
     case PI_PASS2: {
       // nodes a..b-1: FP32C pass 2 of the flagged ones, one at a time with

@@ -170,7 +170,11 @@ template <> struct RVal<double> {
 // waited on 28 such pairs one after the other (k_finalize_cluster on BA
 // n = 200k, m = 5: 56 us, 98 one arc at a time; R-MAT scale 22: 2.49 ms
 // against 2.70; with two or eight arcs at a time 58 and 67 us, 2.52 and 2.69 ms).
-template <typename T>
+// U = 1 in the persistent batch kernel, whose registers are all taken: with four
+// it spills more, and nodes wait for more rounds than they save (8 graphs of
+// 40k-60k nodes, FP32C: 1358 us with one arc and one lane per node in fin_lanes,
+// 1397 with four arcs, 1421 with two lanes as well).
+template <typename T, int U>
 __device__ __forceinline__ void fin_arcs(const int2 *__restrict__ adj2,
                                          const int32_t *__restrict__ rrev,
                                          const int32_t *__restrict__ trec, const void *R,
@@ -179,7 +183,6 @@ __device__ __forceinline__ void fin_arcs(const int2 *__restrict__ adj2,
                                          typename SumT<T>::type &sacc, double &tfix,
                                          int64_t &Tc) {
   using RV = RVal<T>;
-  constexpr int U = 4;
   for (int32_t i = first; i < k; i += U * stride) {
     int32_t e[U], ka[U], rv[U], tr[U];
 #pragma unroll
@@ -243,6 +246,8 @@ __device__ __forceinline__ void fin_store(int32_t v, int32_t k, int64_t As, long
   Nout[v] = Nn;
 }
 
+constexpr int kFinUnroll = 4;  // arcs at a time in the stand-alone kernel
+
 struct FinArgs {
   const int32_t *row_ptr, *deg;
   const int2 *adj2;
@@ -261,7 +266,7 @@ struct FinArgs {
 
 // G lanes per node over `nodes` (NULL: node ids 0..count-1 of degree <= kmax),
 // using blocks 0 .. nblk-1 of this role
-template <typename T, int G>
+template <typename T, int G, int U = kFinUnroll>
 __device__ __forceinline__ void fin_groups(const FinArgs &A, const int32_t *nodes, int64_t count,
                                            int32_t kmax, int64_t blk, int64_t nblk) {
   using Acc = typename SumT<T>::type;
@@ -283,7 +288,7 @@ __device__ __forceinline__ void fin_groups(const FinArgs &A, const int32_t *node
     double tfix = 0.0;
     int64_t Tc = 0;
     if (v >= 0)
-      fin_arcs<T>(A.adj2, A.rrev, A.trec, A.R, A.Y, k, A.row_ptr[v], sub, G, sacc, tfix, Tc);
+      fin_arcs<T, U>(A.adj2, A.rrev, A.trec, A.R, A.Y, k, A.row_ptr[v], sub, G, sacc, tfix, Tc);
     sacc = group_sum<G>(sacc);
     tfix = group_sum<G>(tfix);
     Tc = group_sum<G>(Tc);
@@ -293,7 +298,7 @@ __device__ __forceinline__ void fin_groups(const FinArgs &A, const int32_t *node
   }
 }
 
-// kFinShare lanes per node of degree <= kFinLaneMax over node ids lo..hi-1: the
+// G lanes per node of degree <= kFinLaneMax over node ids lo..hi-1: the
 // loads of all of a node's arcs are issued together (indices clamped to its
 // row, contributions past k masked), so a node costs two dependent round trips.
 // Bound by those and by the random sectors of R and Y: two lanes halve a lane's
@@ -301,11 +306,11 @@ __device__ __forceinline__ void fin_groups(const FinArgs &A, const int32_t *node
 // 70 us for the kernel; one lane 78, four 76, eight 99 us. BA n = 200k, m = 5:
 // 53 us; 56, 53, 54).
 constexpr int kFinShare = 2;
-template <typename T>
+template <typename T, int G = kFinShare>
 __device__ __forceinline__ void fin_lanes(const FinArgs &A, int64_t lo, int64_t hi, int64_t blk,
                                           int64_t nblk) {
   using Acc = typename SumT<T>::type;
-  constexpr int G = kFinShare, K = kFinLaneMax / G;
+  constexpr int K = kFinLaneMax / G;
   const int sub = threadIdx.x & (G - 1);
   const int64_t stride = nblk * (int64_t)blockDim.x / G;
   const int64_t v0 = lo + (blk * (int64_t)blockDim.x + threadIdx.x) / G;
@@ -356,7 +361,7 @@ __device__ __forceinline__ void fin_lanes(const FinArgs &A, int64_t lo, int64_t 
 }
 
 // one workgroup (up to 16 wavefronts) per hub; partials combined in a fixed order
-template <typename T>
+template <typename T, int U = kFinUnroll>
 __device__ __forceinline__ void fin_hubs(const FinArgs &A, const int32_t *nodes, int64_t count,
                                          int64_t blk, int64_t nblk) {
   using Acc = typename SumT<T>::type;
@@ -370,7 +375,7 @@ __device__ __forceinline__ void fin_hubs(const FinArgs &A, const int32_t *nodes,
     Acc sacc = Acc();
     double tfix = 0.0;
     int64_t Tc = 0;
-    fin_arcs<T>(A.adj2, A.rrev, A.trec, A.R, A.Y, k, A.row_ptr[v], tid, (int32_t)blockDim.x, sacc,
+    fin_arcs<T, U>(A.adj2, A.rrev, A.trec, A.R, A.Y, k, A.row_ptr[v], tid, (int32_t)blockDim.x, sacc,
                 tfix, Tc);
     sacc = wave_sum(sacc);
     tfix = wave_sum_f64(tfix);

@@ -19,8 +19,8 @@ def _triangles(count, seed):
     r = np.random.default_rng(seed)
     src, dst, mid, n = [], [], [], 0
     for _ in range(count):
-        la = int(r.integers(0, 5))
-        lb = la + int(r.integers(1, 6))
+        la = int(r.integers(0, 7))
+        lb = int(r.integers(7, 25))  # 9 to 26 neighbours: both sum those on 8 lanes
         lc = lb + int(r.integers(1, 6))
         a, b, c = n, n + 1, n + 2
         n += 3
