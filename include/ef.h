@@ -172,6 +172,11 @@ ef_status ef_graph_info_get(const ef_graph *g, ef_graph_info *out);
  * id, length n) or of seeds[0..n_seeds) (outputs position-aligned with seeds;
  * duplicates allowed). ef receives EF as double; D and N (nullable) receive
  * the exact int64 sums. Selected seeds always use the per-seed formulation.
+ * N and D are exact. The last bits of EF follow the order of its sums, which
+ * depends on the call: on how far the largest seeds are cut into pieces (in
+ * lists with more than some 1.3e8 2-hop entries on all their seeds; not in calls
+ * captured into a HIP graph), and, in double precision, on whether scores come
+ * from a table (not in captured calls, nor without device memory for it).
  * Flags: EF_OUT_DEVICE, EF_PROFILE. */
 ef_status ef_compute(ef_graph *g, ef_algo algo, ef_prec prec, const int32_t *seeds,
                      int32_t n_seeds, double *ef, int64_t *D, int64_t *N, uint32_t flags,
@@ -285,8 +290,10 @@ ef_status ef_topk_values_noalloc(const double *ef_in, int32_t n, int32_t k, int3
  * The launch sequence of a design is captured into a HIP graph on its first
  * use and replayed afterwards. On first use the batch is tuned: both designs
  * are timed with several settings (small-degree bin thresholds; chunk sizes
- * of the persistent items) and the fastest is kept; the choice is cached for
- * the process per size class (graphs, nodes, arcs, largest degree, each
+ * of the persistent items) and the fastest is kept, of the phased design's
+ * thresholds {8, 16, 0} unless others are more than 5% faster (the last bits of
+ * FP32C results follow them, and the best ones differ by less than timing
+ * noise); the choice is cached for the process per size class (graphs, nodes, arcs, largest degree, each
  * rounded up to a power of two) and precision, so a later batch of the same
  * class is not timed again. Outputs are per node of the union, in union
  * order (cluster-centric).
@@ -322,7 +329,7 @@ ef_status ef_batch_create(int32_t n_graphs, const int32_t *node_off, int64_t nnz
                           void *hip_stream, ef_batch **out);
 
 /* Tune the batch (see above): time every candidate of both designs on this
- * batch (eager passes) and keep the fastest, or take the size class's cached
+ * batch (eager passes) and keep the fastest (see above), or take the size class's cached
  * choice; drops any captured graph. */
 ef_status ef_batch_autotune(ef_batch *b, ef_prec prec);
 

@@ -19,7 +19,8 @@
 // thresholds; for the persistent design also the chunk size of its items),
 // keeps the fastest and caches the choice per size class (graph count, nodes,
 // arcs and largest degree, each rounded to a power of two), so later batches
-// of the same class skip the timing.
+// of the same class skip the timing. Of the phased design's settings, one is
+// preferred where it is within 5% of the fastest.
 #include <algorithm>
 #include <cstring>
 #include <map>
@@ -512,10 +513,12 @@ extern "C" ef_status ef_batch_autotune(ef_batch *b, ef_prec prec) {
   Graph &g = b->g->g;
   ef_status s = EF_OK;
   // phased design: small-bin thresholds. The candidates' centres share one
-  // launch, so the best of them differ by no more than two timings of one do (on
-  // 64 graphs of 1000 to 20000 nodes 0 to 3%, the others 4 to 110%), and the last
-  // bits of FP32C results follow the choice: kTuneFirst, unless one is clearly
-  // faster
+  // launch, so the best of them differ by no more than two timings of one do, and
+  // the last bits of FP32C results follow the choice: kTuneFirst, {8, 16, 0},
+  // unless one is clearly faster. (Batches of 512 graphs of 300 nodes, 256 of
+  // 2k-6k, 64 of 1k-20k, 128 of 5k-40k, 8 of 50k, 16 of 50k with hubs and 4 of
+  // 1k, in both precisions: it was the fastest or within 3% of it, most others 4
+  // to 150% slower.)
   TuneEntry best{g.thr, 0, 0, 0};
   for (int i = 0; i < 8; ++i) {
     g.thr = kCandidates[i];

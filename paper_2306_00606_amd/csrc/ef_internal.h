@@ -33,7 +33,8 @@ constexpr int kRecEntries = 2 * kSuper;  // row part + column part per super-til
 // an LDS hash of w's degree-oriented out-list up(w). Nodes w with segments
 // are binned by |up(w)| and by their walk (tail entries, segments):
 //   L: |up| <= kTriLaneM, walk <= kTriLaneWork, segments <= kTriLaneSegs
-//      one lane (up(w) and the credits in registers)
+//      a segment per lane, several nodes on a wavefront (in the persistent
+//      batch kernel one lane, up(w) and the credits in registers)
 //   0: |up| <= kTriBin0, walk <= kTriWaveWork, segments <= kTriWaveSegs
 //      one wavefront
 //   1: |up| <= kTriBin1     one workgroup (8 wavefronts)
@@ -48,7 +49,8 @@ constexpr int kTriBin0 = 64, kTriBin1 = 512, kTriBin2 = 2048;
 // wavefronts, 8 lanes each; degree <= kFinHalfMax: 32 lanes; degree <=
 // kFinBlockMin: a wavefront; hubs of degree > kFinBlockMin: a workgroup.
 constexpr int32_t kFinGroupMax = 32;
-constexpr int32_t kFinLaneMax = 8;  // the cluster finalize: one lane per node up to this degree
+constexpr int32_t kFinLaneMax = 8;  // the cluster finalize: two lanes per node up to this degree
+                                    // (one in the persistent batch kernel)
 constexpr int32_t kFinHalfMax = 512;
 constexpr int32_t kFinBlockMin = 4096;
 constexpr int kTriLongMin = kTriBin2 + 1;
@@ -175,12 +177,12 @@ struct Graph {
   // host copies used for sizing work lists
   std::vector<int32_t> h_deg;
   // triangle-pass node lists (device): see kTriBin*. Bin 0 as records
-  // {w, up_ptr[w], dn_ptr[w], |up(w)| | segments << 16}, bins 1-3 as ids.
+  // {w, up_ptr[w], dn_ptr[w], |up(w)| | segments << 16}, bins 1 and 3 as ids.
   int4 *tri_rec0 = nullptr;
   // lane bin: {w, up_ptr[w], dn_ptr[w], |up(w)| | segments << 8 | walk << 16}, by id
   int4 *tri_recL = nullptr;
   int64_t n_tri_lane = 0;
-  int32_t *tri_list[4] = {nullptr, nullptr, nullptr, nullptr};
+  int32_t *tri_list[4] = {nullptr, nullptr, nullptr, nullptr};  // [1] and [3]
   // bins 1 and 2 as records too: {w, up_ptr[w], dn_ptr[w], |up(w)| | segments << 12}
   int4 *tri_recB[3] = {nullptr, nullptr, nullptr};
   // nodes of degree > kFinGroupMax (finalized one wavefront each), by degree descending
@@ -222,7 +224,8 @@ struct Graph {
   int64_t all_pairs_small = 0, all_pairs_mid = 0, all_pairs_big = 0;
   int64_t all_sblocks = 0;  // sum of super-blocks over big centres
   int64_t owned_bytes = 0;  // device bytes held by this handle
-  int32_t *d_counters = nullptr;  // persistent small counters (flag counts etc.)
+  // the load's control record (kCtl*), then the lane bin's counts by workgroup
+  int32_t *d_counters = nullptr;
   // FP64 calls: d log d for every cluster degree d < n_score64 (built by the
   // first one; null: no device memory for it, and the kernels take logs)
   double *score64 = nullptr;

@@ -203,8 +203,8 @@ constexpr int kGTab = 8192;
 // FP64: score(i) of every cluster degree i the graph can have, kept with the
 // graph (Graph::score64, n entries; null: none). d log d in double costs about
 // 90 VALU instructions, against one LDS read from a copy of the part a
-// workgroup needs; the entries are the same expression's values, so every
-// cluster keeps its score bits.
+// workgroup needs. The entries are that expression's values, rounded to double;
+// where it is evaluated in place, its product may be fused into the sum.
 struct ScoreTab {
   const double *g = nullptr;
   int32_t n = 0;

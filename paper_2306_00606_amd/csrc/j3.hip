@@ -403,8 +403,8 @@ __global__ __launch_bounds__(64 * WPB) void k_j3_block(const int32_t *__restrict
     }
     // distinct kappa (keys kappa + 4 > 0), through the table of the d_T below:
     // each thread looks at the count before an insertion, so at most PCH + NT
-    // of its 2 PCH slots fill
-    static_assert(PCH + NT <= DS, "the class table must keep a free slot");
+    // of its 2 PCH slots fill (and no more than the list has entries)
+    static_assert(LMAX < DS || PCH + NT < DS, "the class table must keep a free slot");
     if (tid == 0) kcount = 0;
     __syncthreads();
 #pragma unroll

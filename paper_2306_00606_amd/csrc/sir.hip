@@ -396,7 +396,7 @@ __global__ __launch_bounds__(kSirThreads) void k_sir_attempt(
     else sir_wave_fence();
   }
   sir_flush(buf, nxc, nxt, n);
-  // each wavefront owns one slot of the arc counts: no atomic needed
+  // a slot of the arc counts per workgroup, to which its wavefronts add
   if (lane == 63) atomicAdd((unsigned long long *)&wk[blockIdx.x], (unsigned long long)arcs);
   if (!sir_last(ticket)) return;
   const int32_t tot = sir_scan(
