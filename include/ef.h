@@ -146,7 +146,7 @@ ef_status ef_validate_csr(int32_t n, int64_t nnz, const int32_t *row_ptr,
  * copied to the host only to word one). The library allocates its own device
  * arrays (degrees, arc sources, reverse arcs, the degree-oriented half
  * adjacency) and keeps them until ef_graph_free, and with them, where it is at
- * most 64 MiB, the block that the first ef_compute of all nodes will use (given
+ * most 256 MiB, the block that the first ef_compute of all nodes will use (given
  * up when the handle runs short of memory for something else). */
 ef_status ef_graph_load_csr(int32_t n, int64_t nnz, const int32_t *row_ptr,
                             const int32_t *col_idx, uint32_t flags, void *hip_stream,

@@ -117,14 +117,11 @@ static ComputeWs compute_ws(const Graph &g, bool fp64, int64_t n_tiles, int64_t 
   return L;
 }
 
-// Largest block that a load keeps for the first ef_compute. An allocation and a
-// free of tens of megabytes cost some 0.3 ms each, a tenth of a load of 2M arcs;
-// larger graphs load for longer, and idle handles would hold gigabytes. A graph
-// with slots for tri_zero has more than kTriBin2^2 arcs and so no such block:
-// that allocation never finds its place taken.
-constexpr size_t kMainKept = (size_t)64 << 20;
-static_assert(kMainKept < (sizeof(float) + sizeof(TriSlot)) * kTriBin2 * kTriBin2,
-              "a load that keeps its block clears no triangle slots");
+// Largest block that a load keeps for the first ef_compute (FP64's size up to
+// kMainKept64, FP32C's above). Allocating and freeing it costs 0.3 ms for tens of
+// megabytes, 1 ms for a hundred, a tenth of the load that is over by then; larger
+// graphs load for longer, and idle handles would hold gigabytes.
+constexpr size_t kMainKept = (size_t)256 << 20, kMainKept64 = (size_t)64 << 20;
 
 // Gives up ef_compute's block when no call is using it (the free waits for work
 // in flight) and no captured graph refers to it.
@@ -496,7 +493,7 @@ ef_status graph_load(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32
   size_t kept_bytes = 0;
   for (const bool fp64 : {false, true}) {
     const size_t w = compute_ws(g, fp64, nn_tiles, n, true).bytes;
-    if (nnz > 0 && w <= kMainKept && w <= 2 * scratch_bytes) kept_bytes = w;
+    if (nnz > 0 && w <= (fp64 ? kMainKept64 : kMainKept) && w <= 2 * scratch_bytes) kept_bytes = w;
   }
   if (st == EF_OK) {
     const size_t want = std::max(scratch_bytes, kept_bytes);
@@ -512,8 +509,13 @@ ef_status graph_load(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32
       return st;
     });
   }
-  int64_t *work = (int64_t *)g.ws[WS_MAIN].p;
-  int32_t *tmp = (int32_t *)((char *)g.ws[WS_MAIN].p + work_bytes);
+  int64_t *work = nullptr;
+  int32_t *tmp = nullptr;
+  auto prepare = [&]() -> hipError_t {
+    work = (int64_t *)g.ws[WS_MAIN].p;
+    tmp = (int32_t *)((char *)g.ws[WS_MAIN].p + work_bytes);
+    return launch_graph_prep(g, tmp, work, validate, stream);
+  };
   hipError_t e = hipSuccess;
   if (!devptr) {
     e = hipMemcpyAsync(g.row_ptr, row_ptr, sizeof(int32_t) * N1, hipMemcpyHostToDevice, stream);
@@ -521,7 +523,7 @@ ef_status graph_load(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32
       e = hipMemcpyAsync(g.col_idx, col_idx, sizeof(int32_t) * (size_t)nnz,
                          hipMemcpyHostToDevice, stream);
   }
-  if (e == hipSuccess) e = launch_graph_prep(g, tmp, work, validate, stream);
+  if (e == hipSuccess) e = prepare();
   // one read-back of the control record and the list offsets, one of the tail
   // entries walked at each node by the triangle pass (binning)
   const size_t ptr_stride = (sizeof(int32_t) * N1 + 255) & ~(size_t)255;
@@ -556,10 +558,20 @@ ef_status graph_load(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32
   }
   g.n_tri_zero = nnz > 0 ? h_ctl[kCtlZero] : 0;
   if (g.n_tri_zero > 0) {
-    st = dev_alloc(g, (void **)&g.tri_zero, sizeof(int32_t) * (size_t)g.n_tri_zero, "zero slots");
-    if (st != EF_OK) {
+    const size_t zero_bytes = sizeof(int32_t) * (size_t)g.n_tri_zero;
+    st = dev_alloc(g, (void **)&g.tri_zero, zero_bytes, "zero slots");
+    if (st != EF_OK && g.ws[WS_MAIN].bytes > scratch_bytes) {
+      // room after all when the block is no more than the preparation's scratch,
+      // whose contents go with it
+      drop_main(g);
+      st = ws_ensure(g, WS_MAIN, scratch_bytes, "preprocessing scratch");
+      if (st == EF_OK) e = prepare();
+      if (st == EF_OK && e == hipSuccess)
+        st = dev_alloc(g, (void **)&g.tri_zero, zero_bytes, "zero slots");
+    }
+    if (st != EF_OK || e != hipSuccess) {
       ef_graph_free(h);
-      return st;
+      return st != EF_OK ? st : hip_status(e, "graph preprocessing");
     }
     e = launch_zero_list(g, tmp, stream);
   }
