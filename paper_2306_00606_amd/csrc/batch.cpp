@@ -248,22 +248,28 @@ static bool split_by_graph(const ef_batch *b, const int32_t *ids, int64_t count,
   return true;
 }
 
-template <typename V>
-static ef_status upload(PersistState &ps, const std::vector<V> &h, V **out, const char *what) {
-  *out = nullptr;
-  const size_t bytes = sizeof(V) * std::max<size_t>(h.size(), 1);
-  hipError_t e = hipMalloc((void **)out, bytes);
-  if (e == hipSuccess) {
-    ps.owned.push_back(*out);
-    if (!h.empty()) e = hipMemcpy(*out, h.data(), sizeof(V) * h.size(), hipMemcpyHostToDevice);
+// (a batch that only ever runs this design has no use for ef_compute's block)
+static hipError_t persist_malloc(ef_batch *b, void **out, size_t bytes) {
+  hipError_t e = hipMalloc(out, bytes);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    if (graph_drop_block(b->g->g)) e = hipMalloc(out, bytes);
   }
+  if (e == hipSuccess) b->ps.owned.push_back(*out);
+  return e;
+}
+
+template <typename V>
+static ef_status upload(ef_batch *b, const std::vector<V> &h, V **out, const char *what) {
+  *out = nullptr;
+  hipError_t e = persist_malloc(b, (void **)out, sizeof(V) * std::max<size_t>(h.size(), 1));
+  if (e == hipSuccess && !h.empty())
+    e = hipMemcpy(*out, h.data(), sizeof(V) * h.size(), hipMemcpyHostToDevice);
   return hip_status(e, what);
 }
 
-static ef_status dev_buffer(PersistState &ps, size_t bytes, void **out, const char *what) {
-  hipError_t e = hipMalloc(out, std::max<size_t>(bytes, 256));
-  if (e == hipSuccess) ps.owned.push_back(*out);
-  return hip_status(e, what);
+static ef_status dev_buffer(ef_batch *b, size_t bytes, void **out, const char *what) {
+  return hip_status(persist_malloc(b, out, std::max<size_t>(bytes, 256)), what);
 }
 
 static ef_status build_persist(ef_batch *b, int32_t cfg_idx) {
@@ -375,15 +381,15 @@ static ef_status build_persist(ef_batch *b, int32_t cfg_idx) {
   }
   ef_status s = EF_OK;
   PersistPlan &P = ps.pl;
-  for (int q = 0; q < 7 && s == EF_OK; ++q) s = upload(ps, pl[q], &P.pair[q], "pair lists");
-  if (s == EF_OK) s = upload(ps, big, &P.big, "big centres");
-  if (s == EF_OK) s = upload(ps, tiles, &P.tiles, "super-tiles");
-  if (s == EF_OK) s = upload(ps, red, &P.reduce, "reduction items");
-  if (s == EF_OK) s = upload(ps, tlong, &P.tri_long, "long triangle nodes");
-  if (s == EF_OK) s = upload(ps, items, &P.items, "work items");
-  if (s == EF_OK) s = upload(ps, pend0, &P.pend0, "item counts");
-  if (s == EF_OK) s = upload(ps, pend0, &P.pend, "item counters");
-  if (s == EF_OK) s = upload(ps, std::vector<int32_t>(16, 0), &P.ctl, "cursor");
+  for (int q = 0; q < 7 && s == EF_OK; ++q) s = upload(b, pl[q], &P.pair[q], "pair lists");
+  if (s == EF_OK) s = upload(b, big, &P.big, "big centres");
+  if (s == EF_OK) s = upload(b, tiles, &P.tiles, "super-tiles");
+  if (s == EF_OK) s = upload(b, red, &P.reduce, "reduction items");
+  if (s == EF_OK) s = upload(b, tlong, &P.tri_long, "long triangle nodes");
+  if (s == EF_OK) s = upload(b, items, &P.items, "work items");
+  if (s == EF_OK) s = upload(b, pend0, &P.pend0, "item counts");
+  if (s == EF_OK) s = upload(b, pend0, &P.pend, "item counters");
+  if (s == EF_OK) s = upload(b, std::vector<int32_t>(16, 0), &P.ctl, "cursor");
   if (s != EF_OK) return s;
   P.tri_wave = g.tri_rec0;
   P.tri_block = g.tri_list[1];
@@ -395,14 +401,14 @@ static ef_status build_persist(ef_batch *b, int32_t cfg_idx) {
   P.n_graphs = G;
   // workspace; R and the records hold float2 or double: 8 bytes either way
   const size_t nnz = (size_t)std::max<int64_t>(g.nnz, 1), n = (size_t)std::max(g.n, 1);
-  if (s == EF_OK) s = dev_buffer(ps, 8 * nnz, &ps.R, "arc sums");
+  if (s == EF_OK) s = dev_buffer(b, 8 * nnz, &ps.R, "arc sums");
   if (s == EF_OK)
-    s = dev_buffer(ps, (size_t)8 * kRecEntries * (size_t)std::max<int64_t>(rec_base, 1), &ps.rec,
+    s = dev_buffer(b, (size_t)8 * kRecEntries * (size_t)std::max<int64_t>(rec_base, 1), &ps.rec,
                    "super-tile records");
-  if (s == EF_OK) s = dev_buffer(ps, sizeof(TriSlot) * nnz, (void **)&ps.Y, "triangle records");
-  if (s == EF_OK) s = dev_buffer(ps, 8 * n, &ps.Z, "triangle node sums");
-  if (s == EF_OK) s = dev_buffer(ps, 8 * n, (void **)&ps.ZT, "triangle node counts");
-  if (s == EF_OK) s = dev_buffer(ps, n, (void **)&ps.fl, "flag bytes");
+  if (s == EF_OK) s = dev_buffer(b, sizeof(TriSlot) * nnz, (void **)&ps.Y, "triangle records");
+  if (s == EF_OK) s = dev_buffer(b, 8 * n, &ps.Z, "triangle node sums");
+  if (s == EF_OK) s = dev_buffer(b, 8 * n, (void **)&ps.ZT, "triangle node counts");
+  if (s == EF_OK) s = dev_buffer(b, n, (void **)&ps.fl, "flag bytes");
   if (s != EF_OK) return s;
   ps.cfg = cfg_idx;
   b->stats.items = P.n_items;

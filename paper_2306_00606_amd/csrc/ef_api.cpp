@@ -841,6 +841,8 @@ ef_status graph_scratch(Graph &g, size_t bytes, void **out) {
   return s;
 }
 
+bool graph_drop_block(Graph &g) { return drop_main(g); }
+
 static bool capturing(hipStream_t st) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(st, &cap) != hipSuccess) {

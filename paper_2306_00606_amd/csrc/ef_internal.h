@@ -263,6 +263,9 @@ ef_status graph_load(int32_t n, int64_t nnz, const int32_t *row_ptr, const int32
 // grow-only device scratch held by the graph handle (one slot shared by the
 // surrogate entry points)
 ef_status graph_scratch(Graph &g, size_t bytes, void **out);
+// gives up the block of ef_compute that the handle keeps, for memory that is
+// short elsewhere; false if there is none, or it is in use
+bool graph_drop_block(Graph &g);
 
 // error text (thread-local)
 void set_error(const char *fmt, ...);

@@ -349,6 +349,30 @@ static void idle() {
     CHECK(ef_graph_free(h) == EF_OK);
   }
 }
+// a batch of the persistent design finds room that the block kept by its load
+// would take
+static void batch_room() {
+  const Csr c = ring(20000, 8);
+  const int32_t off[2] = {0, c.n()};
+  ef_graph *h = load(c);
+  const size_t block = h->g.ws[0].bytes;
+  CHECK(ef_graph_free(h) == EF_OK && block > 0);
+  size_t held = 0;
+  for (int round = 0; round < 2; ++round) {
+    stub::set_capacity(round == 0 ? 0 : held - block / 2);
+    ef_batch *b = nullptr;
+    CHECK(ef_batch_create(1, off, c.nnz(), c.rp.data(), c.ci.data(), 0, nullptr, &b) == EF_OK);
+    Out r((size_t)c.n());
+    CHECK(ef_batch_compute(b, EF_PREC_FP32C, r.ef.data(), r.D.data(), r.N.data(),
+                           EF_BATCH_PERSISTENT, nullptr) == EF_OK);
+    CHECK(expected(r, nullptr));
+    held = stub::live_bytes();
+    stub::set_capacity(0);
+    CHECK(ef_batch_compute(b, EF_PREC_FP32C, r.ef.data(), r.D.data(), r.N.data(), EF_BATCH_PHASED,
+                           nullptr) == EF_OK);
+    CHECK(ef_batch_free(b) == EF_OK);
+  }
+}
 // a load accepted under one limit is accepted under any larger one: here what is
 // left after a block for ef_compute has room for half of the triangle slots that
 // are cleared before each pass
@@ -381,6 +405,7 @@ int main(int argc, char **argv) {
       {"captured", captured},
       {"streams", streams},
       {"idle", idle},
+      {"batch_room", batch_room},
       {"limits", limits},
   };
   const auto it = argc == 2 ? all.find(argv[1]) : all.end();

@@ -31,7 +31,7 @@ void fail(const char *fmt, ...) {
 }
 
 std::map<void *, size_t> g_mem;
-size_t g_fail_bytes = 0, g_fail_copy = 0;
+size_t g_fail_bytes = 0, g_fail_copy = 0, g_capacity = 0;
 
 // What has happened before what: per stream, the operations of every stream
 // that its next one follows; the host follows what it has waited for.
@@ -102,6 +102,7 @@ size_t live_bytes() {
 }
 void fail_mallocs(size_t bytes) { g_fail_bytes = bytes; }
 void fail_copies(size_t bytes) { g_fail_copy = bytes; }
+void set_capacity(size_t bytes) { g_capacity = bytes; }
 void begin_capture(hipStream_t st) { g_capture[st]; }
 void end_capture(hipStream_t st) {
   g_last = g_capture[st];
@@ -136,6 +137,7 @@ hipError_t hipGetLastError() { return hipSuccess; }
 hipError_t hipMalloc(void **p, size_t bytes) {
   if (!g_capture.empty()) fail("hipMalloc while a stream is captured");
   if (g_fail_bytes && bytes == g_fail_bytes) return hipErrorOutOfMemory;
+  if (g_capacity && stub::live_bytes() + bytes > g_capacity) return hipErrorOutOfMemory;
   *p = std::malloc(bytes);  // exactly `bytes`: what follows is not readable
   if (!*p) return hipErrorOutOfMemory;
   std::memset(*p, 0xCD, bytes);

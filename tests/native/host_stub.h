@@ -18,6 +18,8 @@ bool live(const void *p);
 size_t live_bytes();
 // every hipMalloc of exactly `bytes` fails from now on (0: none)
 void fail_mallocs(size_t bytes);
+// hipMalloc fails where more than `bytes` would be held (0: never)
+void set_capacity(size_t bytes);
 // every hipMemcpyAsync of exactly `bytes` fails from now on (0: none)
 void fail_copies(size_t bytes);
 

@@ -49,7 +49,7 @@ def driver(tmp_path_factory):
 
 
 @pytest.mark.parametrize("scenario", ["calls", "batches", "first_use", "captured", "streams", "idle",
-                                      "limits"])
+                                      "batch_room", "limits"])
 def test_host_code(driver, scenario):
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=1:verify_asan_link_order=0",
                UBSAN_OPTIONS="print_stacktrace=1")
