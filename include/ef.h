@@ -71,7 +71,8 @@ typedef enum {
 typedef enum { EF_ALGO_CLUSTER = 0, EF_ALGO_PER_SEED = 1, EF_ALGO_CLUSTER_AGG = 2 } ef_algo;
 
 /* Precision of the cluster-degree logarithms and their sums:
- *   EF_PREC_FP64  - every term and sum in double precision.
+ *   EF_PREC_FP64  - every term and sum in double precision (the triangle
+ *                   corrections kept with an edge in 2^-36 fixed point).
  *   EF_PREC_FP32C - terms in single precision with compensated (double-float)
  *                   sums; the final EF of seeds with more than 2^24 clusters is
  *                   formed in double precision; seeds whose EF would lose
